@@ -172,6 +172,14 @@ struct ephbte_plan_s {
     unsigned long long *lmax_bits = nullptr;  // max |lam| of the pair reverse pass (double bits)
     unsigned long long *mmax_bits = nullptr;  // max |mu| and max |N| of the phonon side's dL/df over
                                               // pair records (its own slots: other passes keep theirs)
+    // pair matrix (built from the pair records where its blocks are filled
+    // enough, see build_matrix_layout): positions, blocks, and the workspace
+    bool mx_ok = false;
+    int mx_nb = 0, mx_max_row = 0;
+    int64_t mx_blocks = 0;
+    int32_t *mx_pos = nullptr, *mx_state = nullptr, *mx_blk = nullptr, *mx_row = nullptr;
+    MxCol *mx_col = nullptr;
+    DevBuf mx_m, mx_u, mx_p1, mx_p2;
     // batched pass: tiles of destinations and per-destination sub-tile offsets
     BTileRec *btiles = nullptr;
     int64_t *sub_off = nullptr;
@@ -237,7 +245,7 @@ struct ephbte_plan_s {
                              &adj_U, &adj_la, &adj_lb, &adj_acc, &adj_g, &adj_f, &cp_Ma, &cp_Mb,
                              &cp_acc, &cp_rate, &ph_part, &ph_tab4, &ca_ckf, &ca_ckN, &ca_U, &ca_M,
                              &ca_gf, &ca_gN, &ca_a, &ca_b, &ca_uf, &ca_uN, &ca_sf, &ca_sN, &ca_mu,
-                             &bs_x, &bs_y, &nvec};
+                             &bs_x, &bs_y, &nvec, &mx_m, &mx_u, &mx_p1, &mx_p2};
         for (auto *x : w) b += x->bytes;
         return b;
     }
@@ -340,14 +348,16 @@ void free_plan(ephbte_plan P) {
                      (void **)&P->pr_chan, (void **)&P->pr_chunk_beg, (void **)&P->pr_chunk_end,
                      (void **)&P->pr_chunk_dest, (void **)&P->pr_dest_chunk, (void **)&P->pr_tiles,
                      (void **)&P->lmax_bits, (void **)&P->mmax_bits, (void **)&P->pr_ch0, (void **)&P->fmax_bits,
-                     (void **)&P->used_rows};
+                     (void **)&P->used_rows, (void **)&P->mx_pos, (void **)&P->mx_state, (void **)&P->mx_blk,
+                     (void **)&P->mx_row, (void **)&P->mx_col};
     for (auto pp : ptrs) dfree(*pp);
     DevBuf *w[] = {&P->part,   &P->sym_part, &P->rk_ua,  &P->rk_ub,   &P->rk_acc, &P->hwN, &P->tr_W,   &P->tr_tau_inv,
                    &P->tr_tau, &P->tr_rhs, &P->tr_xa,   &P->tr_xb,  &P->tr_part, &P->tr_red,
                    &P->tr_red2, &P->adj_ck, &P->adj_U,  &P->adj_la, &P->adj_lb, &P->adj_acc,
                    &P->adj_g,  &P->adj_f, &P->cp_Ma, &P->cp_Mb, &P->cp_acc, &P->cp_rate, &P->ph_part,
                    &P->ph_tab4, &P->ca_ckf, &P->ca_ckN, &P->ca_U, &P->ca_M, &P->ca_gf, &P->ca_gN, &P->ca_a,
-                   &P->ca_b, &P->ca_uf, &P->ca_uN, &P->ca_sf, &P->ca_sN, &P->ca_mu, &P->bs_x, &P->bs_y, &P->nvec};
+                   &P->ca_b, &P->ca_uf, &P->ca_uN, &P->ca_sf, &P->ca_sN, &P->ca_mu, &P->bs_x, &P->bs_y, &P->nvec,
+                   &P->mx_m, &P->mx_u, &P->mx_p1, &P->mx_p2};
     for (auto *b : w) dfree(b->p);
     if (P->host_red) (void)hipHostFree(P->host_red);
     if (P->ev_a) (void)hipEventDestroy(P->ev_a);
@@ -1006,9 +1016,167 @@ size_t tiled_lds_bytes(ephbte_plan P) {
     return static_cast<size_t>(P->lds_states) * (2 * es + 4) + tab;
 }
 
+// ---- pair matrix ----------------------------------------------------------
+template <typename T> MxArgs<T> mx_args(ephbte_plan P) {
+    MxArgs<T> x;
+    x.m = static_cast<T *>(P->mx_m.p);
+    x.pos = P->mx_pos;
+    x.state = P->mx_state;
+    x.blk = P->mx_blk;
+    x.row = P->mx_row;
+    x.col = P->mx_col;
+    x.nb = P->mx_nb;
+    x.S = P->S;
+    return x;
+}
+
+// the plan's prefactor K in FP64
+double k_prefactor(ephbte_plan P) {
+    return 2.0 * kPi / (kHbar * P->nqnorm) / (P->sigma * std::sqrt(2.0 * kPi));
+}
+
+// The matrix and its partials for nc columns, or false where the plan has no
+// matrix or the device memory for it is not there (the caller then takes the
+// pass without one).  Single-vector forms keep the layout the tuning chose.
+template <typename T> bool mx_ensure(ephbte_plan P, int nc, int nsplit) {
+    if (!P->mx_ok) return false;
+    const size_t pos = static_cast<size_t>(P->mx_nb) * 64;
+    try {
+        ensure_zeroed(P, P->mx_m, sizeof(T) * static_cast<size_t>(P->mx_blocks) * kMxBlock);
+        ensure(P->mx_u, sizeof(double) * pos * 4 * static_cast<size_t>(nc), &P->ws_gen);
+        ensure(P->mx_p1, sizeof(double) * pos * static_cast<size_t>(nsplit) * nc, &P->ws_gen);
+        ensure(P->mx_p2, sizeof(double) * static_cast<size_t>(P->mx_blocks) * 64 * nc, &P->ws_gen);
+    } catch (const std::bad_alloc &) {
+        return false;
+    }
+    return true;
+}
+
+// Workgroups per block row of k_mx_vec: about eight blocks each (two a wave),
+// or one a wave where the rows alone would leave compute units idle.
+int mx_vec_split(ephbte_plan P) {
+    const int per = static_cast<int64_t>(P->mx_nb) * ((P->mx_max_row + 7) / 8) >= 2 * P->n_cu ? 8 : 4;
+    return std::max(1, (P->mx_max_row + per - 1) / per);
+}
+
+// Fills the matrix for the {hw, N} table packed last.
+template <typename T> void enqueue_pair_matrix(ephbte_plan P, hipStream_t s) {
+    const TiledArgs<T> a = pair_args<T>(P);
+    const MxArgs<T> x = mx_args<T>(P);
+    const dim3 grid(static_cast<unsigned>(P->n_pr_tiles)), block(1024);
+    const size_t shm = static_cast<size_t>(P->pr_lds_states) * (sizeof(T) + 8) + (sizeof(T) == 8 ? kExpTab * 8 : 0);
+    auto go = [&](auto nmc) {
+        constexpr int NM = decltype(nmc)::value;
+        const bool tab = sizeof(T) == 8 && P->exp_table;
+        if (P->padq && tab) hipLaunchKernelGGL((k_pair_matrix<T, true, NM, true>), grid, block, shm, s, a, x);
+        else if (P->padq) hipLaunchKernelGGL((k_pair_matrix<T, true, NM, false>), grid, block, shm, s, a, x);
+        else if (tab) hipLaunchKernelGGL((k_pair_matrix<T, false, NM, true>), grid, block, shm, s, a, x);
+        else hipLaunchKernelGGL((k_pair_matrix<T, false, NM, false>), grid, block, shm, s, a, x);
+    };
+    if (P->nm <= 1) go(std::integral_constant<int, 1>{});
+    else if (P->nm <= 2) go(std::integral_constant<int, 2>{});
+    else if (P->nm <= 3) go(std::integral_constant<int, 3>{});
+    else if (P->nm <= 4) go(std::integral_constant<int, 4>{});
+    else if (P->nm <= 6) go(std::integral_constant<int, 6>{});
+    else go(std::integral_constant<int, 8>{});
+    HIPC(hipGetLastError());
+}
+
+// M u1 and the transposed product with u2 for NC columns, as partials
+template <typename T, int NC>
+void enqueue_mx_vec(ephbte_plan P, const double *u1, const double *u2, int nsplit, hipStream_t s) {
+    hipLaunchKernelGGL((k_mx_vec<T, NC>), dim3(static_cast<unsigned>(P->mx_nb), static_cast<unsigned>(nsplit)),
+                       dim3(256), 0, s, mx_args<T>(P), u1, u2, static_cast<double *>(P->mx_p1.p),
+                       static_cast<double *>(P->mx_p2.p));
+    HIPC(hipGetLastError());
+}
+
+// Columns of the batched products: the vectors of a group (at most 64) rounded
+// up to the 16 of a matrix instruction
+int mx_columns(int B) { return 16 * ((std::min(B, 64) + 15) / 16); }
+
+// Workgroups per block row of k_mx_gemm: about six a compute unit in all (the
+// last round is then a sixth of the work), each with at least two blocks, at
+// most eight so that the partial sums stay small beside the matrix.
+int mx_gemm_split(ephbte_plan P) {
+    const int want = (6 * P->n_cu + P->mx_nb - 1) / std::max(P->mx_nb, 1);
+    return std::max(1, std::min({want, 8, P->mx_max_row / 2}));
+}
+
+size_t mx_gemm_lds(int NC) { return 2 * 64 * static_cast<size_t>(NC + 4) * sizeof(double); }
+
+// Whether B vectors go through the pair matrix.  Its coefficients are evaluated
+// once per pair (as in the single-vector pass) and applied on the matrix cores:
+// on the 100^3 system in FP64 1.5 ms at B = 64 against 3.9 ms for the pass over
+// entries; below 8 vectors, against one pass per vector.  Below 8 the tuning's
+// layout chooses, as for one vector.
+bool mx_batch_fits(ephbte_plan P, int B) {
+    return P->mx_ok && B >= 2 && P->pr_ok && P->n_pr_tiles > 0 && (B >= P->batch_min || P->layout == 3) &&
+           mx_gemm_lds(mx_columns(B)) <= P->lds_max;
+}
+template <typename T> bool mx_ensure_batch(ephbte_plan P, int B) {
+    if (!mx_batch_fits(P, B)) return false;
+    const size_t cells = static_cast<size_t>(P->mx_nb) * 64 * mx_columns(B) * sizeof(double);
+    try {
+        ensure_zeroed(P, P->mx_m, sizeof(T) * static_cast<size_t>(P->mx_blocks) * kMxBlock);
+        ensure(P->mx_u, 2 * cells, &P->ws_gen);
+        ensure(P->mx_p1, 2 * cells * mx_gemm_split(P), &P->ws_gen);
+    } catch (const std::bad_alloc &) {
+        return false;
+    }
+    return true;
+}
+// true once mx_ensure_batch found the memory
+template <typename T> bool use_mx_batch(ephbte_plan P, int B) {
+    if (!mx_batch_fits(P, B)) return false;
+    const size_t cells = static_cast<size_t>(P->mx_nb) * 64 * mx_columns(B) * sizeof(double);
+    return P->mx_m.bytes >= sizeof(T) * static_cast<size_t>(P->mx_blocks) * kMxBlock && P->mx_u.bytes >= 2 * cells &&
+           P->mx_p1.bytes >= 2 * cells * mx_gemm_split(P);
+}
+
+// part1 += M u1, part2 += M^T u2 for NC columns
+template <typename T>
+void enqueue_mx_gemm(ephbte_plan P, int NC, const double *u1, const double *u2, double *p1, double *p2, int nsplit,
+                     hipStream_t s) {
+    const dim3 grid(static_cast<unsigned>(P->mx_nb), static_cast<unsigned>(nsplit));
+    const MxArgs<T> x = mx_args<T>(P);
+    auto go = [&](auto nct) {
+        constexpr int NCT = decltype(nct)::value;
+        hipLaunchKernelGGL((k_mx_gemm<T, NCT>), grid, dim3(256), mx_gemm_lds(NC), s, x, u1, u2, p1, p2);
+    };
+    if (NC == 16) go(std::integral_constant<int, 1>{});
+    else if (NC == 32) go(std::integral_constant<int, 2>{});
+    else if (NC == 48) go(std::integral_constant<int, 3>{});
+    else go(std::integral_constant<int, 4>{});
+    HIPC(hipGetLastError());
+}
+
+// I for B >= 2 vectors over the pair matrix, in groups of 64 vectors
+template <typename T>
+void enqueue_forward_mx(ephbte_plan P, int B, const T *f, int64_t ldf, const Epi<T> &E, hipStream_t s) {
+    const int nsplit = mx_gemm_split(P);
+    for (int b0 = 0; b0 < B; b0 += 64) {
+        const int nv = std::min(64, B - b0), NC = mx_columns(nv);
+        const int64_t cells = static_cast<int64_t>(P->mx_nb) * 64 * NC;
+        double *u1 = static_cast<double *>(P->mx_u.p), *u2 = u1 + cells;
+        double *p1 = static_cast<double *>(P->mx_p1.p), *p2 = p1 + cells * nsplit;
+        const T *fg = f + b0 * ldf;
+        const dim3 grid(static_cast<unsigned>(P->mx_nb), static_cast<unsigned>(NC / 16));
+        hipLaunchKernelGGL((k_mx_load_batch<T>), grid, dim3(256), 0, s, mx_args<T>(P), fg, ldf, nv, NC, u1, u2);
+        const int64_t kt = b0 == 0 ? ktime_begin(P, s) : -1;
+        enqueue_mx_gemm<T>(P, NC, u1, u2, p1, p2, nsplit, s);
+        ktime_end(P, s, kt);
+        hipLaunchKernelGGL((k_mx_batch_finish<T>), grid, dim3(256), 0, s, tiled_args<T>(P), mx_args<T>(P),
+                           (const double *)p1, (const double *)p2, nsplit, NC, b0, nv, k_prefactor(P),
+                           (const double *)u1, (const double *)u2, f, ldf, E);
+    }
+    HIPC(hipGetLastError());
+}
+
 // Enqueue I[f] for B vectors with epilogue E (no allocation inside; the
 // caller ensured P->part and P->hwN are large enough).  pack = false when the
-// {hw, N} table already holds this call's occupations.
+// {hw, N} table (and, for B vectors over it, the pair matrix) already holds this
+// call's occupations.
 // max |f| over one vector into P->fmax_bits: the fixed-point scale of the
 // single-copy passes for occupations outside [0, 1] (Bose plans)
 template <typename T> void enqueue_fmax(ephbte_plan P, const T *f, hipStream_t s) {
@@ -1020,6 +1188,11 @@ template <typename T>
 void enqueue_forward(ephbte_plan P, int B, const T *f, int64_t ldf, const void *nph,
                      const Epi<T> &E, hipStream_t s, bool pack = true) {
     if (pack) enqueue_pack<T>(P, nph, s);
+    if (use_mx_batch<T>(P, B)) {
+        if (pack) enqueue_pair_matrix<T>(P, s);
+        enqueue_forward_mx<T>(P, B, f, ldf, E, s);
+        return;
+    }
     if (B >= P->batch_min && P->n_btiles > 0) {
         enqueue_forward_batched<T>(P, B, f, ldf, E, s);
         return;
@@ -1076,6 +1249,7 @@ void enqueue_forward(ephbte_plan P, int B, const T *f, int64_t ldf, const void *
 }
 
 template <typename T> void ensure_fwd(ephbte_plan P, int B) {
+    (void)mx_ensure_batch<T>(P, B);
     if (!P->fused) ensure(P->part, sizeof(T) * 2 * static_cast<size_t>(P->n_chunks) * B, &P->ws_gen);
     if (use_sym(P, B))
         ensure(P->sym_part, sizeof(T) * 2 * static_cast<size_t>(std::max<int64_t>(P->n_sym_chunks, 1)),
@@ -1499,6 +1673,28 @@ template <typename T> void upload_pair_rows(ephbte_plan P, const ephbte_problem 
     P->pr_perm.clear();
 }
 
+// The pair matrix's block structure (its values are a workspace)
+void upload_matrix_layout(ephbte_plan P) {
+    MatrixLayout L;
+    if (!P->pr_ok || !build_matrix_layout(P->S, P->pr_rowptr, P->pr_partner_host, &L)) return;
+    size_t &acc = P->layout_bytes;
+    std::vector<MxCol> col(L.col.size());
+    for (size_t x = 0; x < col.size(); ++x) col[x] = MxCol{L.col[x], L.col_t[x]};
+    auto up = [&](auto *&dst, const auto &v) {
+        dalloc(dst, sizeof(v[0]) * v.size(), &acc);
+        HIPC(hipMemcpy(dst, v.data(), sizeof(v[0]) * v.size(), hipMemcpyHostToDevice));
+    };
+    up(P->mx_pos, L.pos);
+    up(P->mx_state, L.state);
+    up(P->mx_blk, L.blk);
+    up(P->mx_row, L.row);
+    up(P->mx_col, col);
+    P->mx_nb = L.nb;
+    P->mx_blocks = L.n_blocks();
+    for (int I = 0; I < L.nb; ++I) P->mx_max_row = std::max(P->mx_max_row, L.row[I + 1] - L.row[I]);
+    P->mx_ok = true;
+}
+
 // The phonon pass's layout (pair records bucketed by {q, -q}, see
 // build_phonon_layout) and its chunks of at most kPhChunk records.
 template <typename T> void upload_phonon_layout(ephbte_plan P, const ephbte_problem *pr, const HostLayout &L) {
@@ -1603,6 +1799,43 @@ void rk4_enqueue_step(ephbte_plan P, int B, T *f, int64_t ldf, const void *nph, 
     enqueue_forward<T>(P, B, ua, S, nph, e, s, false);
 }
 
+// One RK4 step of a single vector over the pair matrix, whose bath holds for the
+// whole call: per stage one pass over the matrix (half a pair record's bytes per
+// pair with one mode, a sixth with six, and no exponentials) and its finish.  On
+// the 100^3 system in FP32 a stage takes 0.07 ms against 0.28 ms for the pass
+// over pair records.  u holds the stage input by position ({f, 1 - f}, two
+// copies that alternate: four stages end where they began).
+template <typename T>
+void mx_rk4_step(ephbte_plan P, T *f, T dt, hipStream_t s, T *ua, T *ub, T *acc, int nsplit) {
+    const int64_t np = static_cast<int64_t>(P->mx_nb) * 64;
+    double *u = static_cast<double *>(P->mx_u.p);
+    double *b1[2] = {u, u + 2 * np}, *b2[2] = {u + np, u + 3 * np};
+    const TiledArgs<T> a = tiled_args<T>(P);
+    const double K = k_prefactor(P);
+    const int modes[4] = {EPI_RK1, EPI_RK2, EPI_RK3, EPI_RK4};
+    T *const out[4] = {ua, ub, ua, nullptr};
+    const T *in = f;
+    Epi<T> e{};
+    e.f0 = f;
+    e.ld_f0 = P->S;
+    e.acc = acc;
+    e.dt = dt;
+    e.f_out = f;
+    for (int k = 0; k < 4; ++k) {
+        e.mode = modes[k];
+        e.u_out = out[k];
+        with_drift<T>(P, e, in, static_cast<int64_t>(P->S), T(1));
+        const int64_t kt = ktime_begin(P, s);
+        enqueue_mx_vec<T, 1>(P, b1[k & 1], b2[k & 1], nsplit, s);
+        ktime_end(P, s, kt);
+        hipLaunchKernelGGL((k_mx_rk_finish<T>), dim3(static_cast<unsigned>(P->mx_nb)), dim3(64 * kMxParts), 0, s, a,
+                           mx_args<T>(P), (const double *)P->mx_p1.p, nsplit, (const double *)P->mx_p2.p, K,
+                           (const double *)b1[k & 1], (const double *)b2[k & 1], b1[(k + 1) & 1], b2[(k + 1) & 1], e);
+        in = out[k];
+    }
+    HIPC(hipGetLastError());
+}
+
 template <typename T>
 ephbte_status rt_step_impl(ephbte_plan P, int B, T *f, int64_t ldf, const void *nph, double dt,
                            int n_steps, int use_graph, hipStream_t s) {
@@ -1615,9 +1848,23 @@ ephbte_status rt_step_impl(ephbte_plan P, int B, T *f, int64_t ldf, const void *
     T *acc = static_cast<T *>(P->rk_acc.p);
     const T tdt = static_cast<T>(dt);
     enqueue_pack<T>(P, nph, s);   // the phonon occupations hold for the whole call
+    // one vector over the pair matrix: its coefficients are evaluated once
+    const int nsplit = mx_vec_split(P);
+    if (n_steps > 0 && use_mx_batch<T>(P, B)) enqueue_pair_matrix<T>(P, s);
+    const bool mx = n_steps > 0 && use_pairs(P, B) && mx_ensure<T>(P, 1, nsplit);
+    if (mx) {
+        enqueue_pair_matrix<T>(P, s);
+        double *u = static_cast<double *>(P->mx_u.p);
+        hipLaunchKernelGGL((k_mx_load<T>), dim3(static_cast<unsigned>((P->mx_nb * 64 + 255) / 256)), dim3(256), 0, s,
+                           mx_args<T>(P), (const T *)f, u, u + static_cast<int64_t>(P->mx_nb) * 64);
+        HIPC(hipGetLastError());
+    }
+    auto step = [&](hipStream_t st) {
+        if (mx) mx_rk4_step<T>(P, f, tdt, st, ua, ub, acc, nsplit);
+        else rk4_enqueue_step<T>(P, B, f, ldf, nph, tdt, st, ua, ub, acc, f, ldf, f);
+    };
     if (!use_graph || n_steps < 2) {
-        for (int k = 0; k < n_steps; ++k)
-            rk4_enqueue_step<T>(P, B, f, ldf, nph, tdt, s, ua, ub, acc, f, ldf, f);
+        for (int k = 0; k < n_steps; ++k) step(s);
         return EPHBTE_OK;
     }
     const int K = std::min(n_steps, 25);
@@ -1639,8 +1886,7 @@ ephbte_status rt_step_impl(ephbte_plan P, int B, T *f, int64_t ldf, const void *
         hipGraph_t graph = nullptr;
         HIPC(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
         try {
-            for (int k = 0; k < K; ++k)
-                rk4_enqueue_step<T>(P, B, f, ldf, nph, tdt, cs, ua, ub, acc, f, ldf, f);
+            for (int k = 0; k < K; ++k) step(cs);
         } catch (...) {
             hipGraph_t junk = nullptr;
             (void)hipStreamEndCapture(cs, &junk);
@@ -1659,8 +1905,7 @@ ephbte_status rt_step_impl(ephbte_plan P, int B, T *f, int64_t ldf, const void *
     }
     int done = 0;
     for (; done + K <= n_steps; done += K) HIPC(hipGraphLaunch(exec, cs));
-    for (; done < n_steps; ++done)
-        rk4_enqueue_step<T>(P, B, f, ldf, nph, tdt, cs, ua, ub, acc, f, ldf, f);
+    for (; done < n_steps; ++done) step(cs);
     if (!s) {
         HIPC(hipEventRecord(P->ev_b, cs));
         HIPC(hipStreamWaitEvent(s, P->ev_b, 0));
@@ -2154,7 +2399,13 @@ ephbte_status transport_impl(ephbte_plan P, const T *f0, const T *vel, double T_
                              const void *nph, double tol, int max_iter, T *x_out, double *mob,
                              int32_t *iters, double *resid, hipStream_t s) {
     const int64_t S = P->S;
-    ensure(P->tr_W, sizeof(T) * (P->E + kEntryPad), &P->ws_gen);
+    // over the pair matrix an iteration reads one value per ordered pair of
+    // states, without it one W and one partner word per entry and mode: on the
+    // 100^3 system 0.53 against 4.8 GB
+    const int nsplit = mx_vec_split(P);
+    if (use_pairs(P, 1)) ensure_fwd<T>(P, 1);   // the {hw, N} table
+    const bool mx = use_pairs(P, 1) && mx_ensure<T>(P, 3, nsplit);
+    if (!mx) ensure(P->tr_W, sizeof(T) * (P->E + kEntryPad), &P->ws_gen);
     ensure(P->tr_tau_inv, sizeof(T) * S, &P->ws_gen);
     ensure(P->tr_tau, sizeof(T) * S, &P->ws_gen);
     ensure(P->tr_rhs, sizeof(Vec4<T>) * S, &P->ws_gen);
@@ -2173,7 +2424,19 @@ ephbte_status transport_impl(ephbte_plan P, const T *f0, const T *vel, double T_
     double *red = static_cast<double *>(P->tr_red.p), *red2 = static_cast<double *>(P->tr_red2.p);
     dim3 grid(static_cast<unsigned>(grid_x(P))), block(P->block_threads);
     dim3 sg((S + 255) / 256);
-    if (P->fused)
+    const int64_t np = static_cast<int64_t>(P->mx_nb) * 64;
+    const dim3 mg(static_cast<unsigned>((np + 255) / 256)), mr(static_cast<unsigned>(P->mx_nb));
+    const double K = k_prefactor(P);
+    double *ux = static_cast<double *>(P->mx_u.p);
+    const double *p1 = static_cast<const double *>(P->mx_p1.p), *p2 = static_cast<const double *>(P->mx_p2.p);
+    if (mx) {
+        enqueue_pack<T>(P, nph, s);
+        enqueue_pair_matrix<T>(P, s);
+        hipLaunchKernelGGL((k_mx_load<T>), mg, dim3(256), 0, s, mx_args<T>(P), f0, ux, ux + np);
+        enqueue_mx_vec<T, 1>(P, ux, ux + np, nsplit, s);
+        hipLaunchKernelGGL((k_mx_tau_finish<T>), mr, dim3(64 * kMxParts), 0, s, tiled_args<T>(P), mx_args<T>(P), p1, nsplit, p2,
+                           K, (const double *)ux, (const double *)(ux + np), tinv);
+    } else if (P->fused)
         hipLaunchKernelGGL((k_transport_setup<T, true>), grid, block, 0, s, t, f0, W, (T *)nullptr,
                            tinv);
     else {
@@ -2184,6 +2447,8 @@ ephbte_status transport_impl(ephbte_plan P, const T *f0, const T *vel, double T_
     }
     hipLaunchKernelGGL((k_transport_prep<T>), sg, dim3(256), 0, s, f0, vel, (const T *)tinv,
                        static_cast<T>(1.0 / (kKb * T_K)), (int)S, tau, rhs, xa);
+    double *ua = ux, *ub = ux ? ux + 3 * np : nullptr;   // x by position, two copies
+    if (mx) hipLaunchKernelGGL((k_mx_load3<T>), mg, dim3(256), 0, s, mx_args<T>(P), (const Vec4<T> *)xa, ua);
     HIPC(hipGetLastError());
     auto mobility = [&](const Vec4<T> *x, bool with_f0, double out[10]) {
         hipLaunchKernelGGL((k_mobility_partial<T>), dim3(kRedBlocks), dim3(256), 0, s, vel, x,
@@ -2206,7 +2471,12 @@ ephbte_status transport_impl(ephbte_plan P, const T *f0, const T *vel, double T_
     int it = 0, since_best = 0;
     bool conv = false, stalled = false;
     for (it = 1; it <= max_iter; ++it) {
-        {
+        if (mx) {
+            enqueue_mx_vec<T, 3>(P, ua, ua, nsplit, s);
+            hipLaunchKernelGGL((k_mx_tr_finish<T>), mr, dim3(64 * kMxParts), 0, s, tiled_args<T>(P), mx_args<T>(P), p1, nsplit,
+                               p2, K, f0, (const Vec4<T> *)rhs, (const T *)tau, (const double *)ua, ub, xb);
+            std::swap(ua, ub);
+        } else {
             TiledArgs<T> ta = tiled_args<T>(P);
             ta.xcd = 0;
             // half-size tiles: measured 3 % faster than the forward's here
@@ -2564,6 +2834,7 @@ ephbte_status ephbte_build_channels(const ephbte_problem *problem, const ephbte_
             upload_phonon_layout<float>(P, problem, L);
             upload_pair_rows<float>(P, problem, L);
         }
+        upload_matrix_layout(P);
         {
             // 2^(j/256) rounded from extended precision
             double tab[kExpTab];

@@ -1787,6 +1787,546 @@ __global__ void k_tr_tiled_finish(TiledArgs<T> A, const Vec4<T> *__restrict__ pa
     x_new[d] = o;
 }
 
+// ---- the pair matrix ---------------------------------------------------------
+// Where a call applies one bath's collision integral more than once (RK4 steps,
+// the transport iteration, several occupation vectors), the coefficients are
+// evaluated once, summed over the modes of each pair, into a matrix over states:
+//   M[d][p] = sum over modes of |g|^2 (t + G(x + hw)),  x = e_d - e_p,
+// the in-scattering weight b of destination d from partner p.  With tables even
+// in q the out-scattering weight a of d to p is M[p][d], so one matrix serves
+//   I_d = K [ (1 - f_d) sum_p M[d][p] f_p  -  f_d sum_p M[p][d] (1 - f_p) ]
+// and, per field direction, W x of the linearised equation,
+//   (W x)_d = K [ (1 - f_d) sum_p M[d][p] x_p + f_d sum_p M[p][d] x_p ].
+// It is stored in 64 x 64 blocks (build_matrix_layout), each as 4 x 4 sub-blocks
+// of 16 x 16 values, row-major: a wave reads a sub-block as one contiguous run
+// for either use (rows for M, columns for its transpose).  Entries without a
+// pair are zero from the allocation; every pair's two entries are rewritten by
+// k_pair_matrix.  Sums over partners are held in FP64 in both precisions.
+struct MxCol {
+    int32_t j, id_t;   // block column and the block (j, row)
+};
+template <typename T> struct MxArgs {
+    T *__restrict__ m;                     // [blocks][64 x 64]
+    const int32_t *__restrict__ pos;       // [S] position of a state
+    const int32_t *__restrict__ state;     // [nb 64] state at a position, -1 past the last
+    const int32_t *__restrict__ blk;       // [nb][nb] block of (I, J), -1: none
+    const int32_t *__restrict__ row;       // [nb + 1]
+    const MxCol *__restrict__ col;         // [blocks]
+    int nb, S;
+};
+constexpr int kMxBlock = 64 * 64;
+
+// offset of row r, column c inside a block
+__device__ __forceinline__ int mx_inner(int r, int c) {
+    return ((((r >> 4) << 2) | (c >> 4)) << 8) | ((r & 15) << 4) | (c & 15);
+}
+
+// Fills the matrix from the pair records, in the forward pass's tiles and
+// pipeline (see pair_chunk); no occupations enter.  The two 8-byte stores of a
+// pair go to different rows for each lane of a q-ordered batch, so the pass is
+// bound by the store requests as well as by the exponentials.
+template <typename T, bool PADQ, int NM, bool TAB, bool QORD>
+__device__ __forceinline__ void mx_chunk(const TiledArgs<T> &A, const MxArgs<T> &X, const T *s_e,
+                                         const uint32_t *s_kq, const int32_t *s_pos, const double *s_tab, int64_t c) {
+    const int lane = threadIdx.x & 63;
+    const int nm = A.nm;
+    const int dc = QORD ? 0 : A.chunk_dest[c];
+    const int64_t beg = A.chunk_beg[c];
+    const int len = static_cast<int>(A.chunk_end[c] - beg);
+    const uint32_t *__restrict__ pb = A.pnu + beg;
+    const T *__restrict__ gb = A.g2 + beg;
+    uint32_t pn0 = pb[lane], pn1 = 0;
+    T g0[NM], g1[NM];
+#pragma unroll
+    for (int m = 0; m < NM; ++m) g0[m] = gb[min(m, nm - 1) * A.pld + lane];
+    auto batch = [&](int r, const uint32_t pn, const T (&g)[NM], uint32_t &pn_next, T (&g_next)[NM]) {
+        const bool v = r + lane < len;
+        T ed, ep;
+        uint32_t kd, kp;
+        int xd, xp;
+        if (QORD) {
+            // a masked lane takes window slot 0 as both states
+            const int wd = v ? static_cast<int>(pn & 0xffffu) : 0;
+            const int wp = v ? static_cast<int>(pn >> 16) : 0;
+            ed = s_e[wd];
+            ep = s_e[wp];
+            kd = s_kq[wd];
+            kp = s_kq[wp];
+            xd = s_pos[wd];
+            xp = s_pos[wp];
+        } else {
+            const int p = v ? static_cast<int>(pn) : dc;
+            const StateRec<T> sd = A.st[dc], sp = A.st[p];
+            ed = sd.eps;
+            ep = sp.eps;
+            kd = PADQ ? sd.kqp : sd.kq;
+            kp = PADQ ? sp.kqp : sp.kq;
+            xd = X.pos[dc];
+            xp = X.pos[p];
+        }
+        const int q = PADQ ? static_cast<int>(kp - kd) + A.qoff : q_linear(kd, kp, A.nq0, A.nq1, A.nq2);
+        const Pair2<T> *__restrict__ wq = A.hwN + static_cast<int64_t>(q) * A.tq;
+        Pair2<T> w[NM];
+#pragma unroll
+        for (int m = 0; m < NM; ++m) w[m] = wq[min(m, nm - 1) * A.tm];
+        const int bd = xd >> 6, bp = xp >> 6;
+        const int id = X.blk[bd * X.nb + bp], it = X.blk[bp * X.nb + bd];
+        __builtin_amdgcn_sched_barrier(0);
+        pn_next = pb[r + 64 + lane];
+#pragma unroll
+        for (int m = 0; m < NM; ++m) g_next[m] = gb[min(m, nm - 1) * A.pld + r + 64 + lane];
+        __builtin_amdgcn_sched_barrier(0);
+        T sa, sb;
+        pair_mode_sums<T, NM, TAB>(A, ed - ep, w, g, v, s_tab, sa, sb);
+        if (v) {
+            X.m[static_cast<int64_t>(id) * kMxBlock + mx_inner(xd & 63, xp & 63)] = sb;
+            X.m[static_cast<int64_t>(it) * kMxBlock + mx_inner(xp & 63, xd & 63)] = sa;
+        }
+    };
+    for (int r = 0; r < len; r += 128) {
+        batch(r, pn0, g0, pn1, g1);
+        if (r + 64 >= len) break;
+        batch(r + 64, pn1, g1, pn0, g0);
+    }
+}
+
+template <typename T, bool PADQ, int NM, bool TAB>
+__global__ __launch_bounds__(1024) void k_pair_matrix(TiledArgs<T> A, MxArgs<T> X) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int64_t ti = tile_of_block(A.n_tiles, A.xcd);
+    if (ti < 0) return;
+    const TileRec t = A.tiles[ti];
+    // LDS: exponential table (FP64), energies, packed k and positions of the window
+    double *s_tab = reinterpret_cast<double *>(smem);
+    T *s_e = reinterpret_cast<T *>(s_tab + (sizeof(T) == 8 ? kExpTab : 0));
+    uint32_t *s_kq = reinterpret_cast<uint32_t *>(s_e + A.lds_states);
+    int32_t *s_pos = reinterpret_cast<int32_t *>(s_kq + A.lds_states);
+    const int n = t.lds == 2 ? t.p_hi - t.p_lo + 1 : 0;
+    for (int i = threadIdx.x; i < n; i += blockDim.x) {
+        const StateRec<T> sr = A.st[t.p_lo + i];
+        s_e[i] = sr.eps;
+        s_kq[i] = PADQ ? sr.kqp : sr.kq;
+        s_pos[i] = X.pos[t.p_lo + i];
+    }
+    if constexpr (sizeof(T) == 8 && TAB)
+        for (int i = threadIdx.x; i < kExpTab; i += blockDim.x) s_tab[i] = A.e2tab[i];
+    __syncthreads();
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+    const int nw = static_cast<int>(blockDim.x >> 6);
+    for (int64_t c = t.c0 + wave; c < t.c1; c += nw) {
+        if (t.lds == 2) mx_chunk<T, PADQ, NM, TAB, true>(A, X, s_e, s_kq, s_pos, s_tab, c);
+        else mx_chunk<T, PADQ, NM, TAB, false>(A, X, s_e, s_kq, s_pos, s_tab, c);
+    }
+}
+
+// The matrix and its transpose applied to NC columns, each value read once:
+// workgroup = block row I and a share of its blocks, a wave takes whole blocks.
+// Lane (i, g) = (lane / 4, lane % 4) holds row i and columns 4 g .. 4 g + 3 of a
+// sub-block.  Rows of I: sum_p M[d][p] u1_p in registers over the wave's blocks,
+// then over the waves in order, to part1[split][position][NC].  Columns of J:
+// sum over the block's rows of M[d][p] u2_d, the share of the transposed product
+// of this block, to part2[block][64][NC]; k_mx_* finish kernels add the shares
+// of a state's block column.  Bound by the matrix bytes.
+template <typename T, int NC>
+__global__ __launch_bounds__(256) void k_mx_vec(MxArgs<T> X, const double *__restrict__ u1,
+                                                const double *__restrict__ u2, double *__restrict__ part1,
+                                                double *__restrict__ part2) {
+    __shared__ double s_r[4][64][NC];
+    const int I = blockIdx.x;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+    const int i = lane >> 2, g = lane & 3;
+    const int r0 = X.row[I], n = X.row[I + 1] - r0;
+    const int xb = r0 + static_cast<int>(static_cast<int64_t>(n) * blockIdx.y / gridDim.y);
+    const int xe = r0 + static_cast<int>(static_cast<int64_t>(n) * (blockIdx.y + 1) / gridDim.y);
+    double v2[4][NC], acc[4][NC];
+#pragma unroll
+    for (int R = 0; R < 4; ++R)
+#pragma unroll
+        for (int k = 0; k < NC; ++k) {
+            v2[R][k] = u2[(I * 64 + R * 16 + i) * NC + k];
+            acc[R][k] = 0.0;
+        }
+    for (int x = xb + wave; x < xe; x += 4) {
+        const int J = X.col[x].j;
+        const T *__restrict__ mb = X.m + static_cast<int64_t>(x) * kMxBlock + lane * 4;
+        const double *__restrict__ ub = u1 + (static_cast<int64_t>(J) * 64 + 4 * g) * NC;
+        double *__restrict__ pc = part2 + static_cast<int64_t>(x) * 64 * NC;
+#pragma unroll
+        for (int C = 0; C < 4; ++C) {
+            double a[4][NC], cs[4][NC];
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int k = 0; k < NC; ++k) {
+                    a[t][k] = ub[(C * 16 + t) * NC + k];
+                    cs[t][k] = 0.0;
+                }
+#pragma unroll
+            for (int R = 0; R < 4; ++R) {
+                const Vec4<T> w4 = *reinterpret_cast<const Vec4<T> *>(mb + (R * 4 + C) * 256);
+                const double w[4] = {static_cast<double>(w4.x), static_cast<double>(w4.y),
+                                     static_cast<double>(w4.z), static_cast<double>(w4.w)};
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+#pragma unroll
+                    for (int k = 0; k < NC; ++k) {
+                        acc[R][k] = fma(w[t], a[t][k], acc[R][k]);
+                        cs[t][k] = fma(w[t], v2[R][k], cs[t][k]);
+                    }
+            }
+            // sum over the 16 rows i: lane bits 5 and 4 each halve the four
+            // columns, bits 3 and 2 add
+            const bool h5 = (lane & 32) != 0, h4 = (lane & 16) != 0;
+#pragma unroll
+            for (int k = 0; k < NC; ++k) {
+                const double p0 = (h5 ? cs[2][k] : cs[0][k]) + __shfl_xor(h5 ? cs[0][k] : cs[2][k], 32, 64);
+                const double p1 = (h5 ? cs[3][k] : cs[1][k]) + __shfl_xor(h5 ? cs[1][k] : cs[3][k], 32, 64);
+                double s = (h4 ? p1 : p0) + __shfl_xor(h4 ? p0 : p1, 16, 64);
+                s += __shfl_xor(s, 8, 64);
+                s += __shfl_xor(s, 4, 64);
+                const int t = (h5 ? 2 : 0) + (h4 ? 1 : 0);
+                if ((lane & 12) == 0) pc[(C * 16 + 4 * g + t) * NC + k] = s;
+            }
+        }
+    }
+#pragma unroll
+    for (int R = 0; R < 4; ++R)
+#pragma unroll
+        for (int k = 0; k < NC; ++k) {
+            double s = acc[R][k];
+            s += __shfl_xor(s, 1, 64);
+            s += __shfl_xor(s, 2, 64);
+            if (g == 0) s_r[wave][R * 16 + i][k] = s;
+        }
+    __syncthreads();
+    double *__restrict__ po = part1 + (static_cast<int64_t>(blockIdx.y) * X.nb + I) * 64 * NC;
+    for (int e = threadIdx.x; e < 64 * NC; e += blockDim.x) {
+        const int r = e / NC, k = e - r * NC;
+        po[e] = ((s_r[0][r][k] + s_r[1][r][k]) + s_r[2][r][k]) + s_r[3][r][k];
+    }
+}
+
+constexpr int kMxParts = 16;   // waves of the finish kernels
+// Sums of a block row's partials (1024 threads, thread = position r and one of
+// 16 parts of the shares, so that few loads follow each other; the parts are
+// added in order): o1 over the splits, o2 over the blocks of the row's block
+// column.  Threads below 64 hold the totals of position I 64 + r.
+template <typename T, int NC>
+__device__ __forceinline__ void mx_vec_sums(const MxArgs<T> &X, const double *__restrict__ part1, int nsplit,
+                                            const double *__restrict__ part2, int I, double (&o1)[NC],
+                                            double (&o2)[NC]) {
+    __shared__ double s_q[kMxParts][2 * NC][64];
+    const int r = threadIdx.x & 63, seg = threadIdx.x >> 6;
+#pragma unroll
+    for (int k = 0; k < NC; ++k) o1[k] = o2[k] = 0.0;
+    for (int x = X.row[I] + seg; x < X.row[I + 1]; x += kMxParts) {
+        const double *__restrict__ p = part2 + (static_cast<int64_t>(X.col[x].id_t) * 64 + r) * NC;
+#pragma unroll
+        for (int k = 0; k < NC; ++k) o2[k] += p[k];
+    }
+    for (int sp = seg; sp < nsplit; sp += kMxParts) {
+        const double *__restrict__ p = part1 + ((static_cast<int64_t>(sp) * X.nb + I) * 64 + r) * NC;
+#pragma unroll
+        for (int k = 0; k < NC; ++k) o1[k] += p[k];
+    }
+#pragma unroll
+    for (int k = 0; k < NC; ++k) {
+        s_q[seg][k][r] = o1[k];
+        s_q[seg][NC + k][r] = o2[k];
+    }
+    __syncthreads();
+    if (seg == 0) {
+#pragma unroll
+        for (int k = 0; k < NC; ++k)
+#pragma unroll
+            for (int q = 1; q < kMxParts; ++q) {
+                o1[k] += s_q[q][k][r];
+                o2[k] += s_q[q][NC + k][r];
+            }
+    }
+}
+
+// A non-finite value of some state reaches every row of its blocks through the
+// blocks' zero entries.  Where a sum of d came out non-finite it is taken again
+// over d's own partners (the entry rows of the destination layout).
+template <typename T>
+__device__ void mx_own_sums(const TiledArgs<T> &A, const MxArgs<T> &X, int d, const double *__restrict__ u1,
+                            const double *__restrict__ u2, int nc, int k, double &o1, double &o2) {
+    const int xd = X.pos[d];
+    int last = -1;
+    o1 = o2 = 0.0;
+    for (int64_t e = A.chunk_beg[A.dest_chunk[d]]; e < A.chunk_beg[A.dest_chunk[d + 1]]; ++e) {
+        const int p = static_cast<int>(A.pnu[e] >> 3);
+        if (p == last) continue;
+        last = p;
+        const int xp = X.pos[p];
+        const int64_t id = X.blk[(xd >> 6) * X.nb + (xp >> 6)], it = X.blk[(xp >> 6) * X.nb + (xd >> 6)];
+        o1 += static_cast<double>(X.m[id * kMxBlock + mx_inner(xd & 63, xp & 63)]) *
+              u1[static_cast<int64_t>(xp) * nc + k];
+        o2 += static_cast<double>(X.m[it * kMxBlock + mx_inner(xp & 63, xd & 63)]) *
+              u2[static_cast<int64_t>(xp) * nc + k];
+    }
+}
+
+__device__ __forceinline__ bool mx_finite(double a, double b) { return fabs(a) + fabs(b) < 1.7e308; }
+
+// u1 = f and u2 = 1 - f by position (0 past the last state)
+template <typename T>
+__global__ void k_mx_load(MxArgs<T> X, const T *__restrict__ f, double *__restrict__ u1, double *__restrict__ u2) {
+    const int x = blockIdx.x * blockDim.x + threadIdx.x;
+    if (x >= X.nb * 64) return;
+    const int d = X.state[x];
+    u1[x] = d >= 0 ? static_cast<double>(f[d]) : 0.0;
+    u2[x] = d >= 0 ? static_cast<double>(T(1) - f[d]) : 0.0;
+}
+
+// I_d = K [(1 - f_d) o1 - f_d o2] of the loaded vector, then the epilogue of the
+// RK4 stage; the next stage's input replaces u1 and u2.  One workgroup per block
+// row.  A: the destination layout (k_mx_own_sums).
+template <typename T>
+__global__ __launch_bounds__(64 * kMxParts) void k_mx_rk_finish(TiledArgs<T> A, MxArgs<T> X, const double *__restrict__ part1,
+                                                      int nsplit, const double *__restrict__ part2, double K,
+                                                      const double *__restrict__ u1, const double *__restrict__ u2,
+                                                      double *__restrict__ n1, double *__restrict__ n2, Epi<T> E) {
+    double o1[1], o2[1];
+    mx_vec_sums<T, 1>(X, part1, nsplit, part2, blockIdx.x, o1, o2);
+    if (threadIdx.x >= 64) return;
+    const int x = blockIdx.x * 64 + threadIdx.x;
+    const int d = X.state[x];
+    if (d < 0) return;
+    if (!mx_finite(o1[0], o2[0])) mx_own_sums<T>(A, X, d, u1, u2, 1, 0, o1[0], o2[0]);
+    apply_epi(E, 0, d, X.S, static_cast<T>(K * (u2[x] * o1[0] - u1[x] * o2[0])));
+    const T y = E.mode == EPI_RK4 ? E.f_out[d] : E.u_out[d];
+    n1[x] = static_cast<double>(y);
+    n2[x] = static_cast<double>(T(1) - y);
+}
+
+// 1 / tau_d = K (o1 + o2) with u1 = f0, u2 = 1 - f0
+template <typename T>
+__global__ __launch_bounds__(64 * kMxParts) void k_mx_tau_finish(TiledArgs<T> A, MxArgs<T> X, const double *__restrict__ part1,
+                                                       int nsplit, const double *__restrict__ part2, double K,
+                                                       const double *__restrict__ u1, const double *__restrict__ u2,
+                                                       T *__restrict__ tau_inv) {
+    double o1[1], o2[1];
+    mx_vec_sums<T, 1>(X, part1, nsplit, part2, blockIdx.x, o1, o2);
+    if (threadIdx.x >= 64) return;
+    const int x = blockIdx.x * 64 + threadIdx.x;
+    const int d = X.state[x];
+    if (d < 0) return;
+    if (!mx_finite(o1[0], o2[0])) mx_own_sums<T>(A, X, d, u1, u2, 1, 0, o1[0], o2[0]);
+    tau_inv[d] = static_cast<T>(K * (o1[0] + o2[0]));
+}
+
+// D += A B on one 16 x 16 tile, A 16 x 4 and B 4 x 16 over the wave: lane
+// (j, g) = (lane % 16, lane / 16) gives A[j][g] and B[g][j] and holds
+// D[4 v + g][j] in d[v].
+#ifdef __HIP__
+typedef double mx_d4 __attribute__((vector_size(32)));
+__device__ __forceinline__ void mx_mfma(double a, double b, double (&d)[4]) {
+    mx_d4 c = {d[0], d[1], d[2], d[3]};
+    c = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+    d[0] = c[0];
+    d[1] = c[1];
+    d[2] = c[2];
+    d[3] = c[3];
+}
+#else   // a build without the matrix instruction: the same product by lane exchange
+inline void mx_mfma(double a, double b, double (&d)[4]) {
+    const int lane = threadIdx.x & 63, j = lane & 15, g = lane >> 4;
+    for (int k = 0; k < 4; ++k) {
+        const double bk = __shfl(b, 16 * k + j, 64);
+        for (int v = 0; v < 4; ++v) d[v] = fma(__shfl(a, 16 * k + 4 * v + g, 64), bk, d[v]);
+    }
+}
+#endif
+
+// The matrix and its transpose applied to 16 NCT columns on the FP64 matrix
+// cores: workgroup = block row I and a share of its blocks, wave = 16 of its
+// rows.  Per block the 64 rows of u1 and u2 ([position][16 NCT]) are staged in
+// LDS (rows padded by 4 values: the four k groups of a wave's read fall on
+// different banks); a wave reads its rows of block (I, J) and its columns of
+// block (J, I) as whole sub-block runs, once each, so the matrix passes through
+// registers only.  The k index of the instruction's step t stands for partner
+// 4 g + t of a sub-block.  Partial sums of a share go to part1 and part2
+// ([split][position][16 NCT]).  Bound by the matrix cores at 64 columns (17 GF
+// on the 100^3 system, 72 TF measured for a large product) and by the matrix
+// bytes below 32.
+template <typename T, int NCT>
+__global__ __launch_bounds__(256, 2) void k_mx_gemm(MxArgs<T> X, const double *__restrict__ u1,
+                                                    const double *__restrict__ u2, double *__restrict__ part1,
+                                                    double *__restrict__ part2) {
+    constexpr int NC = 16 * NCT, LD = NC + 4;
+    extern __shared__ __align__(16) unsigned char smem[];
+    double *s1 = reinterpret_cast<double *>(smem), *s2 = s1 + 64 * LD;
+    const int I = blockIdx.x;
+    const int lane = threadIdx.x & 63;
+    const int R = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+    const int j = lane & 15, g = lane >> 4;
+    const int r0 = X.row[I], n = X.row[I + 1] - r0;
+    const int xb = r0 + static_cast<int>(static_cast<int64_t>(n) * blockIdx.y / gridDim.y);
+    const int xe = r0 + static_cast<int>(static_cast<int64_t>(n) * (blockIdx.y + 1) / gridDim.y);
+    double acc1[NCT][4], acc2[NCT][4];
+#pragma unroll
+    for (int c = 0; c < NCT; ++c)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc1[c][v] = acc2[c][v] = 0.0;
+    for (int x = xb; x < xe; ++x) {
+        const MxCol cl = X.col[x];
+        const T *__restrict__ m1 = X.m + static_cast<int64_t>(x) * kMxBlock + R * 1024 + j * 16 + 4 * g;
+        const T *__restrict__ m2 = X.m + static_cast<int64_t>(cl.id_t) * kMxBlock + R * 256 + g * 64 + j;
+        Vec4<T> a1[4];
+        T a2[4][4];
+#pragma unroll
+        for (int C = 0; C < 4; ++C) {
+            a1[C] = *reinterpret_cast<const Vec4<T> *>(m1 + C * 256);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) a2[C][t] = m2[C * 1024 + t * 16];
+        }
+        __syncthreads();
+        const double2 *__restrict__ g1 = reinterpret_cast<const double2 *>(u1 + static_cast<int64_t>(cl.j) * 64 * NC);
+        const double2 *__restrict__ g2 = reinterpret_cast<const double2 *>(u2 + static_cast<int64_t>(cl.j) * 64 * NC);
+#pragma unroll
+        for (int e = 0; e < 8 * NCT / 4; ++e) {
+            const int idx = e * 256 + static_cast<int>(threadIdx.x);
+            const int r = idx / (NC / 2), k = idx - r * (NC / 2);
+            *reinterpret_cast<double2 *>(s1 + r * LD + 2 * k) = g1[idx];
+            *reinterpret_cast<double2 *>(s2 + r * LD + 2 * k) = g2[idx];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int C = 0; C < 4; ++C) {
+            const double w[4] = {static_cast<double>(a1[C].x), static_cast<double>(a1[C].y),
+                                 static_cast<double>(a1[C].z), static_cast<double>(a1[C].w)};
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const int o = (C * 16 + 4 * g + t) * LD + j;
+                const double wt = static_cast<double>(a2[C][t]);
+#pragma unroll
+                for (int c = 0; c < NCT; ++c) {
+                    mx_mfma(w[t], s1[o + 16 * c], acc1[c]);
+                    mx_mfma(wt, s2[o + 16 * c], acc2[c]);
+                }
+            }
+        }
+    }
+    const int64_t base = (static_cast<int64_t>(blockIdx.y) * X.nb + I) * 64 + R * 16;
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int c = 0; c < NCT; ++c) {
+            part1[(base + 4 * v + g) * NC + 16 * c + j] = acc1[c][v];
+            part2[(base + 4 * v + g) * NC + 16 * c + j] = acc2[c][v];
+        }
+}
+
+// u1 = f and u2 = 1 - f of nb vectors by position, NC columns (0 past the last
+// vector and state): workgroup = 64 positions x 16 columns, turned in LDS
+template <typename T>
+__global__ __launch_bounds__(256) void k_mx_load_batch(MxArgs<T> X, const T *__restrict__ f, int64_t ldf, int nvec,
+                                                       int NC, double *__restrict__ u1, double *__restrict__ u2) {
+    __shared__ T s_f[16][65];
+    const int x0 = blockIdx.x * 64, c0 = blockIdx.y * 16;
+    const int r = threadIdx.x & 63;
+    const int d = X.state[x0 + r];
+    for (int c = threadIdx.x >> 6; c < 16; c += 4)
+        s_f[c][r] = d >= 0 && c0 + c < nvec ? f[static_cast<int64_t>(c0 + c) * ldf + d] : T(0);
+    __syncthreads();
+    const int c = threadIdx.x & 15;
+    for (int q = threadIdx.x >> 4; q < 64; q += 16) {
+        const bool in = X.state[x0 + q] >= 0 && c0 + c < nvec;
+        const T v = s_f[c][q];
+        const int64_t o = static_cast<int64_t>(x0 + q) * NC + c0 + c;
+        u1[o] = static_cast<double>(v);
+        u2[o] = in ? static_cast<double>(T(1) - v) : 0.0;
+    }
+}
+
+// I = K [(1 - f) o1 - f o2] per state and vector b0 + column, then the epilogue;
+// workgroup = 64 positions x 16 columns
+template <typename T>
+__global__ __launch_bounds__(256) void k_mx_batch_finish(TiledArgs<T> A, MxArgs<T> X,
+                                                         const double *__restrict__ part1,
+                                                         const double *__restrict__ part2, int nsplit, int NC, int b0,
+                                                         int nvec, double K, const double *__restrict__ u1,
+                                                         const double *__restrict__ u2, const T *__restrict__ f,
+                                                         int64_t ldf, Epi<T> E) {
+    __shared__ double s_o[2][16][65];
+    const int x0 = blockIdx.x * 64, c0 = blockIdx.y * 16;
+    const int64_t np = static_cast<int64_t>(X.nb) * 64 * NC;
+    {
+        const int c = threadIdx.x & 15;
+        for (int q = threadIdx.x >> 4; q < 64; q += 16) {
+            const int64_t o = static_cast<int64_t>(x0 + q) * NC + c0 + c;
+            double o1 = 0.0, o2 = 0.0;
+            for (int sp = 0; sp < nsplit; ++sp) {
+                o1 += part1[sp * np + o];
+                o2 += part2[sp * np + o];
+            }
+            s_o[0][c][q] = o1;
+            s_o[1][c][q] = o2;
+        }
+    }
+    __syncthreads();
+    const int q = threadIdx.x & 63;
+    const int d = X.state[x0 + q];
+    if (d < 0) return;
+    for (int c = threadIdx.x >> 6; c < 16 && c0 + c < nvec; c += 4) {
+        double o1 = s_o[0][c][q], o2 = s_o[1][c][q];
+        if (!mx_finite(o1, o2)) mx_own_sums<T>(A, X, d, u1, u2, NC, c0 + c, o1, o2);
+        const int b = b0 + c0 + c;
+        const T fd = f[static_cast<int64_t>(b) * ldf + d];
+        apply_epi(E, b, d, X.S,
+                  static_cast<T>(K * (static_cast<double>(T(1) - fd) * o1 - static_cast<double>(fd) * o2)));
+    }
+}
+
+// x by position, three components each
+template <typename T>
+__global__ void k_mx_load3(MxArgs<T> X, const Vec4<T> *__restrict__ x, double *__restrict__ u) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= X.nb * 64) return;
+    const int d = X.state[i];
+    Vec4<T> v;
+    v.x = v.y = v.z = T(0);
+    if (d >= 0) v = x[d];
+    u[3 * i] = static_cast<double>(v.x);
+    u[3 * i + 1] = static_cast<double>(v.y);
+    u[3 * i + 2] = static_cast<double>(v.z);
+}
+
+// x_new_d = tau_d (rhs_d + K [(1 - f0_d) o1 + f0_d o2]); u holds x by position
+// and the next iterate goes to un.
+template <typename T>
+__global__ __launch_bounds__(64 * kMxParts) void k_mx_tr_finish(TiledArgs<T> A, MxArgs<T> X, const double *__restrict__ part1,
+                                                      int nsplit, const double *__restrict__ part2, double K,
+                                                      const T *__restrict__ f0, const Vec4<T> *__restrict__ rhs,
+                                                      const T *__restrict__ tau, const double *__restrict__ u,
+                                                      double *__restrict__ un, Vec4<T> *__restrict__ x_new) {
+    double o1[3], o2[3];
+    mx_vec_sums<T, 3>(X, part1, nsplit, part2, blockIdx.x, o1, o2);
+    if (threadIdx.x >= 64) return;
+    const int x = blockIdx.x * 64 + threadIdx.x;
+    const int d = X.state[x];
+    if (d < 0) return;
+    const double f = static_cast<double>(f0[d]), t = static_cast<double>(tau[d]);
+    const Vec4<T> r = rhs[d];
+    const double rr[3] = {static_cast<double>(r.x), static_cast<double>(r.y), static_cast<double>(r.z)};
+    T y[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        if (!mx_finite(o1[k], o2[k])) mx_own_sums<T>(A, X, d, u, u, 3, k, o1[k], o2[k]);
+        y[k] = static_cast<T>(t * (rr[k] + K * ((1.0 - f) * o1[k] + f * o2[k])));
+        un[3 * x + k] = static_cast<double>(y[k]);
+    }
+    Vec4<T> o;
+    o.x = y[0];
+    o.y = y[1];
+    o.z = y[2];
+    o.w = T(0);
+    x_new[d] = o;
+}
+
 // ---- forward, batched (B vectors in one pass) -----------------------------
 // Workgroup = batch tile: up to DPW destinations per wave, consecutive
 // destinations sharing a partner window.  The window is walked in sub-tiles

@@ -621,6 +621,79 @@ int64_t row_of(const RowKey &k, int32_t d, int32_t p) {
     return q;
 }
 
+bool build_matrix_layout(int32_t S, const std::vector<int64_t> &row_ptr, const std::vector<uint32_t> &partner,
+                         MatrixLayout *out) {
+    *out = MatrixLayout();
+    const int64_t nb = (static_cast<int64_t>(S) + kMxTile - 1) / kMxTile;
+    const int64_t np = static_cast<int64_t>(partner.size());
+    if (np == 0 || nb > kMxMaxRows) return false;
+    // connected components; each is named by its smallest state
+    std::vector<int32_t> root(static_cast<size_t>(S));
+    std::iota(root.begin(), root.end(), 0);
+    auto find = [&](int32_t x) {
+        while (root[x] != x) {
+            root[x] = root[root[x]];
+            x = root[x];
+        }
+        return x;
+    };
+    for (int32_t d = 0; d < S; ++d) {
+        int32_t r = find(d);
+        for (int64_t x = row_ptr[d]; x < row_ptr[d + 1]; ++x) {
+            const int32_t p = static_cast<int32_t>(partner[x]);
+            if (root[p] == r) continue;
+            const int32_t q = find(p);
+            if (q < r) {
+                root[r] = q;
+                r = q;
+            } else {
+                root[q] = r;
+            }
+        }
+    }
+    std::vector<int64_t> key(static_cast<size_t>(S));
+    for (int32_t d = 0; d < S; ++d) key[d] = (static_cast<int64_t>(find(d)) << 32) | d;
+    std::sort(key.begin(), key.end());
+    MatrixLayout m;
+    m.nb = static_cast<int32_t>(nb);
+    m.pos.resize(static_cast<size_t>(S));
+    m.state.assign(static_cast<size_t>(nb * kMxTile), -1);
+    for (int32_t i = 0; i < S; ++i) {
+        const int32_t d = static_cast<int32_t>(key[i] & 0xffffffff);
+        m.state[i] = d;
+        m.pos[d] = i;
+    }
+    std::vector<uint8_t> mark(static_cast<size_t>(nb * nb), 0);
+    parallel_ranges(S, host_threads(), [&](int, int64_t b, int64_t e) {
+        for (int64_t d = b; d < e; ++d) {
+            const int64_t I = m.pos[d] / kMxTile;
+            for (int64_t x = row_ptr[d]; x < row_ptr[d + 1]; ++x) {
+                const int64_t J = m.pos[partner[x]] / kMxTile;
+                __atomic_store_n(&mark[static_cast<size_t>(I * nb + J)], uint8_t(1), __ATOMIC_RELAXED);
+                __atomic_store_n(&mark[static_cast<size_t>(J * nb + I)], uint8_t(1), __ATOMIC_RELAXED);
+            }
+        }
+    });
+    m.blk.assign(static_cast<size_t>(nb * nb), -1);
+    m.row.assign(static_cast<size_t>(nb) + 1, 0);
+    for (int64_t I = 0; I < nb; ++I) {
+        for (int64_t J = 0; J < nb; ++J)
+            if (mark[static_cast<size_t>(I * nb + J)]) {
+                m.blk[static_cast<size_t>(I * nb + J)] = static_cast<int32_t>(m.col.size());
+                m.col.push_back(static_cast<int32_t>(J));
+            }
+        m.row[I + 1] = static_cast<int32_t>(m.col.size());
+    }
+    const int64_t n = m.n_blocks();
+    if (n > kMxSmall && n * kMxTile * kMxTile > kMxSparse * np) return false;
+    m.col_t.resize(static_cast<size_t>(n));
+    for (int64_t I = 0; I < nb; ++I)
+        for (int32_t x = m.row[I]; x < m.row[I + 1]; ++x)
+            m.col_t[x] = m.blk[static_cast<size_t>(m.col[x] * nb + I)];
+    *out = std::move(m);
+    return true;
+}
+
 PairOrder order_pair_tiles(const ChunkTable &pc, const std::vector<Tile> &tiles,
                            const std::vector<uint32_t> &partner, const RowKey &rk, int chunks_per_tile,
                            int64_t max_chunk) {

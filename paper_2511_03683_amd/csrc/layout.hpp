@@ -166,6 +166,30 @@ PairOrder order_pair_tiles(const ChunkTable &pc, const std::vector<Tile> &tiles,
                            const std::vector<uint32_t> &partner, const RowKey &rk, int chunks_per_tile,
                            int64_t max_chunk);
 
+// Block structure of the pair matrix (the weights of every state pair as a
+// matrix over states, stored in dense 64 x 64 blocks).  The states are put in
+// an order that keeps those that scatter into each other together (connected
+// components of the pairs, each in state order), cut into blocks of 64
+// positions; a block (I, J) is stored when some pair has its states in I and
+// J, and then (J, I) is stored too.
+constexpr int32_t kMxTile = 64;
+struct MatrixLayout {
+    int32_t nb = 0;                   // block rows
+    std::vector<int32_t> pos;         // [S] position of each state
+    std::vector<int32_t> state;       // [nb 64] state at each position, -1 past the last
+    std::vector<int32_t> blk;         // [nb][nb] stored block of (I, J), -1: none
+    std::vector<int32_t> row;         // [nb + 1] blocks of row I: [row[I], row[I + 1]), by ascending J
+    std::vector<int32_t> col, col_t;  // [blocks] J of the block and the block (J, I)
+    int64_t n_blocks() const { return static_cast<int64_t>(col.size()); }
+};
+// False (and an empty layout) where the matrix would not pay: more than
+// kMxMaxRows block rows (the block table is nb^2), or more than kMxSparse
+// stored values per pair in a matrix of more than kMxSmall blocks.
+constexpr int32_t kMxMaxRows = 4096;
+constexpr int64_t kMxSparse = 8, kMxSmall = 256;
+bool build_matrix_layout(int32_t S, const std::vector<int64_t> &row_ptr, const std::vector<uint32_t> &partner,
+                         MatrixLayout *out);
+
 // Runs fn(t, begin, end) over [0, n) split into contiguous ranges on up to
 // `threads` host threads (deterministic partition).
 void parallel_ranges(int64_t n, int threads,

@@ -1,0 +1,149 @@
+"""The pair matrix (coefficients summed per state pair in 64 x 64 blocks) behind
+the forms that apply one bath more than once: RK4 steps, the transport iteration
+and several occupation vectors.  Sizes around the block edge, vector counts
+around the 16 columns of a matrix instruction and the 64 of a group, states whose
+components interleave, and non-finite occupations, against the oracle.
+
+Tolerances are the parity tests' (1e-10 FP64, 1e-5 FP32, normwise): a sum of n
+products in FP64 is within n 1.1e-16 of its gross value, and the systems here
+have at most a few hundred partners a state.
+"""
+import copy
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import oracle  # noqa: E402
+import synth  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+TOL = {"f64": 1e-10, "f32": 1e-5}
+DT = {"f64": torch.float64, "f32": torch.float32}
+
+
+@pytest.fixture(scope="module")
+def E():
+    assert torch.cuda.is_available(), "GPU tests need a HIP device"
+    import paper_2511_03683_amd as lib
+    return lib
+
+
+def dev(a, dtype="f64"):
+    return torch.as_tensor(np.ascontiguousarray(a), dtype=DT[dtype], device="cuda:0")
+
+
+def host(t):
+    torch.cuda.synchronize()
+    return t.detach().cpu().numpy().astype(np.float64)
+
+
+def full_system(n_states, kn, n_modes=3, seed=5):
+    """n_states random states on a kn^3 grid, every pair and mode a channel."""
+    s = synth.random_channel_system(n_states=n_states, n_channels=1, kn=kn, n_modes=n_modes, seed=seed)
+    i, j = np.triu_indices(s.n_states, 1)
+    s.ch_i = np.repeat(i, n_modes).astype(np.int32)
+    s.ch_j = np.repeat(j, n_modes).astype(np.int32)
+    s.ch_nu = np.tile(np.arange(n_modes), i.size).astype(np.int8)
+    s.g2 = synth.lognormal_g2(s.ch_i, s.ch_j, s.ch_nu, seed)
+    return s
+
+
+def two_components(n, kn=6, seed=9):
+    """Two all-pairs components whose states alternate in the caller's order."""
+    s = full_system(2 * n, kn, seed=seed)
+    keep = (s.ch_i % 2) == (s.ch_j % 2)
+    s.ch_i, s.ch_j, s.ch_nu, s.g2 = s.ch_i[keep], s.ch_j[keep], s.ch_nu[keep], s.g2[keep]
+    return s
+
+
+def rounded(s, dtype):
+    if dtype == "f64":
+        return s
+    r = copy.copy(s)
+    for k in ("eps", "hw", "g2"):
+        setattr(r, k, getattr(s, k).astype(np.float32).astype(np.float64))
+    return r
+
+
+def cast(a, dtype):
+    return a if dtype == "f64" else a.astype(np.float32).astype(np.float64)
+
+
+def nerr(x, ref, scale=0.0):
+    return float(np.abs(x - ref).max() / max(np.abs(ref).max(), scale))
+
+
+def gross(r, f, nph):
+    return 1e-2 * max(x.max() for x in oracle.collision_inout(r, f, nph))
+
+
+@pytest.mark.parametrize("S,B,dtype", [(2, 2, "f64"), (63, 7, "f64"), (64, 16, "f64"), (65, 17, "f32"), (129, 33, "f64"),
+                                       (200, 48, "f32"), (130, 64, "f64"), (66, 65, "f64"), (128, 130, "f32")])
+def test_vectors_through_the_matrix(E, S, B, dtype):
+    s = full_system(S, 6)
+    rng = np.random.default_rng(S)
+    F, nph = cast(rng.uniform(size=(B, S)), dtype), cast(s.nph(300.0), dtype)
+    plan = E.build_channels(s, dtype=dtype, device=0)
+    out = torch.full((B, S + 3), 7.0, dtype=DT[dtype], device="cuda:0")
+    E.collision_integral(plan, dev(F, dtype), dev(nph, dtype), out=out[:, :S])
+    got = host(out)
+    assert np.all(got[:, S:] == 7.0)
+    r = rounded(s, dtype)
+    for b in sorted({0, 1, B // 2, B - 1}):
+        ref = oracle.collision(r, F[b], nph)
+        assert nerr(got[b, :S], ref, gross(r, F[b], nph)) <= TOL[dtype], b
+    plan.close()
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+def test_interleaved_components(E, dtype):
+    """The matrix orders states by component; results come back in the caller's
+    order, for vectors, RK4 steps (eager and from a graph) and transport."""
+    s = two_components(70)
+    S = s.n_states
+    rng = np.random.default_rng(3)
+    F, nph = cast(rng.uniform(size=(5, S)), dtype), cast(s.nph(300.0), dtype)
+    plan = E.build_channels(s, dtype=dtype, device=0)
+    r = rounded(s, dtype)
+    got = host(E.collision_integral(plan, dev(F, dtype), dev(nph, dtype)))
+    for b in range(5):
+        assert nerr(got[b], oracle.collision(r, F[b], nph), gross(r, F[b], nph)) <= TOL[dtype]
+    ref = F[0].copy()
+    for _ in range(3):
+        ref = oracle.rk4_step(r, ref, nph, 0.01)
+    for graph in (False, True):
+        f = dev(F[0], dtype)
+        E.rt_step(plan, f, dev(nph, dtype), 0.01, 3, use_graph=graph)
+        assert nerr(host(f), ref) <= TOL[dtype]
+    f0 = cast(synth.fermi_dirac(s.eps, 0.1, 300.0), dtype)
+    vel = cast(rng.normal(size=(S, 3)), dtype)
+    out = E.iterate_transport(plan, dev(f0, dtype), dev(vel, dtype), 300.0, dev(nph, dtype), tol=0.0, max_iter=4, want_x=True)
+    want = oracle.transport_solve(r, f0, vel, 300.0, nph, max_iter=4, stop_on_tol=False)
+    assert nerr(out["mu"], want["mu"]) <= TOL[dtype]
+    assert nerr(host(out["x"]), want["x"]) <= TOL[dtype]
+    plan.close()
+
+
+@pytest.mark.parametrize("bad", [np.nan, np.inf])
+def test_non_finite_occupation_reaches_its_partners_only(E, bad):
+    """Zero entries of a block do not carry a non-finite value to states that
+    have no channel with it."""
+    s = synth.random_channel_system(n_states=60, n_channels=700, n_modes=1, seed=3)
+    S, B, p = s.n_states, 9, 17
+    F = np.random.default_rng(4).uniform(size=(B, S))
+    nph = s.nph(300.0)
+    plan = E.build_channels(s, device=0)
+    assert E.plan_info(plan)["pair_records"] > 0
+    clean = host(E.collision_integral(plan, dev(F), dev(nph)))
+    F[2, p] = bad
+    got = host(E.collision_integral(plan, dev(F), dev(nph)))
+    partners = set(s.ch_j[s.ch_i == p]) | set(s.ch_i[s.ch_j == p]) | {p}
+    assert 1 < len(partners) < S
+    touched = np.isin(np.arange(S), list(partners))
+    assert not np.isfinite(got[2, touched]).any()
+    assert nerr(got[2, ~touched], clean[2, ~touched], np.abs(clean[2]).max()) <= 1e-14
+    rest = np.arange(B) != 2
+    assert np.array_equal(got[rest], clean[rest])
+    plan.close()
