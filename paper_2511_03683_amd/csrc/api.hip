@@ -179,7 +179,7 @@ struct ephbte_plan_s {
     int64_t mx_blocks = 0;
     int32_t *mx_pos = nullptr, *mx_state = nullptr, *mx_blk = nullptr, *mx_row = nullptr;
     MxCol *mx_col = nullptr;
-    DevBuf mx_m, mx_u, mx_p1, mx_p2;
+    DevBuf mx_m, mx_g, mx_u, mx_p1, mx_p2;
     // batched pass: tiles of destinations and per-destination sub-tile offsets
     BTileRec *btiles = nullptr;
     int64_t *sub_off = nullptr;
@@ -245,7 +245,7 @@ struct ephbte_plan_s {
                              &adj_U, &adj_la, &adj_lb, &adj_acc, &adj_g, &adj_f, &cp_Ma, &cp_Mb,
                              &cp_acc, &cp_rate, &ph_part, &ph_tab4, &ca_ckf, &ca_ckN, &ca_U, &ca_M,
                              &ca_gf, &ca_gN, &ca_a, &ca_b, &ca_uf, &ca_uN, &ca_sf, &ca_sN, &ca_mu,
-                             &bs_x, &bs_y, &nvec, &mx_m, &mx_u, &mx_p1, &mx_p2};
+                             &bs_x, &bs_y, &nvec, &mx_m, &mx_g, &mx_u, &mx_p1, &mx_p2};
         for (auto *x : w) b += x->bytes;
         return b;
     }
@@ -357,7 +357,7 @@ void free_plan(ephbte_plan P) {
                    &P->adj_g,  &P->adj_f, &P->cp_Ma, &P->cp_Mb, &P->cp_acc, &P->cp_rate, &P->ph_part,
                    &P->ph_tab4, &P->ca_ckf, &P->ca_ckN, &P->ca_U, &P->ca_M, &P->ca_gf, &P->ca_gN, &P->ca_a,
                    &P->ca_b, &P->ca_uf, &P->ca_uN, &P->ca_sf, &P->ca_sN, &P->ca_mu, &P->bs_x, &P->bs_y, &P->nvec,
-                   &P->mx_m, &P->mx_u, &P->mx_p1, &P->mx_p2};
+                   &P->mx_m, &P->mx_g, &P->mx_u, &P->mx_p1, &P->mx_p2};
     for (auto *b : w) dfree(b->p);
     if (P->host_red) (void)hipHostFree(P->host_red);
     if (P->ev_a) (void)hipEventDestroy(P->ev_a);
@@ -1035,16 +1035,28 @@ double k_prefactor(ephbte_plan P) {
     return 2.0 * kPi / (kHbar * P->nqnorm) / (P->sigma * std::sqrt(2.0 * kPi));
 }
 
+// Waves of k_mx_vec: those the device holds at once (12 a compute unit with one
+// column, 8 with three, by their registers), each with an equal run of blocks
+int mx_vec_waves(ephbte_plan P, int nc) {
+    const int64_t groups = std::min<int64_t>((P->mx_blocks + 3) / 4, (nc == 1 ? 3 : 2) * static_cast<int64_t>(P->n_cu));
+    return static_cast<int>(4 * std::max<int64_t>(groups, 1));
+}
+MxRuns mx_runs(ephbte_plan P, int nc) {
+    const int W = mx_vec_waves(P, nc), n = static_cast<int>(P->mx_blocks);
+    return MxRuns{W, n / W, n % W};
+}
+
 // The matrix and its partials for nc columns, or false where the plan has no
 // matrix or the device memory for it is not there (the caller then takes the
-// pass without one).  Single-vector forms keep the layout the tuning chose.
-template <typename T> bool mx_ensure(ephbte_plan P, int nc, int nsplit) {
+// pass without one).
+template <typename T> bool mx_ensure(ephbte_plan P, int nc) {
     if (!P->mx_ok) return false;
     const size_t pos = static_cast<size_t>(P->mx_nb) * 64;
+    const size_t waves = static_cast<size_t>(std::max(mx_vec_waves(P, 1), nc * mx_vec_waves(P, nc)));
     try {
         ensure_zeroed(P, P->mx_m, sizeof(T) * static_cast<size_t>(P->mx_blocks) * kMxBlock);
         ensure(P->mx_u, sizeof(double) * pos * 4 * static_cast<size_t>(nc), &P->ws_gen);
-        ensure(P->mx_p1, sizeof(double) * pos * static_cast<size_t>(nsplit) * nc, &P->ws_gen);
+        ensure(P->mx_p1, sizeof(double) * (waves * 64 + pos * static_cast<size_t>(nc)), &P->ws_gen);
         ensure(P->mx_p2, sizeof(double) * static_cast<size_t>(P->mx_blocks) * 64 * nc, &P->ws_gen);
     } catch (const std::bad_alloc &) {
         return false;
@@ -1052,11 +1064,11 @@ template <typename T> bool mx_ensure(ephbte_plan P, int nc, int nsplit) {
     return true;
 }
 
-// Workgroups per block row of k_mx_vec: about eight blocks each (two a wave),
-// or one a wave where the rows alone would leave compute units idle.
-int mx_vec_split(ephbte_plan P) {
-    const int per = static_cast<int64_t>(P->mx_nb) * ((P->mx_max_row + 7) / 8) >= 2 * P->n_cu ? 8 : 4;
-    return std::max(1, (P->mx_max_row + per - 1) / per);
+// LDS of the passes between pair records and the matrix: energy, packed k and
+// position per window state, and the exponential table
+size_t pair_matrix_lds(ephbte_plan P) {
+    const size_t es = P->dtype == EPHBTE_F64 ? 8 : 4;
+    return static_cast<size_t>(P->pr_lds_states) * (es + 8) + (es == 8 ? kExpTab * sizeof(double) : 0);
 }
 
 // Fills the matrix for the {hw, N} table packed last.
@@ -1064,7 +1076,7 @@ template <typename T> void enqueue_pair_matrix(ephbte_plan P, hipStream_t s) {
     const TiledArgs<T> a = pair_args<T>(P);
     const MxArgs<T> x = mx_args<T>(P);
     const dim3 grid(static_cast<unsigned>(P->n_pr_tiles)), block(1024);
-    const size_t shm = static_cast<size_t>(P->pr_lds_states) * (sizeof(T) + 8) + (sizeof(T) == 8 ? kExpTab * 8 : 0);
+    const size_t shm = pair_matrix_lds(P);
     auto go = [&](auto nmc) {
         constexpr int NM = decltype(nmc)::value;
         const bool tab = sizeof(T) == 8 && P->exp_table;
@@ -1084,10 +1096,10 @@ template <typename T> void enqueue_pair_matrix(ephbte_plan P, hipStream_t s) {
 
 // M u1 and the transposed product with u2 for NC columns, as partials
 template <typename T, int NC>
-void enqueue_mx_vec(ephbte_plan P, const double *u1, const double *u2, int nsplit, hipStream_t s) {
-    hipLaunchKernelGGL((k_mx_vec<T, NC>), dim3(static_cast<unsigned>(P->mx_nb), static_cast<unsigned>(nsplit)),
-                       dim3(256), 0, s, mx_args<T>(P), u1, u2, static_cast<double *>(P->mx_p1.p),
-                       static_cast<double *>(P->mx_p2.p));
+void enqueue_mx_vec(ephbte_plan P, const double *u1, const double *u2, bool rev, hipStream_t s) {
+    hipLaunchKernelGGL((k_mx_vec<T, NC>), dim3(static_cast<unsigned>(mx_vec_waves(P, NC) / 4)), dim3(256), 0, s,
+                       static_cast<const T *>(P->mx_m.p), (const MxCol *)P->mx_col, mx_runs(P, NC), u1, u2,
+                       static_cast<double *>(P->mx_p1.p), static_cast<double *>(P->mx_p2.p), rev ? 1 : 0);
     HIPC(hipGetLastError());
 }
 
@@ -1101,6 +1113,11 @@ int mx_columns(int B) { return 16 * ((std::min(B, 64) + 15) / 16); }
 int mx_gemm_split(ephbte_plan P) {
     const int want = (6 * P->n_cu + P->mx_nb - 1) / std::max(P->mx_nb, 1);
     return std::max(1, std::min({want, 8, P->mx_max_row / 2}));
+}
+
+// workgroups of mx_row_of_block
+unsigned mx_row_grid(ephbte_plan P, int nsplit) {
+    return static_cast<unsigned>(8 * ((P->mx_nb + 7) / 8) * nsplit);
 }
 
 size_t mx_gemm_lds(int NC) { return 2 * 64 * static_cast<size_t>(NC + 4) * sizeof(double); }
@@ -1134,20 +1151,24 @@ template <typename T> bool use_mx_batch(ephbte_plan P, int B) {
            P->mx_p1.bytes >= 2 * cells * mx_gemm_split(P);
 }
 
-// part1 += M u1, part2 += M^T u2 for NC columns
+// M u1 and M^T u2 for NC columns (rows of ld values), 64 columns a launch
 template <typename T>
 void enqueue_mx_gemm(ephbte_plan P, int NC, const double *u1, const double *u2, double *p1, double *p2, int nsplit,
                      hipStream_t s) {
-    const dim3 grid(static_cast<unsigned>(P->mx_nb), static_cast<unsigned>(nsplit));
+    const dim3 grid(mx_row_grid(P, nsplit));
     const MxArgs<T> x = mx_args<T>(P);
-    auto go = [&](auto nct) {
-        constexpr int NCT = decltype(nct)::value;
-        hipLaunchKernelGGL((k_mx_gemm<T, NCT>), grid, dim3(256), mx_gemm_lds(NC), s, x, u1, u2, p1, p2);
-    };
-    if (NC == 16) go(std::integral_constant<int, 1>{});
-    else if (NC == 32) go(std::integral_constant<int, 2>{});
-    else if (NC == 48) go(std::integral_constant<int, 3>{});
-    else go(std::integral_constant<int, 4>{});
+    for (int c0 = 0; c0 < NC; c0 += 64) {
+        const int n = std::min(64, NC - c0);
+        auto go = [&](auto nct) {
+            constexpr int NCT = decltype(nct)::value;
+            hipLaunchKernelGGL((k_mx_gemm<T, NCT>), grid, dim3(512), mx_gemm_lds(n), s, x, u1, u2, NC, c0, nsplit,
+                               p1, p2);
+        };
+        if (n == 16) go(std::integral_constant<int, 1>{});
+        else if (n == 32) go(std::integral_constant<int, 2>{});
+        else if (n == 48) go(std::integral_constant<int, 3>{});
+        else go(std::integral_constant<int, 4>{});
+    }
     HIPC(hipGetLastError());
 }
 
@@ -1166,11 +1187,107 @@ void enqueue_forward_mx(ephbte_plan P, int B, const T *f, int64_t ldf, const Epi
         const int64_t kt = b0 == 0 ? ktime_begin(P, s) : -1;
         enqueue_mx_gemm<T>(P, NC, u1, u2, p1, p2, nsplit, s);
         ktime_end(P, s, kt);
-        hipLaunchKernelGGL((k_mx_batch_finish<T>), grid, dim3(256), 0, s, tiled_args<T>(P), mx_args<T>(P),
+        hipLaunchKernelGGL((k_mx_batch_finish<T>), grid, dim3(1024), 0, s, tiled_args<T>(P), mx_args<T>(P),
                            (const double *)p1, (const double *)p2, nsplit, NC, b0, nv, k_prefactor(P),
                            (const double *)u1, (const double *)u2, f, ldf, E);
     }
     HIPC(hipGetLastError());
+}
+
+// dL/d|g|^2 from G over the pair records (gg2_mode 1 writes, 2 adds)
+template <typename T> void enqueue_mx_gg2(ephbte_plan P, const T *g, double *gg2, int gg2_mode, hipStream_t s) {
+    const TiledArgs<T> a = pair_args<T>(P);
+    const MxArgs<T> x = mx_args<T>(P);
+    const dim3 grid(static_cast<unsigned>(P->n_pr_tiles)), block(1024);
+    const size_t shm = pair_matrix_lds(P);
+    auto go = [&](auto nmc) {
+        constexpr int NM = decltype(nmc)::value;
+        const bool tab = sizeof(T) == 8 && P->exp_table;
+        const int32_t *ch = P->pr_chan, *c0 = P->pr_ch0;
+        if (P->padq && tab)
+            hipLaunchKernelGGL((k_mx_gg2<T, true, NM, true>), grid, block, shm, s, a, x, g, ch, c0, gg2, gg2_mode);
+        else if (P->padq)
+            hipLaunchKernelGGL((k_mx_gg2<T, true, NM, false>), grid, block, shm, s, a, x, g, ch, c0, gg2, gg2_mode);
+        else if (tab)
+            hipLaunchKernelGGL((k_mx_gg2<T, false, NM, true>), grid, block, shm, s, a, x, g, ch, c0, gg2, gg2_mode);
+        else
+            hipLaunchKernelGGL((k_mx_gg2<T, false, NM, false>), grid, block, shm, s, a, x, g, ch, c0, gg2, gg2_mode);
+    };
+    if (P->nm <= 1) go(std::integral_constant<int, 1>{});
+    else if (P->nm <= 2) go(std::integral_constant<int, 2>{});
+    else if (P->nm <= 3) go(std::integral_constant<int, 3>{});
+    else if (P->nm <= 4) go(std::integral_constant<int, 4>{});
+    else if (P->nm <= 6) go(std::integral_constant<int, 6>{});
+    else go(std::integral_constant<int, 8>{});
+    HIPC(hipGetLastError());
+}
+
+// Reverse pass of B >= 2 vectors sharing one bath over the pair matrix, in groups
+// of 64 vectors (false: not available for this plan; the caller takes another
+// pass).  The {hw, N} table must already be packed.  FP32 plans below 8 vectors
+// keep one pass per vector where dL/d|g|^2 is asked for (its FP32 terms are then
+// added in FP64, one vector at a time).
+template <typename T>
+bool enqueue_vjp_mx(ephbte_plan P, int B, const T *f, int64_t ldf, const T *lam, int64_t ldl, T *gf, int64_t ldgf,
+                    double *gg2, int gg2_mode, hipStream_t s) {
+    constexpr bool kF32 = sizeof(T) == 4;
+    const int Vm = mx_columns(B), nsplit = mx_gemm_split(P);
+    const size_t outer_lds = 64 * static_cast<size_t>(2 * Vm + 4) * sizeof(double);
+    if (!mx_batch_fits(P, B) || outer_lds > P->lds_max || mx_gemm_lds(64) > P->lds_max) return false;
+    if (kF32 && gg2_mode && B < P->batch_min) return false;
+    const size_t cells = static_cast<size_t>(P->mx_nb) * 64 * 2 * Vm;
+    const size_t mat = sizeof(T) * static_cast<size_t>(P->mx_blocks) * kMxBlock;
+    try {
+        if (gf) {
+            ensure_zeroed(P, P->mx_m, mat);
+            ensure(P->mx_p1, 2 * cells * sizeof(double) * nsplit, &P->ws_gen);
+        }
+        if (gg2_mode) ensure(P->mx_g, mat, &P->ws_gen);
+        ensure(P->mx_u, 2 * cells * sizeof(double) + cells * sizeof(T), &P->ws_gen);
+    } catch (const std::bad_alloc &) {
+        return false;
+    }
+    if (gf) enqueue_pair_matrix<T>(P, s);
+    const MxArgs<T> x = mx_args<T>(P);
+    const double K = k_prefactor(P);
+    T *gm = static_cast<T *>(P->mx_g.p);
+    const dim3 og(mx_row_grid(P, nsplit));
+    for (int b0 = 0; b0 < B; b0 += 64) {
+        const int nv = std::min(64, B - b0), V = mx_columns(nv);
+        const int64_t n = static_cast<int64_t>(P->mx_nb) * 64 * 2 * V;
+        double *u1 = static_cast<double *>(P->mx_u.p), *u2 = u1 + n;
+        T *fl = kF32 && gg2_mode ? reinterpret_cast<T *>(u2 + n) : nullptr;
+        const dim3 grid(static_cast<unsigned>(P->mx_nb), static_cast<unsigned>(V / 16));
+        hipLaunchKernelGGL((k_mx_load_vjp<T>), grid, dim3(256), 0, s, x, f + b0 * ldf, ldf, lam + b0 * ldl, ldl, nv, V,
+                           u1, u2, fl);
+        if (gf) {
+            double *p1 = static_cast<double *>(P->mx_p1.p), *p2 = p1 + n * nsplit;
+            enqueue_mx_gemm<T>(P, 2 * V, u1, u2, p1, p2, nsplit, s);
+            hipLaunchKernelGGL((k_mx_vjp_finish<T>), grid, dim3(1024), 0, s, tiled_args<T>(P), x, (const double *)p1,
+                               (const double *)p2, nsplit, V, nv, K, (const double *)u1, (const double *)u2,
+                               lam + b0 * ldl, ldl, gf + b0 * ldgf, ldgf);
+        }
+        if (!gg2_mode) continue;
+        auto outer = [&](auto vt) {
+            constexpr int VT = decltype(vt)::value;
+            if constexpr (kF32) {
+                hipLaunchKernelGGL((k_mx_outer_f32<VT>), og, dim3(256), 0, s, x, (const float *)fl, gm, nsplit);
+            } else {
+                const size_t shm = 64 * static_cast<size_t>(2 * V + 4) * sizeof(double);
+                hipLaunchKernelGGL((k_mx_outer<VT>), og, dim3(256), shm, s, x, (const double *)u1, (const double *)u2,
+                                   gm, b0 > 0 ? 1 : 0, nsplit);
+            }
+        };
+        if (V == 16) outer(std::integral_constant<int, 1>{});
+        else if (V == 32) outer(std::integral_constant<int, 2>{});
+        else if (V == 48) outer(std::integral_constant<int, 3>{});
+        else outer(std::integral_constant<int, 4>{});
+        // FP32: each group's gradients go out by themselves (added in FP64)
+        if (kF32) enqueue_mx_gg2<T>(P, gm, gg2, b0 > 0 ? 2 : gg2_mode, s);
+    }
+    if (gg2_mode && !kF32) enqueue_mx_gg2<T>(P, gm, gg2, gg2_mode, s);
+    HIPC(hipGetLastError());
+    return true;
 }
 
 // Enqueue I[f] for B vectors with epilogue E (no allocation inside; the
@@ -1679,7 +1796,9 @@ void upload_matrix_layout(ephbte_plan P) {
     if (!P->pr_ok || !build_matrix_layout(P->S, P->pr_rowptr, P->pr_partner_host, &L)) return;
     size_t &acc = P->layout_bytes;
     std::vector<MxCol> col(L.col.size());
-    for (size_t x = 0; x < col.size(); ++x) col[x] = MxCol{L.col[x], L.col_t[x]};
+    for (size_t x = 0; x < col.size(); ++x) col[x] = MxCol{0, L.col[x], L.col_t[x], 0};
+    for (int I = 0; I < L.nb; ++I)
+        for (int x = L.row[I]; x < L.row[I + 1]; ++x) col[x].i = I;
     auto up = [&](auto *&dst, const auto &v) {
         dalloc(dst, sizeof(v[0]) * v.size(), &acc);
         HIPC(hipMemcpy(dst, v.data(), sizeof(v[0]) * v.size(), hipMemcpyHostToDevice));
@@ -1806,7 +1925,7 @@ void rk4_enqueue_step(ephbte_plan P, int B, T *f, int64_t ldf, const void *nph, 
 // over pair records.  u holds the stage input by position ({f, 1 - f}, two
 // copies that alternate: four stages end where they began).
 template <typename T>
-void mx_rk4_step(ephbte_plan P, T *f, T dt, hipStream_t s, T *ua, T *ub, T *acc, int nsplit) {
+void mx_rk4_step(ephbte_plan P, T *f, T dt, hipStream_t s, T *ua, T *ub, T *acc) {
     const int64_t np = static_cast<int64_t>(P->mx_nb) * 64;
     double *u = static_cast<double *>(P->mx_u.p);
     double *b1[2] = {u, u + 2 * np}, *b2[2] = {u + np, u + 3 * np};
@@ -1826,10 +1945,11 @@ void mx_rk4_step(ephbte_plan P, T *f, T dt, hipStream_t s, T *ua, T *ub, T *acc,
         e.u_out = out[k];
         with_drift<T>(P, e, in, static_cast<int64_t>(P->S), T(1));
         const int64_t kt = ktime_begin(P, s);
-        enqueue_mx_vec<T, 1>(P, b1[k & 1], b2[k & 1], nsplit, s);
+        enqueue_mx_vec<T, 1>(P, b1[k & 1], b2[k & 1], (k & 1) != 0, s);
         ktime_end(P, s, kt);
         hipLaunchKernelGGL((k_mx_rk_finish<T>), dim3(static_cast<unsigned>(P->mx_nb)), dim3(64 * kMxParts), 0, s, a,
-                           mx_args<T>(P), (const double *)P->mx_p1.p, nsplit, (const double *)P->mx_p2.p, K,
+                           mx_args<T>(P), (const double *)P->mx_p1.p, mx_runs(P, 1),
+                           (const double *)P->mx_p2.p, K,
                            (const double *)b1[k & 1], (const double *)b2[k & 1], b1[(k + 1) & 1], b2[(k + 1) & 1], e);
         in = out[k];
     }
@@ -1849,9 +1969,8 @@ ephbte_status rt_step_impl(ephbte_plan P, int B, T *f, int64_t ldf, const void *
     const T tdt = static_cast<T>(dt);
     enqueue_pack<T>(P, nph, s);   // the phonon occupations hold for the whole call
     // one vector over the pair matrix: its coefficients are evaluated once
-    const int nsplit = mx_vec_split(P);
     if (n_steps > 0 && use_mx_batch<T>(P, B)) enqueue_pair_matrix<T>(P, s);
-    const bool mx = n_steps > 0 && use_pairs(P, B) && mx_ensure<T>(P, 1, nsplit);
+    const bool mx = n_steps > 0 && use_pairs(P, B) && mx_ensure<T>(P, 1);
     if (mx) {
         enqueue_pair_matrix<T>(P, s);
         double *u = static_cast<double *>(P->mx_u.p);
@@ -1860,7 +1979,7 @@ ephbte_status rt_step_impl(ephbte_plan P, int B, T *f, int64_t ldf, const void *
         HIPC(hipGetLastError());
     }
     auto step = [&](hipStream_t st) {
-        if (mx) mx_rk4_step<T>(P, f, tdt, st, ua, ub, acc, nsplit);
+        if (mx) mx_rk4_step<T>(P, f, tdt, st, ua, ub, acc);
         else rk4_enqueue_step<T>(P, B, f, ldf, nph, tdt, st, ua, ub, acc, f, ldf, f);
     };
     if (!use_graph || n_steps < 2) {
@@ -2402,9 +2521,8 @@ ephbte_status transport_impl(ephbte_plan P, const T *f0, const T *vel, double T_
     // over the pair matrix an iteration reads one value per ordered pair of
     // states, without it one W and one partner word per entry and mode: on the
     // 100^3 system 0.53 against 4.8 GB
-    const int nsplit = mx_vec_split(P);
     if (use_pairs(P, 1)) ensure_fwd<T>(P, 1);   // the {hw, N} table
-    const bool mx = use_pairs(P, 1) && mx_ensure<T>(P, 3, nsplit);
+    const bool mx = use_pairs(P, 1) && mx_ensure<T>(P, 3);
     if (!mx) ensure(P->tr_W, sizeof(T) * (P->E + kEntryPad), &P->ws_gen);
     ensure(P->tr_tau_inv, sizeof(T) * S, &P->ws_gen);
     ensure(P->tr_tau, sizeof(T) * S, &P->ws_gen);
@@ -2433,9 +2551,9 @@ ephbte_status transport_impl(ephbte_plan P, const T *f0, const T *vel, double T_
         enqueue_pack<T>(P, nph, s);
         enqueue_pair_matrix<T>(P, s);
         hipLaunchKernelGGL((k_mx_load<T>), mg, dim3(256), 0, s, mx_args<T>(P), f0, ux, ux + np);
-        enqueue_mx_vec<T, 1>(P, ux, ux + np, nsplit, s);
-        hipLaunchKernelGGL((k_mx_tau_finish<T>), mr, dim3(64 * kMxParts), 0, s, tiled_args<T>(P), mx_args<T>(P), p1, nsplit, p2,
-                           K, (const double *)ux, (const double *)(ux + np), tinv);
+        enqueue_mx_vec<T, 1>(P, ux, ux + np, false, s);
+        hipLaunchKernelGGL((k_mx_tau_finish<T>), mr, dim3(64 * kMxParts), 0, s, tiled_args<T>(P), mx_args<T>(P), p1,
+                           mx_runs(P, 1), p2, K, (const double *)ux, (const double *)(ux + np), tinv);
     } else if (P->fused)
         hipLaunchKernelGGL((k_transport_setup<T, true>), grid, block, 0, s, t, f0, W, (T *)nullptr,
                            tinv);
@@ -2472,9 +2590,9 @@ ephbte_status transport_impl(ephbte_plan P, const T *f0, const T *vel, double T_
     bool conv = false, stalled = false;
     for (it = 1; it <= max_iter; ++it) {
         if (mx) {
-            enqueue_mx_vec<T, 3>(P, ua, ua, nsplit, s);
-            hipLaunchKernelGGL((k_mx_tr_finish<T>), mr, dim3(64 * kMxParts), 0, s, tiled_args<T>(P), mx_args<T>(P), p1, nsplit,
-                               p2, K, f0, (const Vec4<T> *)rhs, (const T *)tau, (const double *)ua, ub, xb);
+            enqueue_mx_vec<T, 3>(P, ua, ua, (it & 1) != 0, s);
+            hipLaunchKernelGGL((k_mx_tr_finish<T>), mr, dim3(64 * kMxParts), 0, s, tiled_args<T>(P), mx_args<T>(P), p1,
+                               mx_runs(P, 3), p2, K, f0, (const Vec4<T> *)rhs, (const T *)tau, (const double *)ua, ub, xb);
             std::swap(ua, ub);
         } else {
             TiledArgs<T> ta = tiled_args<T>(P);
@@ -3003,9 +3121,11 @@ ephbte_status ephbte_collision_vjp(ephbte_plan plan, int32_t batch, const void *
             bool done = false;
             if (!per_batch) {
                 enqueue_pack<T>(plan, nph, s);
-                done = enqueue_vjp_batched<T>(plan, batch, static_cast<const T *>(f), ldf,
-                                              static_cast<const T *>(gI), ldg, static_cast<T *>(gf), ldgf,
-                                              gg2, gg2 ? (accumulate_gg2 ? 2 : 1) : 0, s);
+                const int gmode = gg2 ? (accumulate_gg2 ? 2 : 1) : 0;
+                const T *ft = static_cast<const T *>(f), *lt = static_cast<const T *>(gI);
+                done = enqueue_vjp_mx<T>(plan, batch, ft, ldf, lt, ldg, static_cast<T *>(gf), ldgf, gg2, gmode, s) ||
+                       enqueue_vjp_batched<T>(plan, batch, ft, ldf, lt, ldg, static_cast<T *>(gf), ldgf, gg2, gmode,
+                                              s);
             } else if (batch >= plan->batch_min) {
                 // a bath per vector, batched: the table's hw from the first bath's pack
                 enqueue_pack<T>(plan, nph, s);

@@ -1803,7 +1803,7 @@ __global__ void k_tr_tiled_finish(TiledArgs<T> A, const Vec4<T> *__restrict__ pa
 // pair are zero from the allocation; every pair's two entries are rewritten by
 // k_pair_matrix.  Sums over partners are held in FP64 in both precisions.
 struct MxCol {
-    int32_t j, id_t;   // block column and the block (j, row)
+    int32_t i, j, id_t, pad;   // block row, block column and the block (j, i)
 };
 template <typename T> struct MxArgs {
     T *__restrict__ m;                     // [blocks][64 x 64]
@@ -1919,101 +1919,159 @@ __global__ __launch_bounds__(1024) void k_pair_matrix(TiledArgs<T> A, MxArgs<T> 
     }
 }
 
-// The matrix and its transpose applied to NC columns, each value read once:
-// workgroup = block row I and a share of its blocks, a wave takes whole blocks.
-// Lane (i, g) = (lane / 4, lane % 4) holds row i and columns 4 g .. 4 g + 3 of a
-// sub-block.  Rows of I: sum_p M[d][p] u1_p in registers over the wave's blocks,
-// then over the waves in order, to part1[split][position][NC].  Columns of J:
-// sum over the block's rows of M[d][p] u2_d, the share of the transposed product
-// of this block, to part2[block][64][NC]; k_mx_* finish kernels add the shares
-// of a state's block column.  Bound by the matrix bytes.
+// Runs of the stored blocks, one a wave: the first r waves take q + 1 blocks, the
+// others q (q W + r blocks over W waves).
+struct MxRuns {
+    int W, q, r;
+};
+__device__ __forceinline__ int mx_wave_of(const MxRuns &N, int x) {
+    const int head = N.r * (N.q + 1);
+    return x < head ? x / (N.q + 1) : N.r + (x - head) / N.q;
+}
+
+// The matrix and its transpose applied to NC columns, each value read once: every
+// wave takes an equal run of the stored blocks, whatever rows they belong to.  Lane (i, g) = (lane / 4, lane %
+// 4) holds row i and columns 4 g .. 4 g + 3 of a sub-block.  Rows: sum_p M[d][p]
+// u1_p in registers while the block row stays I, then to part1[w + I][64][NC]
+// (along a run of blocks w + I never repeats).  Columns: the block's share of the
+// transposed product, sum over its rows of M[d][p] u2_d, to part2[block][64][NC].
+// The k_mx_* finish kernels add the shares.  Bound by the matrix bytes: four
+// sub-blocks are in flight while four are multiplied.  rev != 0 walks the blocks
+// backwards: calls that alternate find the end of the last walk in the 256 MB
+// memory-side cache.
 template <typename T, int NC>
-__global__ __launch_bounds__(256) void k_mx_vec(MxArgs<T> X, const double *__restrict__ u1,
-                                                const double *__restrict__ u2, double *__restrict__ part1,
-                                                double *__restrict__ part2) {
-    __shared__ double s_r[4][64][NC];
-    const int I = blockIdx.x;
+__global__ __launch_bounds__(256, NC == 1 ? 3 : 2) void k_mx_vec(const T *__restrict__ mat,
+                                                                 const MxCol *__restrict__ col, MxRuns N,
+                                                                 const double *__restrict__ u1,
+                                                                 const double *__restrict__ u2,
+                                                                 double *__restrict__ part1,
+                                                                 double *__restrict__ part2, int rev) {
     const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
     const int i = lane >> 2, g = lane & 3;
-    const int r0 = X.row[I], n = X.row[I + 1] - r0;
-    const int xb = r0 + static_cast<int>(static_cast<int64_t>(n) * blockIdx.y / gridDim.y);
-    const int xe = r0 + static_cast<int>(static_cast<int64_t>(n) * (blockIdx.y + 1) / gridDim.y);
-    double v2[4][NC], acc[4][NC];
+    int w = static_cast<int>(blockIdx.x) * 4 + __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+    if (rev) w = N.W - 1 - w;
+    const int xb = w * N.q + min(w, N.r);
+    const int nx = N.q + (w < N.r ? 1 : 0);
+    if (nx == 0) return;
+    auto at = [&](int k) { return rev ? xb + nx - 1 - min(k, nx - 1) : xb + min(k, nx - 1); };
+    const bool h5 = (lane & 32) != 0, h4 = (lane & 16) != 0, h3 = (lane & 8) != 0, h2 = (lane & 4) != 0;
+    double v2[4][NC], acc[4][NC], half[4][NC], a0[4][NC], a1[4][NC];
+    T w0[4][4], w1[4][4];
+    // sub-blocks (0 .. 3, C) of block x and the columns they meet
+    auto load = [&](int x, int C, T (&wt)[4][4], double (&a)[4][NC]) {
+        const T *__restrict__ m = mat + static_cast<int64_t>(x) * kMxBlock + C * 256 + lane * 4;
 #pragma unroll
-    for (int R = 0; R < 4; ++R)
-#pragma unroll
-        for (int k = 0; k < NC; ++k) {
-            v2[R][k] = u2[(I * 64 + R * 16 + i) * NC + k];
-            acc[R][k] = 0.0;
+        for (int R = 0; R < 4; ++R) {
+            const Vec4<T> q = *reinterpret_cast<const Vec4<T> *>(m + R * 1024);
+            wt[R][0] = q.x;
+            wt[R][1] = q.y;
+            wt[R][2] = q.z;
+            wt[R][3] = q.w;
         }
-    for (int x = xb + wave; x < xe; x += 4) {
-        const int J = X.col[x].j;
-        const T *__restrict__ mb = X.m + static_cast<int64_t>(x) * kMxBlock + lane * 4;
-        const double *__restrict__ ub = u1 + (static_cast<int64_t>(J) * 64 + 4 * g) * NC;
-        double *__restrict__ pc = part2 + static_cast<int64_t>(x) * 64 * NC;
+        const double *__restrict__ ub = u1 + (static_cast<int64_t>(col[x].j) * 64 + C * 16 + 4 * g) * NC;
 #pragma unroll
-        for (int C = 0; C < 4; ++C) {
-            double a[4][NC], cs[4][NC];
+        for (int t = 0; t < 4; ++t)
 #pragma unroll
-            for (int t = 0; t < 4; ++t)
+            for (int k = 0; k < NC; ++k) a[t][k] = ub[t * NC + k];
+    };
+    auto step = [&](int C, const T (&wt)[4][4], const double (&a)[4][NC]) {
+        double cs[4][NC];
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int k = 0; k < NC; ++k) cs[t][k] = 0.0;
+#pragma unroll
+        for (int R = 0; R < 4; ++R)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const double m = static_cast<double>(wt[R][t]);
 #pragma unroll
                 for (int k = 0; k < NC; ++k) {
-                    a[t][k] = ub[(C * 16 + t) * NC + k];
-                    cs[t][k] = 0.0;
+                    acc[R][k] = fma(m, a[t][k], acc[R][k]);
+                    cs[t][k] = fma(m, v2[R][k], cs[t][k]);
                 }
-#pragma unroll
-            for (int R = 0; R < 4; ++R) {
-                const Vec4<T> w4 = *reinterpret_cast<const Vec4<T> *>(mb + (R * 4 + C) * 256);
-                const double w[4] = {static_cast<double>(w4.x), static_cast<double>(w4.y),
-                                     static_cast<double>(w4.z), static_cast<double>(w4.w)};
-#pragma unroll
-                for (int t = 0; t < 4; ++t)
-#pragma unroll
-                    for (int k = 0; k < NC; ++k) {
-                        acc[R][k] = fma(w[t], a[t][k], acc[R][k]);
-                        cs[t][k] = fma(w[t], v2[R][k], cs[t][k]);
-                    }
             }
-            // sum over the 16 rows i: lane bits 5 and 4 each halve the four
-            // columns, bits 3 and 2 add
-            const bool h5 = (lane & 32) != 0, h4 = (lane & 16) != 0;
-#pragma unroll
-            for (int k = 0; k < NC; ++k) {
-                const double p0 = (h5 ? cs[2][k] : cs[0][k]) + __shfl_xor(h5 ? cs[0][k] : cs[2][k], 32, 64);
-                const double p1 = (h5 ? cs[3][k] : cs[1][k]) + __shfl_xor(h5 ? cs[1][k] : cs[3][k], 32, 64);
-                double s = (h4 ? p1 : p0) + __shfl_xor(h4 ? p0 : p1, 16, 64);
-                s += __shfl_xor(s, 8, 64);
-                s += __shfl_xor(s, 4, 64);
-                const int t = (h5 ? 2 : 0) + (h4 ? 1 : 0);
-                if ((lane & 12) == 0) pc[(C * 16 + 4 * g + t) * NC + k] = s;
-            }
-        }
-    }
-#pragma unroll
-    for (int R = 0; R < 4; ++R)
+        // half of the sum over the 16 rows i: lane bits 5 and 4 each halve the
+        // four columns
 #pragma unroll
         for (int k = 0; k < NC; ++k) {
-            double s = acc[R][k];
-            s += __shfl_xor(s, 1, 64);
-            s += __shfl_xor(s, 2, 64);
-            if (g == 0) s_r[wave][R * 16 + i][k] = s;
+            const double c0 = cs[0][k], c1 = cs[1][k], c2 = cs[2][k], c3 = cs[3][k];
+            const double p0 = (h5 ? c2 : c0) + __shfl_xor(h5 ? c0 : c2, 32, 64);
+            const double p1 = (h5 ? c3 : c1) + __shfl_xor(h5 ? c1 : c3, 32, 64);
+            half[C][k] = (h4 ? p1 : p0) + __shfl_xor(h4 ? p0 : p1, 16, 64);
         }
-    __syncthreads();
-    double *__restrict__ po = part1 + (static_cast<int64_t>(blockIdx.y) * X.nb + I) * 64 * NC;
-    for (int e = threadIdx.x; e < 64 * NC; e += blockDim.x) {
-        const int r = e / NC, k = e - r * NC;
-        po[e] = ((s_r[0][r][k] + s_r[1][r][k]) + s_r[2][r][k]) + s_r[3][r][k];
+    };
+    // the other half: bits 3 and 2 each halve the four sub-blocks, so that every
+    // lane holds one column of the block (no branch around the store: the
+    // compiler would sink the row sums past it and hold every operand until then)
+    auto end_block = [&](int x) {
+        double *__restrict__ pc =
+            part2 + (static_cast<int64_t>(x) * 64 + (h3 ? 32 : 0) + (h2 ? 16 : 0) + 4 * g + (h5 ? 2 : 0) + (h4 ? 1 : 0)) * NC;
+#pragma unroll
+        for (int k = 0; k < NC; ++k) {
+            const double c0 = half[0][k], c1 = half[1][k], c2 = half[2][k], c3 = half[3][k];
+            const double p0 = (h3 ? c2 : c0) + __shfl_xor(h3 ? c0 : c2, 8, 64);
+            const double p1 = (h3 ? c3 : c1) + __shfl_xor(h3 ? c1 : c3, 8, 64);
+            pc[k] = (h2 ? p1 : p0) + __shfl_xor(h2 ? p0 : p1, 4, 64);
+        }
+    };
+    auto begin_row = [&](int I) {
+#pragma unroll
+        for (int R = 0; R < 4; ++R)
+#pragma unroll
+            for (int k = 0; k < NC; ++k) {
+                v2[R][k] = u2[(static_cast<int64_t>(I) * 64 + R * 16 + i) * NC + k];
+                acc[R][k] = 0.0;
+            }
+    };
+    auto end_row = [&](int I) {
+        double *__restrict__ po = part1 + static_cast<int64_t>(w + I) * 64 * NC;
+#pragma unroll
+        for (int R = 0; R < 4; ++R)
+#pragma unroll
+            for (int k = 0; k < NC; ++k) {
+                double s = acc[R][k];
+                s += __shfl_xor(s, 1, 64);
+                s += __shfl_xor(s, 2, 64);
+                if (g == 0) po[(R * 16 + i) * NC + k] = s;
+            }
+    };
+    int x = at(0), I = col[x].i;
+    load(x, 0, w0, a0);
+    begin_row(I);
+    for (int k = 0; k < nx; ++k) {
+        const int xn = at(k + 1);
+        load(x, 1, w1, a1);
+        __builtin_amdgcn_sched_barrier(0);
+        step(0, w0, a0);
+        load(x, 2, w0, a0);
+        __builtin_amdgcn_sched_barrier(0);
+        step(1, w1, a1);
+        load(x, 3, w1, a1);
+        __builtin_amdgcn_sched_barrier(0);
+        step(2, w0, a0);
+        load(xn, 0, w0, a0);
+        __builtin_amdgcn_sched_barrier(0);
+        step(3, w1, a1);
+        end_block(x);
+        const int In = col[xn].i;
+        if (In != I) {
+            end_row(I);
+            begin_row(In);
+            I = In;
+        }
+        x = xn;
     }
+    end_row(I);
 }
 
 constexpr int kMxParts = 16;   // waves of the finish kernels
 // Sums of a block row's partials (1024 threads, thread = position r and one of
 // 16 parts of the shares, so that few loads follow each other; the parts are
-// added in order): o1 over the splits, o2 over the blocks of the row's block
-// column.  Threads below 64 hold the totals of position I 64 + r.
+// added in order): o1 over the waves that held the row, o2 over the blocks of
+// its block column.  Threads below 64 hold the totals of position I 64 + r.
 template <typename T, int NC>
-__device__ __forceinline__ void mx_vec_sums(const MxArgs<T> &X, const double *__restrict__ part1, int nsplit,
+__device__ __forceinline__ void mx_vec_sums(const MxArgs<T> &X, const double *__restrict__ part1, MxRuns N,
                                             const double *__restrict__ part2, int I, double (&o1)[NC],
                                             double (&o2)[NC]) {
     __shared__ double s_q[kMxParts][2 * NC][64];
@@ -2025,10 +2083,14 @@ __device__ __forceinline__ void mx_vec_sums(const MxArgs<T> &X, const double *__
 #pragma unroll
         for (int k = 0; k < NC; ++k) o2[k] += p[k];
     }
-    for (int sp = seg; sp < nsplit; sp += kMxParts) {
-        const double *__restrict__ p = part1 + ((static_cast<int64_t>(sp) * X.nb + I) * 64 + r) * NC;
+    if (X.row[I] < X.row[I + 1]) {
+        // the waves that held a block of this row (see k_mx_vec)
+        const int we = mx_wave_of(N, X.row[I + 1] - 1);
+        for (int w = mx_wave_of(N, X.row[I]) + seg; w <= we; w += kMxParts) {
+            const double *__restrict__ p = part1 + (static_cast<int64_t>(w + I) * 64 + r) * NC;
 #pragma unroll
-        for (int k = 0; k < NC; ++k) o1[k] += p[k];
+            for (int k = 0; k < NC; ++k) o1[k] += p[k];
+        }
     }
 #pragma unroll
     for (int k = 0; k < NC; ++k) {
@@ -2086,11 +2148,11 @@ __global__ void k_mx_load(MxArgs<T> X, const T *__restrict__ f, double *__restri
 // row.  A: the destination layout (k_mx_own_sums).
 template <typename T>
 __global__ __launch_bounds__(64 * kMxParts) void k_mx_rk_finish(TiledArgs<T> A, MxArgs<T> X, const double *__restrict__ part1,
-                                                      int nsplit, const double *__restrict__ part2, double K,
+                                                      MxRuns N, const double *__restrict__ part2, double K,
                                                       const double *__restrict__ u1, const double *__restrict__ u2,
                                                       double *__restrict__ n1, double *__restrict__ n2, Epi<T> E) {
     double o1[1], o2[1];
-    mx_vec_sums<T, 1>(X, part1, nsplit, part2, blockIdx.x, o1, o2);
+    mx_vec_sums<T, 1>(X, part1, N, part2, blockIdx.x, o1, o2);
     if (threadIdx.x >= 64) return;
     const int x = blockIdx.x * 64 + threadIdx.x;
     const int d = X.state[x];
@@ -2105,17 +2167,29 @@ __global__ __launch_bounds__(64 * kMxParts) void k_mx_rk_finish(TiledArgs<T> A, 
 // 1 / tau_d = K (o1 + o2) with u1 = f0, u2 = 1 - f0
 template <typename T>
 __global__ __launch_bounds__(64 * kMxParts) void k_mx_tau_finish(TiledArgs<T> A, MxArgs<T> X, const double *__restrict__ part1,
-                                                       int nsplit, const double *__restrict__ part2, double K,
+                                                       MxRuns N, const double *__restrict__ part2, double K,
                                                        const double *__restrict__ u1, const double *__restrict__ u2,
                                                        T *__restrict__ tau_inv) {
     double o1[1], o2[1];
-    mx_vec_sums<T, 1>(X, part1, nsplit, part2, blockIdx.x, o1, o2);
+    mx_vec_sums<T, 1>(X, part1, N, part2, blockIdx.x, o1, o2);
     if (threadIdx.x >= 64) return;
     const int x = blockIdx.x * 64 + threadIdx.x;
     const int d = X.state[x];
     if (d < 0) return;
     if (!mx_finite(o1[0], o2[0])) mx_own_sums<T>(A, X, d, u1, u2, 1, 0, o1[0], o2[0]);
     tau_inv[d] = static_cast<T>(K * (o1[0] + o2[0]));
+}
+
+// Block row and share of this workgroup: workgroups go round-robin to the 8 XCDs;
+// each XCD takes a contiguous range of rows, share after share of a row, so that
+// the columns its rows read (those of one component, or a few) stay in its L2.
+// False for the workgroups that pad the grid to 8 ranges.
+__device__ __forceinline__ bool mx_row_of_block(int nb, int nsplit, int &I, int &sp) {
+    const int per = (nb + 7) >> 3;
+    const int w = static_cast<int>(blockIdx.x) >> 3;
+    I = (static_cast<int>(blockIdx.x) & 7) * per + w / nsplit;
+    sp = w % nsplit;
+    return w / nsplit < per && I < nb;
 }
 
 // D += A B on one 16 x 16 tile, A 16 x 4 and B 4 x 16 over the wave: lane
@@ -2142,82 +2216,112 @@ inline void mx_mfma(double a, double b, double (&d)[4]) {
 #endif
 
 // The matrix and its transpose applied to 16 NCT columns on the FP64 matrix
-// cores: workgroup = block row I and a share of its blocks, wave = 16 of its
-// rows.  Per block the 64 rows of u1 and u2 ([position][16 NCT]) are staged in
-// LDS (rows padded by 4 values: the four k groups of a wave's read fall on
-// different banks); a wave reads its rows of block (I, J) and its columns of
-// block (J, I) as whole sub-block runs, once each, so the matrix passes through
+// cores: workgroup = block row I and a share of its blocks; waves 0 - 3 take M u1
+// and waves 4 - 7 the transposed product with u2, 16 rows each.  Per block the 64
+// rows of u1 and u2 ([position][ld], columns from c0) are staged in LDS (rows
+// padded by 4 values: the four k groups of a wave's read fall on different
+// banks); a wave reads its rows of block (I, J) or its columns of block (J, I) as
+// whole sub-block runs, once, a block ahead, so the matrix passes through
 // registers only.  The k index of the instruction's step t stands for partner
-// 4 g + t of a sub-block.  Partial sums of a share go to part1 and part2
-// ([split][position][16 NCT]).  Bound by the matrix cores at 64 columns (17 GF
-// on the 100^3 system, 72 TF measured for a large product) and by the matrix
-// bytes below 32.
+// 4 g + t of a sub-block.  The sums of a share go to part1 and part2
+// ([split][position][ld]).  Bound by the matrix cores at 64 columns (17 GF on the
+// 100^3 system, 72 TF measured for a large product) and by the matrix bytes
+// below 32.
 template <typename T, int NCT>
-__global__ __launch_bounds__(256, 2) void k_mx_gemm(MxArgs<T> X, const double *__restrict__ u1,
-                                                    const double *__restrict__ u2, double *__restrict__ part1,
-                                                    double *__restrict__ part2) {
+__global__ __launch_bounds__(512, 4) void k_mx_gemm(MxArgs<T> X, const double *__restrict__ u1,
+                                                    const double *__restrict__ u2, int ld, int c0, int nsplit,
+                                                    double *__restrict__ part1, double *__restrict__ part2) {
     constexpr int NC = 16 * NCT, LD = NC + 4;
     extern __shared__ __align__(16) unsigned char smem[];
     double *s1 = reinterpret_cast<double *>(smem), *s2 = s1 + 64 * LD;
-    const int I = blockIdx.x;
+    int I, sp;
+    if (!mx_row_of_block(X.nb, nsplit, I, sp)) return;
     const int lane = threadIdx.x & 63;
-    const int R = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+    const int R = wave & 3;
+    const bool tr = wave >= 4;
     const int j = lane & 15, g = lane >> 4;
     const int r0 = X.row[I], n = X.row[I + 1] - r0;
-    const int xb = r0 + static_cast<int>(static_cast<int64_t>(n) * blockIdx.y / gridDim.y);
-    const int xe = r0 + static_cast<int>(static_cast<int64_t>(n) * (blockIdx.y + 1) / gridDim.y);
-    double acc1[NCT][4], acc2[NCT][4];
+    const int xb = r0 + static_cast<int>(static_cast<int64_t>(n) * sp / nsplit);
+    const int xe = r0 + static_cast<int>(static_cast<int64_t>(n) * (sp + 1) / nsplit);
+    double acc[NCT][4];
 #pragma unroll
     for (int c = 0; c < NCT; ++c)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) acc1[c][v] = acc2[c][v] = 0.0;
-    for (int x = xb; x < xe; ++x) {
-        const MxCol cl = X.col[x];
-        const T *__restrict__ m1 = X.m + static_cast<int64_t>(x) * kMxBlock + R * 1024 + j * 16 + 4 * g;
-        const T *__restrict__ m2 = X.m + static_cast<int64_t>(cl.id_t) * kMxBlock + R * 256 + g * 64 + j;
-        Vec4<T> a1[4];
-        T a2[4][4];
+        for (int v = 0; v < 4; ++v) acc[c][v] = 0.0;
+    auto sweep = [&](auto trc) {
+        constexpr bool TR = decltype(trc)::value;
+        const double *__restrict__ su = (TR ? s2 : s1) + 4 * g * LD + j;
+        T w[4][4];
+        auto load = [&](int x, int C) {
+            if constexpr (TR) {
+                const T *__restrict__ m = X.m + static_cast<int64_t>(X.col[x].id_t) * kMxBlock + R * 256 + g * 64 + j;
 #pragma unroll
-        for (int C = 0; C < 4; ++C) {
-            a1[C] = *reinterpret_cast<const Vec4<T> *>(m1 + C * 256);
+                for (int t = 0; t < 4; ++t) w[C][t] = m[C * 1024 + t * 16];
+            } else {
+                const T *__restrict__ m = X.m + static_cast<int64_t>(x) * kMxBlock + R * 1024 + j * 16 + 4 * g;
+                const Vec4<T> v = *reinterpret_cast<const Vec4<T> *>(m + C * 256);
+                w[C][0] = v.x;
+                w[C][1] = v.y;
+                w[C][2] = v.z;
+                w[C][3] = v.w;
+            }
+        };
+        // the next block's rows of u1 and u2 are in registers while this block is
+        // multiplied: a barrier waits for every load in flight, so a load issued
+        // between two barriers would be waited for there
+        double n1[2 * NCT], n2[2 * NCT];
+        auto stage = [&](int x) {
+            const int64_t u0 = static_cast<int64_t>(X.col[x].j) * 64 * ld + c0;
 #pragma unroll
-            for (int t = 0; t < 4; ++t) a2[C][t] = m2[C * 1024 + t * 16];
-        }
-        __syncthreads();
-        const double2 *__restrict__ g1 = reinterpret_cast<const double2 *>(u1 + static_cast<int64_t>(cl.j) * 64 * NC);
-        const double2 *__restrict__ g2 = reinterpret_cast<const double2 *>(u2 + static_cast<int64_t>(cl.j) * 64 * NC);
+            for (int e = 0; e < NCT; ++e) {
+                const int idx = e * 512 + static_cast<int>(threadIdx.x);
+                const int r = idx / (NC / 2), k = idx - r * (NC / 2);
+                const int64_t o = u0 + static_cast<int64_t>(r) * ld + 2 * k;
+                n1[2 * e] = u1[o];
+                n1[2 * e + 1] = u1[o + 1];
+                n2[2 * e] = u2[o];
+                n2[2 * e + 1] = u2[o + 1];
+            }
+        };
+        if (xb >= xe) return;
+        stage(xb);
 #pragma unroll
-        for (int e = 0; e < 8 * NCT / 4; ++e) {
-            const int idx = e * 256 + static_cast<int>(threadIdx.x);
-            const int r = idx / (NC / 2), k = idx - r * (NC / 2);
-            *reinterpret_cast<double2 *>(s1 + r * LD + 2 * k) = g1[idx];
-            *reinterpret_cast<double2 *>(s2 + r * LD + 2 * k) = g2[idx];
-        }
-        __syncthreads();
+        for (int C = 0; C < 4; ++C) load(xb, C);
+        for (int x = xb; x < xe; ++x) {
+            const int xn = min(x + 1, xe - 1);
+            __syncthreads();
 #pragma unroll
-        for (int C = 0; C < 4; ++C) {
-            const double w[4] = {static_cast<double>(a1[C].x), static_cast<double>(a1[C].y),
-                                 static_cast<double>(a1[C].z), static_cast<double>(a1[C].w)};
+            for (int e = 0; e < NCT; ++e) {
+                const int idx = e * 512 + static_cast<int>(threadIdx.x);
+                const int r = idx / (NC / 2), k = idx - r * (NC / 2);
+                s1[r * LD + 2 * k] = n1[2 * e];
+                s1[r * LD + 2 * k + 1] = n1[2 * e + 1];
+                s2[r * LD + 2 * k] = n2[2 * e];
+                s2[r * LD + 2 * k + 1] = n2[2 * e + 1];
+            }
+            __syncthreads();
+            stage(xn);
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const int o = (C * 16 + 4 * g + t) * LD + j;
-                const double wt = static_cast<double>(a2[C][t]);
+            for (int C = 0; C < 4; ++C) {
 #pragma unroll
-                for (int c = 0; c < NCT; ++c) {
-                    mx_mfma(w[t], s1[o + 16 * c], acc1[c]);
-                    mx_mfma(wt, s2[o + 16 * c], acc2[c]);
+                for (int t = 0; t < 4; ++t) {
+                    const double wt = static_cast<double>(w[C][t]);
+#pragma unroll
+                    for (int c = 0; c < NCT; ++c) mx_mfma(wt, su[(C * 16 + t) * LD + 16 * c], acc[c]);
                 }
+                load(xn, C);
             }
         }
-    }
-    const int64_t base = (static_cast<int64_t>(blockIdx.y) * X.nb + I) * 64 + R * 16;
+    };
+    if (tr) sweep(std::integral_constant<bool, true>{});
+    else sweep(std::integral_constant<bool, false>{});
+    double *__restrict__ po = (tr ? part2 : part1) +
+                              ((static_cast<int64_t>(sp) * X.nb + I) * 64 + R * 16) * ld + c0 + j;
 #pragma unroll
     for (int v = 0; v < 4; ++v)
 #pragma unroll
-        for (int c = 0; c < NCT; ++c) {
-            part1[(base + 4 * v + g) * NC + 16 * c + j] = acc1[c][v];
-            part2[(base + 4 * v + g) * NC + 16 * c + j] = acc2[c][v];
-        }
+        for (int c = 0; c < NCT; ++c) po[static_cast<int64_t>(4 * v + g) * ld + 16 * c] = acc[c][v];
 }
 
 // u1 = f and u2 = 1 - f of nb vectors by position, NC columns (0 past the last
@@ -2245,7 +2349,7 @@ __global__ __launch_bounds__(256) void k_mx_load_batch(MxArgs<T> X, const T *__r
 // I = K [(1 - f) o1 - f o2] per state and vector b0 + column, then the epilogue;
 // workgroup = 64 positions x 16 columns
 template <typename T>
-__global__ __launch_bounds__(256) void k_mx_batch_finish(TiledArgs<T> A, MxArgs<T> X,
+__global__ __launch_bounds__(1024) void k_mx_batch_finish(TiledArgs<T> A, MxArgs<T> X,
                                                          const double *__restrict__ part1,
                                                          const double *__restrict__ part2, int nsplit, int NC, int b0,
                                                          int nvec, double K, const double *__restrict__ u1,
@@ -2255,29 +2359,337 @@ __global__ __launch_bounds__(256) void k_mx_batch_finish(TiledArgs<T> A, MxArgs<
     const int x0 = blockIdx.x * 64, c0 = blockIdx.y * 16;
     const int64_t np = static_cast<int64_t>(X.nb) * 64 * NC;
     {
-        const int c = threadIdx.x & 15;
-        for (int q = threadIdx.x >> 4; q < 64; q += 16) {
-            const int64_t o = static_cast<int64_t>(x0 + q) * NC + c0 + c;
-            double o1 = 0.0, o2 = 0.0;
-            for (int sp = 0; sp < nsplit; ++sp) {
-                o1 += part1[sp * np + o];
-                o2 += part2[sp * np + o];
-            }
-            s_o[0][c][q] = o1;
-            s_o[1][c][q] = o2;
+        const int c = threadIdx.x & 15, q = threadIdx.x >> 4;
+        const int64_t o = static_cast<int64_t>(x0 + q) * NC + c0 + c;
+        double o1 = 0.0, o2 = 0.0;
+        for (int sp = 0; sp < nsplit; ++sp) {
+            o1 += part1[sp * np + o];
+            o2 += part2[sp * np + o];
+        }
+        s_o[0][c][q] = o1;
+        s_o[1][c][q] = o2;
+    }
+    __syncthreads();
+    const int q = threadIdx.x & 63, c = threadIdx.x >> 6;
+    const int d = X.state[x0 + q];
+    if (d < 0 || c0 + c >= nvec) return;
+    double o1 = s_o[0][c][q], o2 = s_o[1][c][q];
+    if (!mx_finite(o1, o2)) mx_own_sums<T>(A, X, d, u1, u2, NC, c0 + c, o1, o2);
+    const int b = b0 + c0 + c;
+    const T fd = f[static_cast<int64_t>(b) * ldf + d];
+    apply_epi(E, b, d, X.S, static_cast<T>(K * (static_cast<double>(T(1) - fd) * o1 - static_cast<double>(fd) * o2)));
+}
+
+// ---- reverse, several vectors, over the pair matrix ----------------------------
+// With o1 = M x and o2 = M^T x per column,
+//   dL/df_d = K [ o1(lam f) + o2(lam (1 - f)) - lam_d (o1(f) + o2(1 - f)) ]
+// is one product of the matrix with 2 V columns (u1 = [f, lam f], u2 = [1 - f,
+// lam (1 - f)], V the vectors rounded up to 16), and the gradient of a channel
+// (d, p) sums over the vectors before its Gaussians enter,
+//   dL/d|g|^2 = K [ bh G[d][p] + ah G[p][d] ],
+//   G[d][p] = sum_b (lam_d - lam_p) (1 - f_d) f_p
+//           = sum_b u2[d][V + b] u1[p][b] - u2[d][b] u1[p][V + b],
+// a product of 2 V inner terms per stored block (FP64 plans).  FP32 plans form G
+// from lam_d - lam_p itself, in FP32 (k_mx_outer_f32): the difference of two
+// FP32 products would lose the digits lam_d and lam_p share.
+
+// u1 and u2 of nvec vectors by position, 2 V columns; with fl also f and lam
+// themselves ([2][position][V], for k_mx_outer_f32)
+template <typename T>
+__global__ __launch_bounds__(256) void k_mx_load_vjp(MxArgs<T> X, const T *__restrict__ f, int64_t ldf,
+                                                     const T *__restrict__ lam, int64_t ldl, int nvec, int V,
+                                                     double *__restrict__ u1, double *__restrict__ u2,
+                                                     T *__restrict__ fl) {
+    __shared__ T s_f[16][65], s_l[16][65];
+    const int x0 = blockIdx.x * 64, c0 = blockIdx.y * 16;
+    {
+        const int r = threadIdx.x & 63;
+        const int d = X.state[x0 + r];
+        for (int c = threadIdx.x >> 6; c < 16; c += 4) {
+            const bool in = d >= 0 && c0 + c < nvec;
+            s_f[c][r] = in ? f[static_cast<int64_t>(c0 + c) * ldf + d] : T(0);
+            s_l[c][r] = in ? lam[static_cast<int64_t>(c0 + c) * ldl + d] : T(0);
         }
     }
     __syncthreads();
-    const int q = threadIdx.x & 63;
+    const int c = threadIdx.x & 15;
+    for (int q = threadIdx.x >> 4; q < 64; q += 16) {
+        const bool in = X.state[x0 + q] >= 0 && c0 + c < nvec;
+        const double v = static_cast<double>(s_f[c][q]), l = static_cast<double>(s_l[c][q]);
+        const double w = in ? 1.0 - v : 0.0;
+        const int64_t o = static_cast<int64_t>(x0 + q) * 2 * V + c0 + c;
+        u1[o] = v;
+        u1[o + V] = l * v;
+        u2[o] = w;
+        u2[o + V] = l * w;
+        if (fl) {
+            const int64_t y = static_cast<int64_t>(x0 + q) * V + c0 + c;
+            fl[y] = s_f[c][q];
+            fl[static_cast<int64_t>(X.nb) * 64 * V + y] = s_l[c][q];
+        }
+    }
+}
+
+// dL/df per state and vector; workgroup = 64 positions x 16 vectors
+template <typename T>
+__global__ __launch_bounds__(1024) void k_mx_vjp_finish(TiledArgs<T> A, MxArgs<T> X, const double *__restrict__ part1,
+                                                        const double *__restrict__ part2, int nsplit, int V, int nvec,
+                                                        double K, const double *__restrict__ u1,
+                                                        const double *__restrict__ u2, const T *__restrict__ lam,
+                                                        int64_t ldl, T *__restrict__ gf, int64_t ldgf) {
+    __shared__ double s_o[4][16][65];
+    const int x0 = blockIdx.x * 64, c0 = blockIdx.y * 16;
+    const int64_t np = static_cast<int64_t>(X.nb) * 64 * 2 * V;
+    {
+        const int c = threadIdx.x & 15, q = threadIdx.x >> 4;
+        const int64_t o = static_cast<int64_t>(x0 + q) * 2 * V + c0 + c;
+        double a[4] = {0.0, 0.0, 0.0, 0.0};
+        for (int sp = 0; sp < nsplit; ++sp) {
+            a[0] += part1[sp * np + o];
+            a[1] += part2[sp * np + o];
+            a[2] += part1[sp * np + o + V];
+            a[3] += part2[sp * np + o + V];
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) s_o[k][c][q] = a[k];
+    }
+    __syncthreads();
+    const int q = threadIdx.x & 63, c = threadIdx.x >> 6;
     const int d = X.state[x0 + q];
-    if (d < 0) return;
-    for (int c = threadIdx.x >> 6; c < 16 && c0 + c < nvec; c += 4) {
-        double o1 = s_o[0][c][q], o2 = s_o[1][c][q];
-        if (!mx_finite(o1, o2)) mx_own_sums<T>(A, X, d, u1, u2, NC, c0 + c, o1, o2);
-        const int b = b0 + c0 + c;
-        const T fd = f[static_cast<int64_t>(b) * ldf + d];
-        apply_epi(E, b, d, X.S,
-                  static_cast<T>(K * (static_cast<double>(T(1) - fd) * o1 - static_cast<double>(fd) * o2)));
+    if (d < 0 || c0 + c >= nvec) return;
+    double a[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) a[k] = s_o[k][c][q];
+    if (!mx_finite(a[0], a[1]) || !mx_finite(a[2], a[3])) {
+        mx_own_sums<T>(A, X, d, u1, u2, 2 * V, c0 + c, a[0], a[1]);
+        mx_own_sums<T>(A, X, d, u1, u2, 2 * V, V + c0 + c, a[2], a[3]);
+    }
+    const double l = static_cast<double>(lam[static_cast<int64_t>(c0 + c) * ldl + d]);
+    gf[static_cast<int64_t>(c0 + c) * ldgf + d] = static_cast<T>(K * (a[2] + a[3] - l * (a[0] + a[1])));
+}
+
+// G over the stored blocks ([blocks][64 x 64], the matrix's layout), added to
+// what gm holds when add != 0.  Workgroup = block row I and a share of its
+// blocks, wave = 16 of its rows, whose 2 V values of u2 stay in registers; the
+// 64 rows of u1 of a block are staged in LDS (rows padded by 4).  The k index of
+// step t stands for column 4 g + t of a run of 16.
+template <int VT>
+__global__ __launch_bounds__(256, 2) void k_mx_outer(MxArgs<double> X, const double *__restrict__ u1,
+                                                     const double *__restrict__ u2, double *__restrict__ gm, int add, int nsplit) {
+    constexpr int V = 16 * VT, LD = 2 * V + 4;
+    extern __shared__ __align__(16) unsigned char smem[];
+    double *s1 = reinterpret_cast<double *>(smem);
+    int I, sp;
+    if (!mx_row_of_block(X.nb, nsplit, I, sp)) return;
+    const int lane = threadIdx.x & 63;
+    const int R = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+    const int j = lane & 15, g = lane >> 4;
+    const int r0 = X.row[I], n = X.row[I + 1] - r0;
+    const int xb = r0 + static_cast<int>(static_cast<int64_t>(n) * sp / nsplit);
+    const int xe = r0 + static_cast<int>(static_cast<int64_t>(n) * (sp + 1) / nsplit);
+    // row R 16 + j of u2: {lam (1 - f)} against u1's f, {-(1 - f)} against lam f
+    double xr[2 * VT][4];
+    const double *__restrict__ ur = u2 + (static_cast<int64_t>(I) * 64 + R * 16 + j) * 2 * V + 4 * g;
+#pragma unroll
+    for (int q = 0; q < VT; ++q)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            xr[q][t] = ur[V + 16 * q + t];
+            xr[VT + q][t] = -ur[16 * q + t];
+        }
+    for (int x = xb; x < xe; ++x) {
+        const double2 *__restrict__ gu =
+            reinterpret_cast<const double2 *>(u1 + static_cast<int64_t>(X.col[x].j) * 64 * 2 * V);
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < 4 * VT; ++e) {
+            const int idx = e * 256 + static_cast<int>(threadIdx.x);
+            const int r = idx / V, k = idx - r * V;
+            *reinterpret_cast<double2 *>(s1 + r * LD + 2 * k) = gu[idx];
+        }
+        __syncthreads();
+        double *__restrict__ po = gm + static_cast<int64_t>(x) * kMxBlock + R * 1024 + g * 16 + j;
+#pragma unroll
+        for (int C = 0; C < 4; ++C) {
+            double acc[4] = {0.0, 0.0, 0.0, 0.0};
+            const double *__restrict__ sy = s1 + (C * 16 + j) * LD + 4 * g;
+#pragma unroll
+            for (int q = 0; q < 2 * VT; ++q)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) mx_mfma(xr[q][t], sy[16 * q + t], acc);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const double o = add ? po[C * 256 + v * 64] : 0.0;
+                po[C * 256 + v * 64] = o + acc[v];
+            }
+        }
+    }
+}
+
+// G of an FP32 plan in FP32, with the operations of k_vjp_batched: the vectors'
+// terms (1 - f_p) (f_d (lam_d - lam_p)) are summed as a balanced tree over 64
+// vectors in order, whose first level is a fused multiply-add.  (The other term
+// of a pair, f_p (1 - f_d) (lam_d - lam_p), is minus the first with d and p
+// exchanged, digit for digit, so G[p][d] holds it with its sign turned.)  Lane =
+// column p, wave = 16 rows d whose values are scalar operands; 16 vectors of a
+// column are in registers at a time.  About four operations per pair and vector
+// on the vector units against a 64-lane sum per pair there.
+template <int VT>
+__global__ __launch_bounds__(256) void k_mx_outer_f32(MxArgs<float> X, const float *__restrict__ fl,
+                                                      float *__restrict__ gm, int nsplit) {
+    constexpr int V = 16 * VT;
+    int I, sp;
+    if (!mx_row_of_block(X.nb, nsplit, I, sp)) return;
+    const int lane = threadIdx.x & 63;
+    const int R = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+    const int r0 = X.row[I], n = X.row[I + 1] - r0;
+    const int xb = r0 + static_cast<int>(static_cast<int64_t>(n) * sp / nsplit);
+    const int xe = r0 + static_cast<int>(static_cast<int64_t>(n) * (sp + 1) / nsplit);
+    const float *__restrict__ ll = fl + static_cast<int64_t>(X.nb) * 64 * V;
+    const int64_t row0 = (static_cast<int64_t>(I) * 64 + R * 16) * V;
+    for (int x = xb; x < xe; ++x) {
+        const int64_t col = (static_cast<int64_t>(X.col[x].j) * 64 + lane) * V;
+        float res[16], odd[16];
+#pragma unroll
+        for (int q = 0; q < VT; ++q) {
+            float wc[16], lc[16];
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                wc[k] = 1.0f - fl[col + 16 * q + k];
+                lc[k] = ll[col + 16 * q + k];
+            }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const float *__restrict__ fr = fl + row0 + r * V + 16 * q, *__restrict__ lr = ll + row0 + r * V + 16 * q;
+                float a[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    const float m0 = fr[2 * k] * (lr[2 * k] - lc[2 * k]);
+                    const float m1 = fr[2 * k + 1] * (lr[2 * k + 1] - lc[2 * k + 1]);
+                    a[k] = __builtin_fmaf(wc[2 * k + 1], m1, wc[2 * k] * m0);
+                }
+                const float t = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
+                if (q == 0) res[r] = t;
+                else if (q == 1) res[r] += t;
+                else if (q == 2) odd[r] = t;
+                else odd[r] += t;
+            }
+        }
+        float *__restrict__ po = gm + static_cast<int64_t>(x) * kMxBlock + (R * 4 + (lane >> 4)) * 256 + (lane & 15);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) po[r * 16] = VT > 2 ? res[r] + odd[r] : res[r];
+    }
+}
+
+// dL/d|g|^2 of every channel from G, over the pair records in the forward pass's
+// tiles: the record word, its first channel and two values of G per pair, no
+// |g|^2 stream.  Each channel is written once (gg2_mode as in k_vjp_pairs).
+template <typename T, bool PADQ, int NM, bool TAB, bool QORD>
+__device__ __forceinline__ void mx_gg2_chunk(const TiledArgs<T> &A, const MxArgs<T> &X, const T *__restrict__ gm,
+                                             const T *s_e, const uint32_t *s_kq, const int32_t *s_pos,
+                                             const double *s_tab, int64_t c,
+                                             const int32_t *__restrict__ chan, const int32_t *__restrict__ chan0,
+                                             double *__restrict__ gg2, int gg2_mode) {
+    const int lane = threadIdx.x & 63;
+    const int nm = A.nm;
+    const int dc = QORD ? 0 : A.chunk_dest[c];
+    const int64_t beg = A.chunk_beg[c];
+    const int len = static_cast<int>(A.chunk_end[c] - beg);
+    const uint32_t *__restrict__ pb = A.pnu + beg;
+    const int32_t *__restrict__ cb = chan + beg;
+    const int32_t *__restrict__ cb0 = chan0 + beg;
+    uint32_t pn = pb[lane];
+    int32_t h = cb0[lane];
+    for (int r = 0; r < len; r += 64) {
+        const bool v = r + lane < len;
+        T ed, ep;
+        uint32_t kd, kp;
+        int xd, xp;
+        if (QORD) {
+            const int wd = v ? static_cast<int>(pn & 0xffffu) : 0;
+            const int wp = v ? static_cast<int>(pn >> 16) : 0;
+            ed = s_e[wd];
+            ep = s_e[wp];
+            kd = s_kq[wd];
+            kp = s_kq[wp];
+            xd = s_pos[wd];
+            xp = s_pos[wp];
+        } else {
+            const int p = v ? static_cast<int>(pn) : dc;
+            const StateRec<T> sd = A.st[dc], sp = A.st[p];
+            ed = sd.eps;
+            ep = sp.eps;
+            kd = PADQ ? sd.kqp : sd.kq;
+            kp = PADQ ? sp.kqp : sp.kq;
+            xd = X.pos[dc];
+            xp = X.pos[p];
+        }
+        const int bd = xd >> 6, bp = xp >> 6;
+        // a masked lane may name a block that is not stored
+        const int64_t id = max(X.blk[bd * X.nb + bp], 0), it = max(X.blk[bp * X.nb + bd], 0);
+        const T g1 = gm[id * kMxBlock + mx_inner(xd & 63, xp & 63)];
+        const T g2 = gm[it * kMxBlock + mx_inner(xp & 63, xd & 63)];
+        const int q = PADQ ? static_cast<int>(kp - kd) + A.qoff : q_linear(kd, kp, A.nq0, A.nq1, A.nq2);
+        const Pair2<T> *__restrict__ wq = A.hwN + static_cast<int64_t>(q) * A.tq;
+        Pair2<T> w[NM];
+#pragma unroll
+        for (int m = 0; m < NM; ++m) w[m] = wq[min(m, nm - 1) * A.tm];
+        const int32_t c0 = h;
+        __builtin_amdgcn_sched_barrier(0);
+        pn = pb[r + 64 + lane];
+        h = cb0[r + 64 + lane];
+        __builtin_amdgcn_sched_barrier(0);
+        const T x = ed - ep;
+        double gv[NM];
+#pragma unroll
+        for (int m = 0; m < NM; ++m) {
+            const T xa = x + w[m].a, xe = x - w[m].a;
+            const T da = pair_gauss<T, TAB>(A, xa * xa, s_tab);
+            const T dem = pair_gauss<T, TAB>(A, xe * xe, s_tab);
+            if constexpr (sizeof(T) == 4) {
+                // as k_vjp_batched<float> rounds it
+                const float sm = da + dem;
+                const float bh = __builtin_fmaf(w[m].b, sm, da), ah = __builtin_fmaf(w[m].b, sm, dem);
+                gv[m] = static_cast<double>(A.K * __builtin_fmaf(bh, -g2, -(g1 * ah)));
+            } else {
+                const T t = w[m].b * (da + dem);
+                gv[m] = A.K * (g1 * (t + da) + g2 * (t + dem));
+            }
+        }
+        if (v) write_gg2<NM>(gg2, gg2_mode, c0, cb + r + lane, A.pld, nm, gv);
+    }
+}
+
+template <typename T, bool PADQ, int NM, bool TAB>
+__global__ __launch_bounds__(1024) void k_mx_gg2(TiledArgs<T> A, MxArgs<T> X, const T *__restrict__ gm,
+                                                 const int32_t *__restrict__ chan, const int32_t *__restrict__ chan0,
+                                                 double *__restrict__ gg2, int gg2_mode) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int64_t ti = tile_of_block(A.n_tiles, A.xcd);
+    if (ti < 0) return;
+    const TileRec t = A.tiles[ti];
+    // LDS as in k_pair_matrix
+    double *s_tab = reinterpret_cast<double *>(smem);
+    T *s_e = reinterpret_cast<T *>(s_tab + (sizeof(T) == 8 ? kExpTab : 0));
+    uint32_t *s_kq = reinterpret_cast<uint32_t *>(s_e + A.lds_states);
+    int32_t *s_pos = reinterpret_cast<int32_t *>(s_kq + A.lds_states);
+    const int n = t.lds == 2 ? t.p_hi - t.p_lo + 1 : 0;
+    for (int i = threadIdx.x; i < n; i += blockDim.x) {
+        const StateRec<T> sr = A.st[t.p_lo + i];
+        s_e[i] = sr.eps;
+        s_kq[i] = PADQ ? sr.kqp : sr.kq;
+        s_pos[i] = X.pos[t.p_lo + i];
+    }
+    if constexpr (sizeof(T) == 8 && TAB)
+        for (int i = threadIdx.x; i < kExpTab; i += blockDim.x) s_tab[i] = A.e2tab[i];
+    __syncthreads();
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+    const int nw = static_cast<int>(blockDim.x >> 6);
+    for (int64_t c = t.c0 + wave; c < t.c1; c += nw) {
+        if (t.lds == 2)
+            mx_gg2_chunk<T, PADQ, NM, TAB, true>(A, X, gm, s_e, s_kq, s_pos, s_tab, c, chan, chan0, gg2, gg2_mode);
+        else
+            mx_gg2_chunk<T, PADQ, NM, TAB, false>(A, X, gm, s_e, s_kq, s_pos, s_tab, c, chan, chan0, gg2, gg2_mode);
     }
 }
 
@@ -2299,12 +2711,12 @@ __global__ void k_mx_load3(MxArgs<T> X, const Vec4<T> *__restrict__ x, double *_
 // and the next iterate goes to un.
 template <typename T>
 __global__ __launch_bounds__(64 * kMxParts) void k_mx_tr_finish(TiledArgs<T> A, MxArgs<T> X, const double *__restrict__ part1,
-                                                      int nsplit, const double *__restrict__ part2, double K,
+                                                      MxRuns N, const double *__restrict__ part2, double K,
                                                       const T *__restrict__ f0, const Vec4<T> *__restrict__ rhs,
                                                       const T *__restrict__ tau, const double *__restrict__ u,
                                                       double *__restrict__ un, Vec4<T> *__restrict__ x_new) {
     double o1[3], o2[3];
-    mx_vec_sums<T, 3>(X, part1, nsplit, part2, blockIdx.x, o1, o2);
+    mx_vec_sums<T, 3>(X, part1, N, part2, blockIdx.x, o1, o2);
     if (threadIdx.x >= 64) return;
     const int x = blockIdx.x * 64 + threadIdx.x;
     const int d = X.state[x];

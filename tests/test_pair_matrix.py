@@ -147,3 +147,31 @@ def test_non_finite_occupation_reaches_its_partners_only(E, bad):
     rest = np.arange(B) != 2
     assert np.array_equal(got[rest], clean[rest])
     plan.close()
+
+
+@pytest.mark.parametrize("S,B,modes,dtype", [(2, 2, 1, "f64"), (63, 7, 3, "f64"), (65, 17, 6, "f32"), (129, 33, 3, "f64"),
+                                             (130, 50, 4, "f64"), (64, 64, 2, "f32"), (66, 65, 3, "f64"),
+                                             (100, 130, 3, "f32")])
+def test_reverse_through_the_matrix(E, S, B, modes, dtype):
+    """dL/df of every vector and dL/d|g|^2 summed over them, together and each
+    alone, overwritten and accumulated."""
+    s = full_system(S, 6, n_modes=modes)
+    rng = np.random.default_rng(S + B)
+    F, nph = cast(rng.uniform(size=(B, S)), dtype), cast(s.nph(300.0), dtype)
+    lam = cast(rng.normal(size=(B, S)) + 3.0, dtype)
+    plan = E.build_channels(s, dtype=dtype, device=0)
+    r = rounded(s, dtype)
+    refs = [oracle.collision_vjp(r, F[b], nph, lam[b]) for b in range(B)]
+    rg = sum(x[1] for x in refs)
+    start = torch.full((s.n_channels,), 0.5, dtype=torch.float64, device="cuda:0")
+    args = (plan, dev(F, dtype), dev(nph, dtype), dev(lam, dtype))
+    gf, gg = E.collision_vjp(*args, gg2=start.clone())
+    gf1, none = E.collision_vjp(*args)
+    nogf, gg1 = E.collision_vjp(*args, want_f=False, gg2=start.clone(), accumulate=True)
+    assert none is None and nogf is None
+    assert np.array_equal(host(gf), host(gf1))
+    for b in sorted({0, 1, B // 2, B - 1}):
+        assert nerr(host(gf)[b], refs[b][0]) <= TOL[dtype], b
+    assert nerr(host(gg), rg) <= TOL[dtype]
+    assert nerr(host(gg1) - 0.5, rg) <= TOL[dtype]
+    plan.close()
