@@ -99,7 +99,6 @@ struct ephbte_plan_s {
     // map n to f = -n for the kernels (see boson_neg); max |f| of each pass's
     // input sets the fixed-point scale
     bool boson = false;
-    unsigned long long *fmax_bits = nullptr;
     uint32_t *ph_pa = nullptr, *ph_pb = nullptr;
     void *ph_g2 = nullptr;            // [n_modes][ph_ld]
     int32_t *ph_chan = nullptr;       // [n_modes][ph_ld] caller channel of each slot, -1: none
@@ -137,8 +136,11 @@ struct ephbte_plan_s {
     std::vector<int64_t> upper_beg;        // host: first entry of row d with p > d
     std::vector<int32_t> pmin_up, pmax_up;  // host: partner range of that part
     unsigned long long *jacc = nullptr;     // [S] partner-side fixed-point sums (zero between calls)
-    unsigned long long *nmax_bits = nullptr, *gmax_bits = nullptr;
-    double *pack_bmax = nullptr;            // per-block max |N| of the last pack
+    unsigned long long *gmax_bits = nullptr;
+    // maxima left by k_prep, kPrepMax a list: |N| of the last table, |f|, |lam|
+    // and, for the phonon side's dL/df, |mu| and |N| of the call
+    double *prep_max = nullptr;
+    int prep_n[5] = {0, 0, 0, 0, 0};
     int sym_lds_states = 0;
     int pr_lds_states = 0;      // partner window of the pair-record passes
     int pr_threads = 1024;      // threads per workgroup of the pair forward pass
@@ -169,9 +171,6 @@ struct ephbte_plan_s {
     int64_t n_pr_chunks = 0, n_pr_tiles = 0;
     bool pr_ok = false;
     bool exp_table = true;                 // FP64 Gaussians of the pair pass from the LDS table
-    unsigned long long *lmax_bits = nullptr;  // max |lam| of the pair reverse pass (double bits)
-    unsigned long long *mmax_bits = nullptr;  // max |mu| and max |N| of the phonon side's dL/df over
-                                              // pair records (its own slots: other passes keep theirs)
     // pair matrix (built from the pair records where its blocks are filled
     // enough, see build_matrix_layout): positions, blocks, and the workspace
     bool mx_ok = false;
@@ -338,7 +337,7 @@ void free_plan(ephbte_plan P) {
                      (void **)&P->btiles,    (void **)&P->sub_off,    (void **)&P->e2tab,
                      (void **)&P->sym_chunk_beg, (void **)&P->sym_chunk_end, (void **)&P->sym_chunk_dest,
                      (void **)&P->sym_dest_chunk, (void **)&P->sym_tiles, (void **)&P->jacc,
-                     (void **)&P->nmax_bits, (void **)&P->gmax_bits, (void **)&P->pack_bmax,
+                     (void **)&P->gmax_bits, (void **)&P->prep_max,
                      (void **)&P->drop_idx, (void **)&P->vbtiles, (void **)&P->vsub_off,
                      (void **)&P->nbr, (void **)&P->small_tiles, (void **)&P->ph_pa,
                      (void **)&P->ph_pb, (void **)&P->ph_g2, (void **)&P->ph_chan,
@@ -347,7 +346,7 @@ void free_plan(ephbte_plan P) {
                      (void **)&P->ph_bucket_modes, (void **)&P->pr_partner, (void **)&P->pr_g2,
                      (void **)&P->pr_chan, (void **)&P->pr_chunk_beg, (void **)&P->pr_chunk_end,
                      (void **)&P->pr_chunk_dest, (void **)&P->pr_dest_chunk, (void **)&P->pr_tiles,
-                     (void **)&P->lmax_bits, (void **)&P->mmax_bits, (void **)&P->pr_ch0, (void **)&P->fmax_bits,
+                     (void **)&P->pr_ch0,
                      (void **)&P->used_rows, (void **)&P->mx_pos, (void **)&P->mx_state, (void **)&P->mx_blk,
                      (void **)&P->mx_row, (void **)&P->mx_col};
     for (auto pp : ptrs) dfree(*pp);
@@ -459,6 +458,22 @@ void order_pair_records(ephbte_plan P, ChunkTable &pc, std::vector<Tile> &tp, bo
     tp = std::move(o.tiles);
 }
 
+// Tiles of a single-copy pass: one workgroup a compute unit at a time, so the
+// number of tiles is kept to a whole number of rounds over the compute units (a
+// last round of a few tiles costs a whole tile's time: 1047 tiles on 256 units ran
+// five rounds).  Four rounds, fewer where a tile would hold less than `min_tile`
+// records: each tile waits for its window before its first batch (2 - 4 us).
+template <typename F> std::vector<Tile> round_tiles(int64_t records, int64_t min_tile, int n_cu, F &&make) {
+    const int64_t rounds = std::min<int64_t>(4, std::max<int64_t>(1, records / (min_tile * n_cu)));
+    int64_t target = std::max<int64_t>(records / (rounds * n_cu) + 1, 1024);
+    std::vector<Tile> t = make(target);
+    for (int k = 0; k < 40 && static_cast<int64_t>(t.size()) > rounds * n_cu; ++k) {
+        target += target / 64 + 1;
+        t = make(target);
+    }
+    return t;
+}
+
 void upload_chunks(ephbte_plan P, int64_t chunk_entries) {
     ChunkTable t = make_chunks(P->row_ptr, chunk_entries);
     free_graphs(P);
@@ -502,14 +517,14 @@ void upload_chunks(ephbte_plan P, int64_t chunk_entries) {
     P->n_small_tiles = static_cast<int64_t>(tv.size());
     if (P->upper_beg.empty()) return;
     // single-copy tables over the upper parts of the rows; one workgroup per CU
-    // (1024 threads), about 4 tiles each (measured; smaller tiles pay more
-    // window staging and partner-side flushes)
+    // (1024 threads)
     std::vector<int64_t> row_end(P->row_ptr.begin() + 1, P->row_ptr.end());
     ChunkTable u = make_chunks_seg(P->upper_beg, row_end, chunk_entries);
     const int64_t nch = P->E / 2;
-    const int64_t target_u = P->tile_entries > 0 ? P->tile_entries / 2 + 1
-                                                 : nch / (4 * static_cast<int64_t>(P->n_cu)) + 1;
-    std::vector<Tile> tu = make_tiles(u, P->row_ptr, P->pmin_up, P->pmax_up, P->sym_lds_states, target_u);
+    auto make_u = [&](int64_t target) {
+        return make_tiles(u, P->row_ptr, P->pmin_up, P->pmax_up, P->sym_lds_states, target);
+    };
+    std::vector<Tile> tu = P->tile_entries > 0 ? make_u(P->tile_entries / 2 + 1) : round_tiles(nch, 32768, P->n_cu, make_u);
     dfree(reinterpret_cast<void *&>(P->sym_chunk_beg));
     dfree(reinterpret_cast<void *&>(P->sym_chunk_end));
     dfree(reinterpret_cast<void *&>(P->sym_chunk_dest));
@@ -544,8 +559,6 @@ void upload_chunks(ephbte_plan P, int64_t chunk_entries) {
     std::vector<int64_t> pbeg(P->pr_rowptr.begin(), P->pr_rowptr.end() - 1);
     std::vector<int64_t> pend(P->pr_rowptr.begin() + 1, P->pr_rowptr.end());
     ChunkTable pc = make_chunks_seg(pbeg, pend, chunk_entries);
-    const int64_t target_p = P->tile_entries > 0 ? P->tile_entries / (2 * static_cast<int64_t>(P->nm)) + 1
-                                                 : P->pr_np / (4 * static_cast<int64_t>(P->n_cu)) + 1;
     // in q order, a tile's window stages its destinations too
     const bool qord = P->pair_order == 1 && P->pr_np < (int64_t(1) << 32);
     std::vector<int32_t> wmin;
@@ -554,8 +567,11 @@ void upload_chunks(ephbte_plan P, int64_t chunk_entries) {
         for (int64_t d = 0; d < P->S; ++d)
             if (P->pmax_up[d] >= P->pmin_up[d]) wmin[d] = static_cast<int32_t>(d);
     }
-    std::vector<Tile> tp = make_tiles(pc, P->row_ptr, qord ? wmin : P->pmin_up, P->pmax_up, P->pr_lds_states,
-                                      target_p);
+    auto make_p = [&](int64_t target) {
+        return make_tiles(pc, P->row_ptr, qord ? wmin : P->pmin_up, P->pmax_up, P->pr_lds_states, target);
+    };
+    std::vector<Tile> tp = P->tile_entries > 0 ? make_p(P->tile_entries / (2 * static_cast<int64_t>(P->nm)) + 1)
+                                               : round_tiles(P->pr_np, 8192, P->n_cu, make_p);
     order_pair_records(P, pc, tp, qord);
     dfree(reinterpret_cast<void *&>(P->pr_chunk_beg));
     dfree(reinterpret_cast<void *&>(P->pr_chunk_end));
@@ -619,6 +635,24 @@ template <typename T> Tables<T> tables(ephbte_plan P, const void *nph) {
     return t;
 }
 
+// lists of maxima (k_prep)
+enum { kMaxN = 0, kMaxF = 1, kMaxL = 2, kMaxMu = 3, kMaxNph = 4 };
+constexpr int kPrepMax = 64;   // workgroups of one part of k_prep (a list is one value a lane)
+MaxList max_list(ephbte_plan P, int which) { return MaxList{P->prep_max + which * kPrepMax, P->prep_n[which]}; }
+
+// Where a compute unit runs several tiles one after another, each would wait for
+// the reduction of the lists (about 2 us a tile, 518 against 505 us for the forward
+// pass on the 100^3 system): one more launch (4 us) leaves one value a list.
+template <typename T>
+void reduce_lists(ephbte_plan P, TiledArgs<T> &a, MaxList &l, int64_t tiles, hipStream_t s) {
+    if (tiles <= 2 * P->n_cu || (a.nmax.n <= 1 && a.fmax.n <= 1 && l.n <= 1)) return;
+    double *out = P->prep_max + 5 * kPrepMax;
+    hipLaunchKernelGGL(k_reduce_lists, dim3(1), dim3(64), 0, s, a.nmax, a.fmax, l, out);
+    a.nmax = MaxList{out, 1};
+    if (a.fmax.n) a.fmax = MaxList{out + 1, 1};
+    if (l.n) l = MaxList{out + 2, 1};
+}
+
 template <typename T> TiledArgs<T> tiled_args(ephbte_plan P) {
     TiledArgs<T> a;
     a.pnu = P->pnu;
@@ -648,9 +682,9 @@ template <typename T> TiledArgs<T> tiled_args(ephbte_plan P) {
     a.xcd = P->xcd_map ? 1 : 0;
     a.chunk_end = nullptr;
     a.jacc = P->jacc;
-    a.nmax_bits = P->nmax_bits;
+    a.nmax = max_list(P, kMaxN);
     a.gmax_bits = P->gmax_bits;
-    a.fmax_bits = P->boson ? P->fmax_bits : nullptr;
+    a.fmax = P->boson ? max_list(P, kMaxF) : MaxList{nullptr, 0};
     return a;
 }
 
@@ -741,6 +775,10 @@ void launch_pairs(ephbte_plan P, const TiledArgs<T> &a, const T *f, T *part, siz
 
 bool use_pairs(ephbte_plan P, int B) {
     return B == 1 && P->layout == 3 && P->sym_ok && P->pr_ok && P->n_pr_tiles > 0;
+}
+// the reverse pass over the pair records (its window holds lam too)
+bool vjp_pairs_fit(ephbte_plan P) {
+    return use_pairs(P, 1) && vjp_pair_lds_bytes(P->dtype, P->pr_lds_states) <= P->lds_max;
 }
 
 int64_t nqm_of(ephbte_plan P) {
@@ -983,31 +1021,44 @@ bool enqueue_vjp_batched_pv(ephbte_plan P, int B, const T *f, int64_t ldf, const
     return true;
 }
 
-// workgroups of the {hw, N} pack kernels
-constexpr int64_t kPackBlocks = 8192;
-
-// Interleave the plan's phonon energies with the caller's occupations into
-// one {hw, N} table (one gather per entry instead of two).
+constexpr int kPrepThreads = 1024;
+int prep_blocks(int64_t n) {
+    return static_cast<int>(std::max<int64_t>(std::min<int64_t>((n + kPrepThreads - 1) / kPrepThreads, kPrepMax), 1));
+}
+// The {hw, N} table of a call: one gather per entry instead of two.  tab != null:
+// the plain table (no box) there instead of the plan's.
+template <typename T> PackPart<T> pack_part(ephbte_plan P, const void *nph, Pair2<T> *tab = nullptr) {
+    PackPart<T> p{};
+    p.hw = static_cast<const T *>(P->hw);
+    p.nph = static_cast<const T *>(nph);
+    p.out = tab ? tab : static_cast<Pair2<T> *>(P->hwN.p);
+    p.box = P->qbox;
+    p.padq = P->padq && !tab ? 1 : 0;
+    p.nm = P->nm;
+    p.rows = static_cast<int>(P->qpad_n);
+    p.mode_major = P->tab_mm ? 1 : 0;
+    p.used = P->used_rows;
+    p.n = p.padq ? P->n_used_rows * P->nm : nqm_of(P);
+    p.bmax = P->prep_max + kMaxN * kPrepMax;
+    p.blocks = P->prep_n[kMaxN] = prep_blocks(p.n);
+    return p;
+}
+template <typename T> VecPart<T> vec_part(ephbte_plan P, int which, const T *x, T *neg, int64_t n) {
+    VecPart<T> v{};
+    v.x = x;
+    v.neg = neg;
+    v.n = n;
+    v.bmax = P->prep_max + which * kPrepMax;
+    v.blocks = P->prep_n[which] = prep_blocks(n);
+    return v;
+}
+template <typename T>
+void enqueue_prep(ephbte_plan P, const PackPart<T> &p, const VecPart<T> &v0, const VecPart<T> &v1, hipStream_t s) {
+    hipLaunchKernelGGL((k_prep<T>), dim3(static_cast<unsigned>(p.blocks + v0.blocks + v1.blocks)), dim3(kPrepThreads), 0, s, p,
+                       v0, v1);
+}
 template <typename T> void enqueue_pack(ephbte_plan P, const void *nph, hipStream_t s) {
-    // each pack block also stores the max |N| it saw; one more workgroup reduces
-    // those to the max |N| of this call (the single-copy pass's fixed-point scale)
-    double *bmax = P->pack_bmax;
-    unsigned nb;
-    if (P->padq) {
-        const int64_t n = P->n_used_rows * P->nm;
-        nb = static_cast<unsigned>(std::max<int64_t>(std::min<int64_t>((n + 255) / 256, kPackBlocks), 1));
-        hipLaunchKernelGGL((k_pack_hwN_pad<T>), dim3(nb), dim3(256), 0, s, static_cast<const T *>(P->hw),
-                           static_cast<const T *>(nph), static_cast<Pair2<T> *>(P->hwN.p), P->qbox, P->nm,
-                           static_cast<int>(P->qpad_n), (const int32_t *)P->used_rows,
-                           static_cast<int>(P->n_used_rows), P->tab_mm ? 1 : 0, bmax);
-    } else {
-        const int64_t n = nqm_of(P);
-        nb = static_cast<unsigned>(std::max<int64_t>(std::min<int64_t>((n + 255) / 256, kPackBlocks), 1));
-        hipLaunchKernelGGL((k_pack_hwN<T>), dim3(nb), dim3(256), 0, s, static_cast<const T *>(P->hw),
-                           static_cast<const T *>(nph), static_cast<Pair2<T> *>(P->hwN.p), n, bmax);
-    }
-    hipLaunchKernelGGL(k_max_blocks, dim3(1), dim3(1024), 0, s, (const double *)bmax, static_cast<int>(nb),
-                       P->nmax_bits);
+    enqueue_prep<T>(P, pack_part<T>(P, nph), VecPart<T>{}, VecPart<T>{}, s);
 }
 
 size_t tiled_lds_bytes(ephbte_plan P) {
@@ -1293,18 +1344,16 @@ bool enqueue_vjp_mx(ephbte_plan P, int B, const T *f, int64_t ldf, const T *lam,
 // Enqueue I[f] for B vectors with epilogue E (no allocation inside; the
 // caller ensured P->part and P->hwN are large enough).  pack = false when the
 // {hw, N} table (and, for B vectors over it, the pair matrix) already holds this
-// call's occupations.
-// max |f| over one vector into P->fmax_bits: the fixed-point scale of the
-// single-copy passes for occupations outside [0, 1] (Bose plans)
-template <typename T> void enqueue_fmax(ephbte_plan P, const T *f, hipStream_t s) {
-    hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(64), 0, s, P->fmax_bits, 1);
-    hipLaunchKernelGGL((k_abs_max_bits<T>), dim3(grid_of(P->S)), dim3(256), 0, s, f, int64_t(P->S), P->fmax_bits);
-}
+// call's occupations; ready: a Bose plan's max |f| is there too.
 
 template <typename T>
 void enqueue_forward(ephbte_plan P, int B, const T *f, int64_t ldf, const void *nph,
-                     const Epi<T> &E, hipStream_t s, bool pack = true) {
-    if (pack) enqueue_pack<T>(P, nph, s);
+                     const Epi<T> &E, hipStream_t s, bool pack = true, bool ready = false) {
+    // the single-copy passes of a Bose plan set their fixed-point scale from max |f|
+    const bool fm = !ready && P->boson && (use_pairs(P, B) || use_sym(P, B));
+    if (pack || fm)
+        enqueue_prep<T>(P, pack ? pack_part<T>(P, nph) : PackPart<T>{},
+                        fm ? vec_part<T>(P, kMaxF, f, nullptr, P->S) : VecPart<T>{}, VecPart<T>{}, s);
     if (use_mx_batch<T>(P, B)) {
         if (pack) enqueue_pair_matrix<T>(P, s);
         enqueue_forward_mx<T>(P, B, f, ldf, E, s);
@@ -1314,9 +1363,10 @@ void enqueue_forward(ephbte_plan P, int B, const T *f, int64_t ldf, const void *
         enqueue_forward_batched<T>(P, B, f, ldf, E, s);
         return;
     }
-    if (P->boson && (use_pairs(P, B) || use_sym(P, B))) enqueue_fmax<T>(P, f, s);
     if (use_pairs(P, B)) {
         TiledArgs<T> a = pair_args<T>(P);
+        MaxList none{nullptr, 0};
+        reduce_lists<T>(P, a, none, P->n_pr_tiles, s);
         T *part = static_cast<T *>(P->sym_part.p);
         const size_t shm = sym_lds_bytes(P->dtype, P->pr_lds_states);
         const int64_t kt = ktime_begin(P, s);
@@ -1329,6 +1379,8 @@ void enqueue_forward(ephbte_plan P, int B, const T *f, int64_t ldf, const void *
     }
     if (use_sym(P, B)) {
         TiledArgs<T> a = sym_args<T>(P);
+        MaxList none{nullptr, 0};
+        reduce_lists<T>(P, a, none, P->n_sym_tiles, s);
         T *part = static_cast<T *>(P->sym_part.p);
         // entries per lane and stage: 2 in FP64 keeps the pipeline in the 128
         // registers a lane has at 1024 threads per workgroup
@@ -1404,11 +1456,7 @@ void enqueue_forward_noalloc(ephbte_plan P, const T *f, const void *nph, T *I, u
     Pair2<T> *tab = reinterpret_cast<Pair2<T> *>(base);
     T *part = reinterpret_cast<T *>(base + ((2 * sizeof(T) * static_cast<size_t>(std::max<int64_t>(n, 1)) + 255) &
                                             ~size_t(255)));
-    const unsigned nb = static_cast<unsigned>(std::max<int64_t>(std::min<int64_t>((n + 255) / 256, kPackBlocks), 1));
-    hipLaunchKernelGGL((k_pack_hwN<T>), dim3(nb), dim3(256), 0, s, static_cast<const T *>(P->hw),
-                       static_cast<const T *>(nph), tab, n, P->pack_bmax);
-    hipLaunchKernelGGL(k_max_blocks, dim3(1), dim3(1024), 0, s, (const double *)P->pack_bmax,
-                       static_cast<int>(nb), P->nmax_bits);
+    enqueue_prep<T>(P, pack_part<T>(P, nph, tab), VecPart<T>{}, VecPart<T>{}, s);
     const Epi<T> E = epi_store<T>(I, P->S);
     if (use_pairs(P, 1)) {
         TiledArgs<T> a = pair_args<T>(P);
@@ -1446,18 +1494,20 @@ void enqueue_forward_noalloc(ephbte_plan P, const T *f, const void *nph, T *I, u
 }
 
 // gg2_mode: 0 none, 1 overwrite, 2 accumulate.  E.mode < 0: gradient of g2 only.
-// The caller packed the {hw, N} table for nph and ensured P->part (n_chunks).
+// The caller packed the {hw, N} table for nph and ensured P->part (n_chunks);
+// ready: it left the maxima of lam (and, for a Bose plan, f) too.
 template <typename T>
 void enqueue_vjp(ephbte_plan P, const T *f, const T *lam, const void *nph, const Epi<T> &E,
-                 double *gg2, int gg2_mode, hipStream_t s) {
+                 double *gg2, int gg2_mode, hipStream_t s, bool ready = false) {
     (void)nph;
-    if (use_pairs(P, 1) && vjp_pair_lds_bytes(P->dtype, P->pr_lds_states) <= P->lds_max) {
-        // max |lam| of this call (the partner side's fixed-point scale)
-        hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(64), 0, s, P->lmax_bits, 1);
-        hipLaunchKernelGGL((k_abs_max_bits<T>), dim3(grid_of(P->S)), dim3(256), 0, s, lam, int64_t(P->S),
-                           P->lmax_bits);
-        if (P->boson) enqueue_fmax<T>(P, f, s);
+    if (vjp_pairs_fit(P)) {
+        // max |lam| of this call (the fixed-point scale)
+        if (!ready)
+            enqueue_prep<T>(P, PackPart<T>{}, vec_part<T>(P, kMaxL, lam, nullptr, P->S),
+                            P->boson ? vec_part<T>(P, kMaxF, f, nullptr, P->S) : VecPart<T>{}, s);
         TiledArgs<T> a = pair_args<T>(P);
+        MaxList lm = max_list(P, kMaxL);
+        reduce_lists<T>(P, a, lm, P->n_pr_tiles, s);
         T *part = static_cast<T *>(P->sym_part.p);
         const int want_f = E.mode >= 0 ? 1 : 0;
         const dim3 grid(static_cast<unsigned>(P->n_pr_tiles)), block(kVjpPairThreads);
@@ -1465,7 +1515,6 @@ void enqueue_vjp(ephbte_plan P, const T *f, const T *lam, const void *nph, const
         auto go = [&](auto nmc) {
             constexpr int NM = decltype(nmc)::value;
             const bool tab = sizeof(T) == 8 && P->exp_table;
-            const unsigned long long *lm = P->lmax_bits;
             const int32_t *ch = P->pr_chan, *c0 = P->pr_ch0;
             if (P->padq && tab)
                 hipLaunchKernelGGL((k_vjp_pairs<T, true, NM, true>), grid, block, shm, s, a, f, lam, part, want_f, lm,
@@ -1488,7 +1537,7 @@ void enqueue_vjp(ephbte_plan P, const T *f, const T *lam, const void *nph, const
         else go(std::integral_constant<int, 8>{});
         if (want_f)
             hipLaunchKernelGGL((k_vjp_pairs_finish<T>), dim3((P->S + 255) / 256), dim3(256), 0, s, a,
-                               (const T *)part, (const unsigned long long *)P->lmax_bits, E);
+                               (const T *)part, lm, E);
         HIPC(hipGetLastError());
         return;
     }
@@ -2275,16 +2324,14 @@ void enqueue_phonon_vjp_f(ephbte_plan P, const T *u, const T *N, const T *mu, T 
         // over the q-ordered pair records: max |N| and max |mu| of the call
         // set the fixed-point scale
         const int64_t nqm = nqm_of(P);
-        // (a few hundred workgroups: fewer atomics on the one word)
-        const dim3 gm(std::min<unsigned>(grid_of(nqm), 256u));
-        hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(64), 0, s, P->mmax_bits, 2);
-        hipLaunchKernelGGL((k_abs_max_bits<T>), gm, dim3(256), 0, s, mu, nqm, P->mmax_bits);
-        hipLaunchKernelGGL((k_abs_max_bits<T>), gm, dim3(256), 0, s, N, nqm, P->mmax_bits + 1);
+        enqueue_prep<T>(P, PackPart<T>{}, vec_part<T>(P, kMaxMu, mu, nullptr, nqm),
+                        vec_part<T>(P, kMaxNph, N, nullptr, nqm), s);
         TiledArgs<T> a = pair_args<T>(P);
-        a.nmax_bits = P->mmax_bits + 1;
+        a.nmax = max_list(P, kMaxNph);
+        MaxList mm = max_list(P, kMaxMu);
+        reduce_lists<T>(P, a, mm, P->n_pr_tiles, s);
         const dim3 grid(static_cast<unsigned>(P->n_pr_tiles)), block(1024);
         const size_t shm = sym_lds_bytes(P->dtype, P->pr_lds_states);
-        const unsigned long long *mm = P->mmax_bits;
         auto go = [&](auto nmc) {
             constexpr int NM = decltype(nmc)::value;
             if (P->padq)
@@ -2983,14 +3030,9 @@ ephbte_status ephbte_build_channels(const ephbte_problem *problem, const ephbte_
             if (P->sym_ok && P->pr_ok) P->layout = 3;
             dalloc(P->jacc, sizeof(unsigned long long) * std::max(P->S, 1), &P->layout_bytes);
             HIPC(hipMemset(P->jacc, 0, sizeof(unsigned long long) * std::max(P->S, 1)));
-            dalloc(P->nmax_bits, sizeof(unsigned long long), &P->layout_bytes);
             dalloc(P->gmax_bits, sizeof(unsigned long long), &P->layout_bytes);
-            dalloc(P->pack_bmax, sizeof(double) * kPackBlocks, &P->layout_bytes);
-            dalloc(P->lmax_bits, sizeof(unsigned long long), &P->layout_bytes);
-            dalloc(P->mmax_bits, 2 * sizeof(unsigned long long), &P->layout_bytes);
-            dalloc(P->fmax_bits, sizeof(unsigned long long), &P->layout_bytes);
-            HIPC(hipMemset(P->nmax_bits, 0, sizeof(unsigned long long)));
-            HIPC(hipMemset(P->fmax_bits, 0, sizeof(unsigned long long)));
+            dalloc(P->prep_max, sizeof(double) * (5 * kPrepMax + 3), &P->layout_bytes);
+            HIPC(hipMemset(P->prep_max, 0, sizeof(double) * (5 * kPrepMax + 3)));
         }
         { HostLayout tmp; std::swap(tmp, L); }
         P->block_threads = 512;
@@ -3027,18 +3069,33 @@ ephbte_status ephbte_collision_integral(ephbte_plan plan, int32_t batch, const v
             const T *ft = static_cast<const T *>(f);
             int64_t ldft = ldf;
             T *It = static_cast<T *>(I);
-            if (plan->boson) {   // I_B(n) = -I_F(-n)
+            const bool one = plan->boson && batch == 1 && (use_pairs(plan, 1) || use_sym(plan, 1));
+            if (one) {   // I_B(n) = -I_F(-n): table, -n and its max in one launch
+                ensure_fwd<T>(plan, 1);
+                ensure(plan->bs_x, sizeof(T) * static_cast<size_t>(plan->S), &plan->ws_gen);
+                T *neg = static_cast<T *>(plan->bs_x.p);
+                enqueue_prep<T>(plan, pack_part<T>(plan, nph), vec_part<T>(plan, kMaxF, ft, neg, plan->S),
+                                VecPart<T>{}, s);
+                ft = neg;
+            } else if (plan->boson) {
                 ft = boson_neg<T>(plan, plan->bs_x, f, ldf, batch, s);
                 ldft = plan->S;
             }
+            // (the epilogue turns the sign of a Bose plan's output)
+            auto store = [&](T *out, int64_t ld) {
+                Epi<T> e = epi_store<T>(out, ld);
+                e.neg = plan->boson ? 1 : 0;
+                return e;
+            };
             if (!nph_per_batch || batch == 1) {
                 ensure_fwd<T>(plan, batch);
-                enqueue_forward<T>(plan, batch, ft, ldft, nph, epi_store<T>(It, ldi), s);
+                enqueue_forward<T>(plan, batch, ft, ldft, nph, store(It, ldi), s, !one, one);
             } else if (batch >= plan->batch_min && plan->n_btiles > 0 && pv_table_fits(plan)) {
                 // a bath per vector, batched: the table's hw from the first bath's pack
                 ensure_fwd<T>(plan, batch);
                 enqueue_pack<T>(plan, nph, s);
                 enqueue_forward_batched_pv<T>(plan, batch, ft, ldft, static_cast<const T *>(nph), It, ldi, s);
+                if (plan->boson) neg_in_place<T>(plan, It, ldi, batch, s);
             } else {
                 // one bath per vector: the {hw, N} table differs per vector, so
                 // each vector is a single-vector pass after its own pack
@@ -3046,9 +3103,8 @@ ephbte_status ephbte_collision_integral(ephbte_plan plan, int32_t batch, const v
                 const int64_t tab = nqm_of(plan);
                 for (int b = 0; b < batch; ++b)
                     enqueue_forward<T>(plan, 1, ft + b * ldft, ldft, static_cast<const T *>(nph) + b * tab,
-                                       epi_store<T>(It + b * ldi, ldi), s);
+                                       store(It + b * ldi, ldi), s);
             }
-            if (plan->boson) neg_in_place<T>(plan, It, ldi, batch, s);
         };
         if (plan->dtype == EPHBTE_F64) run(double{});
         else run(float{});
@@ -3106,7 +3162,21 @@ ephbte_status ephbte_collision_vjp(ephbte_plan plan, int32_t batch, const void *
             const bool per_batch = nph_per_batch && batch > 1;
             const void *f = f_in, *gI = gI_in;
             int64_t ldf = ldf_in, ldg = ldg_in;
-            if (plan->boson) {
+            // one vector over the pair records: the table, the maxima and a Bose
+            // plan's negated copies in one launch
+            const bool one = batch == 1 && vjp_pairs_fit(plan);
+            if (one) {
+                const T *f1 = static_cast<const T *>(f), *l1 = static_cast<const T *>(gI);
+                T *nf = nullptr, *nl = nullptr;
+                if (plan->boson) {
+                    ensure(plan->bs_x, sizeof(T) * static_cast<size_t>(S), &plan->ws_gen);
+                    ensure(plan->bs_y, sizeof(T) * static_cast<size_t>(S), &plan->ws_gen);
+                    f = nf = static_cast<T *>(plan->bs_x.p);
+                    gI = nl = static_cast<T *>(plan->bs_y.p);
+                }
+                enqueue_prep<T>(plan, pack_part<T>(plan, nph), vec_part<T>(plan, kMaxL, l1, nl, S),
+                                plan->boson ? vec_part<T>(plan, kMaxF, f1, nf, S) : VecPart<T>{}, s);
+            } else if (plan->boson) {
                 // L = sum lam I_B(n) = sum (-lam) I_F(-n): the Fermi pass on
                 // (-n, -lam) gives dL/d|g|^2 as it is and -dL/dn
                 f = boson_neg<T>(plan, plan->bs_x, f_in, ldf_in, batch, s);
@@ -3119,14 +3189,14 @@ ephbte_status ephbte_collision_vjp(ephbte_plan plan, int32_t batch, const void *
                                    plan->n_drop);
             }
             bool done = false;
-            if (!per_batch) {
+            if (!one && !per_batch) {
                 enqueue_pack<T>(plan, nph, s);
                 const int gmode = gg2 ? (accumulate_gg2 ? 2 : 1) : 0;
                 const T *ft = static_cast<const T *>(f), *lt = static_cast<const T *>(gI);
                 done = enqueue_vjp_mx<T>(plan, batch, ft, ldf, lt, ldg, static_cast<T *>(gf), ldgf, gg2, gmode, s) ||
                        enqueue_vjp_batched<T>(plan, batch, ft, ldf, lt, ldg, static_cast<T *>(gf), ldgf, gg2, gmode,
                                               s);
-            } else if (batch >= plan->batch_min) {
+            } else if (!one && batch >= plan->batch_min) {
                 // a bath per vector, batched: the table's hw from the first bath's pack
                 enqueue_pack<T>(plan, nph, s);
                 done = enqueue_vjp_batched_pv<T>(plan, batch, static_cast<const T *>(f), ldf,
@@ -3144,13 +3214,14 @@ ephbte_status ephbte_collision_vjp(ephbte_plan plan, int32_t batch, const void *
                 Epi<T> e{};
                 if (gf) {
                     e = epi_store<T>(static_cast<T *>(gf) + b * ldgf, S);
+                    e.neg = one && plan->boson ? 1 : 0;
                 } else {
                     e.mode = -1;
                 }
                 const int gmode = gg2 ? ((accumulate_gg2 || b > 0) ? 2 : 1) : 0;
-                enqueue_vjp<T>(plan, fb, lb, nb, e, gg2, gmode, s);
+                enqueue_vjp<T>(plan, fb, lb, nb, e, gg2, gmode, s, one);
             }
-            if (plan->boson && gf) neg_in_place<T>(plan, gf, ldgf, batch, s);
+            if (plan->boson && gf && !one) neg_in_place<T>(plan, gf, ldgf, batch, s);
         };
         if (plan->dtype == EPHBTE_F64) run(double{});
         else run(float{});

@@ -159,6 +159,7 @@ template <typename T> struct Tables {
 // v = dL/df_d (reverse), for vector b.
 template <typename T> struct Epi {
     int mode;              // see apply_epi
+    int neg;               // mode 0: store -v (Bose plans)
     T *out;                // mode 0: output [B][ld_out]
     int64_t ld_out;
     const T *f0;           // RK4: step start f (caller layout, ld_f0)
@@ -213,7 +214,7 @@ __device__ __forceinline__ void apply_epi(const Epi<T> &E, int b, int d, int S, 
     const int64_t iw = static_cast<int64_t>(b) * S + d;
     if (E.mode > EPI_STORE && E.nbr) v += drift_term(E, b, d);
     switch (E.mode) {
-    case EPI_STORE: E.out[static_cast<int64_t>(b) * E.ld_out + d] = v; break;
+    case EPI_STORE: E.out[static_cast<int64_t>(b) * E.ld_out + d] = E.neg ? -v : v; break;
     case EPI_RK1: {
         T f = E.f0[static_cast<int64_t>(b) * E.ld_f0 + d];
         E.acc[iw] = v;
@@ -318,6 +319,14 @@ template <typename T> struct alignas(2 * sizeof(T)) Pair2 {
     T a, b;
 };
 
+// Maxima left by the workgroups of a preparing kernel (k_prep); the kernels that
+// set a fixed-point scale from them take the largest themselves (scale_load), one
+// launch fewer than a kernel that reduces them.  At most 64 values; n = 0: none.
+struct MaxList {
+    const double *v;
+    int n;
+};
+
 template <typename T> struct TiledArgs {
     const uint32_t *__restrict__ pnu;
     const T *__restrict__ g2;
@@ -341,13 +350,13 @@ template <typename T> struct TiledArgs {
     // single-copy pass only
     const int64_t *__restrict__ chunk_end;           // chunk c is [chunk_beg[c], chunk_end[c])
     unsigned long long *__restrict__ jacc;           // [S] partner-side sums, fixed point
-    const unsigned long long *__restrict__ nmax_bits;  // max |N| of the packed table (double bits)
+    MaxList nmax;                                    // max |N| of the packed table
     const unsigned long long *__restrict__ gmax_bits;  // max over states of sum |g|^2 (double bits)
     // pair records (k_fwd_pairs): pnu holds partners, g2 is [n_modes][pld]
     int64_t pld;
     // occupations outside [0, 1] (the Bose plans' negated n): max |f| of the
-    // call's input (double bits), or null when f lies in [0, 1]
-    const unsigned long long *__restrict__ fmax_bits;
+    // call's input, or n = 0 when f lies in [0, 1]
+    MaxList fmax;
 };
 
 // ---- fixed point for the partner side of the single-copy pass -------------
@@ -359,22 +368,47 @@ template <typename T> struct TiledArgs {
 // G_max the largest sum of |g|^2 over one state's channels; s puts that bound
 // below 2^61.  With |f| <= m instead, the occupation products of a term,
 // at most 1 in [0, 1], are at most (1 + 2m)^2, a factor on the bound.
-__device__ __forceinline__ double occ_factor(const unsigned long long *fmax_bits) {
-    if (!fmax_bits) return 1.0;
-    const double m = __longlong_as_double(static_cast<long long>(*fmax_bits));
+// Values a scale is made of, one of each list per lane (lists hold at most 64):
+// loaded at the top of a kernel, so that they arrive while it stages its window.
+struct ScaleIn {
+    double n, f, l, g;
+    bool occ, one;   // one: every list holds one value
+};
+__device__ __forceinline__ double list_value(MaxList l) {
+    const int i = l.n == 1 ? 0 : static_cast<int>(threadIdx.x & 63);
+    return i < l.n ? l.v[i] : 0.0;
+}
+__device__ __forceinline__ ScaleIn scale_load(MaxList nmax, const unsigned long long *gmax_bits, MaxList fmax_l,
+                                              MaxList lmax) {
+    ScaleIn s;
+    s.n = list_value(nmax);
+    s.f = list_value(fmax_l);
+    s.l = list_value(lmax);
+    s.g = __longlong_as_double(static_cast<long long>(*gmax_bits));
+    s.occ = fmax_l.n > 0;
+    s.one = nmax.n <= 1 && fmax_l.n <= 1 && lmax.n <= 1;
+    return s;
+}
+// the largest over the wave (all lanes take part)
+__device__ __forceinline__ double wave_max(double m, bool one) {
+    if (one) return m;
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) m = fmax(m, __shfl_xor(m, off, 64));
+    return m;
+}
+__device__ __forceinline__ double occ_factor(const ScaleIn &s) {
+    if (!s.occ) return 1.0;
+    const double m = wave_max(s.f, s.one);
     return (1.0 + 2.0 * m) * (1.0 + 2.0 * m);
 }
-
-__device__ __forceinline__ double sym_scale(const unsigned long long *nmax_bits,
-                                            const unsigned long long *gmax_bits,
-                                            const unsigned long long *fmax_bits) {
-    const double nmax = __longlong_as_double(static_cast<long long>(*nmax_bits));
-    const double gmax = __longlong_as_double(static_cast<long long>(*gmax_bits));
-    const double bound = (2.0 * nmax + 1.0) * gmax * occ_factor(fmax_bits);
+__device__ __forceinline__ double scale_of_bound(double bound) {
     if (!(bound > 0.0) || !(bound < 1e300)) return 1.0;
     int e;
     (void)frexp(bound, &e);   // bound < 2^e
     return ldexp(1.0, 61 - e);
+}
+__device__ __forceinline__ double sym_scale(const ScaleIn &s) {
+    return scale_of_bound((2.0 * wave_max(s.n, s.one) + 1.0) * s.g * occ_factor(s));
 }
 
 // y integral-valued with |y| < 2^62, as a two's-complement 64-bit integer
@@ -400,19 +434,14 @@ __device__ __forceinline__ void block_max_to(double v, double *dst) {
     }
 }
 
-// one workgroup: the max of n per-block values, as double bits
-__global__ void k_max_blocks(const double *__restrict__ bm, int n, unsigned long long *out_bits) {
-    double m = 0.0;
-    for (int i = threadIdx.x; i < n; i += blockDim.x) m = fmax(m, bm[i]);
-    __shared__ double s_m[16];
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) m = fmax(m, __shfl_xor(m, off, 64));
-    if ((threadIdx.x & 63) == 0) s_m[threadIdx.x >> 6] = m;
-    __syncthreads();
+// each list's largest value, to its own place in out (one wave)
+__global__ __launch_bounds__(64) void k_reduce_lists(MaxList a, MaxList b, MaxList c, double *out) {
+    const double x = wave_max(list_value(a), false), y = wave_max(list_value(b), false),
+                 z = wave_max(list_value(c), false);
     if (threadIdx.x == 0) {
-        for (int w = 1; w < static_cast<int>(blockDim.x >> 6); ++w) m = fmax(m, s_m[w]);
-        m = fmax(m, s_m[0]);
-        *out_bits = static_cast<unsigned long long>(__double_as_longlong(m));
+        out[0] = x;
+        out[1] = y;
+        out[2] = z;
     }
 }
 
@@ -423,21 +452,6 @@ __global__ void k_zero_u64(unsigned long long *p, int n) {
 
 // entries of the exponential table that the FP64 streaming kernels keep in LDS
 constexpr int kExpTab = 256;
-
-template <typename T>
-__global__ void k_pack_hwN(const T *__restrict__ hw, const T *__restrict__ nph,
-                           Pair2<T> *__restrict__ out, int64_t n, double *bmax) {
-    double m = 0.0;
-    for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < n;
-         i += static_cast<int64_t>(gridDim.x) * blockDim.x) {
-        Pair2<T> v;
-        v.a = hw[i];
-        v.b = nph[i];
-        out[i] = v;
-        m = fmax(m, fabs(static_cast<double>(v.b)));
-    }
-    block_max_to(m, bmax + blockIdx.x);
-}
 
 // The padded q table.  States carry k in shifted coordinates c (per axis, 0
 // .. span - 1 after a per-axis origin); a pair's difference c_p - c_d lies in
@@ -470,27 +484,68 @@ __device__ __forceinline__ int box_q(int qp, const QBox &B) {
     return q;
 }
 
-// {hw, N} of the box rows `used` (the rows some entry references), every
-// mode: row qp, mode nu at qp nm + nu (mode_major = 0) or nu rows + qp
-// (mode_major = 1).  The table holds fewer than 2^31 entries (the plan sizes
-// it under 256 MB); rows not listed keep their zeros.
+// What a call prepares before its main kernel, in one launch.
+//  - The {hw, N} table: with the box, of the rows `used` (the rows some entry
+//    references), every mode: row qp, mode nu at qp nm + nu (mode_major = 0) or
+//    nu rows + qp (mode_major = 1), fewer than 2^31 entries (the plan sizes it
+//    under 256 MB); rows not listed keep their zeros.  Without the box, all of it.
+//  - Up to two vectors: max |x|, and -x where a Bose plan asks for it.
+// Each part has its own workgroups, and each workgroup leaves the max of its part.
+template <typename T> struct PackPart {
+    const T *hw, *nph;
+    Pair2<T> *out;
+    QBox box;
+    int padq, nm, rows, mode_major;
+    const int32_t *used;
+    int64_t n;         // entries
+    double *bmax;
+    int blocks;        // 0: no table
+};
+template <typename T> struct VecPart {
+    const T *x;
+    T *neg;            // null: no copy
+    int64_t n;
+    double *bmax;
+    int blocks;        // 0: no vector
+};
 template <typename T>
-__global__ void k_pack_hwN_pad(const T *__restrict__ hw, const T *__restrict__ nph,
-                               Pair2<T> *__restrict__ out, QBox B, int nm, int rows,
-                               const int32_t *__restrict__ used, int n_used, int mode_major, double *bmax) {
+__global__ __launch_bounds__(1024) void k_prep(PackPart<T> P, VecPart<T> V0, VecPart<T> V1) {
     double m = 0.0;
-    const int n = n_used * nm;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-        const int nu = i % nm;
-        const int qp = used[i / nm];
-        const int64_t q = box_q(qp, B);
-        Pair2<T> v;
-        v.a = hw[q * nm + nu];
-        v.b = nph[q * nm + nu];
-        out[mode_major ? nu * rows + qp : qp * nm + nu] = v;
-        m = fmax(m, fabs(static_cast<double>(v.b)));
+    double *dst;
+    int b = blockIdx.x;
+    if (b < P.blocks) {
+        dst = P.bmax + b;
+        for (int64_t i = static_cast<int64_t>(b) * blockDim.x + threadIdx.x; i < P.n;
+             i += static_cast<int64_t>(P.blocks) * blockDim.x) {
+            int64_t src = i, o = i;
+            if (P.padq) {
+                const int i32 = static_cast<int>(i);
+                const int nu = i32 % P.nm, qp = P.used[i32 / P.nm];
+                src = static_cast<int64_t>(box_q(qp, P.box)) * P.nm + nu;
+                o = P.mode_major ? nu * P.rows + qp : qp * P.nm + nu;
+            }
+            Pair2<T> v;
+            v.a = P.hw[src];
+            v.b = P.nph[src];
+            P.out[o] = v;
+            m = fmax(m, fabs(static_cast<double>(v.b)));
+        }
+    } else {
+        b -= P.blocks;
+        const bool second = b >= V0.blocks;
+        if (second) b -= V0.blocks;
+        const T *__restrict__ x = second ? V1.x : V0.x;
+        T *__restrict__ neg = second ? V1.neg : V0.neg;
+        const int64_t n = second ? V1.n : V0.n;
+        const int64_t stride = static_cast<int64_t>(second ? V1.blocks : V0.blocks) * blockDim.x;
+        dst = (second ? V1.bmax : V0.bmax) + b;
+        for (int64_t i = static_cast<int64_t>(b) * blockDim.x + threadIdx.x; i < n; i += stride) {
+            const T v = x[i];
+            if (neg) neg[i] = -v;
+            m = fmax(m, fabs(static_cast<double>(v)));
+        }
     }
-    block_max_to(m, bmax + blockIdx.x);
+    block_max_to(m, dst);
 }
 
 // exp of the Gaussian exponent x2 * (-1/(2 s^2)) for the streaming kernels
@@ -809,6 +864,7 @@ __global__ __launch_bounds__(1024) void k_fwd_sym(TiledArgs<T> A, const T *__res
     const int64_t ti = tile_of_block(A.n_tiles, A.xcd);
     if (ti < 0) return;
     const TileRec t = A.tiles[ti];
+    const ScaleIn si = scale_load(A.nmax, A.gmax_bits, A.fmax, MaxList{nullptr, 0});
     // LDS: partner-side sums (8 B), {eps, f}, packed k, exponential table
     unsigned long long *s_j = reinterpret_cast<unsigned long long *>(smem);
     Pair2<T> *s_ef = reinterpret_cast<Pair2<T> *>(s_j + A.lds_states);
@@ -826,7 +882,7 @@ __global__ __launch_bounds__(1024) void k_fwd_sym(TiledArgs<T> A, const T *__res
     }
     if constexpr (sizeof(T) == 8)
         for (int i = threadIdx.x; i < kExpTab; i += blockDim.x) s_tab[i] = A.e2tab[i];
-    const T scale = static_cast<T>(sym_scale(A.nmax_bits, A.gmax_bits, A.fmax_bits));
+    const T scale = static_cast<T>(sym_scale(si));
     __syncthreads();
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
     const int nw = static_cast<int>(blockDim.x >> 6);
@@ -1063,6 +1119,7 @@ __global__ __launch_bounds__(1024) void k_fwd_pairs(TiledArgs<T> A, const T *__r
     const int64_t ti = tile_of_block(A.n_tiles, A.xcd);
     if (ti < 0) return;
     const TileRec t = A.tiles[ti];
+    const ScaleIn si = scale_load(A.nmax, A.gmax_bits, A.fmax, MaxList{nullptr, 0});
     unsigned long long *s_j = reinterpret_cast<unsigned long long *>(smem);
     Pair2<T> *s_ef = reinterpret_cast<Pair2<T> *>(s_j + A.lds_states);
     uint32_t *s_kq = reinterpret_cast<uint32_t *>(s_ef + A.lds_states);
@@ -1079,7 +1136,7 @@ __global__ __launch_bounds__(1024) void k_fwd_pairs(TiledArgs<T> A, const T *__r
     }
     if constexpr (sizeof(T) == 8 && TAB)
         for (int i = threadIdx.x; i < kExpTab; i += blockDim.x) s_tab[i] = A.e2tab[i];
-    const T scale = static_cast<T>(sym_scale(A.nmax_bits, A.gmax_bits, A.fmax_bits));
+    const T scale = static_cast<T>(sym_scale(si));
     __syncthreads();
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
     const int nw = static_cast<int>(blockDim.x >> 6);
@@ -1110,20 +1167,10 @@ __global__ __launch_bounds__(1024) void k_fwd_pairs(TiledArgs<T> A, const T *__r
 //                consecutive channels of the caller's list, else -1)
 // The partner side of a pair is summed over its modes and added with one
 // integer atomic, on the scale of vjp_scale.  Each channel is read once.
-__device__ __forceinline__ double vjp_scale(const unsigned long long *nmax_bits,
-                                            const unsigned long long *gmax_bits,
-                                            const unsigned long long *lmax_bits,
-                                            const unsigned long long *fmax_bits) {
+__device__ __forceinline__ double vjp_scale(const ScaleIn &s) {
     // |dl| <= 2 max |lam|: a state's column is at most 2 max|lam| (2 N_max + 1) G_max
     // (times occ_factor when f leaves [0, 1])
-    const double nmax = __longlong_as_double(static_cast<long long>(*nmax_bits));
-    const double gmax = __longlong_as_double(static_cast<long long>(*gmax_bits));
-    const double lmax = __longlong_as_double(static_cast<long long>(*lmax_bits));
-    const double bound = 2.0 * lmax * (2.0 * nmax + 1.0) * gmax * occ_factor(fmax_bits);
-    if (!(bound > 0.0) || !(bound < 1e300)) return 1.0;
-    int e;
-    (void)frexp(bound, &e);
-    return ldexp(1.0, 61 - e);
+    return scale_of_bound(2.0 * wave_max(s.l, s.one) * (2.0 * wave_max(s.n, s.one) + 1.0) * s.g * occ_factor(s));
 }
 
 // threads per workgroup of the pair reverse pass: 16 waves, as the forward
@@ -1355,7 +1402,7 @@ __device__ __forceinline__ void vjp_pair_chunk_q(const TiledArgs<T> &A, const Pa
 template <typename T, bool PADQ, int NM, bool TAB>
 __global__ __launch_bounds__(kVjpPairThreads) void k_vjp_pairs(TiledArgs<T> A, const T *__restrict__ f,
                                                     const T *__restrict__ lam, T *__restrict__ part, int want_f,
-                                                    const unsigned long long *__restrict__ lmax_bits,
+                                                    MaxList lmax,
                                                     const int32_t *__restrict__ chan,
                                                     const int32_t *__restrict__ chan0, double *__restrict__ gg2,
                                                     int gg2_mode) {
@@ -1363,6 +1410,7 @@ __global__ __launch_bounds__(kVjpPairThreads) void k_vjp_pairs(TiledArgs<T> A, c
     const int64_t ti = tile_of_block(A.n_tiles, A.xcd);
     if (ti < 0) return;
     const TileRec t = A.tiles[ti];
+    const ScaleIn si = scale_load(A.nmax, A.gmax_bits, A.fmax, lmax);
     unsigned long long *s_j = reinterpret_cast<unsigned long long *>(smem);
     Pair2<T> *s_ef = reinterpret_cast<Pair2<T> *>(s_j + A.lds_states);
     T *s_l = reinterpret_cast<T *>(s_ef + A.lds_states);
@@ -1381,7 +1429,7 @@ __global__ __launch_bounds__(kVjpPairThreads) void k_vjp_pairs(TiledArgs<T> A, c
     }
     if constexpr (sizeof(T) == 8 && TAB)
         for (int i = threadIdx.x; i < kExpTab; i += blockDim.x) s_tab[i] = A.e2tab[i];
-    const T scale = static_cast<T>(vjp_scale(A.nmax_bits, A.gmax_bits, lmax_bits, A.fmax_bits));
+    const T scale = static_cast<T>(vjp_scale(si));
     __syncthreads();
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
     const int nw = static_cast<int>(blockDim.x >> 6);
@@ -1408,12 +1456,12 @@ __global__ __launch_bounds__(kVjpPairThreads) void k_vjp_pairs(TiledArgs<T> A, c
 // epilogue; the partner-side accumulator of d is cleared for the next call.
 template <typename T>
 __global__ void k_vjp_pairs_finish(TiledArgs<T> A, const T *__restrict__ part,
-                                   const unsigned long long *__restrict__ lmax_bits, Epi<T> E) {
+                                   MaxList lmax, Epi<T> E) {
+    const double inv = 1.0 / vjp_scale(scale_load(A.nmax, A.gmax_bits, A.fmax, lmax));
     const int d = blockIdx.x * blockDim.x + threadIdx.x;
     if (d >= A.S) return;
     T a = T(0);
     for (int c = A.dest_chunk[d]; c < A.dest_chunk[d + 1]; ++c) a += part[c];
-    const double inv = 1.0 / vjp_scale(A.nmax_bits, A.gmax_bits, lmax_bits, A.fmax_bits);
     const long long j = static_cast<long long>(A.jacc[d]);
     A.jacc[d] = 0ull;
     const T jside = static_cast<T>(static_cast<double>(j) * inv);
@@ -1426,6 +1474,7 @@ __global__ void k_vjp_pairs_finish(TiledArgs<T> A, const T *__restrict__ part,
 template <typename T>
 __global__ void k_sym_finish(TiledArgs<T> A, const T *__restrict__ f, const T *__restrict__ part,
                              Epi<T> E) {
+    const double inv = 1.0 / sym_scale(scale_load(A.nmax, A.gmax_bits, A.fmax, MaxList{nullptr, 0}));
     const int d = blockIdx.x * blockDim.x + threadIdx.x;
     if (d >= A.S) return;
     T a = T(0), b = T(0);
@@ -1433,7 +1482,6 @@ __global__ void k_sym_finish(TiledArgs<T> A, const T *__restrict__ f, const T *_
         a += part[2 * c];
         b += part[2 * c + 1];
     }
-    const double inv = 1.0 / sym_scale(A.nmax_bits, A.gmax_bits, A.fmax_bits);
     const long long j = static_cast<long long>(A.jacc[d]);
     A.jacc[d] = 0ull;
     const T fd = f[d];
@@ -3658,11 +3706,12 @@ __global__ void k_vjp_phonon_f_finish(TiledArgs<T> A, const T *__restrict__ part
 template <typename T, bool PADQ, int NM>
 __global__ __launch_bounds__(1024) void k_vjp_phonon_pairs(TiledArgs<T> A, const Vec4<T> *__restrict__ tab,
                                                           const T *__restrict__ f, uint32_t elastic,
-                                                          const unsigned long long *__restrict__ mmax_bits) {
+                                                          MaxList mmax) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int64_t ti = tile_of_block(A.n_tiles, A.xcd);
     if (ti < 0) return;
     const TileRec t = A.tiles[ti];
+    const ScaleIn si = scale_load(A.nmax, A.gmax_bits, A.fmax, mmax);
     unsigned long long *s_j = reinterpret_cast<unsigned long long *>(smem);
     Pair2<T> *s_ef = reinterpret_cast<Pair2<T> *>(s_j + A.lds_states);
     uint32_t *s_kq = reinterpret_cast<uint32_t *>(s_ef + A.lds_states);
@@ -3679,7 +3728,7 @@ __global__ __launch_bounds__(1024) void k_vjp_phonon_pairs(TiledArgs<T> A, const
     }
     if constexpr (sizeof(T) == 8)
         for (int i = threadIdx.x; i < kExpTab; i += blockDim.x) s_tab[i] = A.e2tab[i];
-    const T scale = static_cast<T>(vjp_scale(A.nmax_bits, A.gmax_bits, mmax_bits, A.fmax_bits));
+    const T scale = static_cast<T>(vjp_scale(si));
     __syncthreads();
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
@@ -3736,11 +3785,11 @@ __global__ __launch_bounds__(1024) void k_vjp_phonon_pairs(TiledArgs<T> A, const
 // out[d] += Kp (the fixed-point sum of d) / scale; the accumulator of d is
 // cleared for the next call
 template <typename T>
-__global__ void k_vjp_phonon_pairs_finish(TiledArgs<T> A, const unsigned long long *__restrict__ mmax_bits,
+__global__ void k_vjp_phonon_pairs_finish(TiledArgs<T> A, MaxList mmax,
                                           double Kp, T *__restrict__ out) {
+    const double inv = 1.0 / vjp_scale(scale_load(A.nmax, A.gmax_bits, A.fmax, mmax));
     const int d = blockIdx.x * blockDim.x + threadIdx.x;
     if (d >= A.S) return;
-    const double inv = 1.0 / vjp_scale(A.nmax_bits, A.gmax_bits, mmax_bits, A.fmax_bits);
     const long long j = static_cast<long long>(A.jacc[d]);
     A.jacc[d] = 0ull;
     out[d] += static_cast<T>(Kp * static_cast<double>(j) * inv);
@@ -3813,20 +3862,6 @@ __global__ void k_phonon_bins_finish(PhArgs<T> A, const T *__restrict__ part, T 
         }
         out[i] = static_cast<T>(A.Kp * static_cast<double>(sum));
     }
-}
-
-// max |x| over x[0..n) as the bits of a non-negative double (integer order of
-// such bits is their numeric order, so the atomic max is order-independent)
-template <typename T>
-__global__ __launch_bounds__(256) void k_abs_max_bits(const T *__restrict__ x, int64_t n,
-                                                      unsigned long long *out) {
-    double m = 0.0;
-    for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < n;
-         i += static_cast<int64_t>(gridDim.x) * blockDim.x)
-        m = fmax(m, fabs(static_cast<double>(x[i])));
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off, 64));
-    if ((threadIdx.x & 63) == 0) atomicMax(out, static_cast<unsigned long long>(__double_as_longlong(m)));
 }
 
 // Pair records in a new order: slot m of position i takes slot m of position
