@@ -165,6 +165,7 @@ struct ephbte_plan_s {
     std::array<int64_t, 6> pr_key{};       // settings the pair tiles were built with
     bool pr_key_set = false;
     bool pr_all_q = false;                 // every pair tile is q-ordered
+    int pr_window = 0;                     // largest window of a pair tile
     int64_t *pr_chunk_beg = nullptr, *pr_chunk_end = nullptr;
     int32_t *pr_chunk_dest = nullptr, *pr_dest_chunk = nullptr;
     TileRec *pr_tiles = nullptr;
@@ -179,6 +180,7 @@ struct ephbte_plan_s {
     int32_t *mx_pos = nullptr, *mx_state = nullptr, *mx_blk = nullptr, *mx_row = nullptr;
     MxCol *mx_col = nullptr;
     DevBuf mx_m, mx_g, mx_u, mx_p1, mx_p2;
+    DevBuf pv_n, pv_j, pv_max;               // a bath per vector over pair records: N, sums, maxima
     // batched pass: tiles of destinations and per-destination sub-tile offsets
     BTileRec *btiles = nullptr;
     int64_t *sub_off = nullptr;
@@ -244,7 +246,7 @@ struct ephbte_plan_s {
                              &adj_U, &adj_la, &adj_lb, &adj_acc, &adj_g, &adj_f, &cp_Ma, &cp_Mb,
                              &cp_acc, &cp_rate, &ph_part, &ph_tab4, &ca_ckf, &ca_ckN, &ca_U, &ca_M,
                              &ca_gf, &ca_gN, &ca_a, &ca_b, &ca_uf, &ca_uN, &ca_sf, &ca_sN, &ca_mu,
-                             &bs_x, &bs_y, &nvec, &mx_m, &mx_g, &mx_u, &mx_p1, &mx_p2};
+                             &bs_x, &bs_y, &nvec, &mx_m, &mx_g, &mx_u, &mx_p1, &mx_p2, &pv_n, &pv_j, &pv_max};
         for (auto *x : w) b += x->bytes;
         return b;
     }
@@ -356,7 +358,7 @@ void free_plan(ephbte_plan P) {
                    &P->adj_g,  &P->adj_f, &P->cp_Ma, &P->cp_Mb, &P->cp_acc, &P->cp_rate, &P->ph_part,
                    &P->ph_tab4, &P->ca_ckf, &P->ca_ckN, &P->ca_U, &P->ca_M, &P->ca_gf, &P->ca_gN, &P->ca_a,
                    &P->ca_b, &P->ca_uf, &P->ca_uN, &P->ca_sf, &P->ca_sN, &P->ca_mu, &P->bs_x, &P->bs_y, &P->nvec,
-                   &P->mx_m, &P->mx_g, &P->mx_u, &P->mx_p1, &P->mx_p2};
+                   &P->mx_m, &P->mx_g, &P->mx_u, &P->mx_p1, &P->mx_p2, &P->pv_n, &P->pv_j, &P->pv_max};
     for (auto *b : w) dfree(b->p);
     if (P->host_red) (void)hipHostFree(P->host_red);
     if (P->ev_a) (void)hipEventDestroy(P->ev_a);
@@ -465,7 +467,8 @@ void order_pair_records(ephbte_plan P, ChunkTable &pc, std::vector<Tile> &tp, bo
 // records: each tile waits for its window before its first batch (2 - 4 us).
 template <typename F> std::vector<Tile> round_tiles(int64_t records, int64_t min_tile, int n_cu, F &&make) {
     const int64_t rounds = std::min<int64_t>(4, std::max<int64_t>(1, records / (min_tile * n_cu)));
-    int64_t target = std::max<int64_t>(records / (rounds * n_cu) + 1, 1024);
+    // at least a batch for every wave; lists shorter than that stay split by rows
+    int64_t target = records < 1024 ? records / (4 * n_cu) + 1 : std::max<int64_t>(records / (rounds * n_cu) + 1, 1024);
     std::vector<Tile> t = make(target);
     for (int k = 0; k < 40 && static_cast<int64_t>(t.size()) > rounds * n_cu; ++k) {
         target += target / 64 + 1;
@@ -600,7 +603,11 @@ void upload_chunks(ephbte_plan P, int64_t chunk_entries) {
     P->pr_key = pr_key;
     P->pr_key_set = true;
     P->pr_all_q = !tp.empty();
-    for (const Tile &t : tp) P->pr_all_q = P->pr_all_q && t.lds == 2;
+    P->pr_window = 0;
+    for (const Tile &t : tp) {
+        P->pr_all_q = P->pr_all_q && t.lds == 2;
+        P->pr_window = std::max(P->pr_window, t.p_hi - t.p_lo + 1);
+    }
 }
 
 // element (q, mode) of the plan's {hw, N} table is at q tq + mode tm
@@ -1337,6 +1344,158 @@ bool enqueue_vjp_mx(ephbte_plan P, int B, const T *f, int64_t ldf, const T *lam,
         if (kF32) enqueue_mx_gg2<T>(P, gm, gg2, b0 > 0 ? 2 : gg2_mode, s);
     }
     if (gg2_mode && !kF32) enqueue_mx_gg2<T>(P, gm, gg2, gg2_mode, s);
+    HIPC(hipGetLastError());
+    return true;
+}
+
+// ---- a bath per vector over pair records ------------------------------------
+// LDS of k_fwd_pairs_pv / k_vjp_pairs_pv for windows of W states and VB vectors
+size_t pv_lds(ephbte_plan P, int W, int VB, bool vjp) {
+    const size_t es = P->dtype == EPHBTE_F64 ? 8 : 4;
+    return (es == 8 ? kExpTab * sizeof(double) : 0) + static_cast<size_t>(W) * (es + 4) +
+           static_cast<size_t>(W) * VB * (8 + (vjp ? 2 : 1) * es);
+}
+// Vectors a workgroup takes at once, 0: not these passes.  The Gaussians are
+// shared by them, so a window that leaves room for fewer than three keeps the
+// batched pass over entries (on the 100^3 system two fit, 16 ms against 16.6 ms at
+// 64 vectors); below 8 vectors the alternative is one pass each, which one already
+// matches.
+int pv_vectors(ephbte_plan P, int B, bool vjp) {
+    if (!P->pr_ok || !P->pr_all_q || !P->sym_ok || P->n_pr_tiles == 0 || P->pr_window < 1) return 0;
+    if (P->layout != 3 && B < P->batch_min) return 0;
+    int most = 0;
+    while (most < 8 && pv_lds(P, P->pr_window, most + 1, vjp) + 1024 <= P->lds_max) ++most;
+    if (most < (B < P->batch_min ? 1 : 3)) return 0;
+    const int groups = (B + most - 1) / most;
+    return (B + groups - 1) / groups;   // even groups
+}
+
+// Buffers, tables and maxima for B vectors (lam: the reverse pass); false where
+// the memory is not there.
+template <typename T>
+bool pv_prepare(ephbte_plan P, int B, int VB, const T *f, int64_t ldf, const T *lam, int64_t ldl, const T *nph,
+                PvArgs<T> &V, hipStream_t s) {
+    const int groups = (B + VB - 1) / VB;
+    const int64_t rows = P->padq ? P->qpad_n : static_cast<int64_t>(P->nq[0]) * P->nq[1] * P->nq[2];
+    const size_t row = static_cast<size_t>(P->S) * B;
+    try {
+        ensure(P->pv_n, sizeof(T) * static_cast<size_t>(groups) * rows * P->nm * VB, &P->ws_gen);
+        ensure_zeroed(P, P->pv_j, sizeof(unsigned long long) * row);
+        ensure(P->pv_max, sizeof(double) * 3 * 64 * B, &P->ws_gen);
+        if (P->boson) {
+            ensure(P->bs_x, sizeof(T) * row, &P->ws_gen);
+            if (lam) ensure(P->bs_y, sizeof(T) * row, &P->ws_gen);
+        }
+    } catch (const std::bad_alloc &) {
+        return false;
+    }
+    double *mx = static_cast<double *>(P->pv_max.p);
+    PvPrep<T> p{};
+    p.p = pack_part<T>(P, nph);
+    p.tab_n = static_cast<T *>(P->pv_n.p);
+    p.vb = VB;
+    p.rows = rows;
+    p.f = f;
+    p.lam = lam;
+    p.ldf = ldf;
+    p.ldl = ldl;
+    p.neg_f = P->boson ? static_cast<T *>(P->bs_x.p) : nullptr;
+    p.neg_l = P->boson && lam ? static_cast<T *>(P->bs_y.p) : nullptr;
+    p.S = P->S;
+    p.nmax = mx;
+    p.fmax = mx + 64 * B;
+    p.lmax = mx + 2 * 64 * B;
+    const int nb = std::min(64, std::max(1, static_cast<int>((p.p.n + 4095) / 4096)));
+    hipLaunchKernelGGL((k_prep_pv<T>), dim3(static_cast<unsigned>(nb), static_cast<unsigned>(B)), dim3(kPrepThreads), 0,
+                       s, p);
+    V = PvArgs<T>{};
+    V.f = P->boson ? p.neg_f : f;
+    V.ldf = P->boson ? P->S : ldf;
+    V.lam = P->boson && lam ? p.neg_l : lam;
+    V.ldl = P->boson ? P->S : ldl;
+    V.tab_n = p.tab_n;
+    V.gstride = rows * P->nm * VB;
+    V.B = B;
+    V.vb = VB;
+    V.n_list = nb;
+    V.bose = P->boson ? 1 : 0;
+    V.nmax = p.nmax;
+    V.fmax = p.fmax;
+    V.lmax = p.lmax;
+    V.jacc = static_cast<unsigned long long *>(P->pv_j.p);
+    return true;
+}
+
+// f, lam: the caller's (a Bose plan's are negated here).  E as for one vector.
+template <typename T>
+bool enqueue_forward_pv(ephbte_plan P, int B, const T *f, int64_t ldf, const T *nph, const Epi<T> &E, hipStream_t s) {
+    const int VB = pv_vectors(P, B, false);
+    PvArgs<T> V;
+    if (VB == 0 || !pv_prepare<T>(P, B, VB, f, ldf, nullptr, 0, nph, V, s)) return false;
+    TiledArgs<T> a = pair_args<T>(P);
+    a.lds_states = P->pr_window;
+    const size_t shm = pv_lds(P, P->pr_window, VB, false);
+    const dim3 grid(static_cast<unsigned>(P->n_pr_tiles), static_cast<unsigned>((B + VB - 1) / VB)), block(1024);
+    auto go = [&](auto nmc) {
+        constexpr int NM = decltype(nmc)::value;
+        const bool tab = sizeof(T) == 8 && P->exp_table;
+        if (P->padq && tab) hipLaunchKernelGGL((k_fwd_pairs_pv<T, true, NM, true>), grid, block, shm, s, a, V);
+        else if (P->padq) hipLaunchKernelGGL((k_fwd_pairs_pv<T, true, NM, false>), grid, block, shm, s, a, V);
+        else if (tab) hipLaunchKernelGGL((k_fwd_pairs_pv<T, false, NM, true>), grid, block, shm, s, a, V);
+        else hipLaunchKernelGGL((k_fwd_pairs_pv<T, false, NM, false>), grid, block, shm, s, a, V);
+    };
+    const int64_t kt = ktime_begin(P, s);
+    if (P->nm <= 1) go(std::integral_constant<int, 1>{});
+    else if (P->nm <= 2) go(std::integral_constant<int, 2>{});
+    else if (P->nm <= 3) go(std::integral_constant<int, 3>{});
+    else if (P->nm <= 4) go(std::integral_constant<int, 4>{});
+    else if (P->nm <= 6) go(std::integral_constant<int, 6>{});
+    else go(std::integral_constant<int, 8>{});
+    ktime_end(P, s, kt);
+    hipLaunchKernelGGL((k_pv_finish<T>), dim3(static_cast<unsigned>((P->S + 255) / 256), static_cast<unsigned>(B)),
+                       dim3(256), 0, s, a, V, E);
+    HIPC(hipGetLastError());
+    return true;
+}
+
+bool enqueue_vjp_pv(ephbte_plan P, int B, const double *f, int64_t ldf, const double *lam, int64_t ldl,
+                    const double *nph, double *gf, int64_t ldgf, double *gg2, int gg2_mode, hipStream_t s) {
+    const int VB = pv_vectors(P, B, true);
+    PvArgs<double> V;
+    if (VB == 0 || !pv_prepare<double>(P, B, VB, f, ldf, lam, ldl, nph, V, s)) return false;
+    TiledArgs<double> a = pair_args<double>(P);
+    a.lds_states = P->pr_window;
+    const size_t shm = pv_lds(P, P->pr_window, VB, true);
+    const dim3 grid(static_cast<unsigned>(P->n_pr_tiles)), block(1024);
+    const int32_t *ch = P->pr_chan, *c0 = P->pr_ch0;
+    const int wf = gf ? 1 : 0;
+    for (int g = 0; g * VB < B; ++g) {
+        const int gm = gg2_mode == 0 ? 0 : (g == 0 ? gg2_mode : 2);
+        auto go = [&](auto nmc) {
+            constexpr int NM = decltype(nmc)::value;
+            if (P->padq && P->exp_table)
+                hipLaunchKernelGGL((k_vjp_pairs_pv<true, NM, true>), grid, block, shm, s, a, V, g, wf, ch, c0, gg2, gm);
+            else if (P->padq)
+                hipLaunchKernelGGL((k_vjp_pairs_pv<true, NM, false>), grid, block, shm, s, a, V, g, wf, ch, c0, gg2, gm);
+            else if (P->exp_table)
+                hipLaunchKernelGGL((k_vjp_pairs_pv<false, NM, true>), grid, block, shm, s, a, V, g, wf, ch, c0, gg2, gm);
+            else
+                hipLaunchKernelGGL((k_vjp_pairs_pv<false, NM, false>), grid, block, shm, s, a, V, g, wf, ch, c0, gg2, gm);
+        };
+        if (P->nm <= 1) go(std::integral_constant<int, 1>{});
+        else if (P->nm <= 2) go(std::integral_constant<int, 2>{});
+        else if (P->nm <= 3) go(std::integral_constant<int, 3>{});
+        else if (P->nm <= 4) go(std::integral_constant<int, 4>{});
+        else if (P->nm <= 6) go(std::integral_constant<int, 6>{});
+        else go(std::integral_constant<int, 8>{});
+    }
+    if (gf) {
+        Epi<double> e = epi_store<double>(gf, ldgf);
+        e.neg = P->boson ? 1 : 0;
+        hipLaunchKernelGGL((k_pv_finish<double>),
+                           dim3(static_cast<unsigned>((P->S + 255) / 256), static_cast<unsigned>(B)), dim3(256), 0, s,
+                           a, V, e);
+    }
     HIPC(hipGetLastError());
     return true;
 }
@@ -3070,6 +3229,12 @@ ephbte_status ephbte_collision_integral(ephbte_plan plan, int32_t batch, const v
             int64_t ldft = ldf;
             T *It = static_cast<T *>(I);
             const bool one = plan->boson && batch == 1 && (use_pairs(plan, 1) || use_sym(plan, 1));
+            if (nph_per_batch && batch > 1) {
+                ensure_fwd<T>(plan, 1);
+                Epi<T> e = epi_store<T>(It, ldi);
+                e.neg = plan->boson ? 1 : 0;
+                if (enqueue_forward_pv<T>(plan, batch, ft, ldft, static_cast<const T *>(nph), e, s)) return;
+            }
             if (one) {   // I_B(n) = -I_F(-n): table, -n and its max in one launch
                 ensure_fwd<T>(plan, 1);
                 ensure(plan->bs_x, sizeof(T) * static_cast<size_t>(plan->S), &plan->ws_gen);
@@ -3162,6 +3327,22 @@ ephbte_status ephbte_collision_vjp(ephbte_plan plan, int32_t batch, const void *
             const bool per_batch = nph_per_batch && batch > 1;
             const void *f = f_in, *gI = gI_in;
             int64_t ldf = ldf_in, ldg = ldg_in;
+            auto zero_dropped = [&]() {
+                if (!gg2 || accumulate_gg2 || plan->n_drop == 0) return;
+                const unsigned nb = static_cast<unsigned>(std::min<int64_t>((plan->n_drop + 255) / 256, 1024));
+                hipLaunchKernelGGL(k_zero_at, dim3(nb), dim3(256), 0, s, gg2, (const int32_t *)plan->drop_idx,
+                                   plan->n_drop);
+            };
+            if constexpr (sizeof(T) == 8) {
+                // a bath per vector, FP64 (an FP32 plan's gradients are added per vector)
+                if (per_batch && enqueue_vjp_pv(plan, batch, static_cast<const double *>(f), ldf,
+                                                static_cast<const double *>(gI), ldg, static_cast<const double *>(nph),
+                                                static_cast<double *>(gf), ldgf, gg2,
+                                                gg2 ? (accumulate_gg2 ? 2 : 1) : 0, s)) {
+                    zero_dropped();
+                    return;
+                }
+            }
             // one vector over the pair records: the table, the maxima and a Bose
             // plan's negated copies in one launch
             const bool one = batch == 1 && vjp_pairs_fit(plan);
@@ -3183,11 +3364,7 @@ ephbte_status ephbte_collision_vjp(ephbte_plan plan, int32_t batch, const void *
                 gI = boson_neg<T>(plan, plan->bs_y, gI_in, ldg_in, batch, s);
                 ldf = ldg = S;
             }
-            if (gg2 && !accumulate_gg2 && plan->n_drop > 0) {
-                const unsigned nb = static_cast<unsigned>(std::min<int64_t>((plan->n_drop + 255) / 256, 1024));
-                hipLaunchKernelGGL(k_zero_at, dim3(nb), dim3(256), 0, s, gg2, (const int32_t *)plan->drop_idx,
-                                   plan->n_drop);
-            }
+            zero_dropped();
             bool done = false;
             if (!one && !per_batch) {
                 enqueue_pack<T>(plan, nph, s);

@@ -1835,6 +1835,315 @@ __global__ void k_tr_tiled_finish(TiledArgs<T> A, const Vec4<T> *__restrict__ pa
     x_new[d] = o;
 }
 
+// ---- a bath per vector, over pair records -------------------------------------
+// The passes over q-ordered pair records for B vectors with a phonon table each.
+// A pair's Gaussians do not depend on the bath: with c = |g|^2 (G(x + hw) +
+// G(x - hw)) per mode and A0 = sum |g|^2 G(x - hw), B0 = sum |g|^2 G(x + hw),
+//   a_b = A0 + sum_m c_m N_b(q, m),   b_b = B0 + sum_m c_m N_b(q, m),
+// so a workgroup evaluates them once for VB vectors (as many as its LDS holds: f
+// and a fixed-point sum per window state and vector) and each vector adds a short
+// sum of N, which the lanes of a batch read from the few rows they share
+// (tabN: [group of VB][table row][mode][VB]).  Both sides of a pair are
+// fixed-point sums on the vector's own scale.
+
+// tabN of vector blockIdx.y, the {hw, N} table (by vector 0), max |N| and max |f|
+// of the vector (64 values a list), and a Bose plan's -f and -lam.
+template <typename T> struct PvPrep {
+    PackPart<T> p;      // nph: B tables
+    T *tab_n;
+    int vb;
+    int64_t rows;       // table rows (box rows or Nq)
+    const T *f, *lam;   // [B][ld], lam may be null
+    int64_t ldf, ldl;
+    T *neg_f, *neg_l;   // [B][S] or null
+    int S;
+    double *nmax, *fmax, *lmax;   // [B][64]
+};
+template <typename T> __global__ __launch_bounds__(1024) void k_prep_pv(PvPrep<T> P) {
+    const int b = blockIdx.y, nb = gridDim.x;
+    const PackPart<T> &t = P.p;
+    const int64_t tab = static_cast<int64_t>(t.box.n[0]) * t.box.n[1] * t.box.n[2] * t.nm;
+    const T *__restrict__ nph = t.nph + b * tab;
+    T *__restrict__ out = P.tab_n + (b / P.vb) * P.rows * t.nm * P.vb + b % P.vb;
+    double m = 0.0;
+    for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < t.n;
+         i += static_cast<int64_t>(nb) * blockDim.x) {
+        const int64_t r = i / t.nm;
+        const int nu = static_cast<int>(i - r * t.nm);
+        int64_t row = r, src = i;
+        if (t.padq) {
+            row = t.used[r];
+            src = static_cast<int64_t>(box_q(static_cast<int>(row), t.box)) * t.nm + nu;
+        }
+        const T v = nph[src];
+        out[(row * t.nm + nu) * P.vb] = v;
+        if (b == 0) {
+            Pair2<T> w;
+            w.a = t.hw[src];
+            w.b = v;
+            t.out[t.padq && t.mode_major ? nu * static_cast<int64_t>(t.rows) + row : row * t.nm + nu] = w;
+        }
+        m = fmax(m, fabs(static_cast<double>(v)));
+    }
+    block_max_to(m, P.nmax + b * 64 + blockIdx.x);
+    auto vec = [&](const T *__restrict__ x, T *__restrict__ neg, double *dst) {
+        double mv = 0.0;
+        for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < P.S; i += nb * blockDim.x) {
+            const T v = x[i];
+            if (neg) neg[static_cast<int64_t>(b) * P.S + i] = -v;
+            mv = fmax(mv, fabs(static_cast<double>(v)));
+        }
+        __syncthreads();
+        block_max_to(mv, dst + b * 64 + blockIdx.x);
+    };
+    if (P.neg_f) vec(P.f + b * P.ldf, P.neg_f, P.fmax);
+    if (P.lam) vec(P.lam + b * P.ldl, P.neg_l, P.lmax);
+}
+
+template <typename T> struct PvArgs {
+    const T *__restrict__ f, *__restrict__ lam;
+    int64_t ldf, ldl;
+    const T *__restrict__ tab_n;
+    int64_t gstride;        // values of tabN per group
+    int B, vb, n_list, bose;
+    const double *__restrict__ nmax, *__restrict__ fmax, *__restrict__ lmax;
+    unsigned long long *__restrict__ jacc;   // [B][S]
+};
+// the scale of vector b (all lanes of a wave)
+template <typename T>
+__device__ __forceinline__ double pv_scale(const TiledArgs<T> &A, const PvArgs<T> &V, int b) {
+    const MaxList none{nullptr, 0};
+    const ScaleIn s = scale_load(MaxList{V.nmax + b * 64, V.n_list}, A.gmax_bits,
+                                 V.bose ? MaxList{V.fmax + b * 64, V.n_list} : none,
+                                 V.lam ? MaxList{V.lmax + b * 64, V.n_list} : none);
+    return V.lam ? vjp_scale(s) : sym_scale(s);
+}
+
+template <typename T, bool PADQ, int NM, bool TAB>
+__global__ __launch_bounds__(1024) void k_fwd_pairs_pv(TiledArgs<T> A, PvArgs<T> V) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ double s_scale[16];
+    const TileRec t = A.tiles[blockIdx.x];
+    const int W = A.lds_states, VB = V.vb, b0 = blockIdx.y * VB;
+    const int nv = min(VB, V.B - b0);
+    double *s_tab = reinterpret_cast<double *>(smem);
+    unsigned long long *s_j = reinterpret_cast<unsigned long long *>(s_tab + (sizeof(T) == 8 ? kExpTab : 0));
+    T *s_f = reinterpret_cast<T *>(s_j + VB * W);
+    T *s_e = s_f + VB * W;
+    uint32_t *s_kq = reinterpret_cast<uint32_t *>(s_e + W);
+    const int n = t.p_hi - t.p_lo + 1;
+    for (int i = threadIdx.x; i < n; i += blockDim.x) {
+        const StateRec<T> sr = A.st[t.p_lo + i];
+        s_e[i] = sr.eps;
+        s_kq[i] = PADQ ? sr.kqp : sr.kq;
+        for (int v = 0; v < nv; ++v) {
+            s_f[v * W + i] = V.f[static_cast<int64_t>(b0 + v) * V.ldf + t.p_lo + i];
+            s_j[v * W + i] = 0ull;
+        }
+    }
+    if constexpr (sizeof(T) == 8 && TAB)
+        for (int i = threadIdx.x; i < kExpTab; i += blockDim.x) s_tab[i] = A.e2tab[i];
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+    const int nw = static_cast<int>(blockDim.x >> 6);
+    for (int v = wave; v < nv; v += nw) {
+        const double sc = pv_scale(A, V, b0 + v);
+        if ((threadIdx.x & 63) == 0) s_scale[v] = sc;
+    }
+    __syncthreads();
+    const int lane = threadIdx.x & 63;
+    const int nm = A.nm;
+    const T *__restrict__ tn = V.tab_n + blockIdx.y * V.gstride;
+    for (int64_t c = t.c0 + wave; c < t.c1; c += nw) {
+        const int64_t beg = A.chunk_beg[c];
+        const int len = static_cast<int>(A.chunk_end[c] - beg);
+        const uint32_t *__restrict__ pb = A.pnu + beg;
+        const T *__restrict__ gb = A.g2 + beg;
+        uint32_t pn = pb[lane];
+        T g[NM];
+#pragma unroll
+        for (int m = 0; m < NM; ++m) g[m] = gb[min(m, nm - 1) * A.pld + lane];
+        for (int r = 0; r < len; r += 64) {
+            const bool on = r + lane < len;
+            // a masked lane takes window slot 0 as both states and adds nothing
+            const int wd = on ? static_cast<int>(pn & 0xffffu) : 0;
+            const int wp = on ? static_cast<int>(pn >> 16) : 0;
+            const uint32_t kd = s_kq[wd], kp = s_kq[wp];
+            const int q = PADQ ? static_cast<int>(kp - kd) + A.qoff : q_linear(kd, kp, A.nq0, A.nq1, A.nq2);
+            const T x = s_e[wd] - s_e[wp];
+            T cm[NM], a0 = T(0), bb = T(0);
+            bool has[NM];
+#pragma unroll
+            for (int m = 0; m < NM; ++m) {
+                const T w = A.hwN[static_cast<int64_t>(q) * A.tq + min(m, nm - 1) * A.tm].a;
+                const T gm = on && m < nm ? g[m] : T(0);
+                const T xa = x + w, xe = x - w;
+                const T da = pair_gauss<T, TAB>(A, xa * xa, s_tab);
+                const T dem = pair_gauss<T, TAB>(A, xe * xe, s_tab);
+                cm[m] = gm * (da + dem);
+                a0 = fma(gm, dem, a0);
+                bb = fma(gm, da, bb);
+                has[m] = gm != T(0);
+            }
+            pn = pb[r + 64 + lane];
+#pragma unroll
+            for (int m = 0; m < NM; ++m) g[m] = gb[min(m, nm - 1) * A.pld + r + 64 + lane];
+            const T *__restrict__ nq = tn + static_cast<int64_t>(q) * nm * VB;
+            for (int v = 0; v < nv; ++v) {
+                T ns = T(0);
+#pragma unroll
+                for (int m = 0; m < NM; ++m) ns = fma(cm[m], keep_or_zero(nq[min(m, nm - 1) * VB + v], has[m]), ns);
+                const T fd = s_f[v * W + wd], fp = s_f[v * W + wp];
+                const T ta = (a0 + ns) * (T(1) - fp), tb = (bb + ns) * fp;
+                const T y = fma(fd, ta, -(T(1) - fd) * tb);
+                if (on) {
+                    const unsigned long long fx = to_fixed(__builtin_rint(y * static_cast<T>(s_scale[v])));
+                    atomicAdd(s_j + v * W + wp, fx);
+                    atomicAdd(s_j + v * W + wd, 0ull - fx);
+                }
+            }
+        }
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < n; i += blockDim.x)
+        for (int v = 0; v < nv; ++v) {
+            const unsigned long long u = s_j[v * W + i];
+            if (u) atomicAdd(V.jacc + static_cast<int64_t>(b0 + v) * A.S + t.p_lo + i, u);
+        }
+}
+
+// out_b,d = K (fixed-point sum) / scale, then the epilogue; the sums are cleared
+// for the next call (grid.y = vector)
+template <typename T> __global__ void k_pv_finish(TiledArgs<T> A, PvArgs<T> V, Epi<T> E) {
+    const int b = blockIdx.y;
+    const double inv = 1.0 / pv_scale(A, V, b);
+    const int d = blockIdx.x * blockDim.x + threadIdx.x;
+    if (d >= A.S) return;
+    unsigned long long *j = V.jacc + static_cast<int64_t>(b) * A.S + d;
+    const T v = static_cast<T>(static_cast<double>(static_cast<long long>(*j)) * inv);
+    *j = 0ull;
+    apply_epi(E, b, d, A.S, A.K * v);
+}
+
+// The reverse pass (FP64 plans).  Per pair and vector, with dl = lam_d - lam_p,
+// P1 = dl f_d (1 - f_p), P2 = dl f_p (1 - f_d):
+//   dL/df_d += -dl (a_b (1 - f_p) + b_b f_p),  dL/df_p += dl (b_b (1 - f_d) + a_b f_d)
+// (times K), and a channel's gradient is, summed over the vectors of the group in
+// order in the lane that holds the pair,
+//   K [ G(x + hw) sum P2 - G(x - hw) sum P1 + (G(x + hw) + G(x - hw)) sum N_b (P2 - P1) ].
+// A later group adds to it (gg2_mode 2).
+template <bool PADQ, int NM, bool TAB>
+__global__ __launch_bounds__(1024) void k_vjp_pairs_pv(TiledArgs<double> A, PvArgs<double> V, int group, int want_f,
+                                                       const int32_t *__restrict__ chan,
+                                                       const int32_t *__restrict__ chan0, double *__restrict__ gg2,
+                                                       int gg2_mode) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ double s_scale[16];
+    const TileRec t = A.tiles[blockIdx.x];
+    const int W = A.lds_states, VB = V.vb, b0 = group * VB;
+    const int nv = min(VB, V.B - b0);
+    double *s_tab = reinterpret_cast<double *>(smem);
+    unsigned long long *s_j = reinterpret_cast<unsigned long long *>(s_tab + kExpTab);
+    Pair2<double> *s_fl = reinterpret_cast<Pair2<double> *>(s_j + VB * W);
+    double *s_e = reinterpret_cast<double *>(s_fl + VB * W);
+    uint32_t *s_kq = reinterpret_cast<uint32_t *>(s_e + W);
+    const int n = t.p_hi - t.p_lo + 1;
+    for (int i = threadIdx.x; i < n; i += blockDim.x) {
+        const StateRec<double> sr = A.st[t.p_lo + i];
+        s_e[i] = sr.eps;
+        s_kq[i] = PADQ ? sr.kqp : sr.kq;
+        for (int v = 0; v < nv; ++v) {
+            Pair2<double> fl;
+            fl.a = V.f[static_cast<int64_t>(b0 + v) * V.ldf + t.p_lo + i];
+            fl.b = V.lam[static_cast<int64_t>(b0 + v) * V.ldl + t.p_lo + i];
+            s_fl[v * W + i] = fl;
+            s_j[v * W + i] = 0ull;
+        }
+    }
+    if constexpr (TAB)
+        for (int i = threadIdx.x; i < kExpTab; i += blockDim.x) s_tab[i] = A.e2tab[i];
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+    const int nw = static_cast<int>(blockDim.x >> 6);
+    for (int v = wave; v < nv; v += nw) {
+        const double sc = pv_scale(A, V, b0 + v);
+        if ((threadIdx.x & 63) == 0) s_scale[v] = sc;
+    }
+    __syncthreads();
+    const int lane = threadIdx.x & 63;
+    const int nm = A.nm;
+    const double *__restrict__ tn = V.tab_n + group * V.gstride;
+    for (int64_t c = t.c0 + wave; c < t.c1; c += nw) {
+        const int64_t beg = A.chunk_beg[c];
+        const int len = static_cast<int>(A.chunk_end[c] - beg);
+        const uint32_t *__restrict__ pb = A.pnu + beg;
+        const double *__restrict__ gb = A.g2 + beg;
+        const int32_t *__restrict__ cb = chan + beg;
+        const int32_t *__restrict__ cb0 = chan0 + beg;
+        for (int r = 0; r < len; r += 64) {
+            const bool on = r + lane < len;
+            const uint32_t pn = pb[r + lane];
+            const int32_t c0 = gg2_mode ? cb0[r + lane] : -1;
+            const int wd = on ? static_cast<int>(pn & 0xffffu) : 0;
+            const int wp = on ? static_cast<int>(pn >> 16) : 0;
+            const uint32_t kd = s_kq[wd], kp = s_kq[wp];
+            const int q = PADQ ? static_cast<int>(kp - kd) + A.qoff : q_linear(kd, kp, A.nq0, A.nq1, A.nq2);
+            const double x = s_e[wd] - s_e[wp];
+            double da[NM], dem[NM], g[NM], rn[NM], a0 = 0.0, bb = 0.0;
+#pragma unroll
+            for (int m = 0; m < NM; ++m) {
+                const double w = A.hwN[static_cast<int64_t>(q) * A.tq + min(m, nm - 1) * A.tm].a;
+                const double gs = gb[min(m, nm - 1) * A.pld + r + lane];
+                g[m] = on && m < nm ? gs : 0.0;
+                const double xa = x + w, xe = x - w;
+                da[m] = pair_gauss<double, TAB>(A, xa * xa, s_tab);
+                dem[m] = pair_gauss<double, TAB>(A, xe * xe, s_tab);
+                a0 = fma(g[m], dem[m], a0);
+                bb = fma(g[m], da[m], bb);
+                rn[m] = 0.0;
+            }
+            const double *__restrict__ nq = tn + static_cast<int64_t>(q) * nm * VB;
+            double p1 = 0.0, p2 = 0.0;
+            for (int v = 0; v < nv; ++v) {
+                const Pair2<double> fd = s_fl[v * W + wd], fp = s_fl[v * W + wp];
+                const double dl = fd.b - fp.b;
+                const double q1 = dl * fd.a * (1.0 - fp.a), q2 = dl * fp.a * (1.0 - fd.a), dq = q2 - q1;
+                double ns = 0.0;
+#pragma unroll
+                for (int m = 0; m < NM; ++m) {
+                    const double N = nq[min(m, nm - 1) * VB + v];
+                    // a slot without a channel may hold a non-finite N; its
+                    // gradient is not written
+                    ns = fma(g[m] * (da[m] + dem[m]), keep_or_zero(N, g[m] != 0.0), ns);
+                    rn[m] = fma(N, dq, rn[m]);
+                }
+                p1 += q1;
+                p2 += q2;
+                if (want_f && on) {
+                    const double sc = s_scale[v];
+                    const double a = a0 + ns, b = bb + ns;
+                    const double rd = dl * fma(a, 1.0 - fp.a, b * fp.a);
+                    const double y = dl * fma(b, 1.0 - fd.a, a * fd.a);
+                    atomicAdd(s_j + v * W + wp, to_fixed(__builtin_rint(y * sc)));
+                    atomicAdd(s_j + v * W + wd, to_fixed(__builtin_rint(-rd * sc)));
+                }
+            }
+            if (gg2_mode && on) {
+                double gv[NM];
+#pragma unroll
+                for (int m = 0; m < NM; ++m)
+                    gv[m] = A.K * (da[m] * p2 - dem[m] * p1 + (da[m] + dem[m]) * rn[m]);
+                write_gg2<NM>(gg2, gg2_mode, c0, cb + r + lane, A.pld, nm, gv);
+            }
+        }
+    }
+    if (!want_f) return;
+    __syncthreads();
+    for (int i = threadIdx.x; i < n; i += blockDim.x)
+        for (int v = 0; v < nv; ++v) {
+            const unsigned long long u = s_j[v * W + i];
+            if (u) atomicAdd(V.jacc + static_cast<int64_t>(b0 + v) * A.S + t.p_lo + i, u);
+        }
+}
+
 // ---- the pair matrix ---------------------------------------------------------
 // Where a call applies one bath's collision integral more than once (RK4 steps,
 // the transport iteration, several occupation vectors), the coefficients are

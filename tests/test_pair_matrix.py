@@ -175,3 +175,36 @@ def test_reverse_through_the_matrix(E, S, B, modes, dtype):
     assert nerr(host(gg), rg) <= TOL[dtype]
     assert nerr(host(gg1) - 0.5, rg) <= TOL[dtype]
     plan.close()
+
+
+@pytest.mark.parametrize("S,B,modes,dtype,stats", [(2, 2, 1, "f64", "fermi"), (63, 7, 3, "f64", "fermi"),
+                                                   (130, 9, 6, "f32", "fermi"), (200, 17, 8, "f64", "fermi"),
+                                                   (65, 24, 3, "f64", "bose"), (64, 8, 2, "f32", "bose")])
+def test_bath_per_vector_over_pair_records(E, S, B, modes, dtype, stats):
+    """Groups of vectors with a phonon table each, forward and reverse (FP64 over
+    the pair records; the gradient overwritten and accumulated)."""
+    s = full_system(S, 6, n_modes=modes)
+    rng = np.random.default_rng(S + B)
+    bose = stats == "bose"
+    F = cast(rng.uniform(0.0, 3.0 if bose else 1.0, size=(B, S)), dtype)
+    NPH = cast(np.stack([s.nph(150.0 + 30.0 * b) for b in range(B)]), dtype)
+    lam = cast(rng.normal(size=(B, S)), dtype)
+    plan = E.build_channels(s, dtype=dtype, device=0, statistics=stats)
+    r = rounded(s, dtype)
+    fwd = oracle.collision_bose if bose else oracle.collision
+    vjp = oracle.collision_bose_vjp if bose else oracle.collision_vjp
+    got = host(E.collision_integral(plan, dev(F, dtype), dev(NPH, dtype)))
+    start = torch.full((s.n_channels,), 0.5, dtype=torch.float64, device="cuda:0")
+    gf, gg = E.collision_vjp(plan, dev(F, dtype), dev(NPH, dtype), dev(lam, dtype), gg2=start.clone())
+    _, ga = E.collision_vjp(plan, dev(F, dtype), dev(NPH, dtype), dev(lam, dtype), want_f=False, gg2=start.clone(),
+                            accumulate=True)
+    rg = 0.0
+    for b in range(B):
+        ref = fwd(r, F[b], NPH[b])
+        assert nerr(got[b], ref, 0.0 if bose else gross(r, F[b], NPH[b])) <= TOL[dtype], b
+        rf, rgb = vjp(r, F[b], NPH[b], lam[b])[:2]
+        assert nerr(host(gf)[b], rf) <= TOL[dtype], b
+        rg = rg + rgb
+    assert nerr(host(gg), rg) <= TOL[dtype]
+    assert nerr(host(ga) - 0.5, rg) <= TOL[dtype]
+    plan.close()
