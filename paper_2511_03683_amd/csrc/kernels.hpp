@@ -2513,7 +2513,10 @@ __global__ __launch_bounds__(64 * kMxParts) void k_mx_rk_finish(TiledArgs<T> A, 
     if (threadIdx.x >= 64) return;
     const int x = blockIdx.x * 64 + threadIdx.x;
     const int d = X.state[x];
-    if (d < 0) return;
+    if (d < 0) {   // a position without a state: its column is zero in every stage
+        n1[x] = n2[x] = 0.0;
+        return;
+    }
     if (!mx_finite(o1[0], o2[0])) mx_own_sums<T>(A, X, d, u1, u2, 1, 0, o1[0], o2[0]);
     apply_epi(E, 0, d, X.S, static_cast<T>(K * (u2[x] * o1[0] - u1[x] * o2[0])));
     const T y = E.mode == EPI_RK4 ? E.f_out[d] : E.u_out[d];
@@ -3077,7 +3080,10 @@ __global__ __launch_bounds__(64 * kMxParts) void k_mx_tr_finish(TiledArgs<T> A, 
     if (threadIdx.x >= 64) return;
     const int x = blockIdx.x * 64 + threadIdx.x;
     const int d = X.state[x];
-    if (d < 0) return;
+    if (d < 0) {   // a position without a state: its column is zero in every iteration
+        un[3 * x] = un[3 * x + 1] = un[3 * x + 2] = 0.0;
+        return;
+    }
     const double f = static_cast<double>(f0[d]), t = static_cast<double>(tau[d]);
     const Vec4<T> r = rhs[d];
     const double rr[3] = {static_cast<double>(r.x), static_cast<double>(r.y), static_cast<double>(r.z)};
