@@ -168,8 +168,9 @@ struct ephbte_plan_s {
     int pr_window = 0;                     // largest window of a pair tile
     int64_t *pr_chunk_beg = nullptr, *pr_chunk_end = nullptr;
     int32_t *pr_chunk_dest = nullptr, *pr_dest_chunk = nullptr;
-    TileRec *pr_tiles = nullptr;
-    int64_t n_pr_chunks = 0, n_pr_tiles = 0;
+    TileRec *pr_groups = nullptr;          // workgroups of the pair passes
+    std::vector<TileRec> pr_tiles;         // host: their runs (see PairOrder)
+    int64_t n_pr_chunks = 0, n_pr_groups = 0, n_pr_tiles = 0;
     bool pr_ok = false;
     bool exp_table = true;                 // FP64 Gaussians of the pair pass from the LDS table
     // pair matrix (built from the pair records where its blocks are filled
@@ -347,7 +348,7 @@ void free_plan(ephbte_plan P) {
                      (void **)&P->ph_bucket_q, (void **)&P->ph_bucket_qm, (void **)&P->ph_q_bucket,
                      (void **)&P->ph_bucket_modes, (void **)&P->pr_partner, (void **)&P->pr_g2,
                      (void **)&P->pr_chan, (void **)&P->pr_chunk_beg, (void **)&P->pr_chunk_end,
-                     (void **)&P->pr_chunk_dest, (void **)&P->pr_dest_chunk, (void **)&P->pr_tiles,
+                     (void **)&P->pr_chunk_dest, (void **)&P->pr_dest_chunk, (void **)&P->pr_groups,
                      (void **)&P->pr_ch0,
                      (void **)&P->used_rows, (void **)&P->mx_pos, (void **)&P->mx_state, (void **)&P->mx_blk,
                      (void **)&P->mx_row, (void **)&P->mx_col};
@@ -385,7 +386,7 @@ unsigned grid_of(int64_t n) {
 // chunk table and tiles by the renumbered ones.  The stream words are
 // uploaded; the mode slots (|g|^2, channel) and first channels are gathered
 // on the device from their current order.
-void order_pair_records(ephbte_plan P, ChunkTable &pc, std::vector<Tile> &tp, bool qord) {
+void order_pair_records(ephbte_plan P, ChunkTable &pc, std::vector<Tile> &tp, std::vector<Tile> &runs, bool qord) {
     const int64_t np = P->pr_np;
     RowKey rk;
     rk.key = P->st_key.data();
@@ -395,11 +396,11 @@ void order_pair_records(ephbte_plan P, ChunkTable &pc, std::vector<Tile> &tp, bo
     for (int a = 0; a < 3; ++a) rk.n[a] = P->nq[a];
     PairOrder o;
     if (qord) {
-        o = order_pair_tiles(pc, tp, P->pr_partner_host, rk, kPairChunksPerTile, 65536);
+        o = order_pair_tiles(pc, tp, P->pr_partner_host, rk, kRunRecords, 65536);
     } else {
         // destination order: the tiles and chunks as built
         o.chunks = pc;
-        o.tiles = tp;
+        o.groups = o.tiles = tp;
         o.perm.resize(static_cast<size_t>(np));
         for (int64_t x = 0; x < np; ++x) o.perm[x] = static_cast<uint32_t>(x);
         o.word = P->pr_partner_host;
@@ -457,7 +458,8 @@ void order_pair_records(ephbte_plan P, ChunkTable &pc, std::vector<Tile> &tp, bo
     if (ident) P->pr_perm.clear();
     else P->pr_perm = std::move(o.perm);
     pc = std::move(o.chunks);
-    tp = std::move(o.tiles);
+    tp = std::move(o.groups);
+    runs = std::move(o.tiles);
 }
 
 // Tiles of a single-copy pass: one workgroup a compute unit at a time, so the
@@ -575,17 +577,18 @@ void upload_chunks(ephbte_plan P, int64_t chunk_entries) {
     };
     std::vector<Tile> tp = P->tile_entries > 0 ? make_p(P->tile_entries / (2 * static_cast<int64_t>(P->nm)) + 1)
                                                : round_tiles(P->pr_np, 8192, P->n_cu, make_p);
-    order_pair_records(P, pc, tp, qord);
+    std::vector<Tile> runs;
+    order_pair_records(P, pc, tp, runs, qord);
     dfree(reinterpret_cast<void *&>(P->pr_chunk_beg));
     dfree(reinterpret_cast<void *&>(P->pr_chunk_end));
     dfree(reinterpret_cast<void *&>(P->pr_chunk_dest));
     dfree(reinterpret_cast<void *&>(P->pr_dest_chunk));
-    dfree(reinterpret_cast<void *&>(P->pr_tiles));
+    dfree(reinterpret_cast<void *&>(P->pr_groups));
     dalloc(P->pr_chunk_beg, pc.chunk_beg.size() * sizeof(int64_t), &dummy);
     dalloc(P->pr_chunk_end, std::max<size_t>(pc.chunk_end.size(), 1) * sizeof(int64_t), &dummy);
     dalloc(P->pr_chunk_dest, std::max<size_t>(pc.chunk_dest.size(), 1) * sizeof(int32_t), &dummy);
     dalloc(P->pr_dest_chunk, pc.dest_chunk.size() * sizeof(int32_t), &dummy);
-    dalloc(P->pr_tiles, std::max<size_t>(tp.size(), 1) * sizeof(TileRec), &dummy);
+    dalloc(P->pr_groups, std::max<size_t>(tp.size(), 1) * sizeof(TileRec), &dummy);
     HIPC(hipMemcpy(P->pr_chunk_beg, pc.chunk_beg.data(), pc.chunk_beg.size() * sizeof(int64_t),
                    hipMemcpyHostToDevice));
     if (!pc.chunk_end.empty()) {
@@ -597,9 +600,12 @@ void upload_chunks(ephbte_plan P, int64_t chunk_entries) {
     HIPC(hipMemcpy(P->pr_dest_chunk, pc.dest_chunk.data(), pc.dest_chunk.size() * sizeof(int32_t),
                    hipMemcpyHostToDevice));
     if (!tp.empty())
-        HIPC(hipMemcpy(P->pr_tiles, tp.data(), tp.size() * sizeof(TileRec), hipMemcpyHostToDevice));
+        HIPC(hipMemcpy(P->pr_groups, tp.data(), tp.size() * sizeof(TileRec), hipMemcpyHostToDevice));
     P->n_pr_chunks = pc.n_chunks;
-    P->n_pr_tiles = static_cast<int64_t>(tp.size());
+    P->n_pr_groups = static_cast<int64_t>(tp.size());
+    P->pr_tiles.resize(runs.size());
+    if (!runs.empty()) std::memcpy(P->pr_tiles.data(), runs.data(), runs.size() * sizeof(TileRec));
+    P->n_pr_tiles = static_cast<int64_t>(runs.size());
     P->pr_key = pr_key;
     P->pr_key_set = true;
     P->pr_all_q = !tp.empty();
@@ -688,6 +694,7 @@ template <typename T> TiledArgs<T> tiled_args(ephbte_plan P) {
     a.n_tiles = P->n_tiles;
     a.xcd = P->xcd_map ? 1 : 0;
     a.chunk_end = nullptr;
+    a.all_q = 0;
     a.jacc = P->jacc;
     a.nmax = max_list(P, kMaxN);
     a.gmax_bits = P->gmax_bits;
@@ -721,9 +728,10 @@ template <typename T> TiledArgs<T> pair_args(ephbte_plan P) {
     a.chunk_end = P->pr_chunk_end;
     a.chunk_dest = P->pr_chunk_dest;
     a.dest_chunk = P->pr_dest_chunk;
-    a.tiles = P->pr_tiles;
+    a.tiles = P->pr_groups;
     a.n_chunks = P->n_pr_chunks;
-    a.n_tiles = P->n_pr_tiles;
+    a.all_q = P->pr_all_q ? 1 : 0;
+    a.n_tiles = P->n_pr_groups;
     return a;
 }
 
@@ -763,7 +771,7 @@ bool use_sym(ephbte_plan P, int B) {
 template <typename T>
 void launch_pairs(ephbte_plan P, const TiledArgs<T> &a, const T *f, T *part, size_t shm, hipStream_t s,
                   bool padq) {
-    const dim3 grid(static_cast<unsigned>(P->n_pr_tiles)), block(static_cast<unsigned>(P->pr_threads));
+    const dim3 grid(static_cast<unsigned>(P->n_pr_groups)), block(static_cast<unsigned>(P->pr_threads));
     auto go = [&](auto nmc) {
         constexpr int NM = decltype(nmc)::value;
         const bool tab = sizeof(T) == 8 && P->exp_table;
@@ -781,7 +789,7 @@ void launch_pairs(ephbte_plan P, const TiledArgs<T> &a, const T *f, T *part, siz
 }
 
 bool use_pairs(ephbte_plan P, int B) {
-    return B == 1 && P->layout == 3 && P->sym_ok && P->pr_ok && P->n_pr_tiles > 0;
+    return B == 1 && P->layout == 3 && P->sym_ok && P->pr_ok && P->n_pr_groups > 0;
 }
 // the reverse pass over the pair records (its window holds lam too)
 bool vjp_pairs_fit(ephbte_plan P) {
@@ -1133,7 +1141,7 @@ size_t pair_matrix_lds(ephbte_plan P) {
 template <typename T> void enqueue_pair_matrix(ephbte_plan P, hipStream_t s) {
     const TiledArgs<T> a = pair_args<T>(P);
     const MxArgs<T> x = mx_args<T>(P);
-    const dim3 grid(static_cast<unsigned>(P->n_pr_tiles)), block(1024);
+    const dim3 grid(static_cast<unsigned>(P->n_pr_groups)), block(1024);
     const size_t shm = pair_matrix_lds(P);
     auto go = [&](auto nmc) {
         constexpr int NM = decltype(nmc)::value;
@@ -1186,7 +1194,7 @@ size_t mx_gemm_lds(int NC) { return 2 * 64 * static_cast<size_t>(NC + 4) * sizeo
 // entries; below 8 vectors, against one pass per vector.  Below 8 the tuning's
 // layout chooses, as for one vector.
 bool mx_batch_fits(ephbte_plan P, int B) {
-    return P->mx_ok && B >= 2 && P->pr_ok && P->n_pr_tiles > 0 && (B >= P->batch_min || P->layout == 3) &&
+    return P->mx_ok && B >= 2 && P->pr_ok && P->n_pr_groups > 0 && (B >= P->batch_min || P->layout == 3) &&
            mx_gemm_lds(mx_columns(B)) <= P->lds_max;
 }
 template <typename T> bool mx_ensure_batch(ephbte_plan P, int B) {
@@ -1256,7 +1264,7 @@ void enqueue_forward_mx(ephbte_plan P, int B, const T *f, int64_t ldf, const Epi
 template <typename T> void enqueue_mx_gg2(ephbte_plan P, const T *g, double *gg2, int gg2_mode, hipStream_t s) {
     const TiledArgs<T> a = pair_args<T>(P);
     const MxArgs<T> x = mx_args<T>(P);
-    const dim3 grid(static_cast<unsigned>(P->n_pr_tiles)), block(1024);
+    const dim3 grid(static_cast<unsigned>(P->n_pr_groups)), block(1024);
     const size_t shm = pair_matrix_lds(P);
     auto go = [&](auto nmc) {
         constexpr int NM = decltype(nmc)::value;
@@ -1361,7 +1369,7 @@ size_t pv_lds(ephbte_plan P, int W, int VB, bool vjp) {
 // 64 vectors); below 8 vectors the alternative is one pass each, which one already
 // matches.
 int pv_vectors(ephbte_plan P, int B, bool vjp) {
-    if (!P->pr_ok || !P->pr_all_q || !P->sym_ok || P->n_pr_tiles == 0 || P->pr_window < 1) return 0;
+    if (!P->pr_ok || !P->pr_all_q || !P->sym_ok || P->n_pr_groups == 0 || P->pr_window < 1) return 0;
     if (P->layout != 3 && B < P->batch_min) return 0;
     int most = 0;
     while (most < 8 && pv_lds(P, P->pr_window, most + 1, vjp) + 1024 <= P->lds_max) ++most;
@@ -1435,7 +1443,7 @@ bool enqueue_forward_pv(ephbte_plan P, int B, const T *f, int64_t ldf, const T *
     TiledArgs<T> a = pair_args<T>(P);
     a.lds_states = P->pr_window;
     const size_t shm = pv_lds(P, P->pr_window, VB, false);
-    const dim3 grid(static_cast<unsigned>(P->n_pr_tiles), static_cast<unsigned>((B + VB - 1) / VB)), block(1024);
+    const dim3 grid(static_cast<unsigned>(P->n_pr_groups), static_cast<unsigned>((B + VB - 1) / VB)), block(1024);
     auto go = [&](auto nmc) {
         constexpr int NM = decltype(nmc)::value;
         const bool tab = sizeof(T) == 8 && P->exp_table;
@@ -1466,7 +1474,7 @@ bool enqueue_vjp_pv(ephbte_plan P, int B, const double *f, int64_t ldf, const do
     TiledArgs<double> a = pair_args<double>(P);
     a.lds_states = P->pr_window;
     const size_t shm = pv_lds(P, P->pr_window, VB, true);
-    const dim3 grid(static_cast<unsigned>(P->n_pr_tiles)), block(1024);
+    const dim3 grid(static_cast<unsigned>(P->n_pr_groups)), block(1024);
     const int32_t *ch = P->pr_chan, *c0 = P->pr_ch0;
     const int wf = gf ? 1 : 0;
     for (int g = 0; g * VB < B; ++g) {
@@ -1525,7 +1533,7 @@ void enqueue_forward(ephbte_plan P, int B, const T *f, int64_t ldf, const void *
     if (use_pairs(P, B)) {
         TiledArgs<T> a = pair_args<T>(P);
         MaxList none{nullptr, 0};
-        reduce_lists<T>(P, a, none, P->n_pr_tiles, s);
+        reduce_lists<T>(P, a, none, P->n_pr_groups, s);
         T *part = static_cast<T *>(P->sym_part.p);
         const size_t shm = sym_lds_bytes(P->dtype, P->pr_lds_states);
         const int64_t kt = ktime_begin(P, s);
@@ -1599,7 +1607,7 @@ size_t noalloc_bytes(ephbte_plan P) {
     const size_t es = P->dtype == EPHBTE_F64 ? 8 : 4;
     const size_t tab = 2 * es * static_cast<size_t>(std::max<int64_t>(nqm_of(P), 1));
     size_t part = 0;
-    if (use_pairs(P, 1)) part = 2 * es * static_cast<size_t>(std::max<int64_t>(P->n_pr_chunks, 1));
+    if (use_pairs(P, 1)) part = P->pr_all_q ? 0 : 2 * es * static_cast<size_t>(std::max<int64_t>(P->n_pr_chunks, 1));
     else if (use_sym(P, 1)) part = 2 * es * static_cast<size_t>(std::max<int64_t>(P->n_sym_chunks, 1));
     else if (!P->fused) part = 2 * es * static_cast<size_t>(P->n_chunks);
     return ((tab + 255) & ~size_t(255)) + part;
@@ -1666,10 +1674,10 @@ void enqueue_vjp(ephbte_plan P, const T *f, const T *lam, const void *nph, const
                             P->boson ? vec_part<T>(P, kMaxF, f, nullptr, P->S) : VecPart<T>{}, s);
         TiledArgs<T> a = pair_args<T>(P);
         MaxList lm = max_list(P, kMaxL);
-        reduce_lists<T>(P, a, lm, P->n_pr_tiles, s);
+        reduce_lists<T>(P, a, lm, P->n_pr_groups, s);
         T *part = static_cast<T *>(P->sym_part.p);
         const int want_f = E.mode >= 0 ? 1 : 0;
-        const dim3 grid(static_cast<unsigned>(P->n_pr_tiles)), block(kVjpPairThreads);
+        const dim3 grid(static_cast<unsigned>(P->n_pr_groups)), block(kVjpPairThreads);
         const size_t shm = vjp_pair_lds_bytes(P->dtype, P->pr_lds_states);
         auto go = [&](auto nmc) {
             constexpr int NM = decltype(nmc)::value;
@@ -2479,7 +2487,7 @@ void enqueue_phonon_vjp_f(ephbte_plan P, const T *u, const T *N, const T *mu, T 
     hipLaunchKernelGGL((k_pack_hwNmu<T>), dim3(grid_of(n)), dim3(256), 0, s, static_cast<const T *>(P->hw), N, mu,
                        tab, P->padq ? 1 : 0, P->qbox, P->nm, (const int32_t *)P->used_rows, n);
     const double Kp = 2.0 * kPi / (kHbar * P->nk) / (P->sigma * std::sqrt(2.0 * kPi));
-    if (P->pr_ok && P->pr_all_q && P->sym_ok && P->n_pr_tiles > 0) {
+    if (P->pr_ok && P->pr_all_q && P->sym_ok && P->n_pr_groups > 0) {
         // over the q-ordered pair records: max |N| and max |mu| of the call
         // set the fixed-point scale
         const int64_t nqm = nqm_of(P);
@@ -2488,8 +2496,8 @@ void enqueue_phonon_vjp_f(ephbte_plan P, const T *u, const T *N, const T *mu, T 
         TiledArgs<T> a = pair_args<T>(P);
         a.nmax = max_list(P, kMaxNph);
         MaxList mm = max_list(P, kMaxMu);
-        reduce_lists<T>(P, a, mm, P->n_pr_tiles, s);
-        const dim3 grid(static_cast<unsigned>(P->n_pr_tiles)), block(1024);
+        reduce_lists<T>(P, a, mm, P->n_pr_groups, s);
+        const dim3 grid(static_cast<unsigned>(P->n_pr_groups)), block(1024);
         const size_t shm = sym_lds_bytes(P->dtype, P->pr_lds_states);
         auto go = [&](auto nmc) {
             constexpr int NM = decltype(nmc)::value;

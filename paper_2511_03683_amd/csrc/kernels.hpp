@@ -354,6 +354,7 @@ template <typename T> struct TiledArgs {
     const unsigned long long *__restrict__ gmax_bits;  // max over states of sum |g|^2 (double bits)
     // pair records (k_fwd_pairs): pnu holds partners, g2 is [n_modes][pld]
     int64_t pld;
+    int all_q;                                       // every tile is q-ordered: no row partials
     // occupations outside [0, 1] (the Bose plans' negated n): max |f| of the
     // call's input, or n = 0 when f lies in [0, 1]
     MaxList fmax;
@@ -1057,22 +1058,27 @@ __device__ __forceinline__ void pair_chunk(const TiledArgs<T> &A, const T *__res
 // holds the window offsets of its partner (high 16 bits) and destination (low
 // 16 bits); the window stages both.  The destination's side of the pair, -y,
 // goes to the same fixed-point accumulator as the partner's, +y, so the
-// chunk's row partials are zero.
+// tile has no row partials.  The waves take the tile's batches in turn, so that
+// together they sweep its runs: the table rows, the |g|^2 lines and, in the
+// passes that write per pair, the output lines in flight belong to one run.
+// With 100^3 (198 M channels, 2048 records a run) against one sorted range per
+// tile and a part of it per wave: forward 439 us for 466, reverse with channel
+// gradients 1174 for 1227, pair matrix 837 for 940.  Runs of 512 / 8192 / 65536
+// records: reverse 1174 / 1180 / 1196 us, pair matrix 875 / 858 / 900.
 template <typename T, bool PADQ, int NM, bool TAB>
 __device__ __forceinline__ void pair_chunk_q(const TiledArgs<T> &A, const Pair2<T> *s_ef, const uint32_t *s_kq,
-                                             const double *s_tab, unsigned long long *s_j, T scale, int64_t c,
-                                             T *__restrict__ part) {
+                                             const double *s_tab, unsigned long long *s_j, T scale, int64_t beg,
+                                             int len, int wave, int nw) {
     const int lane = threadIdx.x & 63;
     const int nm = A.nm;
-    const int64_t beg = A.chunk_beg[c];
-    const int len = static_cast<int>(A.chunk_end[c] - beg);
+    const int first = wave * 64, step = nw * 64;
     const uint32_t *__restrict__ pb = A.pnu + beg;
     const T *__restrict__ gb = A.g2 + beg;
     // stream one batch ahead, two register sets (see pair_chunk)
-    uint32_t pn0 = pb[lane], pn1 = 0;
+    uint32_t pn0 = pb[first + lane], pn1 = 0;
     T g0[NM], g1[NM];
 #pragma unroll
-    for (int m = 0; m < NM; ++m) g0[m] = gb[min(m, nm - 1) * A.pld + lane];
+    for (int m = 0; m < NM; ++m) g0[m] = gb[min(m, nm - 1) * A.pld + first + lane];
     auto batch = [&](int r, const uint32_t pn, const T (&g)[NM], uint32_t &pn_next, T (&g_next)[NM]) {
         const bool v = r + lane < len;
         // a masked lane takes window slot 0 as both states (q = 0) and adds nothing
@@ -1086,9 +1092,9 @@ __device__ __forceinline__ void pair_chunk_q(const TiledArgs<T> &A, const Pair2<
 #pragma unroll
         for (int m = 0; m < NM; ++m) w[m] = wq[min(m, nm - 1) * A.tm];
         __builtin_amdgcn_sched_barrier(0);
-        pn_next = pb[r + 64 + lane];
+        pn_next = pb[r + step + lane];
 #pragma unroll
-        for (int m = 0; m < NM; ++m) g_next[m] = gb[min(m, nm - 1) * A.pld + r + 64 + lane];
+        for (int m = 0; m < NM; ++m) g_next[m] = gb[min(m, nm - 1) * A.pld + r + step + lane];
         __builtin_amdgcn_sched_barrier(0);
         T sa, sb;
         pair_mode_sums<T, NM, TAB>(A, efd.a - efp.a, w, g, v, s_tab, sa, sb);
@@ -1101,14 +1107,10 @@ __device__ __forceinline__ void pair_chunk_q(const TiledArgs<T> &A, const Pair2<
             atomicAdd(s_j + wd, 0ull - fx);
         }
     };
-    for (int r = 0; r < len; r += 128) {
+    for (int r = first; r < len; r += 2 * step) {
         batch(r, pn0, g0, pn1, g1);
-        if (r + 64 >= len) break;
-        batch(r + 64, pn1, g1, pn0, g0);
-    }
-    if (lane == 0) {
-        part[2 * c] = T(0);
-        part[2 * c + 1] = T(0);
+        if (r + step >= len) break;
+        batch(r + step, pn1, g1, pn0, g0);
     }
 }
 
@@ -1140,10 +1142,15 @@ __global__ __launch_bounds__(1024) void k_fwd_pairs(TiledArgs<T> A, const T *__r
     __syncthreads();
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
     const int nw = static_cast<int>(blockDim.x >> 6);
-    for (int64_t c = t.c0 + wave; c < t.c1; c += nw) {
-        if (t.lds == 2)
-            pair_chunk_q<T, PADQ, NM, TAB>(A, s_ef, s_kq, s_tab, s_j, scale, c, part);
-        else if (t.lds)
+    if (t.lds == 2) {
+        const int64_t beg = A.chunk_beg[t.c0];
+        pair_chunk_q<T, PADQ, NM, TAB>(A, s_ef, s_kq, s_tab, s_j, scale, beg,
+                                       static_cast<int>(A.chunk_end[t.c1 - 1] - beg), wave, nw);
+        if (!A.all_q)
+            for (int64_t c = 2 * t.c0 + threadIdx.x; c < 2 * t.c1; c += blockDim.x) part[c] = T(0);
+    }
+    for (int64_t c = t.c0 + wave; t.lds != 2 && c < t.c1; c += nw) {
+        if (t.lds)
             pair_chunk<T, true, PADQ, NM, TAB>(A, f, s_ef, s_kq, t.p_lo, s_tab, s_j, scale, c, part);
         else
             pair_chunk<T, false, PADQ, NM, TAB>(A, f, s_ef, s_kq, t.p_lo, s_tab, s_j, scale, c, part);
@@ -1177,9 +1184,6 @@ __device__ __forceinline__ double vjp_scale(const ScaleIn &s) {
 // (a lane holds at most 128 registers; the pass needs about 100 with the
 // modes summed per pair)
 constexpr int kVjpPairThreads = 1024;
-
-// chunks of a q-ordered pair tile: one for each wave of a 1024-thread workgroup
-constexpr int kPairChunksPerTile = 16;
 
 // The pair's sums over its modes of |g|^2 ah and |g|^2 bh, and per mode
 // dL/d|g|^2 = kb bh - ka ah (gv); empty slots as in pair_mode_sums.
@@ -1335,28 +1339,27 @@ __device__ __forceinline__ void vjp_pair_chunk(const TiledArgs<T> &A, const T *_
 // The reverse pass over a q-ordered tile (see pair_chunk_q): both sides of a
 // pair go to the fixed-point accumulator, -K dl (ah (1 - f_p) + bh f_p) |g|^2
 // summed over modes to the destination and the partner's side as in
-// vjp_pair_chunk; the chunk's row partial is zero.
+// vjp_pair_chunk.
 template <typename T, bool PADQ, int NM, bool TAB>
 __device__ __forceinline__ void vjp_pair_chunk_q(const TiledArgs<T> &A, const Pair2<T> *s_ef,
                                                  const uint32_t *s_kq, const T *s_l, const double *s_tab,
-                                                 unsigned long long *s_j, T scale, int64_t c, T *__restrict__ part,
-                                                 bool want_f, const int32_t *__restrict__ chan,
+                                                 unsigned long long *s_j, T scale, int64_t beg, int len,
+                                                 int wave, int nw, bool want_f, const int32_t *__restrict__ chan,
                                                  const int32_t *__restrict__ chan0, double *__restrict__ gg2,
                                                  int gg2_mode) {
     const int lane = threadIdx.x & 63;
     const int nm = A.nm;
-    const int64_t beg = A.chunk_beg[c];
-    const int len = static_cast<int>(A.chunk_end[c] - beg);
+    const int first = wave * 64, step = nw * 64;
     const uint32_t *__restrict__ pb = A.pnu + beg;
     const T *__restrict__ gb = A.g2 + beg;
     const int32_t *__restrict__ cb = chan + beg;
     const int32_t *__restrict__ cb0 = chan0 + beg;
     // stream one batch ahead, two register sets (see pair_chunk)
-    uint32_t pn0 = pb[lane], pn1 = 0;
-    int32_t h0 = gg2_mode ? cb0[lane] : -1, h1 = -1;
+    uint32_t pn0 = pb[first + lane], pn1 = 0;
+    int32_t h0 = gg2_mode ? cb0[first + lane] : -1, h1 = -1;
     T g0[NM], g1[NM];
 #pragma unroll
-    for (int m = 0; m < NM; ++m) g0[m] = gb[min(m, nm - 1) * A.pld + lane];
+    for (int m = 0; m < NM; ++m) g0[m] = gb[min(m, nm - 1) * A.pld + first + lane];
     auto batch = [&](int r, const uint32_t pn, const T (&g)[NM], const int32_t c0, uint32_t &pn_next,
                      T (&g_next)[NM], int32_t &c0_next) {
         const bool v = r + lane < len;
@@ -1372,10 +1375,10 @@ __device__ __forceinline__ void vjp_pair_chunk_q(const TiledArgs<T> &A, const Pa
 #pragma unroll
         for (int m = 0; m < NM; ++m) w[m] = wq[min(m, nm - 1) * A.tm];
         __builtin_amdgcn_sched_barrier(0);
-        pn_next = pb[r + 64 + lane];
+        pn_next = pb[r + step + lane];
 #pragma unroll
-        for (int m = 0; m < NM; ++m) g_next[m] = gb[min(m, nm - 1) * A.pld + r + 64 + lane];
-        c0_next = gg2_mode ? cb0[r + 64 + lane] : -1;
+        for (int m = 0; m < NM; ++m) g_next[m] = gb[min(m, nm - 1) * A.pld + r + step + lane];
+        c0_next = gg2_mode ? cb0[r + step + lane] : -1;
         __builtin_amdgcn_sched_barrier(0);
         const T fd = efd.b, cfd = T(1) - fd, fp = efp.b, ofp = T(1) - fp;
         const T dl = ld - lp;
@@ -1391,12 +1394,11 @@ __device__ __forceinline__ void vjp_pair_chunk_q(const TiledArgs<T> &A, const Pa
             atomicAdd(s_j + wd, to_fixed(__builtin_rint(-rd * scale)));
         }
     };
-    for (int r = 0; r < len; r += 128) {
+    for (int r = first; r < len; r += 2 * step) {
         batch(r, pn0, g0, h0, pn1, g1, h1);
-        if (r + 64 >= len) break;
-        batch(r + 64, pn1, g1, h1, pn0, g0, h0);
+        if (r + step >= len) break;
+        batch(r + step, pn1, g1, h1, pn0, g0, h0);
     }
-    if (want_f && lane == 0) part[c] = T(0);
 }
 
 template <typename T, bool PADQ, int NM, bool TAB>
@@ -1433,11 +1435,16 @@ __global__ __launch_bounds__(kVjpPairThreads) void k_vjp_pairs(TiledArgs<T> A, c
     __syncthreads();
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
     const int nw = static_cast<int>(blockDim.x >> 6);
-    for (int64_t c = t.c0 + wave; c < t.c1; c += nw) {
-        if (t.lds == 2)
-            vjp_pair_chunk_q<T, PADQ, NM, TAB>(A, s_ef, s_kq, s_l, s_tab, s_j, scale, c, part, want_f != 0, chan,
-                                               chan0, gg2, gg2_mode);
-        else if (t.lds)
+    if (t.lds == 2) {
+        const int64_t beg = A.chunk_beg[t.c0];
+        vjp_pair_chunk_q<T, PADQ, NM, TAB>(A, s_ef, s_kq, s_l, s_tab, s_j, scale, beg,
+                                           static_cast<int>(A.chunk_end[t.c1 - 1] - beg), wave, nw, want_f != 0, chan,
+                                           chan0, gg2, gg2_mode);
+        if (want_f && !A.all_q)
+            for (int64_t c = t.c0 + threadIdx.x; c < t.c1; c += blockDim.x) part[c] = T(0);
+    }
+    for (int64_t c = t.c0 + wave; t.lds != 2 && c < t.c1; c += nw) {
+        if (t.lds)
             vjp_pair_chunk<T, true, PADQ, NM, TAB>(A, f, lam, s_ef, s_kq, s_l, t.p_lo, s_tab, s_j, scale, c, part,
                                                    want_f != 0, chan, chan0, gg2, gg2_mode);
         else
@@ -1461,7 +1468,8 @@ __global__ void k_vjp_pairs_finish(TiledArgs<T> A, const T *__restrict__ part,
     const int d = blockIdx.x * blockDim.x + threadIdx.x;
     if (d >= A.S) return;
     T a = T(0);
-    for (int c = A.dest_chunk[d]; c < A.dest_chunk[d + 1]; ++c) a += part[c];
+    if (!A.all_q)
+        for (int c = A.dest_chunk[d]; c < A.dest_chunk[d + 1]; ++c) a += part[c];
     const long long j = static_cast<long long>(A.jacc[d]);
     A.jacc[d] = 0ull;
     const T jside = static_cast<T>(static_cast<double>(j) * inv);
@@ -1478,10 +1486,11 @@ __global__ void k_sym_finish(TiledArgs<T> A, const T *__restrict__ f, const T *_
     const int d = blockIdx.x * blockDim.x + threadIdx.x;
     if (d >= A.S) return;
     T a = T(0), b = T(0);
-    for (int c = A.dest_chunk[d]; c < A.dest_chunk[d + 1]; ++c) {
-        a += part[2 * c];
-        b += part[2 * c + 1];
-    }
+    if (!A.all_q)
+        for (int c = A.dest_chunk[d]; c < A.dest_chunk[d + 1]; ++c) {
+            a += part[2 * c];
+            b += part[2 * c + 1];
+        }
     const long long j = static_cast<long long>(A.jacc[d]);
     A.jacc[d] = 0ull;
     const T fd = f[d];
@@ -1953,16 +1962,17 @@ __global__ __launch_bounds__(1024) void k_fwd_pairs_pv(TiledArgs<T> A, PvArgs<T>
     const int lane = threadIdx.x & 63;
     const int nm = A.nm;
     const T *__restrict__ tn = V.tab_n + blockIdx.y * V.gstride;
-    for (int64_t c = t.c0 + wave; c < t.c1; c += nw) {
-        const int64_t beg = A.chunk_beg[c];
-        const int len = static_cast<int>(A.chunk_end[c] - beg);
+    {
+        const int64_t beg = A.chunk_beg[t.c0];
+        const int len = static_cast<int>(A.chunk_end[t.c1 - 1] - beg);
+        const int first = wave * 64, step = nw * 64;
         const uint32_t *__restrict__ pb = A.pnu + beg;
         const T *__restrict__ gb = A.g2 + beg;
-        uint32_t pn = pb[lane];
+        uint32_t pn = pb[first + lane];
         T g[NM];
 #pragma unroll
-        for (int m = 0; m < NM; ++m) g[m] = gb[min(m, nm - 1) * A.pld + lane];
-        for (int r = 0; r < len; r += 64) {
+        for (int m = 0; m < NM; ++m) g[m] = gb[min(m, nm - 1) * A.pld + first + lane];
+        for (int r = first; r < len; r += step) {
             const bool on = r + lane < len;
             // a masked lane takes window slot 0 as both states and adds nothing
             const int wd = on ? static_cast<int>(pn & 0xffffu) : 0;
@@ -1984,9 +1994,9 @@ __global__ __launch_bounds__(1024) void k_fwd_pairs_pv(TiledArgs<T> A, PvArgs<T>
                 bb = fma(gm, da, bb);
                 has[m] = gm != T(0);
             }
-            pn = pb[r + 64 + lane];
+            pn = pb[r + step + lane];
 #pragma unroll
-            for (int m = 0; m < NM; ++m) g[m] = gb[min(m, nm - 1) * A.pld + r + 64 + lane];
+            for (int m = 0; m < NM; ++m) g[m] = gb[min(m, nm - 1) * A.pld + r + step + lane];
             const T *__restrict__ nq = tn + static_cast<int64_t>(q) * nm * VB;
             for (int v = 0; v < nv; ++v) {
                 T ns = T(0);
@@ -2071,14 +2081,15 @@ __global__ __launch_bounds__(1024) void k_vjp_pairs_pv(TiledArgs<double> A, PvAr
     const int lane = threadIdx.x & 63;
     const int nm = A.nm;
     const double *__restrict__ tn = V.tab_n + group * V.gstride;
-    for (int64_t c = t.c0 + wave; c < t.c1; c += nw) {
-        const int64_t beg = A.chunk_beg[c];
-        const int len = static_cast<int>(A.chunk_end[c] - beg);
+    {
+        const int64_t beg = A.chunk_beg[t.c0];
+        const int len = static_cast<int>(A.chunk_end[t.c1 - 1] - beg);
+        const int first = wave * 64, step = nw * 64;
         const uint32_t *__restrict__ pb = A.pnu + beg;
         const double *__restrict__ gb = A.g2 + beg;
         const int32_t *__restrict__ cb = chan + beg;
         const int32_t *__restrict__ cb0 = chan0 + beg;
-        for (int r = 0; r < len; r += 64) {
+        for (int r = first; r < len; r += step) {
             const bool on = r + lane < len;
             const uint32_t pn = pb[r + lane];
             const int32_t c0 = gg2_mode ? cb0[r + lane] : -1;
@@ -2184,18 +2195,17 @@ __device__ __forceinline__ int mx_inner(int r, int c) {
 // bound by the store requests as well as by the exponentials.
 template <typename T, bool PADQ, int NM, bool TAB, bool QORD>
 __device__ __forceinline__ void mx_chunk(const TiledArgs<T> &A, const MxArgs<T> &X, const T *s_e,
-                                         const uint32_t *s_kq, const int32_t *s_pos, const double *s_tab, int64_t c) {
+                                         const uint32_t *s_kq, const int32_t *s_pos, const double *s_tab, int64_t c,
+                                         int64_t beg, int len, int first, int step) {
     const int lane = threadIdx.x & 63;
     const int nm = A.nm;
     const int dc = QORD ? 0 : A.chunk_dest[c];
-    const int64_t beg = A.chunk_beg[c];
-    const int len = static_cast<int>(A.chunk_end[c] - beg);
     const uint32_t *__restrict__ pb = A.pnu + beg;
     const T *__restrict__ gb = A.g2 + beg;
-    uint32_t pn0 = pb[lane], pn1 = 0;
+    uint32_t pn0 = pb[first + lane], pn1 = 0;
     T g0[NM], g1[NM];
 #pragma unroll
-    for (int m = 0; m < NM; ++m) g0[m] = gb[min(m, nm - 1) * A.pld + lane];
+    for (int m = 0; m < NM; ++m) g0[m] = gb[min(m, nm - 1) * A.pld + first + lane];
     auto batch = [&](int r, const uint32_t pn, const T (&g)[NM], uint32_t &pn_next, T (&g_next)[NM]) {
         const bool v = r + lane < len;
         T ed, ep;
@@ -2229,9 +2239,9 @@ __device__ __forceinline__ void mx_chunk(const TiledArgs<T> &A, const MxArgs<T> 
         const int bd = xd >> 6, bp = xp >> 6;
         const int id = X.blk[bd * X.nb + bp], it = X.blk[bp * X.nb + bd];
         __builtin_amdgcn_sched_barrier(0);
-        pn_next = pb[r + 64 + lane];
+        pn_next = pb[r + step + lane];
 #pragma unroll
-        for (int m = 0; m < NM; ++m) g_next[m] = gb[min(m, nm - 1) * A.pld + r + 64 + lane];
+        for (int m = 0; m < NM; ++m) g_next[m] = gb[min(m, nm - 1) * A.pld + r + step + lane];
         __builtin_amdgcn_sched_barrier(0);
         T sa, sb;
         pair_mode_sums<T, NM, TAB>(A, ed - ep, w, g, v, s_tab, sa, sb);
@@ -2240,10 +2250,10 @@ __device__ __forceinline__ void mx_chunk(const TiledArgs<T> &A, const MxArgs<T> 
             X.m[static_cast<int64_t>(it) * kMxBlock + mx_inner(xp & 63, xd & 63)] = sa;
         }
     };
-    for (int r = 0; r < len; r += 128) {
+    for (int r = first; r < len; r += 2 * step) {
         batch(r, pn0, g0, pn1, g1);
-        if (r + 64 >= len) break;
-        batch(r + 64, pn1, g1, pn0, g0);
+        if (r + step >= len) break;
+        batch(r + step, pn1, g1, pn0, g0);
     }
 }
 
@@ -2270,10 +2280,15 @@ __global__ __launch_bounds__(1024) void k_pair_matrix(TiledArgs<T> A, MxArgs<T> 
     __syncthreads();
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
     const int nw = static_cast<int>(blockDim.x >> 6);
-    for (int64_t c = t.c0 + wave; c < t.c1; c += nw) {
-        if (t.lds == 2) mx_chunk<T, PADQ, NM, TAB, true>(A, X, s_e, s_kq, s_pos, s_tab, c);
-        else mx_chunk<T, PADQ, NM, TAB, false>(A, X, s_e, s_kq, s_pos, s_tab, c);
+    if (t.lds == 2) {
+        const int64_t beg = A.chunk_beg[t.c0];
+        mx_chunk<T, PADQ, NM, TAB, true>(A, X, s_e, s_kq, s_pos, s_tab, t.c0, beg,
+                                         static_cast<int>(A.chunk_end[t.c1 - 1] - beg), wave * 64, nw * 64);
+        return;
     }
+    for (int64_t c = t.c0 + wave; c < t.c1; c += nw)
+        mx_chunk<T, PADQ, NM, TAB, false>(A, X, s_e, s_kq, s_pos, s_tab, c, A.chunk_beg[c],
+                                          static_cast<int>(A.chunk_end[c] - A.chunk_beg[c]), 0, 64);
 }
 
 // Runs of the stored blocks, one a wave: the first r waves take q + 1 blocks, the
@@ -2947,20 +2962,19 @@ __global__ __launch_bounds__(256) void k_mx_outer_f32(MxArgs<float> X, const flo
 template <typename T, bool PADQ, int NM, bool TAB, bool QORD>
 __device__ __forceinline__ void mx_gg2_chunk(const TiledArgs<T> &A, const MxArgs<T> &X, const T *__restrict__ gm,
                                              const T *s_e, const uint32_t *s_kq, const int32_t *s_pos,
-                                             const double *s_tab, int64_t c,
+                                             const double *s_tab, int64_t c, int64_t beg,
+                                             int len, int first, int step,
                                              const int32_t *__restrict__ chan, const int32_t *__restrict__ chan0,
                                              double *__restrict__ gg2, int gg2_mode) {
     const int lane = threadIdx.x & 63;
     const int nm = A.nm;
     const int dc = QORD ? 0 : A.chunk_dest[c];
-    const int64_t beg = A.chunk_beg[c];
-    const int len = static_cast<int>(A.chunk_end[c] - beg);
     const uint32_t *__restrict__ pb = A.pnu + beg;
     const int32_t *__restrict__ cb = chan + beg;
     const int32_t *__restrict__ cb0 = chan0 + beg;
-    uint32_t pn = pb[lane];
-    int32_t h = cb0[lane];
-    for (int r = 0; r < len; r += 64) {
+    uint32_t pn = pb[first + lane];
+    int32_t h = cb0[first + lane];
+    for (int r = first; r < len; r += step) {
         const bool v = r + lane < len;
         T ed, ep;
         uint32_t kd, kp;
@@ -2996,8 +3010,8 @@ __device__ __forceinline__ void mx_gg2_chunk(const TiledArgs<T> &A, const MxArgs
         for (int m = 0; m < NM; ++m) w[m] = wq[min(m, nm - 1) * A.tm];
         const int32_t c0 = h;
         __builtin_amdgcn_sched_barrier(0);
-        pn = pb[r + 64 + lane];
-        h = cb0[r + 64 + lane];
+        pn = pb[r + step + lane];
+        h = cb0[r + step + lane];
         __builtin_amdgcn_sched_barrier(0);
         const T x = ed - ep;
         double gv[NM];
@@ -3045,12 +3059,17 @@ __global__ __launch_bounds__(1024) void k_mx_gg2(TiledArgs<T> A, MxArgs<T> X, co
     __syncthreads();
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
     const int nw = static_cast<int>(blockDim.x >> 6);
-    for (int64_t c = t.c0 + wave; c < t.c1; c += nw) {
-        if (t.lds == 2)
-            mx_gg2_chunk<T, PADQ, NM, TAB, true>(A, X, gm, s_e, s_kq, s_pos, s_tab, c, chan, chan0, gg2, gg2_mode);
-        else
-            mx_gg2_chunk<T, PADQ, NM, TAB, false>(A, X, gm, s_e, s_kq, s_pos, s_tab, c, chan, chan0, gg2, gg2_mode);
+    if (t.lds == 2) {
+        const int64_t beg = A.chunk_beg[t.c0];
+        mx_gg2_chunk<T, PADQ, NM, TAB, true>(A, X, gm, s_e, s_kq, s_pos, s_tab, t.c0, beg,
+                                             static_cast<int>(A.chunk_end[t.c1 - 1] - beg), wave * 64, nw * 64, chan,
+                                             chan0, gg2, gg2_mode);
+        return;
     }
+    for (int64_t c = t.c0 + wave; c < t.c1; c += nw)
+        mx_gg2_chunk<T, PADQ, NM, TAB, false>(A, X, gm, s_e, s_kq, s_pos, s_tab, c, A.chunk_beg[c],
+                                              static_cast<int>(A.chunk_end[c] - A.chunk_beg[c]), 0, 64, chan, chan0,
+                                              gg2, gg2_mode);
 }
 
 // x by position, three components each
@@ -4049,12 +4068,13 @@ __global__ __launch_bounds__(1024) void k_vjp_phonon_pairs(TiledArgs<T> A, const
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
     const int nw = static_cast<int>(blockDim.x >> 6);
     const int nm = A.nm;
-    for (int64_t c = t.c0 + wave; c < t.c1; c += nw) {
-        const int64_t beg = A.chunk_beg[c];
-        const int len = static_cast<int>(A.chunk_end[c] - beg);
+    {
+        const int64_t beg = A.chunk_beg[t.c0];
+        const int len = static_cast<int>(A.chunk_end[t.c1 - 1] - beg);
+        const int first = wave * 64, step = nw * 64;
         const uint32_t *__restrict__ pb = A.pnu + beg;
         const T *__restrict__ gb = A.g2 + beg;
-        for (int r = 0; r < len; r += 64) {
+        for (int r = first; r < len; r += step) {
             const bool v = r + lane < len;
             const uint32_t pn = pb[r + lane];
             // a masked lane takes window slot 0 as both states and adds nothing

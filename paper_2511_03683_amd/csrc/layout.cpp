@@ -695,13 +695,12 @@ bool build_matrix_layout(int32_t S, const std::vector<int64_t> &row_ptr, const s
 }
 
 PairOrder order_pair_tiles(const ChunkTable &pc, const std::vector<Tile> &tiles,
-                           const std::vector<uint32_t> &partner, const RowKey &rk, int chunks_per_tile,
+                           const std::vector<uint32_t> &partner, const RowKey &rk, int64_t run_records,
                            int64_t max_chunk) {
     PairOrder o;
     const int64_t np = static_cast<int64_t>(partner.size());
     const int64_t nt = static_cast<int64_t>(tiles.size());
     const int32_t S = static_cast<int32_t>(pc.dest_chunk.size()) - 1;
-    if (chunks_per_tile < 1) chunks_per_tile = 1;
     if (max_chunk < 1) max_chunk = 1;
     o.perm.resize(static_cast<size_t>(np));
     o.word.resize(static_cast<size_t>(np));
@@ -714,6 +713,7 @@ PairOrder order_pair_tiles(const ChunkTable &pc, const std::vector<Tile> &tiles,
     // the tiles that go to q order, and their record ranges
     std::vector<int64_t> r0(static_cast<size_t>(nt), 0), r1(static_cast<size_t>(nt), 0);
     std::vector<char> qt(static_cast<size_t>(nt), 0);
+    std::vector<std::vector<int64_t>> runs(static_cast<size_t>(nt));   // run boundaries of the q-ordered tiles
     for (int64_t i = 0; i < nt; ++i) {
         const Tile &t = tiles[i];
         if (t.c1 <= t.c0) continue;
@@ -723,35 +723,56 @@ PairOrder order_pair_tiles(const ChunkTable &pc, const std::vector<Tile> &tiles,
     }
     parallel_ranges(nt, host_threads(), [&](int, int64_t b, int64_t e) {
         std::vector<std::pair<uint64_t, uint32_t>> keys;
+        std::vector<int64_t> at;
         for (int64_t i = b; i < e; ++i) {
             if (!qt[i]) continue;
             const Tile &t = tiles[i];
-            keys.clear();
             bool ok = true;
+            int64_t nd = 0;
             for (int64_t c = t.c0; c < t.c1 && ok; ++c) {
                 const int32_t d = pc.chunk_dest[c];
+                nd += pc.chunk_end[c] > pc.chunk_beg[c];
                 for (int64_t x = pc.chunk_beg[c]; x < pc.chunk_end[c]; ++x) {
                     const int32_t p = static_cast<int32_t>(partner[x]);
                     if (d < t.p_lo || d > t.p_hi || p < t.p_lo || p > t.p_hi) {
                         ok = false;
                         break;
                     }
-                    const uint64_t row = static_cast<uint64_t>(row_of(rk, d, p) >> rk.shift);
-                    keys.emplace_back((row << 32) | (static_cast<uint64_t>(d - t.p_lo) << 16) |
-                                          static_cast<uint64_t>(p - t.p_lo),
-                                      static_cast<uint32_t>(x));
                 }
             }
             if (!ok) {
                 qt[i] = 0;   // window does not hold the destinations: destination order
                 continue;
             }
-            std::sort(keys.begin(), keys.end());
+            // partners per run: the tile's destinations times these are run_records
+            nd = std::max<int64_t>(nd, 1);
+            const int64_t per = kRunPartners * std::max<int64_t>(1, (run_records + nd * kRunPartners - 1) / (nd * kRunPartners));
+            const int64_t ng = (t.p_hi / per) - (t.p_lo / per) + 1;
+            auto run_of = [&](int64_t x) { return static_cast<int64_t>(partner[x]) / per - t.p_lo / per; };
+            at.assign(static_cast<size_t>(ng) + 1, 0);
+            for (int64_t x = r0[i]; x < r1[i]; ++x) ++at[static_cast<size_t>(run_of(x)) + 1];
+            for (int64_t g = 0; g < ng; ++g) at[g + 1] += at[g];
+            std::vector<int64_t> &rb = runs[i];
+            rb.assign(1, 0);
+            for (int64_t g = 0; g < ng; ++g)
+                if (at[g + 1] > rb.back()) rb.push_back(at[g + 1]);
+            keys.resize(static_cast<size_t>(r1[i] - r0[i]));
+            for (int64_t c = t.c0; c < t.c1; ++c) {
+                const int32_t d = pc.chunk_dest[c];
+                for (int64_t x = pc.chunk_beg[c]; x < pc.chunk_end[c]; ++x) {
+                    const int32_t p = static_cast<int32_t>(partner[x]);
+                    const uint64_t row = static_cast<uint64_t>(row_of(rk, d, p) >> rk.shift);
+                    keys[static_cast<size_t>(at[run_of(x)]++)] = {
+                        (row << 32) | (static_cast<uint64_t>(d - t.p_lo) << 16) | static_cast<uint64_t>(p - t.p_lo),
+                        static_cast<uint32_t>(x)};
+                }
+            }
+            for (size_t k = 0; k + 1 < rb.size(); ++k) std::sort(keys.begin() + rb[k], keys.begin() + rb[k + 1]);
             for (size_t j = 0; j < keys.size(); ++j) {
-                const size_t at = static_cast<size_t>(r0[i]) + j;
+                const size_t pos = static_cast<size_t>(r0[i]) + j;
                 const uint64_t k = keys[j].first;
-                o.perm[at] = keys[j].second;
-                o.word[at] = (static_cast<uint32_t>(k & 0xffffu) << 16) | static_cast<uint32_t>((k >> 16) & 0xffffu);
+                o.perm[pos] = keys[j].second;
+                o.word[pos] = (static_cast<uint32_t>(k & 0xffffu) << 16) | static_cast<uint32_t>((k >> 16) & 0xffffu);
             }
         }
     });
@@ -759,33 +780,42 @@ PairOrder order_pair_tiles(const ChunkTable &pc, const std::vector<Tile> &tiles,
     ChunkTable &ct = o.chunks;
     ct.dest_chunk.assign(static_cast<size_t>(S) + 1, 0);
     std::vector<int32_t> new_of_old(static_cast<size_t>(pc.n_chunks), 0);
-    o.tiles = tiles;
     bool any_q = false;
     for (int64_t i = 0; i < nt; ++i) {
-        Tile &t = o.tiles[i];
+        Tile t = tiles[i];
         const int64_t c0 = static_cast<int64_t>(ct.chunk_dest.size());
+        auto push = [&](int64_t beg, int64_t end, int32_t d) {
+            ct.chunk_beg.push_back(beg);
+            ct.chunk_end.push_back(end);
+            ct.chunk_dest.push_back(d);
+        };
         if (qt[i]) {
             any_q = true;
-            const int64_t len = r1[i] - r0[i];
-            const int64_t per = static_cast<int64_t>(chunks_per_tile) * max_chunk;
-            const int64_t k = static_cast<int64_t>(chunks_per_tile) * std::max<int64_t>(1, (len + per - 1) / per);
-            for (int64_t j = 0; j < k; ++j) {
-                ct.chunk_beg.push_back(r0[i] + len * j / k);
-                ct.chunk_end.push_back(r0[i] + len * (j + 1) / k);
-                ct.chunk_dest.push_back(pc.chunk_dest[t.c0]);
+            t.lds = 2;
+            if (runs[i].size() < 2) runs[i].assign(2, 0);   // no records: one empty run
+            for (size_t k = 0; k + 1 < runs[i].size(); ++k) {
+                Tile run = t;
+                run.c0 = static_cast<int64_t>(ct.chunk_dest.size());
+                int64_t x = runs[i][k];
+                do {
+                    const int64_t end = std::min(runs[i][k + 1], x + max_chunk);
+                    push(r0[i] + x, r0[i] + end, pc.chunk_dest[t.c0]);
+                    x = end;
+                } while (x < runs[i][k + 1]);
+                run.c1 = static_cast<int64_t>(ct.chunk_dest.size());
+                o.tiles.push_back(run);
             }
             for (int64_t c = t.c0; c < t.c1; ++c) new_of_old[c] = static_cast<int32_t>(c0);
-            t.lds = 2;
         } else {
             for (int64_t c = t.c0; c < t.c1; ++c) {
                 new_of_old[c] = static_cast<int32_t>(ct.chunk_dest.size());
-                ct.chunk_beg.push_back(pc.chunk_beg[c]);
-                ct.chunk_end.push_back(pc.chunk_end[c]);
-                ct.chunk_dest.push_back(pc.chunk_dest[c]);
+                push(pc.chunk_beg[c], pc.chunk_end[c], pc.chunk_dest[c]);
             }
         }
         t.c0 = c0;
         t.c1 = static_cast<int64_t>(ct.chunk_dest.size());
+        o.groups.push_back(t);
+        if (!qt[i]) o.tiles.push_back(t);
     }
     ct.n_chunks = static_cast<int64_t>(ct.chunk_dest.size());
     for (int32_t d = 0; d < S; ++d) {

@@ -141,29 +141,34 @@ struct RowKey {
 };
 int64_t row_of(const RowKey &k, int32_t d, int32_t p);
 
-// Pair records in q order.  Inside every LDS tile (lds = 1) of the pair
-// pass, the records are sorted by (table row of k_p - k_d >> rk.shift,
-// destination, partner), so that the lanes of a batch read few rows of the
-// {hw, N} table (2^shift neighbouring rows form one group, inside which the
-// records of a destination are consecutive, and so are their channels when
-// the caller lists the channels by state pair),
-// and the tile's records are cut into chunks_per_tile equal chunks (a
-// multiple of it when a chunk would exceed max_chunk records).  The window
-// of such a tile must hold its destinations too (p_lo <= every destination
-// with records).  A record's word is then (partner - p_lo) << 16 |
-// (destination - p_lo); elsewhere it stays the absolute partner.  A tile
-// whose window exceeds 65536 states keeps destination order.  The chunk
-// table is renumbered: destinations of a q-ordered tile own no chunk of
-// their own (their dest_chunk ranges cover only q-ordered chunks, which
-// carry no row partials).
+// Pair records in q order.  The records of every LDS tile (lds = 1) of the pair
+// pass are cut into runs of neighbouring partners (run_records or a little more
+// records each, kRunPartners partners at least), and a run is sorted by (table row
+// of k_p - k_d >> rk.shift, destination, partner): the lanes of a batch read few
+// rows of the {hw, N} table (2^shift neighbouring rows form one group, inside
+// which the records of a destination are consecutive, and so are their channels
+// when the caller lists the channels by state pair), and what a batch writes per
+// pair (a channel's gradient, a pair's matrix entries) lies in a part of the
+// output small enough to stay in L2 until its cache lines are whole.  The window
+// of such a tile must hold its destinations too (p_lo <= every destination with
+// records).  A record's word is then (partner - p_lo) << 16 | (destination -
+// p_lo); elsewhere it stays the absolute partner.  A tile whose window exceeds
+// 65536 states keeps destination order.  The chunk table is renumbered: each run
+// is a chunk (cut further above max_chunk records); destinations of a q-ordered
+// tile own no chunk of their own (their dest_chunk ranges cover only q-ordered
+// chunks, which carry no row partials).
+// 2048: measured best for the passes that write per pair (see pair_chunk_q)
+constexpr int64_t kRunRecords = 2048;
+constexpr int32_t kRunPartners = 64;
 struct PairOrder {
     ChunkTable chunks;
-    std::vector<Tile> tiles;          // c0, c1 renumbered; lds = 2 for q-ordered tiles
+    std::vector<Tile> groups;         // one a workgroup; c0, c1 renumbered; lds = 2 for q-ordered tiles
+    std::vector<Tile> tiles;          // the runs of q-ordered groups (their group's window), the other groups
     std::vector<uint32_t> perm;       // [n_pairs] new position -> record in destination order
     std::vector<uint32_t> word;       // [n_pairs] stream word of the record at that position
 };
 PairOrder order_pair_tiles(const ChunkTable &pc, const std::vector<Tile> &tiles,
-                           const std::vector<uint32_t> &partner, const RowKey &rk, int chunks_per_tile,
+                           const std::vector<uint32_t> &partner, const RowKey &rk, int64_t run_records,
                            int64_t max_chunk);
 
 // Block structure of the pair matrix (the weights of every state pair as a
