@@ -1678,23 +1678,28 @@ void enqueue_vjp(ephbte_plan P, const T *f, const T *lam, const void *nph, const
         T *part = static_cast<T *>(P->sym_part.p);
         const int want_f = E.mode >= 0 ? 1 : 0;
         const dim3 grid(static_cast<unsigned>(P->n_pr_groups)), block(kVjpPairThreads);
-        const size_t shm = vjp_pair_lds_bytes(P->dtype, P->pr_lds_states);
         auto go = [&](auto nmc) {
             constexpr int NM = decltype(nmc)::value;
+            // the channel gradients of a wave's batch pass through LDS where it
+            // has room beside the window (see wave_write_gg2)
+            size_t shm = vjp_pair_lds_bytes(P->dtype, P->pr_lds_states);
+            const size_t st = static_cast<size_t>(kVjpPairThreads) * NM * sizeof(double);
+            const int staged = gg2_mode != 0 && NM > 1 && NM == P->nm && shm + st <= P->lds_max ? 1 : 0;
+            if (staged) shm += st;
             const bool tab = sizeof(T) == 8 && P->exp_table;
             const int32_t *ch = P->pr_chan, *c0 = P->pr_ch0;
             if (P->padq && tab)
                 hipLaunchKernelGGL((k_vjp_pairs<T, true, NM, true>), grid, block, shm, s, a, f, lam, part, want_f, lm,
-                                   ch, c0, gg2, gg2_mode);
+                                   ch, c0, gg2, gg2_mode, staged);
             else if (P->padq)
                 hipLaunchKernelGGL((k_vjp_pairs<T, true, NM, false>), grid, block, shm, s, a, f, lam, part, want_f,
-                                   lm, ch, c0, gg2, gg2_mode);
+                                   lm, ch, c0, gg2, gg2_mode, staged);
             else if (tab)
                 hipLaunchKernelGGL((k_vjp_pairs<T, false, NM, true>), grid, block, shm, s, a, f, lam, part, want_f,
-                                   lm, ch, c0, gg2, gg2_mode);
+                                   lm, ch, c0, gg2, gg2_mode, staged);
             else
                 hipLaunchKernelGGL((k_vjp_pairs<T, false, NM, false>), grid, block, shm, s, a, f, lam, part, want_f,
-                                   lm, ch, c0, gg2, gg2_mode);
+                                   lm, ch, c0, gg2, gg2_mode, staged);
         };
         if (P->nm <= 1) go(std::integral_constant<int, 1>{});
         else if (P->nm <= 2) go(std::integral_constant<int, 2>{});
