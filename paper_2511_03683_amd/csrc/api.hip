@@ -1366,14 +1366,15 @@ size_t pv_lds(ephbte_plan P, int W, int VB, bool vjp) {
 // Vectors a workgroup takes at once, 0: not these passes.  The Gaussians are
 // shared by them, so a window that leaves room for fewer than three keeps the
 // batched pass over entries (on the 100^3 system two fit, 16 ms against 16.6 ms at
-// 64 vectors); below 8 vectors the alternative is one pass each, which one already
-// matches.
+// 64 vectors); below 8 vectors the alternative is a pass each, which two beat
+// (forward of four there: 1.49 ms for 2.33) and one, whose workgroup prepares and
+// reads more than the plain pass, does not (reverse of four: 3.04 for 2.15).
 int pv_vectors(ephbte_plan P, int B, bool vjp) {
     if (!P->pr_ok || !P->pr_all_q || !P->sym_ok || P->n_pr_groups == 0 || P->pr_window < 1) return 0;
     if (P->layout != 3 && B < P->batch_min) return 0;
     int most = 0;
     while (most < 8 && pv_lds(P, P->pr_window, most + 1, vjp) + 1024 <= P->lds_max) ++most;
-    if (most < (B < P->batch_min ? 1 : 3)) return 0;
+    if (most < (B < P->batch_min ? 2 : 3)) return 0;
     const int groups = (B + most - 1) / most;
     return (B + groups - 1) / groups;   // even groups
 }
@@ -3778,7 +3779,14 @@ static ephbte_status autotune_timed(ephbte_plan plan, int32_t batch, ephbte_tuni
             return ms;
         };
         if (batch >= plan->batch_min) {
-            // batched pass: partner sub-tile sizes that fit the LDS of a workgroup
+            // batched pass: partner sub-tile sizes that fit the LDS of a workgroup.
+            // The calls that take it are timed, not those over the pair matrix.
+            struct NoMatrix {
+                ephbte_plan P;
+                bool was;
+                ~NoMatrix() { P->mx_ok = was; }
+            } no_matrix{plan, plan->mx_ok};
+            plan->mx_ok = false;
             const int pt64[] = {48, 64, 96, 128, 160};
             const int pt32[] = {96, 128, 192, 256, 320};
             const int *cand = plan->dtype == EPHBTE_F64 ? pt64 : pt32;
