@@ -1061,10 +1061,11 @@ __device__ __forceinline__ void pair_chunk(const TiledArgs<T> &A, const T *__res
 // tile has no row partials.  The waves take the tile's batches in turn, so that
 // together they sweep its runs: the table rows, the |g|^2 lines and, in the
 // passes that write per pair, the output lines in flight belong to one run.
-// With 100^3 (198 M channels, 2048 records a run) against one sorted range per
-// tile and a part of it per wave: forward 439 us for 466, reverse with channel
-// gradients 1174 for 1227, pair matrix 837 for 940.  Runs of 512 / 8192 / 65536
-// records: reverse 1174 / 1180 / 1196 us, pair matrix 875 / 858 / 900.
+// With 100^3 (198 M channels) against one sorted range per tile and a part of it
+// per wave: forward 466 -> 430 us, reverse with channel gradients 1227 -> 1124,
+// pair matrix 940 -> 756.  Runs of 384 / 768 / 1536 / 4096 / 16384 records:
+// reverse 1124 / 1134 / 1135 / 1146 / 1155 us, pair matrix 756 / 776 / 801 / 832 /
+// 879; the forward pass, which writes nothing per pair, 420 .. 445 without a trend.
 template <typename T, bool PADQ, int NM, bool TAB>
 __device__ __forceinline__ void pair_chunk_q(const TiledArgs<T> &A, const Pair2<T> *s_ef, const uint32_t *s_kq,
                                              const double *s_tab, unsigned long long *s_j, T scale, int64_t beg,

@@ -744,9 +744,8 @@ PairOrder order_pair_tiles(const ChunkTable &pc, const std::vector<Tile> &tiles,
                 qt[i] = 0;   // window does not hold the destinations: destination order
                 continue;
             }
-            // partners per run: the tile's destinations times these are run_records
-            nd = std::max<int64_t>(nd, 1);
-            const int64_t per = kRunPartners * std::max<int64_t>(1, (run_records + nd * kRunPartners - 1) / (nd * kRunPartners));
+            // partners per run: with the tile's destinations these make run_records
+            const int64_t per = std::max(run_records / std::max<int64_t>(nd, 1) / kRunPartners, int64_t(1)) * kRunPartners;
             const int64_t ng = (t.p_hi / per) - (t.p_lo / per) + 1;
             auto run_of = [&](int64_t x) { return static_cast<int64_t>(partner[x]) / per - t.p_lo / per; };
             at.assign(static_cast<size_t>(ng) + 1, 0);

@@ -142,8 +142,8 @@ struct RowKey {
 int64_t row_of(const RowKey &k, int32_t d, int32_t p);
 
 // Pair records in q order.  The records of every LDS tile (lds = 1) of the pair
-// pass are cut into runs of neighbouring partners (run_records or a little more
-// records each, kRunPartners partners at least), and a run is sorted by (table row
+// pass are cut into runs of neighbouring partners (at most run_records
+// records each unless kRunPartners partners have more), and a run is sorted by (table row
 // of k_p - k_d >> rk.shift, destination, partner): the lanes of a batch read few
 // rows of the {hw, N} table (2^shift neighbouring rows form one group, inside
 // which the records of a destination are consecutive, and so are their channels
@@ -157,9 +157,9 @@ int64_t row_of(const RowKey &k, int32_t d, int32_t p);
 // is a chunk (cut further above max_chunk records); destinations of a q-ordered
 // tile own no chunk of their own (their dest_chunk ranges cover only q-ordered
 // chunks, which carry no row partials).
-// 2048: measured best for the passes that write per pair (see pair_chunk_q)
-constexpr int64_t kRunRecords = 2048;
-constexpr int32_t kRunPartners = 64;
+// 384: measured best for the passes that write per pair (see pair_chunk_q)
+constexpr int64_t kRunRecords = 384;
+constexpr int32_t kRunPartners = 16;
 struct PairOrder {
     ChunkTable chunks;
     std::vector<Tile> groups;         // one a workgroup; c0, c1 renumbered; lds = 2 for q-ordered tiles
