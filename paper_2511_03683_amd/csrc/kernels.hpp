@@ -3843,7 +3843,12 @@ __global__ __launch_bounds__(256) void k_phonon_bins(PhArgs<T> A, const T *__res
 // k_phonon_bins.  With gg2, the old values of a batch's channels are loaded
 // before the next batch's stream is issued, so that waiting for them does
 // not wait for the stream; each channel has one slot, so nothing else writes
-// it in between.  A lane past the chunk's end, or a slot without a channel,
+// it in between.  Where the channels of every record of a batch are consecutive
+// they are read and written in channel order, the values passing through LDS
+// (see wave_write_gg2).  Bound by that and by the few waves in flight (207 VGPRs
+// in FP64 at six modes, two waves a SIMD; three waves by launch bounds spill:
+// 237 us).  1.9 M records, six modes, FP64: 148 us, 198 with a lane per record
+// and the mode constants in registers (276, one wave).  A lane past the chunk's end, or a slot without a channel,
 // loads a valid address and stores nothing.
 template <typename T, int NM>
 __global__ __launch_bounds__(256) void k_phonon_bins_adj(PhArgs<T> A, const T *__restrict__ f,
@@ -3851,6 +3856,8 @@ __global__ __launch_bounds__(256) void k_phonon_bins_adj(PhArgs<T> A, const T *_
                                                          const T *__restrict__ mu, T *__restrict__ part,
                                                          double *__restrict__ gg2, double Ke) {
     __shared__ double s_tab[kExpTab];
+    __shared__ double s_g[4][64 * NM];
+    __shared__ T s_k[4][6 * NM];
     if constexpr (sizeof(T) == 8)
         for (int i = threadIdx.x; i < kExpTab; i += blockDim.x) s_tab[i] = A.e2tab[i];
     __syncthreads();
@@ -3858,6 +3865,7 @@ __global__ __launch_bounds__(256) void k_phonon_bins_adj(PhArgs<T> A, const T *_
     const int64_t c = static_cast<int64_t>(blockIdx.x) * (blockDim.x >> 6) +
                       __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
     if (c >= A.n_chunks) return;
+    double *s_w = s_g[threadIdx.x >> 6];
     const int nm = A.nm;
     const int bk = A.chunk_bucket[c];
     const int64_t qc = A.bucket_q[bk], qm = A.bucket_qm[bk];
@@ -3865,23 +3873,29 @@ __global__ __launch_bounds__(256) void k_phonon_bins_adj(PhArgs<T> A, const T *_
     const uint32_t phon = mu ? modes & ~A.elastic : 0u;
     const bool want_g = gg2 != nullptr && phon != 0u;
     const T ke = static_cast<T>(Ke), kp = static_cast<T>(A.Kp);
-    T w1[NM], n1[NM], w2[NM], n2[NM], m1[NM], m2[NM], acc1[NM], acc2[NM];
-    bool same = true;   // hw(-qc) = hw(qc) for every mode of the bucket
-#pragma unroll
-    for (int m = 0; m < NM; ++m) {
-        const int mm = min(m, nm - 1);
-        const bool on = m < nm && ((modes >> m) & 1u);
-        const bool ph = m < nm && ((phon >> m) & 1u);
-        w1[m] = on ? A.hw[qc * nm + mm] : T(0);
-        w2[m] = on ? A.hw[qm * nm + mm] : T(0);
-        n1[m] = ph ? nph[qc * nm + mm] : T(0);
-        n2[m] = ph ? nph[qm * nm + mm] : T(0);
-        m1[m] = ph ? mu[qc * nm + mm] : T(0);
-        m2[m] = ph ? mu[qm * nm + mm] : T(0);
-        same = same && w2[m] == w1[m];
-        acc1[m] = T(0);
-        acc2[m] = T(0);
+    // per mode hw(qc), hw(-qc), mu and N of both: the wave's, kept in LDS (in
+    // registers they cost 72 VGPRs in FP64 at six modes, and with them all but one
+    // wave of a SIMD)
+    T *s_c = s_k[threadIdx.x >> 6];
+    bool other = false;   // hw(-qc) != hw(qc) for a mode of the bucket
+    if (lane < NM) {
+        const int mm = min(lane, nm - 1);
+        const bool on = lane < nm && ((modes >> lane) & 1u);
+        const bool ph = lane < nm && ((phon >> lane) & 1u);
+        const T wa = on ? A.hw[qc * nm + mm] : T(0), wb = on ? A.hw[qm * nm + mm] : T(0);
+        s_c[6 * lane] = wa;
+        s_c[6 * lane + 1] = wb;
+        s_c[6 * lane + 2] = ph ? mu[qc * nm + mm] : T(0);
+        s_c[6 * lane + 3] = ph ? mu[qm * nm + mm] : T(0);
+        s_c[6 * lane + 4] = ph ? nph[qc * nm + mm] : T(0);
+        s_c[6 * lane + 5] = ph ? nph[qm * nm + mm] : T(0);
+        other = wb != wa;
     }
+    const bool same = __ballot(other) == 0;
+    wave_lds_sync();
+    T acc1[NM], acc2[NM];
+#pragma unroll
+    for (int m = 0; m < NM; ++m) acc1[m] = acc2[m] = T(0);
     const int64_t beg = A.chunk_beg[c];
     const int n = static_cast<int>(A.chunk_beg[c + 1] - beg);
     auto rec = [&](int r) { return beg + min(r + lane, n - 1); };
@@ -3900,9 +3914,24 @@ __global__ __launch_bounds__(256) void k_phonon_bins_adj(PhArgs<T> A, const T *_
         const T la = lam ? lam[a] : T(0), lb = lam ? lam[b] : T(0);
         const T x = A.st[a].eps - A.st[b].eps;
         double old[NM];
+        bool seq = false;
+        const int32_t cv = v ? h[0] : -1;
         if (want_g) {
+            bool own = nm == NM && h[0] >= 0;
 #pragma unroll
-            for (int m = 0; m < NM; ++m) old[m] = gg2[h[m] >= 0 ? h[m] : 0];
+            for (int m = 1; m < NM; ++m) own = own && h[m] == h[0] + m;
+            seq = NM > 1 && __ballot(v && !own) == 0;
+            if (seq) {
+#pragma unroll
+                for (int j = 0; j < NM; ++j) {
+                    const int u = j * 64 + lane, rec = u / NM;
+                    const int32_t ch = __shfl(cv, rec, 64);
+                    old[j] = gg2[ch >= 0 ? ch + (u - rec * NM) : 0];
+                }
+            } else {
+#pragma unroll
+                for (int m = 0; m < NM; ++m) old[m] = gg2[h[m] >= 0 ? h[m] : 0];
+            }
         }
         __builtin_amdgcn_sched_barrier(0);
         const int64_t xi = rec(r + 64);
@@ -3920,18 +3949,33 @@ __global__ __launch_bounds__(256) void k_phonon_bins_adj(PhArgs<T> A, const T *_
         for (int m = 0; m < NM; ++m) {
             const bool on = v && m < nm && ((modes >> m) & 1u);
             const T gm = keep_or_zero(g[m], on);
-            const T gq1 = ph_gauss(A, x + w1[m], s_tab);
-            const T e1 = ph_gauss(A, x - w1[m], s_tab);
+            const T *k = s_c + 6 * m;
+            const T w1 = k[0], w2 = k[1], m1 = k[2], m2 = k[3];
+            const T gq1 = ph_gauss(A, x + w1, s_tab);
+            const T e1 = ph_gauss(A, x - w1, s_tab);
             T gq2 = gq1, e2 = e1;
             if (!same) {
-                gq2 = ph_gauss(A, x + w2[m], s_tab);
-                e2 = ph_gauss(A, x - w2[m], s_tab);
+                gq2 = ph_gauss(A, x + w2, s_tab);
+                e2 = ph_gauss(A, x - w2, s_tab);
             }
-            acc1[m] += gm * dp * (ke * la * (gq1 + e1) + kp * m1[m] * gq1);
-            acc2[m] -= gm * dp * (ke * lb * (gq2 + e2) + kp * m2[m] * e2);
-            if (want_g && on && ((phon >> m) & 1u) && h[m] >= 0)
-                gg2[h[m]] = old[m] + static_cast<double>(kp * (m1[m] * gq1 * (p1 + n1[m] * dp) +
-                                                                m2[m] * e2 * (p2 - n2[m] * dp)));
+            acc1[m] += gm * dp * (ke * la * (gq1 + e1) + kp * m1 * gq1);
+            acc2[m] -= gm * dp * (ke * lb * (gq2 + e2) + kp * m2 * e2);
+            if (want_g) {
+                const double dg = static_cast<double>(kp * (m1 * gq1 * (p1 + k[4] * dp) +
+                                                            m2 * e2 * (p2 - k[5] * dp)));
+                if (seq) s_w[lane * NM + m] = dg;
+                else if (on && ((phon >> m) & 1u) && h[m] >= 0) gg2[h[m]] = old[m] + dg;
+            }
+        }
+        if (seq) {
+            wave_lds_sync();
+#pragma unroll
+            for (int j = 0; j < NM; ++j) {
+                const int u = j * 64 + lane, rec = u / NM, m = u - rec * NM;
+                const int32_t ch = __shfl(cv, rec, 64);
+                if (ch >= 0 && ((phon >> m) & 1u)) gg2[ch + m] = old[j] + s_w[u];
+            }
+            wave_lds_sync();
         }
     };
     for (int r = 0; r < n; r += 128) {

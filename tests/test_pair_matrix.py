@@ -208,3 +208,33 @@ def test_bath_per_vector_over_pair_records(E, S, B, modes, dtype, stats):
     assert nerr(host(gg), rg) <= TOL[dtype]
     assert nerr(host(ga) - 0.5, rg) <= TOL[dtype]
     plan.close()
+
+
+@pytest.mark.parametrize("n_modes", [1, 2, 3, 5, 6, 8])
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+def test_channel_gradients_in_any_channel_order(E, dtype, n_modes):
+    """Gradients of records whose channels follow each other (written in channel
+    order by the wave) against the same channels shuffled (written by the lane):
+    the same products, added to one old value, so they differ by a rounding of the
+    FP64 sum at most.  The 37 states leave a remainder in every batch."""
+    s = rounded(full_system(37, 4, n_modes=n_modes, seed=21), dtype)
+    perm = np.random.default_rng(22).permutation(s.n_channels)
+    t = copy.copy(s)
+    for k in ("ch_i", "ch_j", "ch_nu", "g2"):
+        setattr(t, k, getattr(s, k)[perm])
+    rng = np.random.default_rng(23)
+    f, lam = rng.uniform(0.1, 0.9, s.n_states), rng.normal(size=s.n_states)
+    N, mu = s.nph(300.0), rng.normal(size=s.hw.shape)
+    out = []
+    for x in (s, t):
+        plan = E.build_channels(x, dtype=dtype, device=0)
+        a = torch.full((x.n_channels,), 0.25, dtype=torch.float64, device="cuda:0")
+        b = a.clone()
+        c = a.clone()
+        E.collision_vjp(plan, dev(f, dtype), dev(N, dtype), dev(lam, dtype), gg2=a)
+        E.collision_vjp(plan, dev(f, dtype), dev(N, dtype), dev(lam, dtype), gg2=b, accumulate=True)
+        E.phonon_rate_vjp(plan, dev(f, dtype), dev(N, dtype), dev(mu, dtype), gg2=c, accumulate=True)
+        out.append([host(v) for v in (a, b, c)])
+    for got, ref in zip(*out):
+        assert nerr(ref, got[perm]) <= 4e-16
+    assert nerr(out[0][1] - 0.25, out[0][0]) <= 4e-16 * (1 + 0.25 / np.abs(out[0][0]).max())
