@@ -232,17 +232,22 @@ ephbte_status ephbte_layout_host(const ephbte_problem *problem, const ephbte_bui
  * f:   device [B][ldf], plan dtype, 0 <= f <= 1 expected (not checked).
  * nph: device, plan dtype, phonon occupations N.  nph_per_batch == 0: one
  *      table [Nq][n_modes] shared by every vector (one (alpha, beta) per
- *      entry serves the whole batch).  nph_per_batch != 0: B tables
- *      [B][Nq][n_modes], vector b with its own bath; the vectors are then
- *      evaluated one after another, each a single-vector pass.
+ *      entry serves the whole batch; from B = 2 on, where the plan has the
+ *      pair matrix, the coefficients are formed once per state pair and call
+ *      and applied as a matrix).  nph_per_batch != 0: B tables
+ *      [B][Nq][n_modes], vector b with its own bath; in FP64 over q-ordered
+ *      pair records the Gaussians of a pair serve up to eight vectors.
  * I:   device [B][ldi], plan dtype, written.  I must not alias f.
  * B >= 1; ldf, ldi >= S.
  * Reductions: with B = 1 and the single-copy layout every channel is read
  * once; the partner side is summed in 64-bit fixed point with integer
  * atomics (associative, so the result is bitwise reproducible), and so is the
  * row side over pair records in q order (pair_order 1); otherwise the row
- * side is summed in registers in a fixed order.  Other forms reduce each
- * destination's entries with no atomics.
+ * side is summed in registers in a fixed order.  Vectors with a bath each over
+ * pair records use the same fixed point; the pair matrix sums in FP64 in a
+ * fixed order, and a sum that is not finite is formed again over the row's own
+ * partners, so that a non-finite occupation reaches its partners only.  Other
+ * forms reduce each destination's entries with no atomics.
  */
 ephbte_status ephbte_collision_integral(ephbte_plan plan, int32_t batch, const void *f,
                                         int64_t ldf, const void *nph, int32_t nph_per_batch,
@@ -388,8 +393,9 @@ ephbte_status ephbte_set_field(ephbte_plan plan, const double rate[3]);
  * Real-time BTE, df/dt = I[f] (Eq. 1; with the field term when
  * ephbte_set_field has set one): advances f
  * (device [B][ldf], in place) by n_steps classical RK4 steps of dt_fs.  The
- * stage updates are fused into the collision kernels (four launches per
- * step).  use_graph != 0 captures the step sequence in a HIP graph on the
+ * stage updates are fused into the collision kernels; with B = 1, no field
+ * and the pair matrix, the coefficients of the bath are formed once per call
+ * and each stage is a matrix-vector product.  use_graph != 0 captures the step sequence in a HIP graph on the
  * first call and replays it (the graph is cached per (f, nph, dt, B, stream)).
  */
 ephbte_status ephbte_rt_step(ephbte_plan plan, int32_t batch, void *f, int64_t ldf,
@@ -444,7 +450,8 @@ ephbte_status ephbte_set_tuning(ephbte_plan plan, const ephbte_tuning *tuning);
  * HIP events and keep the fastest; writes the chosen tuning to *chosen (may be
  * NULL).  For batch < 8 the candidates are chunk sizes x block sizes of the
  * single-vector kernel; for batch >= 8, partner sub-tile sizes of the batched
- * kernel.  Allocates and frees its own half-filled occupations.  Synchronous.
+ * kernel (in plans with the pair matrix, the calls that do not take it).
+ * Allocates and frees its own half-filled occupations.  Synchronous.
  * cache_path (may be NULL): a JSON file mapping a key (device architecture and
  * compute-unit count, dtype, states, entries, modes, q grid, single or
  * batched) to the tuning chosen for it.  An entry for this plan is applied
@@ -456,7 +463,8 @@ ephbte_status ephbte_autotune(ephbte_plan plan, int32_t batch, ephbte_tuning *ch
 
 /* Launch timing of the forward pass's main kernel, for measurement (not a
  * step of the method): the single-copy kernel at B = 1, the per-row kernel for
- * B = 2 .. 7 (or layout 1) and the batched kernel for B >= 8.
+ * B = 2 .. 7 (or layout 1) and the batched kernel for B >= 8, where the call
+ * uses them (not over the pair matrix).
  * mode 1: clears the record and starts it; every eager launch of that kernel
  *   on this plan is then bracketed by two HIP events recorded on its launch
  *   stream (launches under graph capture are not timed; at most 4096 launches

@@ -1190,7 +1190,7 @@ size_t mx_gemm_lds(int NC) { return 2 * 64 * static_cast<size_t>(NC + 4) * sizeo
 
 // Whether B vectors go through the pair matrix.  Its coefficients are evaluated
 // once per pair (as in the single-vector pass) and applied on the matrix cores:
-// on the 100^3 system in FP64 1.5 ms at B = 64 against 3.9 ms for the pass over
+// on the 100^3 system in FP64 1.22 ms at B = 64 against 3.9 ms for the pass over
 // entries; below 8 vectors, against one pass per vector.  Below 8 the tuning's
 // layout chooses, as for one vector.
 bool mx_batch_fits(ephbte_plan P, int B) {
@@ -2143,7 +2143,7 @@ void rk4_enqueue_step(ephbte_plan P, int B, T *f, int64_t ldf, const void *nph, 
 // One RK4 step of a single vector over the pair matrix, whose bath holds for the
 // whole call: per stage one pass over the matrix (half a pair record's bytes per
 // pair with one mode, a sixth with six, and no exponentials) and its finish.  On
-// the 100^3 system in FP32 a stage takes 0.07 ms against 0.28 ms for the pass
+// the 100^3 system in FP32 a stage takes 0.053 ms against 0.28 ms for the pass
 // over pair records.  u holds the stage input by position ({f, 1 - f}, two
 // copies that alternate: four stages end where they began).
 template <typename T>
