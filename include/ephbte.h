@@ -393,7 +393,7 @@ ephbte_status ephbte_set_field(ephbte_plan plan, const double rate[3]);
  * Real-time BTE, df/dt = I[f] (Eq. 1; with the field term when
  * ephbte_set_field has set one): advances f
  * (device [B][ldf], in place) by n_steps classical RK4 steps of dt_fs.  The
- * stage updates are fused into the collision kernels; with B = 1, no field
+ * stage updates are fused into the collision kernels; with B = 1
  * and the pair matrix, the coefficients of the bath are formed once per call
  * and each stage is a matrix-vector product.  use_graph != 0 captures the step sequence in a HIP graph on the
  * first call and replays it (the graph is cached per (f, nph, dt, B, stream)).
