@@ -3737,6 +3737,10 @@ template <typename T> struct PhArgs {
     const int32_t *__restrict__ chan;   // [n_modes][ld] caller channel of each slot, -1: none
 };
 
+// a b + c rounded once, in the type of its arguments
+__device__ __forceinline__ float fused(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fused(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
 template <typename T>
 __device__ __forceinline__ T ph_gauss(const PhArgs<T> &A, T x, const double *tab) {
     if constexpr (sizeof(T) == 8) return gauss_exp2_tab(x * x * A.mc256, tab);
@@ -3850,6 +3854,12 @@ __global__ __launch_bounds__(256) void k_phonon_bins(PhArgs<T> A, const T *__res
 // 237 us).  1.9 M records, six modes, FP64: 148 us, 198 with a lane per record
 // and the mode constants in registers (276, one wave).  A lane past the chunk's end, or a slot without a channel,
 // loads a valid address and stores nothing.
+// Which products are fused into an addition is written out: dL/d|g|^2 is an FP64
+// output in FP32 plans too, and the choice, left to the compiler, moved it by FP32
+// roundings (4e-9 of its norm over a coupled adjoint) when the constants went to
+// LDS.  It is the one that the build with the constants in registers made: in a
+// bin's term the sum of the Gaussians is the fused factor in the even batches of
+// more than one mode slot, the channel's mu elsewhere.
 template <typename T, int NM>
 __global__ __launch_bounds__(256) void k_phonon_bins_adj(PhArgs<T> A, const T *__restrict__ f,
                                                          const T *__restrict__ nph, const T *__restrict__ lam,
@@ -3907,8 +3917,12 @@ __global__ __launch_bounds__(256) void k_phonon_bins_adj(PhArgs<T> A, const T *_
         g0[m] = A.g2[min(m, nm - 1) * A.ld + rec(0)];
         h0[m] = want_g ? A.chan[min(m, nm - 1) * A.ld + rec(0)] : -1;
     }
-    auto batch = [&](int r, const uint32_t a, const uint32_t b, const T (&g)[NM], const int32_t (&h)[NM],
+    auto batch = [&](auto oddc, int r, const uint32_t a, const uint32_t b, const T (&g)[NM], const int32_t (&h)[NM],
                      uint32_t &an, uint32_t &bn, T (&gn)[NM], int32_t (&hn)[NM]) {
+        // a b + c d (which product is fused: see above)
+        auto term = [](T a, T b, T c, T d) {
+            return NM == 1 || decltype(oddc)::value ? fused(c, d, a * b) : fused(a, b, c * d);
+        };
         const bool v = r + lane < n;
         const T fa = f[a], fb = f[b];
         const T la = lam ? lam[a] : T(0), lb = lam ? lam[b] : T(0);
@@ -3943,8 +3957,8 @@ __global__ __launch_bounds__(256) void k_phonon_bins_adj(PhArgs<T> A, const T *_
             hn[m] = want_g ? A.chan[min(m, nm - 1) * A.ld + xi] : -1;
         }
         __builtin_amdgcn_sched_barrier(0);
-        const T p1 = fb * (T(1) - fa), p2 = fa * (T(1) - fb);
-        const T dp = p1 - p2;   // = f_b - f_a
+        const T ofa = T(1) - fa, p1 = fb * ofa, p2 = fa * (T(1) - fb);
+        const T dp = fused(fb, ofa, -p2);   // = f_b - f_a
 #pragma unroll
         for (int m = 0; m < NM; ++m) {
             const bool on = v && m < nm && ((modes >> m) & 1u);
@@ -3958,11 +3972,12 @@ __global__ __launch_bounds__(256) void k_phonon_bins_adj(PhArgs<T> A, const T *_
                 gq2 = ph_gauss(A, x + w2, s_tab);
                 e2 = ph_gauss(A, x - w2, s_tab);
             }
-            acc1[m] += gm * dp * (ke * la * (gq1 + e1) + kp * m1 * gq1);
-            acc2[m] -= gm * dp * (ke * lb * (gq2 + e2) + kp * m2 * e2);
+            const T gd = gm * dp;
+            acc1[m] = fused(gd, term(ke * la, gq1 + e1, kp * m1, gq1), acc1[m]);
+            acc2[m] = fused(-gd, term(ke * lb, gq2 + e2, kp * m2, e2), acc2[m]);
             if (want_g) {
-                const double dg = static_cast<double>(kp * (m1 * gq1 * (p1 + k[4] * dp) +
-                                                            m2 * e2 * (p2 - k[5] * dp)));
+                const T c2 = m2 * e2 * fused(-k[5], dp, p2);
+                const double dg = static_cast<double>(kp * fused(m1 * gq1, fused(k[4], dp, p1), c2));
                 if (seq) s_w[lane * NM + m] = dg;
                 else if (on && ((phon >> m) & 1u) && h[m] >= 0) gg2[h[m]] = old[m] + dg;
             }
@@ -3979,9 +3994,9 @@ __global__ __launch_bounds__(256) void k_phonon_bins_adj(PhArgs<T> A, const T *_
         }
     };
     for (int r = 0; r < n; r += 128) {
-        batch(r, a0, b0, g0, h0, a1, b1, g1, h1);
+        batch(std::false_type{}, r, a0, b0, g0, h0, a1, b1, g1, h1);
         if (r + 64 >= n) break;
-        batch(r + 64, a1, b1, g1, h1, a0, b0, g0, h0);
+        batch(std::true_type{}, r + 64, a1, b1, g1, h1, a0, b0, g0, h0);
     }
 #pragma unroll
     for (int m = 0; m < NM; ++m) {
@@ -4133,7 +4148,8 @@ __global__ void k_vjp_phonon_f_finish(TiledArgs<T> A, const T *__restrict__ part
 // (max |mu| in place of max |lambda|), flushed to the global accumulator;
 // k_vjp_phonon_pairs_finish adds them to out.  A slot without a channel (or
 // of an elastic mode) is masked after its product, since its N may be
-// infinite (acoustic modes at q = 0).
+// infinite (acoustic modes at q = 0).  Fused products are written out, as in
+// k_phonon_bins_adj, whose input lam these sums lead to.
 template <typename T, bool PADQ, int NM>
 __global__ __launch_bounds__(1024) void k_vjp_phonon_pairs(TiledArgs<T> A, const Vec4<T> *__restrict__ tab,
                                                           const T *__restrict__ f, uint32_t elastic,
@@ -4198,8 +4214,8 @@ __global__ __launch_bounds__(1024) void k_vjp_phonon_pairs(TiledArgs<T> A, const
                 const T ga = stream_gauss(A, (x + t1.x) * (x + t1.x), s_tab);
                 const T ge = stream_gauss(A, (x - t2.x) * (x - t2.x), s_tab);
                 const T a1 = t1.z * ga, a2 = t2.z * ge;
-                sd += keep_or_zero(g * (a2 * (t2.y + T(1) - fp) - a1 * (t1.y + fp)), on);
-                sp += keep_or_zero(g * (a1 * (t1.y + T(1) - fd) - a2 * (t2.y + fd)), on);
+                sd += keep_or_zero(g * fused(a2, t2.y + T(1) - fp, -(a1 * (t1.y + fp))), on);
+                sp += keep_or_zero(g * fused(a1, t1.y + T(1) - fd, -(a2 * (t2.y + fd))), on);
             }
             if (v) {
                 atomicAdd(s_j + wd, to_fixed(__builtin_rint(sd * scale)));

@@ -387,6 +387,35 @@ int main(int argc, char **argv) {
         std::vector<double> gg(static_cast<size_t>(nch));
         hipMemcpy(gg.data(), dgg, 8 * static_cast<size_t>(nch), hipMemcpyDeviceToHost);
         wr("out_gg2.bin", gg);   // accumulated onto 0.25
+    } else if (mode == "phonon_adj") {
+        // the phonon side's reverse kernel by itself, both loss gradients set;
+        // with the record and bucket of each chunk, for a term-by-term check
+        auto f = rd<double>("f.bin", static_cast<size_t>(S));
+        auto lam = rd<double>("lam.bin", static_cast<size_t>(S));
+        auto mu = rd<double>("mu.bin", nqm);
+        void *df = dv.up(f), *dl = dv.up(lam), *dm = dv.up(mu), *dgN = dv.alloc(nqm);
+        double *dgg = nullptr;
+        hipMalloc(reinterpret_cast<void **>(&dgg), 8 * static_cast<size_t>(nch));
+        std::memset(dgg, 0, 8 * static_cast<size_t>(nch));
+        ensure_phonon(plan);
+        auto go = [&](auto tag) {
+            using T = decltype(tag);
+            enqueue_phonon_adj<T>(plan, static_cast<T *>(df), static_cast<T *>(dN), static_cast<T *>(dl),
+                                  static_cast<T *>(dm), static_cast<T *>(dgN), dgg, nullptr);
+        };
+        if (f32) go(float{});
+        else go(double{});
+        wr("out_gN.bin", dv.down(dgN, nqm));
+        wr("out_gg2.bin", std::vector<double>(dgg, dgg + nch));
+        std::vector<double> rec;   // per chunk: records, bucket q, bucket -q, first record's states
+        for (int64_t c = 0; c < plan->ph_nchunks; ++c) {
+            const int64_t r = plan->ph_chunk_beg[c];
+            const int bk = plan->ph_chunk_bucket[c];
+            for (double v : {double(plan->ph_chunk_beg[c + 1] - r), double(plan->ph_bucket_q[bk]),
+                             double(plan->ph_bucket_qm[bk]), double(plan->ph_pa[r]), double(plan->ph_pb[r])})
+                rec.push_back(v);
+        }
+        wr("out_rec.bin", rec);
     } else if (mode == "coupled_adjoint") {
         const double dt = meta("dt");
         const int n = static_cast<int>(meta("steps"));
