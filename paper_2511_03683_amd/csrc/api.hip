@@ -2740,9 +2740,15 @@ ephbte_status transport_impl(ephbte_plan P, const T *f0, const T *vel, double T_
     const int64_t S = P->S;
     // over the pair matrix an iteration reads one value per ordered pair of
     // states, without it one W and one partner word per entry and mode: on the
-    // 100^3 system 0.53 against 4.8 GB
-    if (use_pairs(P, 1)) ensure_fwd<T>(P, 1);   // the {hw, N} table
-    const bool mx = use_pairs(P, 1) && mx_ensure<T>(P, 3);
+    // 100^3 system 0.53 against 4.8 GB.  FP64 plans only: the mobility is an FP64
+    // output of FP32 plans too, and the matrix, which rounds the sum of a pair's
+    // modes once and sums in FP64, moves it by up to 1e-7.
+    constexpr bool kF64 = sizeof(T) == 8;
+    bool mx = false;
+    if constexpr (kF64) {
+        if (use_pairs(P, 1)) ensure_fwd<T>(P, 1);   // the {hw, N} table
+        mx = use_pairs(P, 1) && mx_ensure<T>(P, 3);
+    }
     if (!mx) ensure(P->tr_W, sizeof(T) * (P->E + kEntryPad), &P->ws_gen);
     ensure(P->tr_tau_inv, sizeof(T) * S, &P->ws_gen);
     ensure(P->tr_tau, sizeof(T) * S, &P->ws_gen);
@@ -2767,17 +2773,20 @@ ephbte_status transport_impl(ephbte_plan P, const T *f0, const T *vel, double T_
     const double K = k_prefactor(P);
     double *ux = static_cast<double *>(P->mx_u.p);
     const double *p1 = static_cast<const double *>(P->mx_p1.p), *p2 = static_cast<const double *>(P->mx_p2.p);
-    if (mx) {
-        enqueue_pack<T>(P, nph, s);
-        enqueue_pair_matrix<T>(P, s);
-        hipLaunchKernelGGL((k_mx_load<T>), mg, dim3(256), 0, s, mx_args<T>(P), f0, ux, ux + np);
-        enqueue_mx_vec<T, 1>(P, ux, ux + np, false, s);
-        hipLaunchKernelGGL((k_mx_tau_finish<T>), mr, dim3(64 * kMxParts), 0, s, tiled_args<T>(P), mx_args<T>(P), p1,
-                           mx_runs(P, 1), p2, K, (const double *)ux, (const double *)(ux + np), tinv);
-    } else if (P->fused)
+    if constexpr (kF64) {
+        if (mx) {
+            enqueue_pack<T>(P, nph, s);
+            enqueue_pair_matrix<T>(P, s);
+            hipLaunchKernelGGL((k_mx_load<T>), mg, dim3(256), 0, s, mx_args<T>(P), f0, ux, ux + np);
+            enqueue_mx_vec<T, 1>(P, ux, ux + np, false, s);
+            hipLaunchKernelGGL(k_mx_tau_finish, mr, dim3(64 * kMxParts), 0, s, tiled_args<T>(P), mx_args<T>(P), p1,
+                               mx_runs(P, 1), p2, K, (const double *)ux, (const double *)(ux + np), tinv);
+        }
+    }
+    if (!mx && P->fused)
         hipLaunchKernelGGL((k_transport_setup<T, true>), grid, block, 0, s, t, f0, W, (T *)nullptr,
                            tinv);
-    else {
+    else if (!mx) {
         hipLaunchKernelGGL((k_transport_setup<T, false>), grid, block, 0, s, t, f0, W,
                            reinterpret_cast<T *>(part), tinv);
         hipLaunchKernelGGL((k_transport_setup_finish<T>), sg, dim3(256), 0, s, t,
@@ -2786,7 +2795,8 @@ ephbte_status transport_impl(ephbte_plan P, const T *f0, const T *vel, double T_
     hipLaunchKernelGGL((k_transport_prep<T>), sg, dim3(256), 0, s, f0, vel, (const T *)tinv,
                        static_cast<T>(1.0 / (kKb * T_K)), (int)S, tau, rhs, xa);
     double *ua = ux, *ub = ux ? ux + 3 * np : nullptr;   // x by position, two copies
-    if (mx) hipLaunchKernelGGL((k_mx_load3<T>), mg, dim3(256), 0, s, mx_args<T>(P), (const Vec4<T> *)xa, ua);
+    if constexpr (kF64)
+        if (mx) hipLaunchKernelGGL(k_mx_load3, mg, dim3(256), 0, s, mx_args<T>(P), (const Vec4<T> *)xa, ua);
     HIPC(hipGetLastError());
     auto mobility = [&](const Vec4<T> *x, bool with_f0, double out[10]) {
         hipLaunchKernelGGL((k_mobility_partial<T>), dim3(kRedBlocks), dim3(256), 0, s, vel, x,
@@ -2809,12 +2819,16 @@ ephbte_status transport_impl(ephbte_plan P, const T *f0, const T *vel, double T_
     int it = 0, since_best = 0;
     bool conv = false, stalled = false;
     for (it = 1; it <= max_iter; ++it) {
-        if (mx) {
-            enqueue_mx_vec<T, 3>(P, ua, ua, (it & 1) != 0, s);
-            hipLaunchKernelGGL((k_mx_tr_finish<T>), mr, dim3(64 * kMxParts), 0, s, tiled_args<T>(P), mx_args<T>(P), p1,
-                               mx_runs(P, 3), p2, K, f0, (const Vec4<T> *)rhs, (const T *)tau, (const double *)ua, ub, xb);
-            std::swap(ua, ub);
-        } else {
+        if constexpr (kF64) {
+            if (mx) {
+                enqueue_mx_vec<T, 3>(P, ua, ua, (it & 1) != 0, s);
+                hipLaunchKernelGGL(k_mx_tr_finish, mr, dim3(64 * kMxParts), 0, s, tiled_args<T>(P), mx_args<T>(P), p1,
+                                   mx_runs(P, 3), p2, K, f0, (const Vec4<T> *)rhs, (const T *)tau, (const double *)ua,
+                                   ub, xb);
+                std::swap(ua, ub);
+            }
+        }
+        if (!mx) {
             TiledArgs<T> ta = tiled_args<T>(P);
             ta.xcd = 0;
             // half-size tiles: measured 3 % faster than the forward's here

@@ -2593,19 +2593,20 @@ __global__ __launch_bounds__(64 * kMxParts) void k_mx_rk_finish(TiledArgs<T> A, 
 }
 
 // 1 / tau_d = K (o1 + o2) with u1 = f0, u2 = 1 - f0
-template <typename T>
-__global__ __launch_bounds__(64 * kMxParts) void k_mx_tau_finish(TiledArgs<T> A, MxArgs<T> X, const double *__restrict__ part1,
-                                                       MxRuns N, const double *__restrict__ part2, double K,
-                                                       const double *__restrict__ u1, const double *__restrict__ u2,
-                                                       T *__restrict__ tau_inv) {
+__global__ __launch_bounds__(64 * kMxParts) void k_mx_tau_finish(TiledArgs<double> A, MxArgs<double> X,
+                                                                 const double *__restrict__ part1, MxRuns N,
+                                                                 const double *__restrict__ part2, double K,
+                                                                 const double *__restrict__ u1,
+                                                                 const double *__restrict__ u2,
+                                                                 double *__restrict__ tau_inv) {
     double o1[1], o2[1];
-    mx_vec_sums<T, 1>(X, part1, N, part2, blockIdx.x, o1, o2);
+    mx_vec_sums<double, 1>(X, part1, N, part2, blockIdx.x, o1, o2);
     if (threadIdx.x >= 64) return;
     const int x = blockIdx.x * 64 + threadIdx.x;
     const int d = X.state[x];
     if (d < 0) return;
-    if (!mx_finite(o1[0], o2[0])) mx_own_sums<T>(A, X, d, u1, u2, 1, 0, o1[0], o2[0]);
-    tau_inv[d] = static_cast<T>(K * (o1[0] + o2[0]));
+    if (!mx_finite(o1[0], o2[0])) mx_own_sums<double>(A, X, d, u1, u2, 1, 0, o1[0], o2[0]);
+    tau_inv[d] = K * (o1[0] + o2[0]);
 }
 
 // Block row and share of this workgroup: workgroups go round-robin to the 8 XCDs;
@@ -3126,29 +3127,30 @@ __global__ __launch_bounds__(1024) void k_mx_gg2(TiledArgs<T> A, MxArgs<T> X, co
 }
 
 // x by position, three components each
-template <typename T>
-__global__ void k_mx_load3(MxArgs<T> X, const Vec4<T> *__restrict__ x, double *__restrict__ u) {
+__global__ void k_mx_load3(MxArgs<double> X, const Vec4<double> *__restrict__ x, double *__restrict__ u) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= X.nb * 64) return;
     const int d = X.state[i];
-    Vec4<T> v;
-    v.x = v.y = v.z = T(0);
+    Vec4<double> v;
+    v.x = v.y = v.z = 0.0;
     if (d >= 0) v = x[d];
-    u[3 * i] = static_cast<double>(v.x);
-    u[3 * i + 1] = static_cast<double>(v.y);
-    u[3 * i + 2] = static_cast<double>(v.z);
+    u[3 * i] = v.x;
+    u[3 * i + 1] = v.y;
+    u[3 * i + 2] = v.z;
 }
 
 // x_new_d = tau_d (rhs_d + K [(1 - f0_d) o1 + f0_d o2]); u holds x by position
 // and the next iterate goes to un.
-template <typename T>
-__global__ __launch_bounds__(64 * kMxParts) void k_mx_tr_finish(TiledArgs<T> A, MxArgs<T> X, const double *__restrict__ part1,
-                                                      MxRuns N, const double *__restrict__ part2, double K,
-                                                      const T *__restrict__ f0, const Vec4<T> *__restrict__ rhs,
-                                                      const T *__restrict__ tau, const double *__restrict__ u,
-                                                      double *__restrict__ un, Vec4<T> *__restrict__ x_new) {
+__global__ __launch_bounds__(64 * kMxParts) void k_mx_tr_finish(TiledArgs<double> A, MxArgs<double> X,
+                                                                const double *__restrict__ part1, MxRuns N,
+                                                                const double *__restrict__ part2, double K,
+                                                                const double *__restrict__ f0,
+                                                                const Vec4<double> *__restrict__ rhs,
+                                                                const double *__restrict__ tau,
+                                                                const double *__restrict__ u, double *__restrict__ un,
+                                                                Vec4<double> *__restrict__ x_new) {
     double o1[3], o2[3];
-    mx_vec_sums<T, 3>(X, part1, N, part2, blockIdx.x, o1, o2);
+    mx_vec_sums<double, 3>(X, part1, N, part2, blockIdx.x, o1, o2);
     if (threadIdx.x >= 64) return;
     const int x = blockIdx.x * 64 + threadIdx.x;
     const int d = X.state[x];
@@ -3156,21 +3158,21 @@ __global__ __launch_bounds__(64 * kMxParts) void k_mx_tr_finish(TiledArgs<T> A, 
         un[3 * x] = un[3 * x + 1] = un[3 * x + 2] = 0.0;
         return;
     }
-    const double f = static_cast<double>(f0[d]), t = static_cast<double>(tau[d]);
-    const Vec4<T> r = rhs[d];
-    const double rr[3] = {static_cast<double>(r.x), static_cast<double>(r.y), static_cast<double>(r.z)};
-    T y[3];
+    const double f = f0[d], t = tau[d];
+    const Vec4<double> r = rhs[d];
+    const double rr[3] = {r.x, r.y, r.z};
+    double y[3];
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-        if (!mx_finite(o1[k], o2[k])) mx_own_sums<T>(A, X, d, u, u, 3, k, o1[k], o2[k]);
-        y[k] = static_cast<T>(t * (rr[k] + K * ((1.0 - f) * o1[k] + f * o2[k])));
-        un[3 * x + k] = static_cast<double>(y[k]);
+        if (!mx_finite(o1[k], o2[k])) mx_own_sums<double>(A, X, d, u, u, 3, k, o1[k], o2[k]);
+        y[k] = t * (rr[k] + K * ((1.0 - f) * o1[k] + f * o2[k]));
+        un[3 * x + k] = y[k];
     }
-    Vec4<T> o;
+    Vec4<double> o;
     o.x = y[0];
     o.y = y[1];
     o.z = y[2];
-    o.w = T(0);
+    o.w = 0.0;
     x_new[d] = o;
 }
 
