@@ -71,6 +71,7 @@ struct GraphEntry {
     double dt;
     hipStream_t stream;
     int64_t ws_gen;
+    bool mx;   // the steps go over the pair matrix, formed outside the graph
     hipGraphExec_t exec;
 };
 
@@ -1188,17 +1189,74 @@ unsigned mx_row_grid(ephbte_plan P, int nsplit) {
 
 size_t mx_gemm_lds(int NC) { return 2 * 64 * static_cast<size_t>(NC + 4) * sizeof(double); }
 
-// Whether B vectors go through the pair matrix.  Its coefficients are evaluated
-// once per pair (as in the single-vector pass) and applied on the matrix cores:
-// on the 100^3 system in FP64 1.22 ms at B = 64 against 3.9 ms for the pass over
-// entries; below 8 vectors, against one pass per vector.  Below 8 the tuning's
-// layout chooses, as for one vector.
+// ---- where the pair matrix pays ------------------------------------------------
+// Forming the matrix costs more than one pass over the pair records (it writes two
+// values per pair), and a product reads every stored value, also those of a block
+// without a pair.  Few modes, few products and blocks that an energy selection left
+// sparse favour the passes without it.  The estimates below, in microseconds with
+// pairs, mode slots, channels and stored values in millions, are fits to calls timed
+// both ways on 62^3 and 88^3 systems (1.4 and 11.7 M pairs, 1 to 6 modes, every pair or
+// a window of 3, 5 or 8 sigma); at the edges, without the matrix against with it:
+//   2 vectors, 11.7 M pairs: 1 mode 180 against 240 us, 2 modes 326 against 255;
+//   3 vectors, 3.8 M pairs in 23 M values, 1 mode: 153 against 171;
+//   20 RK4 stages, FP64: 2 modes, 3.6 M pairs 1008 against 1064, 4.7 M 1128 against
+//   1083; 1 mode, 5.4 M 970 against 1078, 11.7 M 1381 against 1143;
+//   reverse pass, FP64, 1 mode, 4 vectors: 3.8 M pairs 314 against 398, 11.7 M 614
+//   against 466.
+struct MxSize {
+    double np, slots, ch, v;   // ch: channels
+    int m;
+    bool f64, part;   // part: some records have empty slots
+};
+MxSize mx_size(ephbte_plan P) {
+    MxSize z;
+    z.np = 1e-6 * static_cast<double>(P->pr_np);
+    z.slots = z.np * P->nm;
+    z.v = 1e-6 * static_cast<double>(P->mx_blocks) * kMxBlock;
+    z.ch = 0.5e-6 * static_cast<double>(P->E);
+    z.m = P->nm;
+    z.f64 = P->dtype == EPHBTE_F64;
+    z.part = z.ch < 0.95 * z.slots;
+    return z;
+}
+double mx_fill_us(const MxSize &z) { return z.np * (z.f64 ? 7.2 + 1.8 * z.m : 1.7 + 1.5 * z.m); }
+// I of B vectors; the matrix, formed once, serves `products` such calls
+bool mx_pays_batch(ephbte_plan P, int B, double products) {
+    if (B >= P->batch_min) return true;   // against the pass over entries: 1.2 against 3.9 ms (100^3, B = 64)
+    const MxSize z = mx_size(P);
+    const double with = 42.0 + (z.f64 ? 4.1 : 2.4) * z.v + mx_fill_us(z) / products;
+    const double small = std::min(z.np, 1.0);   // a pass that does not fill the device costs less
+    return with < 27.0 + B * (z.f64 ? 5.0 + 8.0 * small + 7.0 * z.ch : 2.3 + 3.2 * small + 3.5 * z.ch);
+}
+// The reverse pass of 2 .. 7 vectors.  FP64: both gradients, whichever are asked for,
+// so that dL/df does not depend on that; gradients of records with empty slots cost
+// 2.8 times as much a record from one vector's pass, twice as much from G.  FP32:
+// dL/df alone (enqueue_vjp_mx keeps dL/d|g|^2 to one vector at a time there).
+bool mx_pays_vjp(ephbte_plan P, int B) {
+    if (B >= P->batch_min) return true;
+    const MxSize z = mx_size(P);
+    if (!z.f64)
+        return 45.0 + 3.2 * z.v + (4.5 + 1.3 * z.m) * z.np < 25.0 + B * (8.0 + (2.5 + 1.1 * z.m) * z.np);
+    return 40.0 + 13.0 * z.v + (1.0 + 7.3 * z.m) * (z.part ? 2.0 : 1.0) * z.np <
+           25.0 + B * (10.0 + (2.5 + 5.2 * z.m) * (z.part ? 2.8 : 1.0) * z.np);
+}
+// RK4 steps of one vector (4 n_steps products)
+bool mx_pays_rt(ephbte_plan P, double n_steps) {
+    const MxSize z = mx_size(P);
+    const double with = 12.0 + (z.f64 ? 1.7 : 0.85) * z.v;
+    const double without = z.f64 ? 30.0 + (0.6 + 2.25 * z.m) * z.np : 25.0 + (0.6 + 1.2 * z.m) * z.np;
+    return 4.0 * n_steps * (without - with) > mx_fill_us(z);
+}
+
+// Whether B vectors can go through the pair matrix.  Below 8 the tuning's layout
+// chooses, as for one vector.
 bool mx_batch_fits(ephbte_plan P, int B) {
     return P->mx_ok && B >= 2 && P->pr_ok && P->n_pr_groups > 0 && (B >= P->batch_min || P->layout == 3) &&
            mx_gemm_lds(mx_columns(B)) <= P->lds_max;
 }
-template <typename T> bool mx_ensure_batch(ephbte_plan P, int B) {
-    if (!mx_batch_fits(P, B)) return false;
+// The workspaces of I for B vectors over the matrix, where it pays
+template <typename T> bool mx_ensure_batch(ephbte_plan P, int B, double products) {
+    if (!mx_batch_fits(P, B) || !mx_pays_batch(P, B, products)) return false;
     const size_t cells = static_cast<size_t>(P->mx_nb) * 64 * mx_columns(B) * sizeof(double);
     try {
         ensure_zeroed(P, P->mx_m, sizeof(T) * static_cast<size_t>(P->mx_blocks) * kMxBlock);
@@ -1210,8 +1268,8 @@ template <typename T> bool mx_ensure_batch(ephbte_plan P, int B) {
     return true;
 }
 // true once mx_ensure_batch found the memory
-template <typename T> bool use_mx_batch(ephbte_plan P, int B) {
-    if (!mx_batch_fits(P, B)) return false;
+template <typename T> bool use_mx_batch(ephbte_plan P, int B, double products) {
+    if (!mx_batch_fits(P, B) || !mx_pays_batch(P, B, products)) return false;
     const size_t cells = static_cast<size_t>(P->mx_nb) * 64 * mx_columns(B) * sizeof(double);
     return P->mx_m.bytes >= sizeof(T) * static_cast<size_t>(P->mx_blocks) * kMxBlock && P->mx_u.bytes >= 2 * cells &&
            P->mx_p1.bytes >= 2 * cells * mx_gemm_split(P);
@@ -1301,6 +1359,7 @@ bool enqueue_vjp_mx(ephbte_plan P, int B, const T *f, int64_t ldf, const T *lam,
     const size_t outer_lds = 64 * static_cast<size_t>(2 * Vm + 4) * sizeof(double);
     if (!mx_batch_fits(P, B) || outer_lds > P->lds_max || mx_gemm_lds(64) > P->lds_max) return false;
     if (kF32 && gg2_mode && B < P->batch_min) return false;
+    if (!mx_pays_vjp(P, B)) return false;
     const size_t cells = static_cast<size_t>(P->mx_nb) * 64 * 2 * Vm;
     const size_t mat = sizeof(T) * static_cast<size_t>(P->mx_blocks) * kMxBlock;
     try {
@@ -1512,17 +1571,18 @@ bool enqueue_vjp_pv(ephbte_plan P, int B, const double *f, int64_t ldf, const do
 // Enqueue I[f] for B vectors with epilogue E (no allocation inside; the
 // caller ensured P->part and P->hwN are large enough).  pack = false when the
 // {hw, N} table (and, for B vectors over it, the pair matrix) already holds this
-// call's occupations; ready: a Bose plan's max |f| is there too.
+// call's occupations; ready: a Bose plan's max |f| is there too; products: calls that
+// one pair matrix serves (as ensure_fwd was told).
 
 template <typename T>
 void enqueue_forward(ephbte_plan P, int B, const T *f, int64_t ldf, const void *nph,
-                     const Epi<T> &E, hipStream_t s, bool pack = true, bool ready = false) {
+                     const Epi<T> &E, hipStream_t s, bool pack = true, bool ready = false, double products = 1.0) {
     // the single-copy passes of a Bose plan set their fixed-point scale from max |f|
     const bool fm = !ready && P->boson && (use_pairs(P, B) || use_sym(P, B));
     if (pack || fm)
         enqueue_prep<T>(P, pack ? pack_part<T>(P, nph) : PackPart<T>{},
                         fm ? vec_part<T>(P, kMaxF, f, nullptr, P->S) : VecPart<T>{}, VecPart<T>{}, s);
-    if (use_mx_batch<T>(P, B)) {
+    if (use_mx_batch<T>(P, B, products)) {
         if (pack) enqueue_pair_matrix<T>(P, s);
         enqueue_forward_mx<T>(P, B, f, ldf, E, s);
         return;
@@ -1585,8 +1645,8 @@ void enqueue_forward(ephbte_plan P, int B, const T *f, int64_t ldf, const void *
     HIPC(hipGetLastError());
 }
 
-template <typename T> void ensure_fwd(ephbte_plan P, int B) {
-    (void)mx_ensure_batch<T>(P, B);
+template <typename T> void ensure_fwd(ephbte_plan P, int B, double products = 1.0) {
+    (void)mx_ensure_batch<T>(P, B, products);
     if (!P->fused) ensure(P->part, sizeof(T) * 2 * static_cast<size_t>(P->n_chunks) * B, &P->ws_gen);
     if (use_sym(P, B))
         ensure(P->sym_part, sizeof(T) * 2 * static_cast<size_t>(std::max<int64_t>(P->n_sym_chunks, 1)),
@@ -2112,7 +2172,7 @@ template <typename T> void with_drift(ephbte_plan P, Epi<T> &e, const T *x, int6
 template <typename T>
 void rk4_enqueue_step(ephbte_plan P, int B, T *f, int64_t ldf, const void *nph, T dt,
                       hipStream_t s, T *ua, T *ub, T *acc, const T *f_in, int64_t ld_in,
-                      T *f_out) {
+                      T *f_out, double products = 1.0) {
     // stage inputs: u1 = f_in, u2 -> ua, u3 -> ub, u4 -> ua; f_out = f_in + dt/6 (...)
     (void)f;
     (void)ldf;
@@ -2125,19 +2185,19 @@ void rk4_enqueue_step(ephbte_plan P, int B, T *f, int64_t ldf, const void *nph, 
     e.mode = EPI_RK1;
     e.u_out = ua;
     with_drift<T>(P, e, f_in, ld_in, T(1));
-    enqueue_forward<T>(P, B, f_in, ld_in, nph, e, s, false);
+    enqueue_forward<T>(P, B, f_in, ld_in, nph, e, s, false, false, products);
     e.mode = EPI_RK2;
     e.u_out = ub;
     with_drift<T>(P, e, ua, S, T(1));
-    enqueue_forward<T>(P, B, ua, S, nph, e, s, false);
+    enqueue_forward<T>(P, B, ua, S, nph, e, s, false, false, products);
     e.mode = EPI_RK3;
     e.u_out = ua;
     with_drift<T>(P, e, ub, S, T(1));
-    enqueue_forward<T>(P, B, ub, S, nph, e, s, false);
+    enqueue_forward<T>(P, B, ub, S, nph, e, s, false, false, products);
     e.mode = EPI_RK4;
     e.f_out = f_out;
     with_drift<T>(P, e, ua, S, T(1));
-    enqueue_forward<T>(P, B, ua, S, nph, e, s, false);
+    enqueue_forward<T>(P, B, ua, S, nph, e, s, false, false, products);
 }
 
 // One RK4 step of a single vector over the pair matrix, whose bath holds for the
@@ -2185,14 +2245,16 @@ ephbte_status rt_step_impl(ephbte_plan P, int B, T *f, int64_t ldf, const void *
     ensure(P->rk_ua, vec, &P->ws_gen);
     ensure(P->rk_ub, vec, &P->ws_gen);
     ensure(P->rk_acc, vec, &P->ws_gen);
-    ensure_fwd<T>(P, B);
+    const double products = 4.0 * n_steps;
+    ensure_fwd<T>(P, B, products);
     T *ua = static_cast<T *>(P->rk_ua.p), *ub = static_cast<T *>(P->rk_ub.p);
     T *acc = static_cast<T *>(P->rk_acc.p);
     const T tdt = static_cast<T>(dt);
     enqueue_pack<T>(P, nph, s);   // the phonon occupations hold for the whole call
-    // one vector over the pair matrix: its coefficients are evaluated once
-    if (n_steps > 0 && use_mx_batch<T>(P, B)) enqueue_pair_matrix<T>(P, s);
-    const bool mx = n_steps > 0 && use_pairs(P, B) && mx_ensure<T>(P, 1);
+    // over the pair matrix its coefficients are evaluated once
+    const bool mx_b = n_steps > 0 && use_mx_batch<T>(P, B, products);
+    if (mx_b) enqueue_pair_matrix<T>(P, s);
+    const bool mx = n_steps > 0 && use_pairs(P, B) && mx_pays_rt(P, n_steps) && mx_ensure<T>(P, 1);
     if (mx) {
         enqueue_pair_matrix<T>(P, s);
         double *u = static_cast<double *>(P->mx_u.p);
@@ -2202,7 +2264,7 @@ ephbte_status rt_step_impl(ephbte_plan P, int B, T *f, int64_t ldf, const void *
     }
     auto step = [&](hipStream_t st) {
         if (mx) mx_rk4_step<T>(P, f, tdt, st, ua, ub, acc);
-        else rk4_enqueue_step<T>(P, B, f, ldf, nph, tdt, st, ua, ub, acc, f, ldf, f);
+        else rk4_enqueue_step<T>(P, B, f, ldf, nph, tdt, st, ua, ub, acc, f, ldf, f, products);
     };
     if (!use_graph || n_steps < 2) {
         for (int k = 0; k < n_steps; ++k) step(s);
@@ -2221,7 +2283,7 @@ ephbte_status rt_step_impl(ephbte_plan P, int B, T *f, int64_t ldf, const void *
     hipGraphExec_t exec = nullptr;
     for (auto &g : P->graphs)
         if (g.f == f && g.nph == nph && g.ldf == ldf && g.B == B && g.steps == K && g.dt == dt &&
-            g.stream == cs && g.ws_gen == P->ws_gen)
+            g.stream == cs && g.ws_gen == P->ws_gen && g.mx == (mx || mx_b))
             exec = g.exec;
     if (!exec) {
         hipGraph_t graph = nullptr;
@@ -2242,7 +2304,7 @@ ephbte_status rt_step_impl(ephbte_plan P, int B, T *f, int64_t ldf, const void *
             (void)hipGraphExecDestroy(P->graphs.front().exec);
             P->graphs.erase(P->graphs.begin());
         }
-        P->graphs.push_back(GraphEntry{f, nph, ldf, B, K, dt, cs, P->ws_gen, exec});
+        P->graphs.push_back(GraphEntry{f, nph, ldf, B, K, dt, cs, P->ws_gen, mx || mx_b, exec});
     }
     int done = 0;
     for (; done + K <= n_steps; done += K) HIPC(hipGraphLaunch(exec, cs));
@@ -2742,12 +2804,22 @@ ephbte_status transport_impl(ephbte_plan P, const T *f0, const T *vel, double T_
     // states, without it one W and one partner word per entry and mode: on the
     // 100^3 system 0.53 against 4.8 GB.  FP64 plans only: the mobility is an FP64
     // output of FP32 plans too, and the matrix, which rounds the sum of a pair's
-    // modes once and sums in FP64, moves it by up to 1e-7.
+    // modes once and sums in FP64, moves it by up to 1e-7.  On systems of fewer than
+    // 2048 states and 2 M entries the two are a few launches each and the matrix's
+    // take longer (8^3 k points, every pair, 3 modes: 575 against 468 us a solve; 44^3,
+    // 1704 states, 6 modes, 2.2 M entries 1731 against 2076), and blocks with few
+    // pairs cost more than the entries they save (88^3, 1 mode, window of 8 sigma,
+    // 10.8 M entries in 23 M values: 1340 against 1254; 3 modes, 3 sigma, 21 M: 1152
+    // against 1268).
     constexpr bool kF64 = sizeof(T) == 8;
     bool mx = false;
     if constexpr (kF64) {
-        if (use_pairs(P, 1)) ensure_fwd<T>(P, 1);   // the {hw, N} table
-        mx = use_pairs(P, 1) && mx_ensure<T>(P, 3);
+        const MxSize z = mx_size(P);
+        const bool pays = (P->S >= 2048 || 2.0 * z.slots >= 2.0) && 2.0 * z.slots + 2.0 >= 0.7 * z.v;
+        if (use_pairs(P, 1) && pays) {
+            ensure_fwd<T>(P, 1);   // the {hw, N} table
+            mx = mx_ensure<T>(P, 3);
+        }
     }
     if (!mx) ensure(P->tr_W, sizeof(T) * (P->E + kEntryPad), &P->ws_gen);
     ensure(P->tr_tau_inv, sizeof(T) * S, &P->ws_gen);

@@ -1,0 +1,103 @@
+"""Where calls go over the pair matrix: its workspace tells (the matrix is most of
+it), and results on both sides of the rule are the oracle's (tolerances as in
+test_pair_matrix: 1e-10 FP64, 1e-5 FP32, normwise)."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import oracle  # noqa: E402
+from test_pair_matrix import TOL, cast, dev, full_system, gross, host, nerr, rounded  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def E():
+    assert torch.cuda.is_available(), "GPU tests need a HIP device"
+    import paper_2511_03683_amd as lib
+    return lib
+
+
+def matrix_bytes(s, dtype):
+    nb = (s.n_states + 63) // 64
+    return nb * nb * 4096 * (8 if dtype == "f64" else 4)
+
+
+# pairs 180 k; few modes and vectors: one pass a vector is cheaper than forming it
+@pytest.mark.parametrize("dtype,modes,B,matrix", [("f64", 1, 2, False), ("f64", 6, 2, True), ("f64", 1, 7, True),
+                                                  ("f32", 1, 2, False), ("f32", 1, 3, False), ("f32", 6, 6, True),
+                                                  ("f32", 1, 8, True)])
+def test_few_vectors(E, dtype, modes, B, matrix):
+    s = full_system(600, 9, n_modes=modes)
+    rng = np.random.default_rng(B)
+    F, nph = cast(rng.uniform(size=(B, 600)), dtype), cast(s.nph(300.0), dtype)
+    plan = E.build_channels(s, dtype=dtype, device=0)
+    E.collision_integral(plan, dev(F[0], dtype), dev(nph, dtype))
+    b0 = E.plan_info(plan)["bytes"]
+    got = host(E.collision_integral(plan, dev(F, dtype), dev(nph, dtype)))
+    assert (E.plan_info(plan)["bytes"] - b0 >= matrix_bytes(s, dtype)) == matrix
+    r = rounded(s, dtype)
+    for b in (0, B - 1):
+        assert nerr(got[b], oracle.collision(r, F[b], nph), gross(r, F[b], nph)) <= TOL[dtype]
+    plan.close()
+
+
+# every pair of 600 states, and 2 of 5 pairs of 1200 states: the product reads their
+# 1.5 M values for 0.29 M pairs
+@pytest.mark.parametrize("S,share,B,matrix", [(600, 1.0, 2, True), (600, 1.0, 7, True), (1200, 0.4, 2, False),
+                                              (1200, 0.4, 7, True)])
+def test_few_vectors_reverse(E, S, share, B, matrix):
+    s = full_system(S, 9 if S == 600 else 11, n_modes=2)
+    rng = np.random.default_rng(B)
+    keep = np.repeat(rng.uniform(size=s.n_channels // 2) < share, 2)
+    s.ch_i, s.ch_j, s.ch_nu, s.g2 = s.ch_i[keep], s.ch_j[keep], s.ch_nu[keep], s.g2[keep]
+    F, lam, nph = rng.uniform(size=(B, S)), rng.normal(size=(B, S)), s.nph(300.0)
+    plan = E.build_channels(s, device=0)
+    gg = torch.empty(s.n_channels, dtype=torch.float64, device="cuda:0")
+    E.collision_vjp(plan, dev(F[0]), dev(nph), dev(lam[0]), gg2=gg)
+    b0 = E.plan_info(plan)["bytes"]
+    gf, gg = E.collision_vjp(plan, dev(F), dev(nph), dev(lam), gg2=gg)
+    grown = E.plan_info(plan)["bytes"] - b0
+    assert (grown >= matrix_bytes(s, "f64")) == matrix, grown
+    refs = [oracle.collision_vjp(s, F[b], nph, lam[b]) for b in range(B)]
+    assert nerr(host(gf)[B - 1], refs[B - 1][0]) <= 1e-10
+    assert nerr(host(gg), sum(x[1] for x in refs)) <= 1e-10
+    plan.close()
+
+
+def islands(n_islands, per, kn, n_modes):
+    """Components of `per` states each (all pairs), interleaved in the caller's order."""
+    s = full_system(2, kn, n_modes=n_modes)
+    S = n_islands * per
+    rng = np.random.default_rng(8)
+    s.state_k = rng.choice(kn ** 3, size=S, replace=False).astype(np.int32)
+    s.state_band = np.zeros(S, np.int8)
+    s.eps = rng.uniform(0.0, 0.3, S)
+    a, b = np.triu_indices(per, 1)
+    i = (a[None, :] * n_islands + np.arange(n_islands)[:, None]).ravel()
+    j = (b[None, :] * n_islands + np.arange(n_islands)[:, None]).ravel()
+    s.ch_i = np.repeat(i, n_modes).astype(np.int32)
+    s.ch_j = np.repeat(j, n_modes).astype(np.int32)
+    s.ch_nu = np.tile(np.arange(n_modes), i.size).astype(np.int8)
+    s.g2 = rng.uniform(1e-4, 2e-3, s.ch_i.size)
+    return s
+
+
+@pytest.mark.parametrize("n_islands,matrix", [(30, True), (20, False)])
+def test_transport(E, n_islands, matrix):
+    """2100 states take the matrix, 1400 the entries."""
+    s = islands(n_islands, 70, 13, 3)
+    S = s.n_states
+    rng = np.random.default_rng(9)
+    f0, vel, nph = rng.uniform(0.05, 0.4, S), rng.normal(size=(S, 3)), s.nph(300.0)
+    plan = E.build_channels(s, device=0)
+    E.collision_integral(plan, dev(f0), dev(nph))
+    b0 = E.plan_info(plan)["bytes"]
+    out = E.iterate_transport(plan, dev(f0), dev(vel), 300.0, dev(nph), tol=0.0, max_iter=4, want_x=True)
+    grown = E.plan_info(plan)["bytes"] - b0
+    assert (grown >= 30 * 4096 * 8 * 4) == matrix, grown     # at least 4 blocks an island
+    want = oracle.transport_solve(s, f0, vel, 300.0, nph, max_iter=4, stop_on_tol=False)
+    assert nerr(out["mu"], want["mu"]) <= 1e-10
+    assert nerr(host(out["x"]), want["x"]) <= 1e-10
+    plan.close()
