@@ -2105,9 +2105,10 @@ __global__ __launch_bounds__(1024) void k_vjp_pairs_pv(TiledArgs<double> A, PvAr
     const int W = A.lds_states, VB = V.vb, b0 = group * VB;
     const int nv = min(VB, V.B - b0);
     double *s_tab = reinterpret_cast<double *>(smem);
-    unsigned long long *s_j = reinterpret_cast<unsigned long long *>(s_tab + kExpTab);
-    Pair2<double> *s_fl = reinterpret_cast<Pair2<double> *>(s_j + VB * W);
-    double *s_e = reinterpret_cast<double *>(s_fl + VB * W);
+    // {f, lam} first: 16-byte values, and W and VB may both be odd
+    Pair2<double> *s_fl = reinterpret_cast<Pair2<double> *>(s_tab + kExpTab);
+    unsigned long long *s_j = reinterpret_cast<unsigned long long *>(s_fl + VB * W);
+    double *s_e = reinterpret_cast<double *>(s_j + VB * W);
     uint32_t *s_kq = reinterpret_cast<uint32_t *>(s_e + W);
     const int n = t.p_hi - t.p_lo + 1;
     for (int i = threadIdx.x; i < n; i += blockDim.x) {
