@@ -1448,7 +1448,7 @@ bool pv_prepare(ephbte_plan P, int B, int VB, const T *f, int64_t ldf, const T *
     const size_t row = static_cast<size_t>(P->S) * B;
     try {
         ensure(P->pv_n, sizeof(T) * static_cast<size_t>(groups) * rows * P->nm * VB, &P->ws_gen);
-        ensure_zeroed(P, P->pv_j, sizeof(unsigned long long) * row);
+        ensure_zeroed(P, P->pv_j, (sizeof(unsigned long long) + sizeof(uint32_t)) * row);
         ensure(P->pv_max, sizeof(double) * 3 * 64 * B, &P->ws_gen);
         if (P->boson) {
             ensure(P->bs_x, sizeof(T) * row, &P->ws_gen);
@@ -1486,11 +1486,11 @@ bool pv_prepare(ephbte_plan P, int B, int VB, const T *f, int64_t ldf, const T *
     V.B = B;
     V.vb = VB;
     V.n_list = nb;
-    V.bose = P->boson ? 1 : 0;
     V.nmax = p.nmax;
     V.fmax = p.fmax;
     V.lmax = p.lmax;
     V.jacc = static_cast<unsigned long long *>(P->pv_j.p);
+    V.bad = reinterpret_cast<uint32_t *>(V.jacc + row);
     return true;
 }
 
@@ -1521,7 +1521,7 @@ bool enqueue_forward_pv(ephbte_plan P, int B, const T *f, int64_t ldf, const T *
     else go(std::integral_constant<int, 8>{});
     ktime_end(P, s, kt);
     hipLaunchKernelGGL((k_pv_finish<T>), dim3(static_cast<unsigned>((P->S + 255) / 256), static_cast<unsigned>(B)),
-                       dim3(256), 0, s, a, V, E);
+                       dim3(256), 0, s, a, tiled_args<T>(P), V, E);
     HIPC(hipGetLastError());
     return true;
 }
@@ -1562,7 +1562,7 @@ bool enqueue_vjp_pv(ephbte_plan P, int B, const double *f, int64_t ldf, const do
         e.neg = P->boson ? 1 : 0;
         hipLaunchKernelGGL((k_pv_finish<double>),
                            dim3(static_cast<unsigned>((P->S + 255) / 256), static_cast<unsigned>(B)), dim3(256), 0, s,
-                           a, V, e);
+                           a, tiled_args<double>(P), V, e);
     }
     HIPC(hipGetLastError());
     return true;

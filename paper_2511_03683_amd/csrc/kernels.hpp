@@ -1906,10 +1906,14 @@ __global__ void k_tr_tiled_finish(TiledArgs<T> A, const Vec4<T> *__restrict__ pa
 // and a fixed-point sum per window state and vector) and each vector adds a short
 // sum of N, which the lanes of a batch read from the few rows they share
 // (tabN: [group of VB][table row][mode][VB]).  Both sides of a pair are
-// fixed-point sums on the vector's own scale.
+// fixed-point sums on the vector's own scale.  A term that is not finite marks the
+// two states it belongs to, and a vector whose numbers leave no scale marks all:
+// their sums are formed again by k_pv_finish over their own entries, so that such a
+// value reaches its partners, and them only.
 
-// tabN of vector blockIdx.y, the {hw, N} table (by vector 0), max |N| and max |f|
-// of the vector (64 values a list), and a Bose plan's -f and -lam.
+// tabN of vector blockIdx.y, the {hw, N} table (by vector 0), and the largest finite
+// |N|, max(|f|, |1 - f|) and |lam| of the vector (64 values a list), and a Bose plan's
+// -f and -lam.
 template <typename T> struct PvPrep {
     PackPart<T> p;      // nph: B tables
     T *tab_n;
@@ -1921,6 +1925,10 @@ template <typename T> struct PvPrep {
     int S;
     double *nmax, *fmax, *lmax;   // [B][64]
 };
+__device__ __forceinline__ double max_finite(double m, double v) {
+    v = fabs(v);
+    return v <= 1.7976931348623157e308 ? fmax(m, v) : m;
+}
 template <typename T> __global__ __launch_bounds__(1024) void k_prep_pv(PvPrep<T> P) {
     const int b = blockIdx.y, nb = gridDim.x;
     const PackPart<T> &t = P.p;
@@ -1945,21 +1953,23 @@ template <typename T> __global__ __launch_bounds__(1024) void k_prep_pv(PvPrep<T
             w.b = v;
             t.out[t.padq && t.mode_major ? nu * static_cast<int64_t>(t.rows) + row : row * t.nm + nu] = w;
         }
-        m = fmax(m, fabs(static_cast<double>(v)));
+        m = max_finite(m, static_cast<double>(v));
     }
     block_max_to(m, P.nmax + b * 64 + blockIdx.x);
-    auto vec = [&](const T *__restrict__ x, T *__restrict__ neg, double *dst) {
+    auto vec = [&](const T *__restrict__ x, T *__restrict__ neg, double *dst, bool occ) {
         double mv = 0.0;
         for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < P.S; i += nb * blockDim.x) {
             const T v = x[i];
             if (neg) neg[static_cast<int64_t>(b) * P.S + i] = -v;
-            mv = fmax(mv, fabs(static_cast<double>(v)));
+            const double u = neg ? -static_cast<double>(v) : static_cast<double>(v);
+            mv = max_finite(mv, u);
+            if (occ) mv = max_finite(mv, 1.0 - u);
         }
         __syncthreads();
         block_max_to(mv, dst + b * 64 + blockIdx.x);
     };
-    if (P.neg_f) vec(P.f + b * P.ldf, P.neg_f, P.fmax);
-    if (P.lam) vec(P.lam + b * P.ldl, P.neg_l, P.lmax);
+    vec(P.f + b * P.ldf, P.neg_f, P.fmax, true);
+    if (P.lam) vec(P.lam + b * P.ldl, P.neg_l, P.lmax, false);
 }
 
 template <typename T> struct PvArgs {
@@ -1967,18 +1977,28 @@ template <typename T> struct PvArgs {
     int64_t ldf, ldl;
     const T *__restrict__ tab_n;
     int64_t gstride;        // values of tabN per group
-    int B, vb, n_list, bose;
+    int B, vb, n_list;
     const double *__restrict__ nmax, *__restrict__ fmax, *__restrict__ lmax;
     unsigned long long *__restrict__ jacc;   // [B][S]
+    uint32_t *__restrict__ bad;              // [B][S] nonzero: the sum is formed again
 };
-// the scale of vector b (all lanes of a wave)
+// The scale of vector b (all lanes of a wave): as sym_scale and vjp_scale, with the
+// occupation products of a term, at most 1 in [0, 1], at most 2 m^2 where m =
+// max(|f|, |1 - f|) is more than 1.  0 where the bound leaves no power of two.
 template <typename T>
 __device__ __forceinline__ double pv_scale(const TiledArgs<T> &A, const PvArgs<T> &V, int b) {
-    const MaxList none{nullptr, 0};
-    const ScaleIn s = scale_load(MaxList{V.nmax + b * 64, V.n_list}, A.gmax_bits,
-                                 V.bose ? MaxList{V.fmax + b * 64, V.n_list} : none,
-                                 V.lam ? MaxList{V.lmax + b * 64, V.n_list} : none);
-    return V.lam ? vjp_scale(s) : sym_scale(s);
+    const ScaleIn s = scale_load(MaxList{V.nmax + b * 64, V.n_list}, A.gmax_bits, MaxList{V.fmax + b * 64, V.n_list},
+                                 V.lam ? MaxList{V.lmax + b * 64, V.n_list} : MaxList{nullptr, 0});
+    const double m = wave_max(s.f, s.one), n = wave_max(s.n, s.one), l = V.lam ? 2.0 * wave_max(s.l, s.one) : 1.0;
+    const double bound = l * (2.0 * n + 1.0) * s.g * (m > 1.0 ? 2.0 * m * m : 1.0);
+    if (bound == 0.0) return 1.0;   // every term is 0
+    return bound > 1e-200 && bound < 1e200 ? scale_of_bound(bound) : 0.0;
+}
+// A term in the fixed point of a scale; false where it is not finite.
+__device__ __forceinline__ bool pv_fixed(double z, unsigned long long &fx) {
+    if (!(fabs(z) < 4.6e18)) return false;   // 2^62
+    fx = to_fixed(__builtin_rint(z));
+    return true;
 }
 
 template <typename T, bool PADQ, int NM, bool TAB>
@@ -2059,9 +2079,15 @@ __global__ __launch_bounds__(1024) void k_fwd_pairs_pv(TiledArgs<T> A, PvArgs<T>
                 const T ta = (a0 + ns) * (T(1) - fp), tb = (bb + ns) * fp;
                 const T y = fma(fd, ta, -(T(1) - fd) * tb);
                 if (on) {
-                    const unsigned long long fx = to_fixed(__builtin_rint(y * static_cast<T>(s_scale[v])));
-                    atomicAdd(s_j + v * W + wp, fx);
-                    atomicAdd(s_j + v * W + wd, 0ull - fx);
+                    unsigned long long fx;
+                    if (pv_fixed(static_cast<double>(y) * s_scale[v], fx)) {
+                        atomicAdd(s_j + v * W + wp, fx);
+                        atomicAdd(s_j + v * W + wd, 0ull - fx);
+                    } else {
+                        uint32_t *bad = V.bad + static_cast<int64_t>(b0 + v) * A.S + t.p_lo;
+                        bad[wp] = 1u;
+                        bad[wd] = 1u;
+                    }
                 }
             }
         }
@@ -2069,21 +2095,52 @@ __global__ __launch_bounds__(1024) void k_fwd_pairs_pv(TiledArgs<T> A, PvArgs<T>
     __syncthreads();
     for (int i = threadIdx.x; i < n; i += blockDim.x)
         for (int v = 0; v < nv; ++v) {
+            const int64_t o = static_cast<int64_t>(b0 + v) * A.S + t.p_lo + i;
             const unsigned long long u = s_j[v * W + i];
-            if (u) atomicAdd(V.jacc + static_cast<int64_t>(b0 + v) * A.S + t.p_lo + i, u);
+            if (u) atomicAdd(V.jacc + o, u);
         }
+}
+
+// The sums of state d and vector b over d's own entries (the destination layout D):
+// - (1 / K) I_d, or with V.lam the reverse pass's sum; used where the fixed point has none.
+template <typename T>
+__device__ T pv_own_sum(const TiledArgs<T> &D, const PvArgs<T> &V, int b, int d) {
+    const T *__restrict__ tn = V.tab_n + (b / V.vb) * V.gstride + b % V.vb;
+    const T *__restrict__ f = V.f + b * V.ldf, *__restrict__ lam = V.lam ? V.lam + b * V.ldl : nullptr;
+    const StateRec<T> sd = D.st[d];
+    const T fd = f[d], ld = lam ? lam[d] : T(0);
+    T sa = T(0), sb = T(0), sl = T(0);
+    for (int64_t e = D.chunk_beg[D.dest_chunk[d]]; e < D.chunk_beg[D.dest_chunk[d + 1]]; ++e) {
+        const uint32_t w = D.pnu[e];
+        const int p = static_cast<int>(w >> 3), nu = static_cast<int>(w & 7u);
+        const StateRec<T> sp = D.st[p];
+        const int64_t q = D.padq ? static_cast<int>(sp.kqp - sd.kqp) + D.qoff : q_linear(sd.kq, sp.kq, D.nq0, D.nq1, D.nq2);
+        const T hw = D.hwN[q * D.tq + nu * D.tm].a, N = tn[(q * D.nm + nu) * V.vb], g = D.g2[e];
+        const T x = sd.eps - sp.eps, xa = x + hw, xe = x - hw;
+        const T da = pair_gauss<T, false>(D, xa * xa, nullptr), dem = pair_gauss<T, false>(D, xe * xe, nullptr);
+        const T t = N * (da + dem), a = g * (t + dem), bw = g * (t + da), fp = f[p];
+        if (lam) {
+            sl += (ld - lam[p]) * (a * (T(1) - fp) + bw * fp);
+        } else {
+            sa += a * (T(1) - fp);
+            sb += bw * fp;
+        }
+    }
+    return lam ? -sl : (T(1) - fd) * sb - fd * sa;
 }
 
 // out_b,d = K (fixed-point sum) / scale, then the epilogue; the sums are cleared
 // for the next call (grid.y = vector)
-template <typename T> __global__ void k_pv_finish(TiledArgs<T> A, PvArgs<T> V, Epi<T> E) {
+template <typename T> __global__ void k_pv_finish(TiledArgs<T> A, TiledArgs<T> D, PvArgs<T> V, Epi<T> E) {
     const int b = blockIdx.y;
-    const double inv = 1.0 / pv_scale(A, V, b);
+    const double sc = pv_scale(A, V, b), inv = sc != 0.0 ? 1.0 / sc : 0.0;
     const int d = blockIdx.x * blockDim.x + threadIdx.x;
     if (d >= A.S) return;
-    unsigned long long *j = V.jacc + static_cast<int64_t>(b) * A.S + d;
-    const T v = static_cast<T>(static_cast<double>(static_cast<long long>(*j)) * inv);
-    *j = 0ull;
+    const int64_t o = static_cast<int64_t>(b) * A.S + d;
+    T v = static_cast<T>(static_cast<double>(static_cast<long long>(V.jacc[o])) * inv);
+    V.jacc[o] = 0ull;
+    if (V.bad[o] != 0u || sc == 0.0) v = pv_own_sum<T>(D, V, b, d);
+    V.bad[o] = 0u;
     apply_epi(E, b, d, A.S, A.K * v);
 }
 
@@ -2187,8 +2244,12 @@ __global__ __launch_bounds__(1024) void k_vjp_pairs_pv(TiledArgs<double> A, PvAr
                     const double a = a0 + ns, b = bb + ns;
                     const double rd = dl * fma(a, 1.0 - fp.a, b * fp.a);
                     const double y = dl * fma(b, 1.0 - fd.a, a * fd.a);
-                    atomicAdd(s_j + v * W + wp, to_fixed(__builtin_rint(y * sc)));
-                    atomicAdd(s_j + v * W + wd, to_fixed(__builtin_rint(-rd * sc)));
+                    unsigned long long xp, xd;
+                    uint32_t *bad = V.bad + static_cast<int64_t>(b0 + v) * A.S + t.p_lo;
+                    if (pv_fixed(y * sc, xp)) atomicAdd(s_j + v * W + wp, xp);
+                    else bad[wp] = 1u;
+                    if (pv_fixed(-rd * sc, xd)) atomicAdd(s_j + v * W + wd, xd);
+                    else bad[wd] = 1u;
                 }
             }
             if (gg2_mode && on) {
@@ -2204,8 +2265,9 @@ __global__ __launch_bounds__(1024) void k_vjp_pairs_pv(TiledArgs<double> A, PvAr
     __syncthreads();
     for (int i = threadIdx.x; i < n; i += blockDim.x)
         for (int v = 0; v < nv; ++v) {
+            const int64_t o = static_cast<int64_t>(b0 + v) * A.S + t.p_lo + i;
             const unsigned long long u = s_j[v * W + i];
-            if (u) atomicAdd(V.jacc + static_cast<int64_t>(b0 + v) * A.S + t.p_lo + i, u);
+            if (u) atomicAdd(V.jacc + o, u);
         }
 }
 

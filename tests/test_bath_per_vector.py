@@ -46,3 +46,122 @@ def test_odd_window_and_vector_count(driver, tmp_path, S, B):  # noqa: F811
         assert nerr(gf[b], rf) <= 1e-10, b
         rg = rg + g
     assert nerr(_out(tmp_path, "gg2"), rg) <= 1e-10
+
+
+def sparse_system():
+    """60 states, one mode, 700 of the 1770 pairs: pair records, and states that are no
+    partners of each other."""
+    return synth.random_channel_system(n_states=60, n_channels=700, n_modes=1, seed=3)
+
+
+def touched(s, p):
+    t = set(s.ch_j[s.ch_i == p]) | set(s.ch_i[s.ch_j == p]) | {p}
+    assert 1 < len(t) < s.n_states
+    return np.isin(np.arange(s.n_states), list(t))
+
+
+class Cpu:
+    def __init__(self, driver, folder):  # noqa: F811
+        self.driver, self.folder = driver, folder
+
+    def __call__(self, s, dtype, F, NPH, L=None):
+        B = len(F)
+        kw = dict(f=F, nph=NPH, B=B, nph_per_batch=1)
+        if L is None:
+            _write(self.folder, s, dtype, **kw)
+            _run(self.driver, self.folder, "forward")
+            return _out(self.folder, "I", F.shape)
+        _write(self.folder, s, dtype, lam=L, **kw)
+        _run(self.driver, self.folder, "vjp")
+        return _out(self.folder, "gf", F.shape), _out(self.folder, "gg2")
+
+
+class Gpu:
+    def __call__(self, s, dtype, F, NPH, L=None):
+        import torch
+
+        import paper_2511_03683_amd as E
+        d = lambda a: torch.as_tensor(a, dtype=torch.float64 if dtype == "f64" else torch.float32, device="cuda:0")
+        h = lambda t: t.cpu().numpy().astype(np.float64)
+        plan = E.build_channels(s, dtype=dtype, device=0)
+        assert E.plan_info(plan)["pair_records"] > 0
+        if L is None:
+            r = h(E.collision_integral(plan, d(F), d(NPH)))
+        else:
+            gf, gg = E.collision_vjp(plan, d(F), d(NPH), d(L), gg2=True)
+            r = h(gf), h(gg)
+        plan.close()
+        return r
+
+
+@pytest.fixture(params=["cpu", pytest.param("gpu", marks=pytest.mark.gpu)])
+def call(request):
+    if request.param == "gpu":
+        return Gpu()
+    return Cpu(request.getfixturevalue("driver"), request.getfixturevalue("tmp_path"))
+
+
+@pytest.mark.parametrize("bad", [np.nan, np.inf])
+@pytest.mark.parametrize("B,dtype", [(9, "f64"), (3, "f64"), (9, "f32")])
+def test_non_finite_occupation_reaches_its_partners_only(call, B, dtype, bad):
+    s = sparse_system()
+    F, NPH, _ = inputs(s, B, 4)
+    clean = call(s, dtype, F, NPH)
+    F[2, 17] = bad
+    got = call(s, dtype, F, NPH)
+    t = touched(s, 17)
+    assert not np.isfinite(got[2, t]).any()
+    assert np.array_equal(got[2, ~t], clean[2, ~t])
+    rest = np.arange(B) != 2
+    assert np.array_equal(got[rest], clean[rest])
+
+
+@pytest.mark.parametrize("where", ["f", "lam"])
+@pytest.mark.parametrize("B,bad", [(9, np.nan), (9, np.inf), (3, np.nan)])
+def test_non_finite_input_of_the_reverse_pass(call, B, bad, where):
+    s = sparse_system()
+    F, NPH, L = inputs(s, B, 5)
+    clean, cg = call(s, "f64", F, NPH, L)
+    (F if where == "f" else L)[1, 17] = bad
+    got, gg = call(s, "f64", F, NPH, L)
+    t = touched(s, 17)
+    # a state's own gradient does not contain its own occupation
+    own = t & (np.arange(s.n_states) != 17) if where == "f" else t
+    assert not np.isfinite(got[1, own]).any()
+    assert np.array_equal(got[1, ~t], clean[1, ~t])
+    rest = np.arange(B) != 1
+    assert np.array_equal(got[rest], clean[rest])
+    ch = (s.ch_i == 17) | (s.ch_j == 17)
+    assert not np.isfinite(gg[ch]).any()
+    assert np.array_equal(gg[~ch], cg[~ch])
+
+
+@pytest.mark.parametrize("B", [9, 3])
+def test_unused_infinite_phonon_occupation(call, B):
+    """N = 1 / expm1(0) at q = 0, which no channel uses."""
+    s = full_system(40, 4)
+    F, NPH, L = inputs(s, B, 6)
+    assert not np.any(s.state_k[s.ch_i] == s.state_k[s.ch_j])
+    ref, (rf, rg) = call(s, "f64", F, NPH), call(s, "f64", F, NPH, L)
+    NPH = NPH.copy()
+    NPH[:, 0, :] = np.inf
+    got, (gf, gg) = call(s, "f64", F, NPH), call(s, "f64", F, NPH, L)
+    for a, b in ((got, ref), (gf, rf), (gg, rg)):
+        assert nerr(a, b) <= 1e-10
+
+
+@pytest.mark.parametrize("scale", [1e3, 1e150])
+def test_numbers_of_any_size(call, scale):
+    """Occupations of a Fermi plan outside [0, 1], and loss gradients that leave the
+    fixed point no scale."""
+    s = full_system(40, 4)
+    F, NPH, L = inputs(s, 9, 7)
+    F[3] = 40.0 * F[3] - 20.0
+    F[4, 5] = 1e3
+    L[2] *= scale
+    L[5] *= 1.0 / scale
+    L[6] *= scale * scale
+    got, (gf, _) = call(s, "f64", F, NPH), call(s, "f64", F, NPH, L)
+    for b in range(9):
+        assert nerr(got[b], oracle.collision(s, F[b], NPH[b])) <= 1e-10, b
+        assert nerr(gf[b], oracle.collision_vjp(s, F[b], NPH[b], L[b])[0]) <= 1e-10, b
