@@ -1416,12 +1416,15 @@ bool enqueue_vjp_mx(ephbte_plan P, int B, const T *f, int64_t ldf, const T *lam,
 }
 
 // ---- a bath per vector over pair records ------------------------------------
-// LDS of k_fwd_pairs_pv / k_vjp_pairs_pv for windows of W states and VB vectors
-size_t pv_lds(ephbte_plan P, int W, int VB, bool vjp) {
+// LDS of k_fwd_pairs_pv / k_vjp_pairs_pv for windows of W states and VB vectors (fine:
+// sums of two words)
+size_t pv_lds(ephbte_plan P, int W, int VB, bool vjp, bool fine) {
     const size_t es = P->dtype == EPHBTE_F64 ? 8 : 4;
     return (es == 8 ? kExpTab * sizeof(double) : 0) + static_cast<size_t>(W) * (es + 4) +
-           static_cast<size_t>(W) * VB * (8 + (vjp ? 2 : 1) * es);
+           static_cast<size_t>(W) * VB * (8 + (fine ? 8 : 0) + (vjp ? 2 : 1) * es);
 }
+// two words where the alternative is the pass over entries in floating point
+bool pv_fine(ephbte_plan P, int B) { return B >= P->batch_min; }
 // Vectors a workgroup takes at once, 0: not these passes.  The Gaussians are
 // shared by them, so a window that leaves room for fewer than three keeps the
 // batched pass over entries (on the 100^3 system two fit, 16 ms against 16.6 ms at
@@ -1432,7 +1435,7 @@ int pv_vectors(ephbte_plan P, int B, bool vjp) {
     if (!P->pr_ok || !P->pr_all_q || !P->sym_ok || P->n_pr_groups == 0 || P->pr_window < 1) return 0;
     if (P->layout != 3 && B < P->batch_min) return 0;
     int most = 0;
-    while (most < 8 && pv_lds(P, P->pr_window, most + 1, vjp) + 1024 <= P->lds_max) ++most;
+    while (most < 8 && pv_lds(P, P->pr_window, most + 1, vjp, pv_fine(P, B)) + 1024 <= P->lds_max) ++most;
     if (most < (B < P->batch_min ? 2 : 3)) return 0;
     const int groups = (B + most - 1) / most;
     return (B + groups - 1) / groups;   // even groups
@@ -1448,8 +1451,8 @@ bool pv_prepare(ephbte_plan P, int B, int VB, const T *f, int64_t ldf, const T *
     const size_t row = static_cast<size_t>(P->S) * B;
     try {
         ensure(P->pv_n, sizeof(T) * static_cast<size_t>(groups) * rows * P->nm * VB, &P->ws_gen);
-        ensure_zeroed(P, P->pv_j, (sizeof(unsigned long long) + sizeof(uint32_t)) * row);
-        ensure(P->pv_max, sizeof(double) * 3 * 64 * B, &P->ws_gen);
+        ensure_zeroed(P, P->pv_j, (2 * sizeof(unsigned long long) + sizeof(uint32_t)) * row);
+        ensure(P->pv_max, sizeof(double) * 4 * 64 * B, &P->ws_gen);
         if (P->boson) {
             ensure(P->bs_x, sizeof(T) * row, &P->ws_gen);
             if (lam) ensure(P->bs_y, sizeof(T) * row, &P->ws_gen);
@@ -1473,6 +1476,7 @@ bool pv_prepare(ephbte_plan P, int B, int VB, const T *f, int64_t ldf, const T *
     p.nmax = mx;
     p.fmax = mx + 64 * B;
     p.lmax = mx + 2 * 64 * B;
+    p.cmax = mx + 3 * 64 * B;
     const int nb = std::min(64, std::max(1, static_cast<int>((p.p.n + 4095) / 4096)));
     hipLaunchKernelGGL((k_prep_pv<T>), dim3(static_cast<unsigned>(nb), static_cast<unsigned>(B)), dim3(kPrepThreads), 0,
                        s, p);
@@ -1489,8 +1493,10 @@ bool pv_prepare(ephbte_plan P, int B, int VB, const T *f, int64_t ldf, const T *
     V.nmax = p.nmax;
     V.fmax = p.fmax;
     V.lmax = p.lmax;
+    V.cmax = p.cmax;
     V.jacc = static_cast<unsigned long long *>(P->pv_j.p);
-    V.bad = reinterpret_cast<uint32_t *>(V.jacc + row);
+    V.jlo = pv_fine(P, B) ? V.jacc + row : nullptr;
+    V.bad = reinterpret_cast<uint32_t *>(V.jacc + 2 * row);
     return true;
 }
 
@@ -1502,7 +1508,7 @@ bool enqueue_forward_pv(ephbte_plan P, int B, const T *f, int64_t ldf, const T *
     if (VB == 0 || !pv_prepare<T>(P, B, VB, f, ldf, nullptr, 0, nph, V, s)) return false;
     TiledArgs<T> a = pair_args<T>(P);
     a.lds_states = P->pr_window;
-    const size_t shm = pv_lds(P, P->pr_window, VB, false);
+    const size_t shm = pv_lds(P, P->pr_window, VB, false, pv_fine(P, B));
     const dim3 grid(static_cast<unsigned>(P->n_pr_groups), static_cast<unsigned>((B + VB - 1) / VB)), block(1024);
     auto go = [&](auto nmc) {
         constexpr int NM = decltype(nmc)::value;
@@ -1533,7 +1539,7 @@ bool enqueue_vjp_pv(ephbte_plan P, int B, const double *f, int64_t ldf, const do
     if (VB == 0 || !pv_prepare<double>(P, B, VB, f, ldf, lam, ldl, nph, V, s)) return false;
     TiledArgs<double> a = pair_args<double>(P);
     a.lds_states = P->pr_window;
-    const size_t shm = pv_lds(P, P->pr_window, VB, true);
+    const size_t shm = pv_lds(P, P->pr_window, VB, true, pv_fine(P, B));
     const dim3 grid(static_cast<unsigned>(P->n_pr_groups)), block(1024);
     const int32_t *ch = P->pr_chan, *c0 = P->pr_ch0;
     const int wf = gf ? 1 : 0;

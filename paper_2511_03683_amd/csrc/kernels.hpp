@@ -1906,13 +1906,17 @@ __global__ void k_tr_tiled_finish(TiledArgs<T> A, const Vec4<T> *__restrict__ pa
 // and a fixed-point sum per window state and vector) and each vector adds a short
 // sum of N, which the lanes of a batch read from the few rows they share
 // (tabN: [group of VB][table row][mode][VB]).  Both sides of a pair are
-// fixed-point sums on the vector's own scale.  A term that is not finite marks the
+// fixed-point sums on the vector's own scale.  From 8 vectors on (where the pass over
+// entries sums in floating point) a second word keeps 2^-48 of the first one's unit:
+// one word's unit is 2^-61 of a bound over all states, which left an element 5e-13 of
+// itself in the median and 3e-10 at the 99th percentile (50^3, 20 baths), against
+// 4e-15 and 3e-13 by entries and with two words.  A term that is not finite marks the
 // two states it belongs to, and a vector whose numbers leave no scale marks all:
 // their sums are formed again by k_pv_finish over their own entries, so that such a
 // value reaches its partners, and them only.
 
 // tabN of vector blockIdx.y, the {hw, N} table (by vector 0), and the largest finite
-// |N|, max(|f|, |1 - f|) and |lam| of the vector (64 values a list), and a Bose plan's
+// |N|, |f|, |1 - f| and |lam| of the vector (64 values a list), and a Bose plan's
 // -f and -lam.
 template <typename T> struct PvPrep {
     PackPart<T> p;      // nph: B tables
@@ -1923,7 +1927,7 @@ template <typename T> struct PvPrep {
     int64_t ldf, ldl;
     T *neg_f, *neg_l;   // [B][S] or null
     int S;
-    double *nmax, *fmax, *lmax;   // [B][64]
+    double *nmax, *fmax, *cmax, *lmax;   // [B][64]
 };
 __device__ __forceinline__ double max_finite(double m, double v) {
     v = fabs(v);
@@ -1956,20 +1960,23 @@ template <typename T> __global__ __launch_bounds__(1024) void k_prep_pv(PvPrep<T
         m = max_finite(m, static_cast<double>(v));
     }
     block_max_to(m, P.nmax + b * 64 + blockIdx.x);
-    auto vec = [&](const T *__restrict__ x, T *__restrict__ neg, double *dst, bool occ) {
-        double mv = 0.0;
+    auto vec = [&](const T *__restrict__ x, T *__restrict__ neg, double *dst, double *dst_c) {
+        double mv = 0.0, mc = 0.0;
         for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < P.S; i += nb * blockDim.x) {
             const T v = x[i];
             if (neg) neg[static_cast<int64_t>(b) * P.S + i] = -v;
             const double u = neg ? -static_cast<double>(v) : static_cast<double>(v);
             mv = max_finite(mv, u);
-            if (occ) mv = max_finite(mv, 1.0 - u);
+            mc = max_finite(mc, 1.0 - u);
         }
         __syncthreads();
         block_max_to(mv, dst + b * 64 + blockIdx.x);
+        if (!dst_c) return;
+        __syncthreads();
+        block_max_to(mc, dst_c + b * 64 + blockIdx.x);
     };
-    vec(P.f + b * P.ldf, P.neg_f, P.fmax, true);
-    if (P.lam) vec(P.lam + b * P.ldl, P.neg_l, P.lmax, false);
+    vec(P.f + b * P.ldf, P.neg_f, P.fmax, P.cmax);
+    if (P.lam) vec(P.lam + b * P.ldl, P.neg_l, P.lmax, nullptr);
 }
 
 template <typename T> struct PvArgs {
@@ -1978,26 +1985,38 @@ template <typename T> struct PvArgs {
     const T *__restrict__ tab_n;
     int64_t gstride;        // values of tabN per group
     int B, vb, n_list;
-    const double *__restrict__ nmax, *__restrict__ fmax, *__restrict__ lmax;
+    const double *__restrict__ nmax, *__restrict__ fmax, *__restrict__ cmax, *__restrict__ lmax;
     unsigned long long *__restrict__ jacc;   // [B][S]
     uint32_t *__restrict__ bad;              // [B][S] nonzero: the sum is formed again
+    unsigned long long *__restrict__ jlo;    // [B][S] second words, or null: one word
 };
 // The scale of vector b (all lanes of a wave): as sym_scale and vjp_scale, with the
-// occupation products of a term, at most 1 in [0, 1], at most 2 m^2 where m =
-// max(|f|, |1 - f|) is more than 1.  0 where the bound leaves no power of two.
+// occupations as they are.  f in [0, 1]: a forward term's products are at most
+// max f max (1 - f), a reverse term's at most 1; else 2 max|f| max|1 - f| and
+// 2 max(max|f|, max|1 - f|).  0 where the bound leaves no power of two.
 template <typename T>
 __device__ __forceinline__ double pv_scale(const TiledArgs<T> &A, const PvArgs<T> &V, int b) {
+    const MaxList none{nullptr, 0};
     const ScaleIn s = scale_load(MaxList{V.nmax + b * 64, V.n_list}, A.gmax_bits, MaxList{V.fmax + b * 64, V.n_list},
-                                 V.lam ? MaxList{V.lmax + b * 64, V.n_list} : MaxList{nullptr, 0});
-    const double m = wave_max(s.f, s.one), n = wave_max(s.n, s.one), l = V.lam ? 2.0 * wave_max(s.l, s.one) : 1.0;
-    const double bound = l * (2.0 * n + 1.0) * s.g * (m > 1.0 ? 2.0 * m * m : 1.0);
+                                 V.lam ? MaxList{V.lmax + b * 64, V.n_list} : none);
+    const double mf = wave_max(s.f, s.one), mc = wave_max(list_value(MaxList{V.cmax + b * 64, V.n_list}), s.one);
+    const double n = wave_max(s.n, s.one), l = wave_max(s.l, s.one), m = fmax(mf, mc);
+    const double occ = V.lam ? 2.0 * l * (m > 1.0 ? 2.0 * m : 1.0) : (m > 1.0 ? 2.0 * mf * mc : mf * mc);
+    const double bound = (2.0 * n + 1.0) * s.g * occ;
     if (bound == 0.0) return 1.0;   // every term is 0
     return bound > 1e-200 && bound < 1e200 ? scale_of_bound(bound) : 0.0;
 }
-// A term in the fixed point of a scale; false where it is not finite.
-__device__ __forceinline__ bool pv_fixed(double z, unsigned long long &fx) {
+// A term z in units of the scale, added to a window state's sum (one or two words);
+// false where it is not finite.  A window holds fewer than 2^13 terms of a state, so
+// the sum of second words, at most 2^47 each, stays below 2^60.
+__device__ __forceinline__ bool pv_add(double z, unsigned long long *j, unsigned long long *lo) {
     if (!(fabs(z) < 4.6e18)) return false;   // 2^62
-    fx = to_fixed(__builtin_rint(z));
+    const double h = __builtin_rint(z);
+    atomicAdd(j, to_fixed(h));
+    if (lo) {
+        const double l = __builtin_rint((z - h) * 281474976710656.0);   // 2^48
+        if (l != 0.0) atomicAdd(lo, to_fixed(l));
+    }
     return true;
 }
 
@@ -2010,7 +2029,8 @@ __global__ __launch_bounds__(1024) void k_fwd_pairs_pv(TiledArgs<T> A, PvArgs<T>
     const int nv = min(VB, V.B - b0);
     double *s_tab = reinterpret_cast<double *>(smem);
     unsigned long long *s_j = reinterpret_cast<unsigned long long *>(s_tab + (sizeof(T) == 8 ? kExpTab : 0));
-    T *s_f = reinterpret_cast<T *>(s_j + VB * W);
+    unsigned long long *s_lo = V.jlo ? s_j + VB * W : nullptr;
+    T *s_f = reinterpret_cast<T *>(s_j + (V.jlo ? 2 : 1) * VB * W);
     T *s_e = s_f + VB * W;
     uint32_t *s_kq = reinterpret_cast<uint32_t *>(s_e + W);
     const int n = t.p_hi - t.p_lo + 1;
@@ -2019,6 +2039,7 @@ __global__ __launch_bounds__(1024) void k_fwd_pairs_pv(TiledArgs<T> A, PvArgs<T>
         s_e[i] = sr.eps;
         s_kq[i] = PADQ ? sr.kqp : sr.kq;
         for (int v = 0; v < nv; ++v) {
+            if (s_lo) s_lo[v * W + i] = 0ull;
             s_f[v * W + i] = V.f[static_cast<int64_t>(b0 + v) * V.ldf + t.p_lo + i];
             s_j[v * W + i] = 0ull;
         }
@@ -2079,10 +2100,10 @@ __global__ __launch_bounds__(1024) void k_fwd_pairs_pv(TiledArgs<T> A, PvArgs<T>
                 const T ta = (a0 + ns) * (T(1) - fp), tb = (bb + ns) * fp;
                 const T y = fma(fd, ta, -(T(1) - fd) * tb);
                 if (on) {
-                    unsigned long long fx;
-                    if (pv_fixed(static_cast<double>(y) * s_scale[v], fx)) {
-                        atomicAdd(s_j + v * W + wp, fx);
-                        atomicAdd(s_j + v * W + wd, 0ull - fx);
+                    const double z = static_cast<double>(y) * s_scale[v];
+                    const int xp = v * W + wp, xd = v * W + wd;
+                    if (pv_add(z, s_j + xp, s_lo ? s_lo + xp : nullptr)) {
+                        (void)pv_add(-z, s_j + xd, s_lo ? s_lo + xd : nullptr);
                     } else {
                         uint32_t *bad = V.bad + static_cast<int64_t>(b0 + v) * A.S + t.p_lo;
                         bad[wp] = 1u;
@@ -2098,6 +2119,7 @@ __global__ __launch_bounds__(1024) void k_fwd_pairs_pv(TiledArgs<T> A, PvArgs<T>
             const int64_t o = static_cast<int64_t>(b0 + v) * A.S + t.p_lo + i;
             const unsigned long long u = s_j[v * W + i];
             if (u) atomicAdd(V.jacc + o, u);
+            if (s_lo && s_lo[v * W + i]) atomicAdd(V.jlo + o, s_lo[v * W + i]);
         }
 }
 
@@ -2137,8 +2159,14 @@ template <typename T> __global__ void k_pv_finish(TiledArgs<T> A, TiledArgs<T> D
     const int d = blockIdx.x * blockDim.x + threadIdx.x;
     if (d >= A.S) return;
     const int64_t o = static_cast<int64_t>(b) * A.S + d;
-    T v = static_cast<T>(static_cast<double>(static_cast<long long>(V.jacc[o])) * inv);
+    double j = static_cast<double>(static_cast<long long>(V.jacc[o]));
     V.jacc[o] = 0ull;
+    if (V.jlo) {
+        // (a window's second words may sum to several units of the first)
+        j += static_cast<double>(static_cast<long long>(V.jlo[o])) * 3.552713678800501e-15;   // 2^-48
+        V.jlo[o] = 0ull;
+    }
+    T v = static_cast<T>(j * inv);
     if (V.bad[o] != 0u || sc == 0.0) v = pv_own_sum<T>(D, V, b, d);
     V.bad[o] = 0u;
     apply_epi(E, b, d, A.S, A.K * v);
@@ -2165,7 +2193,8 @@ __global__ __launch_bounds__(1024) void k_vjp_pairs_pv(TiledArgs<double> A, PvAr
     // {f, lam} first: 16-byte values, and W and VB may both be odd
     Pair2<double> *s_fl = reinterpret_cast<Pair2<double> *>(s_tab + kExpTab);
     unsigned long long *s_j = reinterpret_cast<unsigned long long *>(s_fl + VB * W);
-    double *s_e = reinterpret_cast<double *>(s_j + VB * W);
+    unsigned long long *s_lo = V.jlo ? s_j + VB * W : nullptr;
+    double *s_e = reinterpret_cast<double *>(s_j + (V.jlo ? 2 : 1) * VB * W);
     uint32_t *s_kq = reinterpret_cast<uint32_t *>(s_e + W);
     const int n = t.p_hi - t.p_lo + 1;
     for (int i = threadIdx.x; i < n; i += blockDim.x) {
@@ -2173,6 +2202,7 @@ __global__ __launch_bounds__(1024) void k_vjp_pairs_pv(TiledArgs<double> A, PvAr
         s_e[i] = sr.eps;
         s_kq[i] = PADQ ? sr.kqp : sr.kq;
         for (int v = 0; v < nv; ++v) {
+            if (s_lo) s_lo[v * W + i] = 0ull;
             Pair2<double> fl;
             fl.a = V.f[static_cast<int64_t>(b0 + v) * V.ldf + t.p_lo + i];
             fl.b = V.lam[static_cast<int64_t>(b0 + v) * V.ldl + t.p_lo + i];
@@ -2244,12 +2274,10 @@ __global__ __launch_bounds__(1024) void k_vjp_pairs_pv(TiledArgs<double> A, PvAr
                     const double a = a0 + ns, b = bb + ns;
                     const double rd = dl * fma(a, 1.0 - fp.a, b * fp.a);
                     const double y = dl * fma(b, 1.0 - fd.a, a * fd.a);
-                    unsigned long long xp, xd;
+                    const int xp = v * W + wp, xd = v * W + wd;
                     uint32_t *bad = V.bad + static_cast<int64_t>(b0 + v) * A.S + t.p_lo;
-                    if (pv_fixed(y * sc, xp)) atomicAdd(s_j + v * W + wp, xp);
-                    else bad[wp] = 1u;
-                    if (pv_fixed(-rd * sc, xd)) atomicAdd(s_j + v * W + wd, xd);
-                    else bad[wd] = 1u;
+                    if (!pv_add(y * sc, s_j + xp, s_lo ? s_lo + xp : nullptr)) bad[wp] = 1u;
+                    if (!pv_add(-rd * sc, s_j + xd, s_lo ? s_lo + xd : nullptr)) bad[wd] = 1u;
                 }
             }
             if (gg2_mode && on) {
@@ -2268,6 +2296,7 @@ __global__ __launch_bounds__(1024) void k_vjp_pairs_pv(TiledArgs<double> A, PvAr
             const int64_t o = static_cast<int64_t>(b0 + v) * A.S + t.p_lo + i;
             const unsigned long long u = s_j[v * W + i];
             if (u) atomicAdd(V.jacc + o, u);
+            if (s_lo && s_lo[v * W + i]) atomicAdd(V.jlo + o, s_lo[v * W + i]);
         }
 }
 
