@@ -1444,7 +1444,7 @@ int pv_vectors(ephbte_plan P, int B, bool vjp) {
 // Buffers, tables and maxima for B vectors (lam: the reverse pass); false where
 // the memory is not there.
 template <typename T>
-bool pv_prepare(ephbte_plan P, int B, int VB, const T *f, int64_t ldf, const T *lam, int64_t ldl, const T *nph,
+bool pv_prepare(ephbte_plan P, int B, int VB, bool fine, const T *f, int64_t ldf, const T *lam, int64_t ldl, const T *nph,
                 PvArgs<T> &V, hipStream_t s) {
     const int groups = (B + VB - 1) / VB;
     const int64_t rows = P->padq ? P->qpad_n : static_cast<int64_t>(P->nq[0]) * P->nq[1] * P->nq[2];
@@ -1495,39 +1495,50 @@ bool pv_prepare(ephbte_plan P, int B, int VB, const T *f, int64_t ldf, const T *
     V.lmax = p.lmax;
     V.cmax = p.cmax;
     V.jacc = static_cast<unsigned long long *>(P->pv_j.p);
-    V.jlo = pv_fine(P, B) ? V.jacc + row : nullptr;
+    V.jlo = fine ? V.jacc + row : nullptr;
     V.bad = reinterpret_cast<uint32_t *>(V.jacc + 2 * row);
     return true;
 }
 
-// f, lam: the caller's (a Bose plan's are negated here).  E as for one vector.
+// f, lam: the caller's (a Bose plan's are negated here).  Workspaces hold at most 64
+// vectors (as those of the pass over entries), in whole groups of VB; a larger batch
+// goes through them in turns.
+int pv_chunk(int B, int VB) { return std::min(B, std::max(64 / VB, 1) * VB); }
+
+// e: mode EPI_STORE
 template <typename T>
-bool enqueue_forward_pv(ephbte_plan P, int B, const T *f, int64_t ldf, const T *nph, const Epi<T> &E, hipStream_t s) {
+bool enqueue_forward_pv(ephbte_plan P, int B, const T *f, int64_t ldf, const T *nph, const Epi<T> &e0, hipStream_t s) {
     const int VB = pv_vectors(P, B, false);
-    PvArgs<T> V;
-    if (VB == 0 || !pv_prepare<T>(P, B, VB, f, ldf, nullptr, 0, nph, V, s)) return false;
+    if (VB == 0) return false;
     TiledArgs<T> a = pair_args<T>(P);
     a.lds_states = P->pr_window;
     const size_t shm = pv_lds(P, P->pr_window, VB, false, pv_fine(P, B));
-    const dim3 grid(static_cast<unsigned>(P->n_pr_groups), static_cast<unsigned>((B + VB - 1) / VB)), block(1024);
-    auto go = [&](auto nmc) {
-        constexpr int NM = decltype(nmc)::value;
-        const bool tab = sizeof(T) == 8 && P->exp_table;
-        if (P->padq && tab) hipLaunchKernelGGL((k_fwd_pairs_pv<T, true, NM, true>), grid, block, shm, s, a, V);
-        else if (P->padq) hipLaunchKernelGGL((k_fwd_pairs_pv<T, true, NM, false>), grid, block, shm, s, a, V);
-        else if (tab) hipLaunchKernelGGL((k_fwd_pairs_pv<T, false, NM, true>), grid, block, shm, s, a, V);
-        else hipLaunchKernelGGL((k_fwd_pairs_pv<T, false, NM, false>), grid, block, shm, s, a, V);
-    };
-    const int64_t kt = ktime_begin(P, s);
-    if (P->nm <= 1) go(std::integral_constant<int, 1>{});
-    else if (P->nm <= 2) go(std::integral_constant<int, 2>{});
-    else if (P->nm <= 3) go(std::integral_constant<int, 3>{});
-    else if (P->nm <= 4) go(std::integral_constant<int, 4>{});
-    else if (P->nm <= 6) go(std::integral_constant<int, 6>{});
-    else go(std::integral_constant<int, 8>{});
-    ktime_end(P, s, kt);
-    hipLaunchKernelGGL((k_pv_finish<T>), dim3(static_cast<unsigned>((P->S + 255) / 256), static_cast<unsigned>(B)),
-                       dim3(256), 0, s, a, tiled_args<T>(P), V, E);
+    for (int c0 = 0, nc = pv_chunk(B, VB); c0 < B; c0 += nc) {
+        const int n = std::min(nc, B - c0);
+        PvArgs<T> V;
+        if (!pv_prepare<T>(P, n, VB, pv_fine(P, B), f + c0 * ldf, ldf, nullptr, 0, nph + c0 * nqm_of(P), V, s)) return false;
+        const dim3 grid(static_cast<unsigned>(P->n_pr_groups), static_cast<unsigned>((n + VB - 1) / VB)), block(1024);
+        auto go = [&](auto nmc) {
+            constexpr int NM = decltype(nmc)::value;
+            const bool tab = sizeof(T) == 8 && P->exp_table;
+            if (P->padq && tab) hipLaunchKernelGGL((k_fwd_pairs_pv<T, true, NM, true>), grid, block, shm, s, a, V);
+            else if (P->padq) hipLaunchKernelGGL((k_fwd_pairs_pv<T, true, NM, false>), grid, block, shm, s, a, V);
+            else if (tab) hipLaunchKernelGGL((k_fwd_pairs_pv<T, false, NM, true>), grid, block, shm, s, a, V);
+            else hipLaunchKernelGGL((k_fwd_pairs_pv<T, false, NM, false>), grid, block, shm, s, a, V);
+        };
+        const int64_t kt = c0 == 0 ? ktime_begin(P, s) : -1;
+        if (P->nm <= 1) go(std::integral_constant<int, 1>{});
+        else if (P->nm <= 2) go(std::integral_constant<int, 2>{});
+        else if (P->nm <= 3) go(std::integral_constant<int, 3>{});
+        else if (P->nm <= 4) go(std::integral_constant<int, 4>{});
+        else if (P->nm <= 6) go(std::integral_constant<int, 6>{});
+        else go(std::integral_constant<int, 8>{});
+        ktime_end(P, s, kt);
+        Epi<T> e = e0;
+        e.out += c0 * e.ld_out;
+        hipLaunchKernelGGL((k_pv_finish<T>), dim3(static_cast<unsigned>((P->S + 255) / 256), static_cast<unsigned>(n)),
+                           dim3(256), 0, s, a, tiled_args<T>(P), V, e);
+    }
     HIPC(hipGetLastError());
     return true;
 }
@@ -1535,40 +1546,45 @@ bool enqueue_forward_pv(ephbte_plan P, int B, const T *f, int64_t ldf, const T *
 bool enqueue_vjp_pv(ephbte_plan P, int B, const double *f, int64_t ldf, const double *lam, int64_t ldl,
                     const double *nph, double *gf, int64_t ldgf, double *gg2, int gg2_mode, hipStream_t s) {
     const int VB = pv_vectors(P, B, true);
-    PvArgs<double> V;
-    if (VB == 0 || !pv_prepare<double>(P, B, VB, f, ldf, lam, ldl, nph, V, s)) return false;
+    if (VB == 0) return false;
     TiledArgs<double> a = pair_args<double>(P);
     a.lds_states = P->pr_window;
     const size_t shm = pv_lds(P, P->pr_window, VB, true, pv_fine(P, B));
     const dim3 grid(static_cast<unsigned>(P->n_pr_groups)), block(1024);
     const int32_t *ch = P->pr_chan, *c0 = P->pr_ch0;
     const int wf = gf ? 1 : 0;
-    for (int g = 0; g * VB < B; ++g) {
-        const int gm = gg2_mode == 0 ? 0 : (g == 0 ? gg2_mode : 2);
-        auto go = [&](auto nmc) {
-            constexpr int NM = decltype(nmc)::value;
-            if (P->padq && P->exp_table)
-                hipLaunchKernelGGL((k_vjp_pairs_pv<true, NM, true>), grid, block, shm, s, a, V, g, wf, ch, c0, gg2, gm);
-            else if (P->padq)
-                hipLaunchKernelGGL((k_vjp_pairs_pv<true, NM, false>), grid, block, shm, s, a, V, g, wf, ch, c0, gg2, gm);
-            else if (P->exp_table)
-                hipLaunchKernelGGL((k_vjp_pairs_pv<false, NM, true>), grid, block, shm, s, a, V, g, wf, ch, c0, gg2, gm);
-            else
-                hipLaunchKernelGGL((k_vjp_pairs_pv<false, NM, false>), grid, block, shm, s, a, V, g, wf, ch, c0, gg2, gm);
-        };
-        if (P->nm <= 1) go(std::integral_constant<int, 1>{});
-        else if (P->nm <= 2) go(std::integral_constant<int, 2>{});
-        else if (P->nm <= 3) go(std::integral_constant<int, 3>{});
-        else if (P->nm <= 4) go(std::integral_constant<int, 4>{});
-        else if (P->nm <= 6) go(std::integral_constant<int, 6>{});
-        else go(std::integral_constant<int, 8>{});
-    }
-    if (gf) {
-        Epi<double> e = epi_store<double>(gf, ldgf);
-        e.neg = P->boson ? 1 : 0;
-        hipLaunchKernelGGL((k_pv_finish<double>),
-                           dim3(static_cast<unsigned>((P->S + 255) / 256), static_cast<unsigned>(B)), dim3(256), 0, s,
-                           a, tiled_args<double>(P), V, e);
+    for (int b0 = 0, nc = pv_chunk(B, VB); b0 < B; b0 += nc) {
+        const int n = std::min(nc, B - b0);
+        PvArgs<double> V;
+        if (!pv_prepare<double>(P, n, VB, pv_fine(P, B), f + b0 * ldf, ldf, lam + b0 * ldl, ldl, nph + b0 * nqm_of(P), V, s))
+            return false;
+        for (int g = 0; g * VB < n; ++g) {
+            const int gm = gg2_mode == 0 ? 0 : (b0 + g == 0 ? gg2_mode : 2);
+            auto go = [&](auto nmc) {
+                constexpr int NM = decltype(nmc)::value;
+                if (P->padq && P->exp_table)
+                    hipLaunchKernelGGL((k_vjp_pairs_pv<true, NM, true>), grid, block, shm, s, a, V, g, wf, ch, c0, gg2, gm);
+                else if (P->padq)
+                    hipLaunchKernelGGL((k_vjp_pairs_pv<true, NM, false>), grid, block, shm, s, a, V, g, wf, ch, c0, gg2, gm);
+                else if (P->exp_table)
+                    hipLaunchKernelGGL((k_vjp_pairs_pv<false, NM, true>), grid, block, shm, s, a, V, g, wf, ch, c0, gg2, gm);
+                else
+                    hipLaunchKernelGGL((k_vjp_pairs_pv<false, NM, false>), grid, block, shm, s, a, V, g, wf, ch, c0, gg2, gm);
+            };
+            if (P->nm <= 1) go(std::integral_constant<int, 1>{});
+            else if (P->nm <= 2) go(std::integral_constant<int, 2>{});
+            else if (P->nm <= 3) go(std::integral_constant<int, 3>{});
+            else if (P->nm <= 4) go(std::integral_constant<int, 4>{});
+            else if (P->nm <= 6) go(std::integral_constant<int, 6>{});
+            else go(std::integral_constant<int, 8>{});
+        }
+        if (gf) {
+            Epi<double> e = epi_store<double>(gf + b0 * ldgf, ldgf);
+            e.neg = P->boson ? 1 : 0;
+            hipLaunchKernelGGL((k_pv_finish<double>),
+                               dim3(static_cast<unsigned>((P->S + 255) / 256), static_cast<unsigned>(n)), dim3(256), 0, s,
+                               a, tiled_args<double>(P), V, e);
+        }
     }
     HIPC(hipGetLastError());
     return true;

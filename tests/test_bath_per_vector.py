@@ -207,3 +207,30 @@ def test_small_elements_keep_their_digits(call):
     for x, ref in ((got, I), (gf, rf)):
         rel = (np.abs(x - ref) / np.abs(ref)).astype(float)
         assert np.median(rel) <= 3e-14 and np.quantile(rel, 0.9) <= 1e-12, np.quantile(rel, [0.5, 0.9, 0.99])
+
+
+@pytest.mark.gpu
+def test_many_vectors_take_the_workspace_of_64():
+    import torch
+
+    import paper_2511_03683_amd as E
+    s = full_system(48, 6)
+    F, NPH, L = inputs(s, 200, 12)
+    NPH = NPH * np.linspace(0.5, 1.0, 200)[:, None, None]
+    d = lambda a: torch.as_tensor(a, dtype=torch.float64, device="cuda:0")
+    plan = E.build_channels(s, device=0)
+    E.collision_integral(plan, d(F[:64]), d(NPH[:64]))
+    E.collision_vjp(plan, d(F[:64]), d(NPH[:64]), d(L[:64]), gg2=True)
+    held = E.plan_info(plan)["bytes"]
+    got = E.collision_integral(plan, d(F), d(NPH)).cpu().numpy()
+    gf, gg = (x.cpu().numpy() for x in E.collision_vjp(plan, d(F), d(NPH), d(L), gg2=True))
+    assert E.plan_info(plan)["bytes"] == held
+    plan.close()
+    rg = 0.0
+    for b in range(200):
+        rf, g = oracle.collision_vjp(s, F[b], NPH[b], L[b])
+        rg = rg + g
+        if b in (0, 63, 64, 127, 128, 199):
+            assert nerr(got[b], oracle.collision(s, F[b], NPH[b])) <= 1e-10, b
+            assert nerr(gf[b], rf) <= 1e-10, b
+    assert nerr(gg, rg) <= 1e-10
