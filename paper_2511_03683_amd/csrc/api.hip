@@ -12,6 +12,7 @@
 #include <cstdio>
 #include <cstring>
 #include <fstream>
+#include <initializer_list>
 #include <map>
 #include <memory>
 #include <mutex>
@@ -182,6 +183,7 @@ struct ephbte_plan_s {
     int32_t *mx_pos = nullptr, *mx_state = nullptr, *mx_blk = nullptr, *mx_row = nullptr;
     MxCol *mx_col = nullptr;
     DevBuf mx_m, mx_g, mx_u, mx_p1, mx_p2;
+    bool in_capture = false;                 // the call at hand runs under the caller's capture
     DevBuf pv_n, pv_j, pv_max;               // a bath per vector over pair records: N, sums, maxima
     // batched pass: tiles of destinations and per-destination sub-tile offsets
     BTileRec *btiles = nullptr;
@@ -310,6 +312,40 @@ void ensure_zeroed(ephbte_plan P, DevBuf &b, size_t bytes) {
         HIPC(hipMemset(b.p, 0, b.bytes));
         HIPC(hipDeviceSynchronize());
     }
+}
+
+void release(ephbte_plan P, std::initializer_list<DevBuf *> bufs) {
+    ++P->ws_gen;
+    for (DevBuf *b : bufs) {
+        dfree(b->p);
+        b->bytes = 0;
+    }
+}
+
+// Workspaces of a route that has an alternative: true once all of them are there.
+// Under the caller's capture, which allows no allocation, only what earlier calls
+// left serves; where the memory is not there, all of them are given back, so that
+// the alternative has what it had without the attempt.
+struct Want {
+    DevBuf *b;
+    size_t bytes;
+    bool zeroed;   // a new allocation is cleared
+};
+bool ensure_optional(ephbte_plan P, std::initializer_list<Want> want) {
+    bool all = true;
+    for (const Want &w : want) all = all && (w.bytes == 0 || (w.b->p && w.b->bytes >= w.bytes));
+    if (all) return true;
+    if (P->in_capture) return false;
+    try {
+        for (const Want &w : want)
+            if (w.bytes && !w.zeroed) ensure(*w.b, w.bytes, &P->ws_gen);
+        for (const Want &w : want)
+            if (w.bytes && w.zeroed) ensure_zeroed(P, *w.b, w.bytes);
+    } catch (const std::bad_alloc &) {
+        for (const Want &w : want) release(P, {w.b});
+        return false;
+    }
+    return true;
 }
 
 // Device address of `scratch` on device dev (which must be current), looked
@@ -1120,15 +1156,10 @@ template <typename T> bool mx_ensure(ephbte_plan P, int nc) {
     if (!P->mx_ok) return false;
     const size_t pos = static_cast<size_t>(P->mx_nb) * 64;
     const size_t waves = static_cast<size_t>(std::max(mx_vec_waves(P, 1), nc * mx_vec_waves(P, nc)));
-    try {
-        ensure_zeroed(P, P->mx_m, sizeof(T) * static_cast<size_t>(P->mx_blocks) * kMxBlock);
-        ensure(P->mx_u, sizeof(double) * pos * 4 * static_cast<size_t>(nc), &P->ws_gen);
-        ensure(P->mx_p1, sizeof(double) * (waves * 64 + pos * static_cast<size_t>(nc)), &P->ws_gen);
-        ensure(P->mx_p2, sizeof(double) * static_cast<size_t>(P->mx_blocks) * 64 * nc, &P->ws_gen);
-    } catch (const std::bad_alloc &) {
-        return false;
-    }
-    return true;
+    return ensure_optional(P, {{&P->mx_m, sizeof(T) * static_cast<size_t>(P->mx_blocks) * kMxBlock, true},
+                               {&P->mx_u, sizeof(double) * pos * 4 * static_cast<size_t>(nc), false},
+                               {&P->mx_p1, sizeof(double) * (waves * 64 + pos * static_cast<size_t>(nc)), false},
+                               {&P->mx_p2, sizeof(double) * static_cast<size_t>(P->mx_blocks) * 64 * nc, false}});
 }
 
 // LDS of the passes between pair records and the matrix: energy, packed k and
@@ -1258,14 +1289,9 @@ bool mx_batch_fits(ephbte_plan P, int B) {
 template <typename T> bool mx_ensure_batch(ephbte_plan P, int B, double products) {
     if (!mx_batch_fits(P, B) || !mx_pays_batch(P, B, products)) return false;
     const size_t cells = static_cast<size_t>(P->mx_nb) * 64 * mx_columns(B) * sizeof(double);
-    try {
-        ensure_zeroed(P, P->mx_m, sizeof(T) * static_cast<size_t>(P->mx_blocks) * kMxBlock);
-        ensure(P->mx_u, 2 * cells, &P->ws_gen);
-        ensure(P->mx_p1, 2 * cells * mx_gemm_split(P), &P->ws_gen);
-    } catch (const std::bad_alloc &) {
-        return false;
-    }
-    return true;
+    return ensure_optional(P, {{&P->mx_m, sizeof(T) * static_cast<size_t>(P->mx_blocks) * kMxBlock, true},
+                               {&P->mx_u, 2 * cells, false},
+                               {&P->mx_p1, 2 * cells * mx_gemm_split(P), false}});
 }
 // true once mx_ensure_batch found the memory
 template <typename T> bool use_mx_batch(ephbte_plan P, int B, double products) {
@@ -1362,16 +1388,12 @@ bool enqueue_vjp_mx(ephbte_plan P, int B, const T *f, int64_t ldf, const T *lam,
     if (!mx_pays_vjp(P, B)) return false;
     const size_t cells = static_cast<size_t>(P->mx_nb) * 64 * 2 * Vm;
     const size_t mat = sizeof(T) * static_cast<size_t>(P->mx_blocks) * kMxBlock;
-    try {
-        if (gf) {
-            ensure_zeroed(P, P->mx_m, mat);
-            ensure(P->mx_p1, 2 * cells * sizeof(double) * nsplit, &P->ws_gen);
-        }
-        if (gg2_mode) ensure(P->mx_g, mat, &P->ws_gen);
-        ensure(P->mx_u, 2 * cells * sizeof(double) + cells * sizeof(T), &P->ws_gen);
-    } catch (const std::bad_alloc &) {
+    // (0 bytes: not needed by this call)
+    if (!ensure_optional(P, {{&P->mx_m, gf ? mat : 0, true},
+                             {&P->mx_p1, gf ? 2 * cells * sizeof(double) * nsplit : 0, false},
+                             {&P->mx_g, gg2_mode ? mat : 0, false},
+                             {&P->mx_u, 2 * cells * sizeof(double) + cells * sizeof(T), false}}))
         return false;
-    }
     if (gf) enqueue_pair_matrix<T>(P, s);
     const MxArgs<T> x = mx_args<T>(P);
     const double K = k_prefactor(P);
@@ -1449,17 +1471,12 @@ bool pv_prepare(ephbte_plan P, int B, int VB, bool fine, const T *f, int64_t ldf
     const int groups = (B + VB - 1) / VB;
     const int64_t rows = P->padq ? P->qpad_n : static_cast<int64_t>(P->nq[0]) * P->nq[1] * P->nq[2];
     const size_t row = static_cast<size_t>(P->S) * B;
-    try {
-        ensure(P->pv_n, sizeof(T) * static_cast<size_t>(groups) * rows * P->nm * VB, &P->ws_gen);
-        ensure_zeroed(P, P->pv_j, (2 * sizeof(unsigned long long) + sizeof(uint32_t)) * row);
-        ensure(P->pv_max, sizeof(double) * 4 * 64 * B, &P->ws_gen);
-        if (P->boson) {
-            ensure(P->bs_x, sizeof(T) * row, &P->ws_gen);
-            if (lam) ensure(P->bs_y, sizeof(T) * row, &P->ws_gen);
-        }
-    } catch (const std::bad_alloc &) {
+    if (!ensure_optional(P, {{&P->pv_n, sizeof(T) * static_cast<size_t>(groups) * rows * P->nm * VB, false},
+                             {&P->pv_j, (2 * sizeof(unsigned long long) + sizeof(uint32_t)) * row, true},
+                             {&P->pv_max, sizeof(double) * 4 * 64 * B, false},
+                             {&P->bs_x, P->boson ? sizeof(T) * row : 0, false},
+                             {&P->bs_y, P->boson && lam ? sizeof(T) * row : 0, false}}))
         return false;
-    }
     double *mx = static_cast<double *>(P->pv_max.p);
     PvPrep<T> p{};
     p.p = pack_part<T>(P, nph);
@@ -2838,9 +2855,13 @@ ephbte_status transport_impl(ephbte_plan P, const T *f0, const T *vel, double T_
     if constexpr (kF64) {
         const MxSize z = mx_size(P);
         const bool pays = (P->S >= 2048 || 2.0 * z.slots >= 2.0) && 2.0 * z.slots + 2.0 >= 0.7 * z.v;
-        if (use_pairs(P, 1) && pays) {
-            ensure_fwd<T>(P, 1);   // the {hw, N} table
-            mx = mx_ensure<T>(P, 3);
+        if (use_pairs(P, 1) && pays && mx_ensure<T>(P, 3)) {
+            try {
+                ensure_fwd<T>(P, 1);   // the {hw, N} table
+                mx = true;
+            } catch (const std::bad_alloc &) {
+                release(P, {&P->mx_m, &P->mx_u, &P->mx_p1, &P->mx_p2});
+            }
         }
     }
     if (!mx) ensure(P->tr_W, sizeof(T) * (P->E + kEntryPad), &P->ws_gen);
@@ -3010,6 +3031,7 @@ template <typename F> ephbte_status guarded(ephbte_plan P, void *stream, F &&fn)
     if (!P) return fail(EPHBTE_INVALID_ARGUMENT, "plan is NULL");
     try {
         DeviceGuard g(P->device);
+        P->in_capture = capturing(static_cast<hipStream_t>(stream));
         PlanUse use(P, static_cast<hipStream_t>(stream));
         ephbte_status st = fn();
         use.done();

@@ -198,6 +198,29 @@ int main(int argc, char **argv) {
         check(ephbte_kernel_timing(plan, 0, &kms, &kn), "kernel_timing stop");
         wr("out_I.bin", dv.down(dI, static_cast<size_t>(B) * S));
         wr("out_timing.bin", {kms, static_cast<double>(kn)});
+    } else if (mode == "capture") {
+        // one vector outside a capture, then B vectors recorded, which may not allocate;
+        // the recorded work is run and its results taken
+        auto f = rd<double>("f.bin", static_cast<size_t>(B) * S);
+        auto lam = rd<double>("lam.bin", static_cast<size_t>(B) * S);
+        void *df = dv.up(f), *dl = dv.up(lam), *dI = dv.alloc(static_cast<size_t>(B) * S),
+             *dg = dv.alloc(static_cast<size_t>(B) * S);
+        double *dgg = nullptr;
+        hipMalloc(reinterpret_cast<void **>(&dgg), 8 * static_cast<size_t>(nch));
+        check(ephbte_collision_integral(plan, 1, df, S, dN, 0, dI, S, nullptr), "collision_integral");
+        check(ephbte_collision_vjp(plan, 1, df, S, dN, 0, dl, S, dg, S, dgg, 0, nullptr), "collision_vjp");
+        const long long m0 = emu::n_malloc;
+        hipGraph_t g = nullptr;
+        hipStreamBeginCapture(nullptr, 0);
+        check(ephbte_collision_integral(plan, B, df, S, dN, per_batch, dI, S, nullptr), "captured collision_integral");
+        check(ephbte_collision_vjp(plan, B, df, S, dN, per_batch, dl, S, dg, S, dgg, 0, nullptr), "captured collision_vjp");
+        hipStreamEndCapture(nullptr, &g);
+        wr("out_mallocs.bin", {static_cast<double>(emu::n_malloc - m0)});
+        hipGraphExec_t x = nullptr;
+        hipGraphInstantiate(&x, g, nullptr, nullptr, 0);
+        hipGraphLaunch(x, nullptr);
+        wr("out_I.bin", dv.down(dI, static_cast<size_t>(B) * S));
+        wr("out_gf.bin", dv.down(dg, static_cast<size_t>(B) * S));
     } else if (mode == "noalloc") {
         // the allocation-free pass after the plain one, on scratch that holds
         // fresh-memory bytes; it must make no hipMalloc call
@@ -494,6 +517,7 @@ int main(int argc, char **argv) {
         void *df = dv.up(f0), *dv3 = dv.up(vel), *dx = dv.alloc(static_cast<size_t>(S) * 3);
         double mob[9], resid = 0;
         int32_t iters = 0;
+        if (meta("room", 0.0) > 0.0) emu::room = static_cast<size_t>(meta("room"));
         const ephbte_status st = ephbte_iterate_transport(plan, df, dv3, meta("T"), dN, meta("tol"),
                                                           static_cast<int32_t>(meta("max_iter")), dx,
                                                           mob, &iters, &resid, nullptr);

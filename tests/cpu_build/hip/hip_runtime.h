@@ -23,6 +23,7 @@
 #include <algorithm>
 #include <functional>
 #include <numeric>
+#include <map>
 #include <memory>
 #include <mutex>
 #include <sys/mman.h>
@@ -227,7 +228,7 @@ inline unsigned long long atomicMax(unsigned long long *p, unsigned long long v)
 
 // ---------------------------------------------------------------- runtime
 typedef int hipError_t;
-enum { hipSuccess = 0, hipErrorInvalidValue = 1, hipErrorInvalidDevice = 101, hipErrorInvalidSymbol = 701 };
+enum { hipSuccess = 0, hipErrorInvalidValue = 1, hipErrorOutOfMemory = 2, hipErrorInvalidDevice = 101, hipErrorInvalidSymbol = 701 };
 typedef struct emu_stream *hipStream_t;
 typedef struct emu_event *hipEvent_t;
 struct emu_graph { std::vector<std::function<void()>> ops; };
@@ -245,6 +246,8 @@ namespace emu {
 inline emu_graph *capture = nullptr;
 inline int n_cu = 256;
 inline long long n_malloc = 0;   // hipMalloc calls so far (allocation-free checks)
+inline size_t room = SIZE_MAX;   // bytes that hipMalloc still gives (low-memory checks)
+inline std::map<void *, size_t> held;
 }
 // Fill of fresh device memory and of LDS at the start of each workgroup:
 // CPU_BUILD_FILL = pattern (default: 0xA5 for device memory, 0xFF for LDS) or
@@ -268,13 +271,25 @@ inline void fill_unwritten(void *p, size_t n, unsigned char pattern) {
 }
 inline hipError_t hipMalloc(void **p, size_t n) {
     ++emu::n_malloc;
+    *p = nullptr;
+    if (n > emu::room) return hipErrorOutOfMemory;
     *p = aligned_alloc(256, (n + 255) / 256 * 256);
-    if (!*p) return 1;
+    if (!*p) return hipErrorOutOfMemory;
+    emu::held[*p] = n;
+    if (emu::room != SIZE_MAX) emu::room -= n;
     fill_unwritten(*p, n, 0xA5);
     __asan_poison_memory_region((char *)*p + n, (n + 255) / 256 * 256 - n);
     return hipSuccess;
 }
-inline hipError_t hipFree(void *p) { free(p); return hipSuccess; }
+inline hipError_t hipFree(void *p) {
+    const auto it = emu::held.find(p);
+    if (it != emu::held.end()) {
+        if (emu::room != SIZE_MAX) emu::room += it->second;
+        emu::held.erase(it);
+    }
+    free(p);
+    return hipSuccess;
+}
 // a file-scope device array is a host global here
 #define HIP_SYMBOL(x) reinterpret_cast<const void *>(&(x))
 inline hipError_t hipGetSymbolAddress(void **p, const void *sym) {
@@ -282,7 +297,7 @@ inline hipError_t hipGetSymbolAddress(void **p, const void *sym) {
     return hipSuccess;
 }
 inline hipError_t hipHostMalloc(void **p, size_t n, unsigned) { return hipMalloc(p, n); }
-inline hipError_t hipHostFree(void *p) { free(p); return hipSuccess; }
+inline hipError_t hipHostFree(void *p) { return hipFree(p); }
 inline hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) { if (n) std::memmove(d, s, n); return hipSuccess; }
 inline hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind k, hipStream_t) {
     if (emu::capture) { emu::capture->ops.push_back([=] { if (n) std::memmove(d, s, n); }); return hipSuccess; }
