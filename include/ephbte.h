@@ -449,8 +449,9 @@ ephbte_status ephbte_set_tuning(ephbte_plan plan, const ephbte_tuning *tuning);
 /* Time candidate tunings of the B-vector collision integral on this plan with
  * HIP events and keep the fastest; writes the chosen tuning to *chosen (may be
  * NULL).  For batch < 8 the candidates are chunk sizes x block sizes of the
- * single-vector kernel; for batch >= 8, partner sub-tile sizes of the batched
- * kernel (in plans with the pair matrix, the calls that do not take it).
+ * single-vector kernel (batch = 1) or the per-row kernel; for batch >= 8, partner
+ * sub-tile sizes of the batched kernel.  In plans with the pair matrix the calls
+ * that do not take it are timed.
  * Allocates and frees its own half-filled occupations.  Synchronous.
  * cache_path (may be NULL): a JSON file mapping a key (device architecture and
  * compute-unit count, dtype, states, entries, modes, q grid, single or

@@ -3887,6 +3887,13 @@ static ephbte_status autotune_timed(ephbte_plan plan, int32_t batch, ephbte_tuni
         hipEvent_t e0, e1;
         HIPC(hipEventCreate(&e0));
         HIPC(hipEventCreate(&e1));
+        // the passes that the knobs are for are timed, not those over the pair matrix
+        struct NoMatrix {
+            ephbte_plan P;
+            bool was;
+            ~NoMatrix() { P->mx_ok = was; }
+        } no_matrix{plan, plan->mx_ok};
+        plan->mx_ok = false;
         auto once = [&]() {
             if (plan->dtype == EPHBTE_F64) {
                 ensure_fwd<double>(plan, batch);
@@ -3909,14 +3916,7 @@ static ephbte_status autotune_timed(ephbte_plan plan, int32_t batch, ephbte_tuni
             return ms;
         };
         if (batch >= plan->batch_min) {
-            // batched pass: partner sub-tile sizes that fit the LDS of a workgroup.
-            // The calls that take it are timed, not those over the pair matrix.
-            struct NoMatrix {
-                ephbte_plan P;
-                bool was;
-                ~NoMatrix() { P->mx_ok = was; }
-            } no_matrix{plan, plan->mx_ok};
-            plan->mx_ok = false;
+            // batched pass: partner sub-tile sizes that fit the LDS of a workgroup
             const int pt64[] = {48, 64, 96, 128, 160};
             const int pt32[] = {96, 128, 192, 256, 320};
             const int *cand = plan->dtype == EPHBTE_F64 ? pt64 : pt32;
