@@ -2914,6 +2914,28 @@ __global__ __launch_bounds__(1024) void k_mx_batch_finish(TiledArgs<T> A, MxArgs
 // from lam_d - lam_p itself, in FP32 (k_mx_outer_f32): the difference of two
 // FP32 products would lose the digits lam_d and lam_p share.
 
+// Only differences of lam enter, but dL/df takes them as differences of sums, which
+// lose the digits that a vector's lam share.  Where a vector has such an offset (the
+// middle three of five of its values lie closer to each other than to 0) it is taken
+// off first: a constant lam gives 0 exactly (energy or particle number as a loss), an
+// offset costs no digits, and a few values far from the others do not matter.
+__device__ __forceinline__ void order2(double &a, double &b) {
+    const double lo = fmin(a, b), hi = fmax(a, b);
+    a = lo;
+    b = hi;
+}
+template <typename T>
+__device__ __forceinline__ double lam_offset(const T *__restrict__ lam, int S) {
+    double v[5];
+#pragma unroll
+    for (int k = 0; k < 5; ++k) v[k] = static_cast<double>(lam[static_cast<int64_t>(S - 1) * k / 4]);
+#pragma unroll
+    for (int k = 4; k >= 1; --k)
+#pragma unroll
+        for (int m = 0; m < k; ++m) order2(v[m], v[m + 1]);
+    return v[3] - v[1] < fabs(v[2]) && fabs(v[2]) < 1.7e308 ? v[2] : 0.0;
+}
+
 // u1 and u2 of nvec vectors by position, 2 V columns; with fl also f and lam
 // themselves ([2][position][V], for k_mx_outer_f32)
 template <typename T>
@@ -2934,9 +2956,10 @@ __global__ __launch_bounds__(256) void k_mx_load_vjp(MxArgs<T> X, const T *__res
     }
     __syncthreads();
     const int c = threadIdx.x & 15;
+    const double off = c0 + c < nvec ? lam_offset(lam + static_cast<int64_t>(c0 + c) * ldl, X.S) : 0.0;
     for (int q = threadIdx.x >> 4; q < 64; q += 16) {
         const bool in = X.state[x0 + q] >= 0 && c0 + c < nvec;
-        const double v = static_cast<double>(s_f[c][q]), l = static_cast<double>(s_l[c][q]);
+        const double v = static_cast<double>(s_f[c][q]), l = in ? static_cast<double>(s_l[c][q]) - off : 0.0;
         const double w = in ? 1.0 - v : 0.0;
         const int64_t o = static_cast<int64_t>(x0 + q) * 2 * V + c0 + c;
         u1[o] = v;
@@ -2985,7 +3008,8 @@ __global__ __launch_bounds__(1024) void k_mx_vjp_finish(TiledArgs<T> A, MxArgs<T
         mx_own_sums<T>(A, X, d, u1, u2, 2 * V, c0 + c, a[0], a[1]);
         mx_own_sums<T>(A, X, d, u1, u2, 2 * V, V + c0 + c, a[2], a[3]);
     }
-    const double l = static_cast<double>(lam[static_cast<int64_t>(c0 + c) * ldl + d]);
+    const T *__restrict__ lv = lam + static_cast<int64_t>(c0 + c) * ldl;
+    const double l = static_cast<double>(lv[d]) - lam_offset(lv, X.S);
     gf[static_cast<int64_t>(c0 + c) * ldgf + d] = static_cast<T>(K * (a[2] + a[3] - l * (a[0] + a[1])));
 }
 
