@@ -687,7 +687,9 @@ template <typename T> Tables<T> tables(ephbte_plan P, const void *nph) {
 
 // lists of maxima (k_prep)
 enum { kMaxN = 0, kMaxF = 1, kMaxL = 2, kMaxMu = 3, kMaxNph = 4 };
-constexpr int kPrepMax = 64;   // workgroups of one part of k_prep (a list is one value a lane)
+constexpr int kPrepMax = 64;     // values of a list (one a lane)
+constexpr int kPrepFold = 1024;  // workgroups of one part of k_prep whose maxima are folded
+constexpr int kPrepRaw = 5 * kPrepMax + 3;   // their maxima, behind the lists and their reduction
 MaxList max_list(ephbte_plan P, int which) { return MaxList{P->prep_max + which * kPrepMax, P->prep_n[which]}; }
 
 // Where a compute unit runs several tiles one after another, each would wait for
@@ -1074,9 +1076,16 @@ bool enqueue_vjp_batched_pv(ephbte_plan P, int B, const T *f, int64_t ldf, const
 }
 
 constexpr int kPrepThreads = 1024;
+// Workgroups of a part of k_prep: as many as a list holds values, and above 2^20
+// entries, where 64 of them leave the memory idle, up to 1024 whose maxima one more
+// launch folds (q grid 128^3, six modes, a call with 60 k channels in FP64: 188 us
+// with 64, 129 before there was a list).
 int prep_blocks(int64_t n) {
+    if (n > (int64_t(1) << 20)) return static_cast<int>(std::min<int64_t>((n + 4095) / 4096, kPrepFold));
     return static_cast<int>(std::max<int64_t>(std::min<int64_t>((n + kPrepThreads - 1) / kPrepThreads, kPrepMax), 1));
 }
+// values in the list that `blocks` workgroups leave
+int prep_values(int blocks) { return blocks > kPrepMax ? 1 : blocks; }
 // The {hw, N} table of a call: one gather per entry instead of two.  tab != null:
 // the plain table (no box) there instead of the plan's.
 template <typename T> PackPart<T> pack_part(ephbte_plan P, const void *nph, Pair2<T> *tab = nullptr) {
@@ -1092,7 +1101,8 @@ template <typename T> PackPart<T> pack_part(ephbte_plan P, const void *nph, Pair
     p.used = P->used_rows;
     p.n = p.padq ? P->n_used_rows * P->nm : nqm_of(P);
     p.bmax = P->prep_max + kMaxN * kPrepMax;
-    p.blocks = P->prep_n[kMaxN] = prep_blocks(p.n);
+    p.blocks = prep_blocks(p.n);
+    P->prep_n[kMaxN] = prep_values(p.blocks);
     return p;
 }
 template <typename T> VecPart<T> vec_part(ephbte_plan P, int which, const T *x, T *neg, int64_t n) {
@@ -1101,13 +1111,26 @@ template <typename T> VecPart<T> vec_part(ephbte_plan P, int which, const T *x, 
     v.neg = neg;
     v.n = n;
     v.bmax = P->prep_max + which * kPrepMax;
-    v.blocks = P->prep_n[which] = prep_blocks(n);
+    v.blocks = prep_blocks(n);
+    P->prep_n[which] = prep_values(v.blocks);
     return v;
 }
 template <typename T>
-void enqueue_prep(ephbte_plan P, const PackPart<T> &p, const VecPart<T> &v0, const VecPart<T> &v1, hipStream_t s) {
+void enqueue_prep(ephbte_plan P, PackPart<T> p, VecPart<T> v0, VecPart<T> v1, hipStream_t s) {
+    FoldPart fold[3] = {};
+    double *raw = P->prep_max + kPrepRaw;
+    auto take = [&](auto &part, int k) {
+        if (part.blocks <= kPrepMax) return;
+        fold[k] = FoldPart{raw + k * kPrepFold, part.blocks, part.bmax};
+        part.bmax = raw + k * kPrepFold;
+    };
+    take(p, 0);
+    take(v0, 1);
+    take(v1, 2);
     hipLaunchKernelGGL((k_prep<T>), dim3(static_cast<unsigned>(p.blocks + v0.blocks + v1.blocks)), dim3(kPrepThreads), 0, s, p,
                        v0, v1);
+    if (fold[0].n + fold[1].n + fold[2].n > 0)
+        hipLaunchKernelGGL(k_fold_max, dim3(3), dim3(kPrepFold), 0, s, fold[0], fold[1], fold[2]);
 }
 template <typename T> void enqueue_pack(ephbte_plan P, const void *nph, hipStream_t s) {
     enqueue_prep<T>(P, pack_part<T>(P, nph), VecPart<T>{}, VecPart<T>{}, s);
@@ -3334,8 +3357,8 @@ ephbte_status ephbte_build_channels(const ephbte_problem *problem, const ephbte_
             dalloc(P->jacc, sizeof(unsigned long long) * std::max(P->S, 1), &P->layout_bytes);
             HIPC(hipMemset(P->jacc, 0, sizeof(unsigned long long) * std::max(P->S, 1)));
             dalloc(P->gmax_bits, sizeof(unsigned long long), &P->layout_bytes);
-            dalloc(P->prep_max, sizeof(double) * (5 * kPrepMax + 3), &P->layout_bytes);
-            HIPC(hipMemset(P->prep_max, 0, sizeof(double) * (5 * kPrepMax + 3)));
+            dalloc(P->prep_max, sizeof(double) * (kPrepRaw + 3 * kPrepFold), &P->layout_bytes);
+            HIPC(hipMemset(P->prep_max, 0, sizeof(double) * (kPrepRaw + 3 * kPrepFold)));
         }
         { HostLayout tmp; std::swap(tmp, L); }
         P->block_threads = 512;

@@ -435,6 +435,19 @@ __device__ __forceinline__ void block_max_to(double v, double *dst) {
     }
 }
 
+// The maxima that the workgroups of a part of k_prep left, more than a list holds,
+// folded into one (workgroup = part; n = 0: none)
+struct FoldPart {
+    const double *v;
+    int n;             // at most 1024
+    double *out;
+};
+__global__ __launch_bounds__(1024) void k_fold_max(FoldPart a, FoldPart b, FoldPart c) {
+    const FoldPart p = blockIdx.x == 0 ? a : blockIdx.x == 1 ? b : c;
+    if (p.n == 0) return;
+    block_max_to(static_cast<int>(threadIdx.x) < p.n ? p.v[threadIdx.x] : 0.0, p.out);
+}
+
 // each list's largest value, to its own place in out (one wave)
 __global__ __launch_bounds__(64) void k_reduce_lists(MaxList a, MaxList b, MaxList c, double *out) {
     const double x = wave_max(list_value(a), false), y = wave_max(list_value(b), false),
