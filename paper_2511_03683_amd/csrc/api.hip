@@ -559,14 +559,15 @@ void upload_chunks(ephbte_plan P, int64_t chunk_entries) {
     P->n_small_tiles = static_cast<int64_t>(tv.size());
     if (P->upper_beg.empty()) return;
     // single-copy tables over the upper parts of the rows; one workgroup per CU
-    // (1024 threads)
+    // (1024 threads).  A tile of FP32 takes less time, so a round more pays earlier:
+    // 16.7 M channels in one round 137 us, in two 117 (FP64 151 and 152).
     std::vector<int64_t> row_end(P->row_ptr.begin() + 1, P->row_ptr.end());
     ChunkTable u = make_chunks_seg(P->upper_beg, row_end, chunk_entries);
     const int64_t nch = P->E / 2;
     auto make_u = [&](int64_t target) {
         return make_tiles(u, P->row_ptr, P->pmin_up, P->pmax_up, P->sym_lds_states, target);
     };
-    std::vector<Tile> tu = P->tile_entries > 0 ? make_u(P->tile_entries / 2 + 1) : round_tiles(nch, 32768, P->n_cu, make_u);
+    std::vector<Tile> tu = P->tile_entries > 0 ? make_u(P->tile_entries / 2 + 1) : round_tiles(nch, P->dtype == EPHBTE_F64 ? 32768 : 24576, P->n_cu, make_u);
     dfree(reinterpret_cast<void *&>(P->sym_chunk_beg));
     dfree(reinterpret_cast<void *&>(P->sym_chunk_end));
     dfree(reinterpret_cast<void *&>(P->sym_chunk_dest));
