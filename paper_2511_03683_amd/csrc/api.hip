@@ -1285,15 +1285,16 @@ bool mx_pays_batch(ephbte_plan P, int B, double products) {
 }
 // The reverse pass of 2 .. 7 vectors.  FP64: both gradients, whichever are asked for,
 // so that dL/df does not depend on that; gradients of records with empty slots cost
-// 2.8 times as much a record from one vector's pass, twice as much from G.  FP32:
-// dL/df alone (enqueue_vjp_mx keeps dL/d|g|^2 to one vector at a time there).
+// more on both sides, a channel of one vector's pass 2.6 times as much (108 calls of 2
+// to 4 vectors from 0.3 to 70 M channels, each timed both ways: the choice costs 1 % in
+// the mean and 19 % at worst against the faster one).  FP32: dL/df alone (enqueue_vjp_mx keeps dL/d|g|^2 to one vector at a time there).
 bool mx_pays_vjp(ephbte_plan P, int B) {
     if (B >= P->batch_min) return true;
     const MxSize z = mx_size(P);
     if (!z.f64)
         return 45.0 + 3.2 * z.v + (4.5 + 1.3 * z.m) * z.np < 25.0 + B * (8.0 + (2.5 + 1.1 * z.m) * z.np);
-    return 40.0 + 13.0 * z.v + (1.0 + 7.3 * z.m) * (z.part ? 2.0 : 1.0) * z.np <
-           25.0 + B * (10.0 + (2.5 + 5.2 * z.m) * (z.part ? 2.8 : 1.0) * z.np);
+    return 78.0 + 17.0 * z.v + 6.0 * z.ch + (z.part ? 7.5 * z.slots : 0.0) <
+           40.0 + B * (9.0 + 4.6 * z.np + (z.part ? 11.4 : 4.4) * z.ch);
 }
 // RK4 steps of one vector (4 n_steps products)
 bool mx_pays_rt(ephbte_plan P, double n_steps) {
@@ -1406,8 +1407,7 @@ bool enqueue_vjp_mx(ephbte_plan P, int B, const T *f, int64_t ldf, const T *lam,
                     double *gg2, int gg2_mode, hipStream_t s) {
     constexpr bool kF32 = sizeof(T) == 4;
     const int Vm = mx_columns(B), nsplit = mx_gemm_split(P);
-    const size_t outer_lds = 64 * static_cast<size_t>(2 * Vm + 4) * sizeof(double);
-    if (!mx_batch_fits(P, B) || outer_lds > P->lds_max || mx_gemm_lds(64) > P->lds_max) return false;
+    if (!mx_batch_fits(P, B) || mx_gemm_lds(64) > P->lds_max) return false;
     if (kF32 && gg2_mode && B < P->batch_min) return false;
     if (!mx_pays_vjp(P, B)) return false;
     const size_t cells = static_cast<size_t>(P->mx_nb) * 64 * 2 * Vm;
@@ -1416,18 +1416,20 @@ bool enqueue_vjp_mx(ephbte_plan P, int B, const T *f, int64_t ldf, const T *lam,
     if (!ensure_optional(P, {{&P->mx_m, gf ? mat : 0, true},
                              {&P->mx_p1, gf ? 2 * cells * sizeof(double) * nsplit : 0, false},
                              {&P->mx_g, gg2_mode ? mat : 0, false},
-                             {&P->mx_u, 2 * cells * sizeof(double) + cells * sizeof(T), false}}))
+                             {&P->mx_u, 2 * cells * sizeof(double) + 2 * cells * sizeof(T), false}}))
         return false;
     if (gf) enqueue_pair_matrix<T>(P, s);
     const MxArgs<T> x = mx_args<T>(P);
     const double K = k_prefactor(P);
     T *gm = static_cast<T *>(P->mx_g.p);
-    const dim3 og(mx_row_grid(P, nsplit));
+    // k_mx_outer has no partial sums, so a row may be cut down to single blocks
+    const int osplit = std::max(1, std::min((6 * P->n_cu + P->mx_nb - 1) / std::max(P->mx_nb, 1), P->mx_max_row));
+    const dim3 og(mx_row_grid(P, osplit));
     for (int b0 = 0; b0 < B; b0 += 64) {
         const int nv = std::min(64, B - b0), V = mx_columns(nv);
         const int64_t n = static_cast<int64_t>(P->mx_nb) * 64 * 2 * V;
         double *u1 = static_cast<double *>(P->mx_u.p), *u2 = u1 + n;
-        T *fl = kF32 && gg2_mode ? reinterpret_cast<T *>(u2 + n) : nullptr;
+        T *fl = gg2_mode ? reinterpret_cast<T *>(u2 + n) : nullptr;
         const dim3 grid(static_cast<unsigned>(P->mx_nb), static_cast<unsigned>(V / 16));
         hipLaunchKernelGGL((k_mx_load_vjp<T>), grid, dim3(256), 0, s, x, f + b0 * ldf, ldf, lam + b0 * ldl, ldl, nv, V,
                            u1, u2, fl);
@@ -1441,19 +1443,14 @@ bool enqueue_vjp_mx(ephbte_plan P, int B, const T *f, int64_t ldf, const T *lam,
         if (!gg2_mode) continue;
         auto outer = [&](auto vt) {
             constexpr int VT = decltype(vt)::value;
-            if constexpr (kF32) {
-                hipLaunchKernelGGL((k_mx_outer_f32<VT>), og, dim3(256), 0, s, x, (const float *)fl, gm, nsplit);
-            } else {
-                const size_t shm = 64 * static_cast<size_t>(2 * V + 4) * sizeof(double);
-                hipLaunchKernelGGL((k_mx_outer<VT>), og, dim3(256), shm, s, x, (const double *)u1, (const double *)u2,
-                                   gm, b0 > 0 ? 1 : 0, nsplit);
-            }
+            // FP32: each group's gradients go out by themselves (added in FP64)
+            hipLaunchKernelGGL((k_mx_outer<T, VT>), og, dim3(256), 0, s, x, (const T *)fl, gm,
+                               !kF32 && b0 > 0 ? 1 : 0, osplit);
         };
         if (V == 16) outer(std::integral_constant<int, 1>{});
         else if (V == 32) outer(std::integral_constant<int, 2>{});
         else if (V == 48) outer(std::integral_constant<int, 3>{});
         else outer(std::integral_constant<int, 4>{});
-        // FP32: each group's gradients go out by themselves (added in FP64)
         if (kF32) enqueue_mx_gg2<T>(P, gm, gg2, b0 > 0 ? 2 : gg2_mode, s);
     }
     if (gg2_mode && !kF32) enqueue_mx_gg2<T>(P, gm, gg2, gg2_mode, s);

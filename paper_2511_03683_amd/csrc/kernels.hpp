@@ -2921,11 +2921,10 @@ __global__ __launch_bounds__(1024) void k_mx_batch_finish(TiledArgs<T> A, MxArgs
 // lam (1 - f)], V the vectors rounded up to 16), and the gradient of a channel
 // (d, p) sums over the vectors before its Gaussians enter,
 //   dL/d|g|^2 = K [ bh G[d][p] + ah G[p][d] ],
-//   G[d][p] = sum_b (lam_d - lam_p) (1 - f_d) f_p
-//           = sum_b u2[d][V + b] u1[p][b] - u2[d][b] u1[p][V + b],
-// a product of 2 V inner terms per stored block (FP64 plans).  FP32 plans form G
-// from lam_d - lam_p itself, in FP32 (k_mx_outer_f32): the difference of two
-// FP32 products would lose the digits lam_d and lam_p share.
+//   G[d][p] = sum_b (lam_d - lam_p) (1 - f_d) f_p,
+// formed from lam_d - lam_p itself in the plan's type (k_mx_outer): the difference of two products, which the matrix cores could take, loses the digits
+// that lam_d and lam_p share (FP64, 64 vectors, lam a smooth function of the energy:
+// error of dL/d|g|^2 1.1e-15 of its norm, 2.4e-16 from the differences).
 
 // Only differences of lam enter, but dL/df takes them as differences of sums, which
 // lose the digits that a vector's lam share.  Where a vector has such an offset (the
@@ -2950,7 +2949,7 @@ __device__ __forceinline__ double lam_offset(const T *__restrict__ lam, int S) {
 }
 
 // u1 and u2 of nvec vectors by position, 2 V columns; with fl also f and lam
-// themselves ([2][position][V], for k_mx_outer_f32)
+// themselves (for k_mx_outer: f, lam [position][V], f, lam [block][V][64])
 template <typename T>
 __global__ __launch_bounds__(256) void k_mx_load_vjp(MxArgs<T> X, const T *__restrict__ f, int64_t ldf,
                                                      const T *__restrict__ lam, int64_t ldl, int nvec, int V,
@@ -2984,6 +2983,14 @@ __global__ __launch_bounds__(256) void k_mx_load_vjp(MxArgs<T> X, const T *__res
             fl[y] = s_f[c][q];
             fl[static_cast<int64_t>(X.nb) * 64 * V + y] = s_l[c][q];
         }
+    }
+    if (!fl) return;
+    T *__restrict__ ft = fl + 2 * static_cast<int64_t>(X.nb) * 64 * V;
+    const int r = threadIdx.x & 63;
+    for (int k = threadIdx.x >> 6; k < 16; k += 4) {
+        const int64_t y = (static_cast<int64_t>(blockIdx.x) * V + c0 + k) * 64 + r;
+        ft[y] = s_f[k][r];
+        ft[static_cast<int64_t>(X.nb) * 64 * V + y] = s_l[k][r];
     }
 }
 
@@ -3026,76 +3033,29 @@ __global__ __launch_bounds__(1024) void k_mx_vjp_finish(TiledArgs<T> A, MxArgs<T
     gf[static_cast<int64_t>(c0 + c) * ldgf + d] = static_cast<T>(K * (a[2] + a[3] - l * (a[0] + a[1])));
 }
 
-// G over the stored blocks ([blocks][64 x 64], the matrix's layout), added to
-// what gm holds when add != 0.  Workgroup = block row I and a share of its
-// blocks, wave = 16 of its rows, whose 2 V values of u2 stay in registers; the
-// 64 rows of u1 of a block are staged in LDS (rows padded by 4).  The k index of
-// step t stands for column 4 g + t of a run of 16.
-template <int VT>
-__global__ __launch_bounds__(256, 2) void k_mx_outer(MxArgs<double> X, const double *__restrict__ u1,
-                                                     const double *__restrict__ u2, double *__restrict__ gm, int add, int nsplit) {
-    constexpr int V = 16 * VT, LD = 2 * V + 4;
-    extern __shared__ __align__(16) unsigned char smem[];
-    double *s1 = reinterpret_cast<double *>(smem);
-    int I, sp;
-    if (!mx_row_of_block(X.nb, nsplit, I, sp)) return;
-    const int lane = threadIdx.x & 63;
-    const int R = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
-    const int j = lane & 15, g = lane >> 4;
-    const int r0 = X.row[I], n = X.row[I + 1] - r0;
-    const int xb = r0 + static_cast<int>(static_cast<int64_t>(n) * sp / nsplit);
-    const int xe = r0 + static_cast<int>(static_cast<int64_t>(n) * (sp + 1) / nsplit);
-    // row R 16 + j of u2: {lam (1 - f)} against u1's f, {-(1 - f)} against lam f
-    double xr[2 * VT][4];
-    const double *__restrict__ ur = u2 + (static_cast<int64_t>(I) * 64 + R * 16 + j) * 2 * V + 4 * g;
-#pragma unroll
-    for (int q = 0; q < VT; ++q)
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            xr[q][t] = ur[V + 16 * q + t];
-            xr[VT + q][t] = -ur[16 * q + t];
-        }
-    for (int x = xb; x < xe; ++x) {
-        const double2 *__restrict__ gu =
-            reinterpret_cast<const double2 *>(u1 + static_cast<int64_t>(X.col[x].j) * 64 * 2 * V);
-        __syncthreads();
-#pragma unroll
-        for (int e = 0; e < 4 * VT; ++e) {
-            const int idx = e * 256 + static_cast<int>(threadIdx.x);
-            const int r = idx / V, k = idx - r * V;
-            *reinterpret_cast<double2 *>(s1 + r * LD + 2 * k) = gu[idx];
-        }
-        __syncthreads();
-        double *__restrict__ po = gm + static_cast<int64_t>(x) * kMxBlock + R * 1024 + g * 16 + j;
-#pragma unroll
-        for (int C = 0; C < 4; ++C) {
-            double acc[4] = {0.0, 0.0, 0.0, 0.0};
-            const double *__restrict__ sy = s1 + (C * 16 + j) * LD + 4 * g;
-#pragma unroll
-            for (int q = 0; q < 2 * VT; ++q)
-#pragma unroll
-                for (int t = 0; t < 4; ++t) mx_mfma(xr[q][t], sy[16 * q + t], acc);
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const double o = add ? po[C * 256 + v * 64] : 0.0;
-                po[C * 256 + v * 64] = o + acc[v];
-            }
-        }
-    }
-}
-
-// G of an FP32 plan in FP32, with the operations of k_vjp_batched: the vectors'
-// terms (1 - f_p) (f_d (lam_d - lam_p)) are summed as a balanced tree over 64
-// vectors in order, whose first level is a fused multiply-add.  (The other term
-// of a pair, f_p (1 - f_d) (lam_d - lam_p), is minus the first with d and p
-// exchanged, digit for digit, so G[p][d] holds it with its sign turned.)  Lane =
-// column p, wave = 16 rows d whose values are scalar operands; 16 vectors of a
-// column are in registers at a time.  About four operations per pair and vector
-// on the vector units against a 64-lane sum per pair there.
-template <int VT>
-__global__ __launch_bounds__(256) void k_mx_outer_f32(MxArgs<float> X, const float *__restrict__ fl,
-                                                      float *__restrict__ gm, int nsplit) {
+// G over the stored blocks ([blocks][64 x 64], the matrix's layout) in the plan's
+// type, as H[d][p] = -G[p][d] = sum_b (lam_d - lam_p) f_d (1 - f_p), added to what gm
+// holds when add != 0.  With the operations of k_vjp_batched<float>: the vectors' terms
+// (1 - f_p) (f_d (lam_d - lam_p)) are summed as a balanced tree over 64 vectors in order,
+// whose first level is a fused multiply-add (FP64: trees over 16, then in order).  (The
+// other term of a pair, f_p (1 - f_d) (lam_d - lam_p), is minus the first with d and p
+// exchanged, digit for digit.)  Not on the matrix cores: as sum_b f_d lam_d (1 - f_p)
+// - ... the difference would lose the digits that lam_d and lam_p share (2-norm error of
+// dL/d|g|^2 for slowly varying lam, 64 vectors: 1.1e-15 against 2.4e-16 here).  Lane =
+// column p, wave = 16 rows d whose values are scalar operands; 16 vectors of a column
+// are in registers at a time, and the loop over such groups stays a loop: unrolled, the
+// loads of all groups are issued first, and one wave a SIMD is left (62^3, 64 vectors,
+// FP64, whole reverse pass: 712 us, 327 now).  About three and a half operations per
+// pair and vector on the vector units, which bound it, against a 64-lane sum per pair
+// over entries (1149 us).
+template <typename T, int VT>
+__global__ __launch_bounds__(256) void k_mx_outer(MxArgs<T> X, const T *__restrict__ fl, T *__restrict__ gm, int add,
+                                                  int nsplit) {
     constexpr int V = 16 * VT;
+    auto fma1 = [](T a, T b, T c) {
+        if constexpr (sizeof(T) == 4) return __builtin_fmaf(a, b, c);
+        else return __builtin_fma(a, b, c);
+    };
     int I, sp;
     if (!mx_row_of_block(X.nb, nsplit, I, sp)) return;
     const int lane = threadIdx.x & 63;
@@ -3103,39 +3063,41 @@ __global__ __launch_bounds__(256) void k_mx_outer_f32(MxArgs<float> X, const flo
     const int r0 = X.row[I], n = X.row[I + 1] - r0;
     const int xb = r0 + static_cast<int>(static_cast<int64_t>(n) * sp / nsplit);
     const int xe = r0 + static_cast<int>(static_cast<int64_t>(n) * (sp + 1) / nsplit);
-    const float *__restrict__ ll = fl + static_cast<int64_t>(X.nb) * 64 * V;
+    const int64_t np = static_cast<int64_t>(X.nb) * 64 * V;
+    const T *__restrict__ ll = fl + np, *__restrict__ ft = fl + 2 * np, *__restrict__ lt = fl + 3 * np;
     const int64_t row0 = (static_cast<int64_t>(I) * 64 + R * 16) * V;
     for (int x = xb; x < xe; ++x) {
-        const int64_t col = (static_cast<int64_t>(X.col[x].j) * 64 + lane) * V;
-        float res[16], odd[16];
-#pragma unroll
+        const int64_t col = static_cast<int64_t>(X.col[x].j) * 64 * V + lane;
+        T res[16], odd[16];
+#pragma unroll 1
         for (int q = 0; q < VT; ++q) {
-            float wc[16], lc[16];
+            T wc[16], lc[16];
 #pragma unroll
             for (int k = 0; k < 16; ++k) {
-                wc[k] = 1.0f - fl[col + 16 * q + k];
-                lc[k] = ll[col + 16 * q + k];
+                wc[k] = T(1) - ft[col + (16 * q + k) * 64];
+                lc[k] = lt[col + (16 * q + k) * 64];
             }
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const float *__restrict__ fr = fl + row0 + r * V + 16 * q, *__restrict__ lr = ll + row0 + r * V + 16 * q;
-                float a[8];
+                const T *__restrict__ fr = fl + row0 + r * V + 16 * q, *__restrict__ lr = ll + row0 + r * V + 16 * q;
+                T a[8];
 #pragma unroll
                 for (int k = 0; k < 8; ++k) {
-                    const float m0 = fr[2 * k] * (lr[2 * k] - lc[2 * k]);
-                    const float m1 = fr[2 * k + 1] * (lr[2 * k + 1] - lc[2 * k + 1]);
-                    a[k] = __builtin_fmaf(wc[2 * k + 1], m1, wc[2 * k] * m0);
+                    const T m0 = fr[2 * k] * (lr[2 * k] - lc[2 * k]);
+                    const T m1 = fr[2 * k + 1] * (lr[2 * k + 1] - lc[2 * k + 1]);
+                    a[k] = fma1(wc[2 * k + 1], m1, wc[2 * k] * m0);
                 }
-                const float t = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
-                if (q == 0) res[r] = t;
-                else if (q == 1) res[r] += t;
-                else if (q == 2) odd[r] = t;
-                else odd[r] += t;
+                const T t = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
+                if (sizeof(T) == 8 || q < 2) res[r] = q == 0 ? t : res[r] + t;
+                else odd[r] = q == 2 ? t : odd[r] + t;
             }
         }
-        float *__restrict__ po = gm + static_cast<int64_t>(x) * kMxBlock + (R * 4 + (lane >> 4)) * 256 + (lane & 15);
+        T *__restrict__ po = gm + static_cast<int64_t>(x) * kMxBlock + (R * 4 + (lane >> 4)) * 256 + (lane & 15);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) po[r * 16] = VT > 2 ? res[r] + odd[r] : res[r];
+        for (int r = 0; r < 16; ++r) {
+            const T t = VT > 2 && sizeof(T) == 4 ? res[r] + odd[r] : res[r];
+            po[r * 16] = add ? po[r * 16] + t : t;
+        }
     }
 }
 
@@ -3210,7 +3172,7 @@ __device__ __forceinline__ void mx_gg2_chunk(const TiledArgs<T> &A, const MxArgs
                 gv[m] = static_cast<double>(A.K * __builtin_fmaf(bh, -g2, -(g1 * ah)));
             } else {
                 const T t = w[m].b * (da + dem);
-                gv[m] = A.K * (g1 * (t + da) + g2 * (t + dem));
+                gv[m] = -A.K * (g2 * (t + da) + g1 * (t + dem));
             }
         }
         if (v) write_gg2<NM>(gg2, gg2_mode, c0, cb + r + lane, A.pld, nm, gv);
