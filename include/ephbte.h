@@ -16,7 +16,10 @@
  *   linear k index state_k[s] = (k0*N1 + k1)*N2 + k2 on the k grid (N0,N1,N2).
  * Phonons: tables indexed [q][nu] (q-major, q linear on the q grid like k),
  *   n_modes <= 8.  The tables must be even in q (hw(-q) = hw(q), N(-q) = N(q)),
- *   as time-reversal symmetry gives; each orientation of a channel uses its own q.
+ *   as time-reversal symmetry gives.  Passes over entries take each orientation
+ *   of a channel at its own q; passes over state pairs (B = 1 in layout 3, the
+ *   pair matrix, a bath per vector) take both at the q of one of them, which is
+ *   the same where the tables are even.
  * Channel: an unordered state pair {i, j} plus a mode nu, with one |g|^2 value.
  *   It enters I(i) with partner j and q = k_j - k_i, and I(j) with partner i
  *   and q = k_i - k_j (Optimized GPU algorithm, step 1: each channel feeds two
@@ -56,7 +59,10 @@
  *   channels (and max |lambda| in the reverse pass); Fermi plans assume
  *   occupations f in [0, 1] (a caller's f outside that range, or RK stage
  *   inputs that leave it, can overflow the partner-side sums), Bose plans
- *   take max |n| of each pass's input into the scale.
+ *   take max |n| of each pass's input into the scale.  With a bath per vector
+ *   each vector has a scale of its own, from its max |f| and max |1 - f| as
+ *   they are, and from B = 8 on the values have a second 64-bit word (2^-48 of
+ *   the first one's unit).
  */
 #ifndef EPHBTE_H
 #define EPHBTE_H
@@ -233,10 +239,11 @@ ephbte_status ephbte_layout_host(const ephbte_problem *problem, const ephbte_bui
  * nph: device, plan dtype, phonon occupations N.  nph_per_batch == 0: one
  *      table [Nq][n_modes] shared by every vector (one (alpha, beta) per
  *      entry serves the whole batch; from B = 2 on, where the plan has the
- *      pair matrix, the coefficients are formed once per state pair and call
- *      and applied as a matrix).  nph_per_batch != 0: B tables
- *      [B][Nq][n_modes], vector b with its own bath; in FP64 over q-ordered
- *      pair records the Gaussians of a pair serve up to eight vectors.
+ *      pair matrix and B is large enough for it to pay, the coefficients are
+ *      formed once per state pair and call and applied as a matrix).
+ *      nph_per_batch != 0: B tables [B][Nq][n_modes], vector b with its own
+ *      bath; over q-ordered pair records the Gaussians of a pair serve up to
+ *      eight vectors (in the reverse pass of FP64 plans only).
  * I:   device [B][ldi], plan dtype, written.  I must not alias f.
  * B >= 1; ldf, ldi >= S.
  * Reductions: with B = 1 and the single-copy layout every channel is read
@@ -244,10 +251,12 @@ ephbte_status ephbte_layout_host(const ephbte_problem *problem, const ephbte_bui
  * atomics (associative, so the result is bitwise reproducible), and so is the
  * row side over pair records in q order (pair_order 1); otherwise the row
  * side is summed in registers in a fixed order.  Vectors with a bath each over
- * pair records use the same fixed point; the pair matrix sums in FP64 in a
- * fixed order, and a sum that is not finite is formed again over the row's own
- * partners, so that a non-finite occupation reaches its partners only.  Other
- * forms reduce each destination's entries with no atomics.
+ * pair records use fixed point as well; the sum of a state with a non-finite
+ * term, and those of a vector whose bound leaves no scale, are formed in
+ * floating point over the state's own entries instead.  The pair matrix sums in
+ * FP64 in a fixed order, and a sum that is not finite is formed again over the
+ * row's own partners.  In both a non-finite occupation reaches its partners
+ * only.  Other forms reduce each destination's entries with no atomics.
  */
 ephbte_status ephbte_collision_integral(ephbte_plan plan, int32_t batch, const void *f,
                                         int64_t ldf, const void *nph, int32_t nph_per_batch,
@@ -464,8 +473,9 @@ ephbte_status ephbte_autotune(ephbte_plan plan, int32_t batch, ephbte_tuning *ch
 
 /* Launch timing of the forward pass's main kernel, for measurement (not a
  * step of the method): the single-copy kernel at B = 1, the per-row kernel for
- * B = 2 .. 7 (or layout 1) and the batched kernel for B >= 8, where the call
- * uses them (not over the pair matrix).
+ * B = 2 .. 7 (or layout 1) and the batched kernel for B >= 8; where a call goes
+ * over the pair matrix its product, and with a bath per vector over pair records
+ * the pair kernel (the first group of vectors of a call).
  * mode 1: clears the record and starts it; every eager launch of that kernel
  *   on this plan is then bracketed by two HIP events recorded on its launch
  *   stream (launches under graph capture are not timed; at most 4096 launches

@@ -171,7 +171,7 @@ struct ephbte_plan_s {
     int64_t *pr_chunk_beg = nullptr, *pr_chunk_end = nullptr;
     int32_t *pr_chunk_dest = nullptr, *pr_dest_chunk = nullptr;
     TileRec *pr_groups = nullptr;          // workgroups of the pair passes
-    std::vector<TileRec> pr_tiles;         // host: their runs (see PairOrder)
+    std::vector<TileRec> pr_tiles;         // host: their runs (see PairOrder), for inspection (no pass reads it)
     int64_t n_pr_chunks = 0, n_pr_groups = 0, n_pr_tiles = 0;
     bool pr_ok = false;
     bool exp_table = true;                 // FP64 Gaussians of the pair pass from the LDS table
@@ -1256,8 +1256,8 @@ size_t mx_gemm_lds(int NC) { return 2 * 64 * static_cast<size_t>(NC + 4) * sizeo
 //   3 vectors, 3.8 M pairs in 23 M values, 1 mode: 153 against 171;
 //   20 RK4 stages, FP64: 2 modes, 3.6 M pairs 1008 against 1064, 4.7 M 1128 against
 //   1083; 1 mode, 5.4 M 970 against 1078, 11.7 M 1381 against 1143;
-//   reverse pass, FP64, 1 mode, 4 vectors: 3.8 M pairs 314 against 398, 11.7 M 614
-//   against 466.
+//   reverse pass, FP64, 1 mode, 4 vectors: 3.8 M pairs 236 against 495, 11.7 M 482
+//   against 560; 6 modes, 11.7 M pairs, 3 vectors: 1382 against 965.
 struct MxSize {
     double np, slots, ch, v;   // ch: channels
     int m;
@@ -1470,8 +1470,8 @@ size_t pv_lds(ephbte_plan P, int W, int VB, bool vjp, bool fine) {
 bool pv_fine(ephbte_plan P, int B) { return B >= P->batch_min; }
 // Vectors a workgroup takes at once, 0: not these passes.  The Gaussians are
 // shared by them, so a window that leaves room for fewer than three keeps the
-// batched pass over entries (on the 100^3 system two fit, 16 ms against 16.6 ms at
-// 64 vectors); below 8 vectors the alternative is a pass each, which two beat
+// batched pass over entries (on the 100^3 system two fit with sums of one word, 16 ms
+// against 16.6 ms at 64 vectors); below 8 vectors the alternative is a pass each, which two beat
 // (forward of four there: 1.49 ms for 2.33) and one, whose workgroup prepares and
 // reads more than the plain pass, does not (reverse of four: 3.04 for 2.15).
 int pv_vectors(ephbte_plan P, int B, bool vjp) {

@@ -1078,7 +1078,7 @@ __device__ __forceinline__ void pair_chunk(const TiledArgs<T> &A, const T *__res
 // per wave: forward 466 -> 430 us, reverse with channel gradients 1227 -> 1124,
 // pair matrix 940 -> 756.  Runs of 384 / 768 / 1536 / 4096 / 16384 records:
 // reverse 1124 / 1134 / 1135 / 1146 / 1155 us, pair matrix 756 / 776 / 801 / 832 /
-// 879; the forward pass, which writes nothing per pair, 420 .. 445 without a trend.
+// 879 (727 over 100 calls traced later, 389 FP32); the forward pass, which writes nothing per pair, 420 .. 445 without a trend.
 template <typename T, bool PADQ, int NM, bool TAB>
 __device__ __forceinline__ void pair_chunk_q(const TiledArgs<T> &A, const Pair2<T> *s_ef, const uint32_t *s_kq,
                                              const double *s_tab, unsigned long long *s_j, T scale, int64_t beg,
@@ -1926,7 +1926,10 @@ __global__ void k_tr_tiled_finish(TiledArgs<T> A, const Vec4<T> *__restrict__ pa
 // 4e-15 and 3e-13 by entries and with two words.  A term that is not finite marks the
 // two states it belongs to, and a vector whose numbers leave no scale marks all:
 // their sums are formed again by k_pv_finish over their own entries, so that such a
-// value reaches its partners, and them only.
+// value reaches its partners, and them only.  Bound by LDS atomics (two a pair and
+// vector, the second words mostly skipped in FP32) and FP64 issue: 50^3, 6 modes, 20
+// baths, whole calls: forward 1002 us by entries, 96 with one word, 110 now (kernel 96
+// of it), reverse 2764 and 185.
 
 // tabN of vector blockIdx.y, the {hw, N} table (by vector 0), and the largest finite
 // |N|, |f|, |1 - f| and |lam| of the vector (64 values a list), and a Bose plan's
